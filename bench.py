@@ -293,7 +293,7 @@ def summarize_surrogate_trace(trace_dir: str, log_path: str, out_path: str):
                 short = name.replace("void ", "").split("(")[0].replace("fsc::", "")
             else:
                 continue
-            if short.split("<")[0] in ("k_input", "k_first", "k_mid", "k_mid_lds", "k_last",
+            if short.split("<")[0] in ("k_first", "k_mid", "k_mid_lds", "k_last",
                                        "k_img_part", "k_img_total", "k_pred"):
                 per[short].append(int(r["End_Timestamp"]) - int(r["Start_Timestamp"]))
     lines = ["# Surrogate kernels: rocprofv3 kernel trace of bench.py (rollout part)", "",
@@ -331,7 +331,7 @@ def summarize_surrogate_trace(trace_dir: str, log_path: str, out_path: str):
     for name, mo in models.items():
         K = 2 if "2ch" in name else 1
         layers = int(name.split("layer")[0])
-        first = means.get(f"k_first<{K}, false, true>")
+        first = means.get(f"k_first<{K}, false>")
         if first and mid and "k_last" in means and "k_pred" in means:
             tot = first + (layers - 2) * mid + means["k_last"] + means["k_pred"]
             lines.append(f"\n{name}: kernel time per pass {tot / 1e3:.1f} us (k_first + "

@@ -19,6 +19,7 @@
 // Adam; BF16 copies feed the matrix cores.
 //
 // Activations are NHWC: pixel p = (n H + y) W + x, channel fastest.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <deque>
@@ -116,30 +117,15 @@ __global__ void k_mfma_probe(const float *A, const float *B, float *Cm) {
 }
 
 // ---------------------------------------------------------------------------
-// Network input X[p][K] (FP32) from the current and previous fields.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_input(const float *__restrict__ cur,
-                                               const float *__restrict__ prev, int P, int K,
-                                               float mean, float inv_in, float inv_out,
-                                               float *__restrict__ X) {
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= P) return;
-    const float c = cur[p];
-    X[size_t(p) * K] = (c - mean) * inv_in;
-    if (K == 2) X[size_t(p) * K + 1] = (c - prev[p]) * inv_out;
-}
-
-// ---------------------------------------------------------------------------
 // Layer 0 (K -> C) forward, FP32: one lane per pixel computes all 32 output
 // channels.  The weights and biases are the same for every lane, so they are
 // read through the scalar cache and enter the FMAs as scalar operands.  ZOUT
-// keeps the FP32 pre-activations for the backward pass (training); FUSED
-// forms the network input from the fields on the fly (inference: no X buffer,
-// one launch less).  A pixel's 32 BF16 activations go out as four 16-byte
-// stores.
+// keeps the FP32 pre-activations for the backward pass (training).  The
+// network input is formed from the fields on the fly.  A pixel's 32 BF16
+// activations go out as four 16-byte stores.
 // ---------------------------------------------------------------------------
-template <int K, bool ZOUT, bool FUSED>
-__global__ void __launch_bounds__(256) k_first(const float *__restrict__ X, const float *__restrict__ cur,
+template <int K, bool ZOUT>
+__global__ void __launch_bounds__(256) k_first(const float *__restrict__ cur,
                                                const float *__restrict__ prev, float mean, float inv_in,
                                                float inv_out, int B, int H, int W,
                                                const float *__restrict__ w,
@@ -155,14 +141,9 @@ __global__ void __launch_bounds__(256) k_first(const float *__restrict__ X, cons
 #pragma unroll
         for (int kx = 0; kx < 3; ++kx) {
             const size_t q = size_t((n * H + wrapi(y + ky - 1, H)) * W + wrapi(x + kx - 1, W));
-            if constexpr (FUSED) {
-                const float c = cur[q];
-                xi[0][ky * 3 + kx] = (c - mean) * inv_in;
-                if constexpr (K == 2) xi[1][ky * 3 + kx] = (c - prev[q]) * inv_out;
-            } else {
-#pragma unroll
-                for (int ci = 0; ci < K; ++ci) xi[ci][ky * 3 + kx] = X[q * K + ci];
-            }
+            const float c = cur[q];
+            xi[0][ky * 3 + kx] = (c - mean) * inv_in;
+            if constexpr (K == 2) xi[1][ky * 3 + kx] = (c - prev[q]) * inv_out;
         }
 #pragma unroll
     for (int c8 = 0; c8 < SC / 8; ++c8) {
@@ -580,207 +561,435 @@ __global__ void __launch_bounds__(256) k_loss(const float *__restrict__ in,
 }
 
 // Last layer backward-data: dZ_{L-2}[p][c] = SiLU'(z) sum_t dy[p - off(t)] W[c][t]
-// with dy = g - <g>_image (the mean-free projection's adjoint).
+// with dy = g - <g>_image (the mean-free projection's adjoint).  Four lanes per
+// pixel, eight channels each: the FP32 pre-activations arrive and the BF16
+// gradients leave as whole 16-byte pieces of consecutive lanes (the kernel
+// moves 192 B per pixel and little else; one lane per pixel with 2-byte stores
+// took 36 us at 32 images of 128^2, this form 20 us).
 __global__ void __launch_bounds__(256) k_last_bwd(const float *__restrict__ g,
                                                   const double *__restrict__ gsum, int B, int H,
                                                   int W, const float *__restrict__ w,
                                                   const float *__restrict__ zprev,
                                                   bf16 *__restrict__ dz) {
+    __shared__ __attribute__((aligned(16))) float wt[9][SC];
+    for (int k = threadIdx.x; k < 9 * SC; k += 256) wt[k % 9][k / 9] = w[k];
+    __syncthreads();
     const int P = B * H * W;
-    const int p = blockIdx.x * 256 + threadIdx.x;
+    const int o = threadIdx.x & 3;
+    const int p = blockIdx.x * 64 + (threadIdx.x >> 2);
     if (p >= P) return;
+    const size_t at = size_t(p) * SC + 8 * o;
+    const f32x4 zp[2] = {*reinterpret_cast<const f32x4 *>(zprev + at),
+                         *reinterpret_cast<const f32x4 *>(zprev + at + 4)};
     const int x = p % W, t = p / W, yy = t % H, n = t / H;
     const float gm = float(gsum[n] / (H * W));
-    float dyv[9];
+    float da[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
-        for (int kx = 0; kx < 3; ++kx)
-            dyv[ky * 3 + kx] = g[(n * H + wrapi(yy - ky + 1, H)) * W + wrapi(x - kx + 1, W)] - gm;
+        for (int kx = 0; kx < 3; ++kx) {
+            const float dy = g[(n * H + wrapi(yy - ky + 1, H)) * W + wrapi(x - kx + 1, W)] - gm;
+            const f32x4 w0 = *reinterpret_cast<const f32x4 *>(&wt[ky * 3 + kx][8 * o]);
+            const f32x4 w1 = *reinterpret_cast<const f32x4 *>(&wt[ky * 3 + kx][8 * o + 4]);
 #pragma unroll
-    for (int c = 0; c < SC; ++c) {
-        float da = 0.f;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) da += dyv[k] * w[c * 9 + k];
-        dz[size_t(p) * SC + c] = bf16(da * dsilu(zprev[size_t(p) * SC + c]));
-    }
-}
-
-// Weight gradient of the last layer: dW[c][t] = sum_p dy[p] a[p + off(t)][c],
-// db = sum_p dy[p].  Block: 32 channels x 8 pixel groups; FP32 atomics.
-__global__ void __launch_bounds__(256) k_last_wgrad(const float *__restrict__ g,
-                                                    const double *__restrict__ gsum, int B,
-                                                    int H, int W, const bf16 *__restrict__ a,
-                                                    float *__restrict__ dw, float *__restrict__ db,
-                                                    int chunk) {
-    __shared__ float red[8][SC][10];
-    const int c = threadIdx.x & 31, grp = threadIdx.x >> 5;
-    const int P = B * H * W;
-    float acc[10] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const int p_begin = blockIdx.x * chunk, p_end = min(P, p_begin + chunk);
-    for (int p = p_begin + grp; p < p_end; p += 8) {
-        const int x = p % W, t = p / W, yy = t % H, n = t / H;
-        const float dy = g[p] - float(gsum[n] / (H * W));
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx) {
-                const int q = (n * H + wrapi(yy + ky - 1, H)) * W + wrapi(x + kx - 1, W);
-                acc[ky * 3 + kx] += dy * float(a[size_t(q) * SC + c]);
+            for (int c = 0; c < 4; ++c) {
+                da[c] += dy * w0[c];
+                da[4 + c] += dy * w1[c];
             }
-        acc[9] += dy;
-    }
-#pragma unroll
-    for (int k = 0; k < 10; ++k) red[grp][c][k] = acc[k];
-    __syncthreads();
-    if (grp == 0) {
-#pragma unroll
-        for (int k = 0; k < 10; ++k) {
-            float s = 0.f;
-            for (int q = 0; q < 8; ++q) s += red[q][c][k];
-            if (k < 9) atomicAdd(&dw[c * 9 + k], s);
-            else if (c == 0) atomicAdd(db, s);
         }
-    }
-}
-
-// Weight gradient of layer 0: dW[c][ci][t] = sum_p dZ0[p][c] X[p + off(t)][ci],
-// db[c] = sum_p dZ0[p][c].  Block: 32 channels x 8 pixel groups; FP32 atomics.
-template <int K>
-__global__ void __launch_bounds__(256) k_first_wgrad(const bf16 *__restrict__ dz,
-                                                     const float *__restrict__ X, int B, int H,
-                                                     int W, float *__restrict__ dw,
-                                                     float *__restrict__ db, int chunk) {
-    constexpr int NT = 9 * K + 1;
-    __shared__ float red[8][SC][NT];
-    const int c = threadIdx.x & 31, grp = threadIdx.x >> 5;
-    const int P = B * H * W;
-    float acc[NT];
+    bf16x8 out;
 #pragma unroll
-    for (int k = 0; k < NT; ++k) acc[k] = 0.f;
-    const int p_begin = blockIdx.x * chunk, p_end = min(P, p_begin + chunk);
-    for (int p = p_begin + grp; p < p_end; p += 8) {
-        const int x = p % W, t = p / W, yy = t % H, n = t / H;
-        const float d = float(dz[size_t(p) * SC + c]);
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx) {
-                const size_t q = size_t((n * H + wrapi(yy + ky - 1, H)) * W + wrapi(x + kx - 1, W)) * K;
-#pragma unroll
-                for (int ci = 0; ci < K; ++ci) acc[ci * 9 + ky * 3 + kx] += d * X[q + ci];
-            }
-        acc[NT - 1] += d;
-    }
-#pragma unroll
-    for (int k = 0; k < NT; ++k) red[grp][c][k] = acc[k];
-    __syncthreads();
-    if (grp == 0) {
-#pragma unroll
-        for (int k = 0; k < NT; ++k) {
-            float s = 0.f;
-            for (int q = 0; q < 8; ++q) s += red[q][c][k];
-            if (k < NT - 1) atomicAdd(&dw[c * 9 * K + k], s);
-            else atomicAdd(&db[c], s);
-        }
-    }
+    for (int c = 0; c < 8; ++c) out[c] = bf16(da[c] * dsilu(zp[c >> 2][c & 3]));
+    *reinterpret_cast<bf16x8 *>(dz + at) = out;
 }
 
 // ---------------------------------------------------------------------------
-// Weight gradient of a C -> C layer on the matrix cores:
-//   dW[co][ci][t] = sum_p dZ[p][co] a[p + off(t)][ci],  db[co] = sum_p dZ[p][co]
-// a GEMM over K = pixels.  A block stages 32 consecutive pixels of dZ and, for
-// the nine taps, of the shifted activations in LDS, transposed to
-// [channel][pixel] (one copy per horizontal shift keeps 16-byte reads aligned);
-// wave w accumulates taps w, w + 4, w + 8 as 2 x 2 tiles of 16x16x32 MFMA.
+// Weight gradients: GEMMs over the pixels on the matrix cores,
+//   C -> C layers:  dW[co][ci][t] = sum_p dZ[p][co] a[p + off(t)][ci]
+//   first layer:    dW[co][ci][t] = sum_p dZ[p][co] X[p + off(t)][ci]
+//   last layer:     dW[c][t]      = sum_q a[q][c] dy[q - off(t)]
+// and the biases sum_p dZ[p][co], sum_p dy[p].
+//
+// The operands have the pixel as the MFMA's K index, so a lane needs one
+// channel of eight pixels, while memory holds the channels of a pixel side by
+// side.  A tile is staged in LDS as it lies in memory (16-byte pieces).  Lane
+// (r, g) = (l % 16, l / 16) then reads the channel pair (2r, 2r + 1) of pixels
+// g + 4j, j = 0..7, as eight words: the 64 lanes of one read cover four
+// consecutive pixels, 256 contiguous bytes, free of bank conflicts.  The low
+// halves of the words are the operand of the even channels and the high halves
+// that of the odd ones (v_perm), so row m of operand tile mt is channel 2m + mt;
+// any order of K that is the same for both operands gives the same product.
+//
+// Every block sums its tiles in FP32 accumulators and writes one partial
+// result; k_wgrad_sum adds the partials in FP64 in a fixed order, so the
+// gradient does not depend on the order in which blocks finish.
 // ---------------------------------------------------------------------------
-constexpr int WSEG = 32;
-constexpr int WPAD = 40;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-__global__ void __launch_bounds__(256) k_mid_wgrad(const bf16 *__restrict__ dz,
+constexpr int WG_TR = 16, WG_TW = 32;  // pixel tile (W is a multiple of 32)
+constexpr int WG_AW = WG_TW + 2;       // activations with their one-pixel halo
+constexpr int WG_MAX_BLOCKS = 256;     // one per CU
+constexpr int WG_EDGE_BLOCKS = 512;    // two per CU
+constexpr int WG_LEN = 9 * SC * SC + SC;
+constexpr int WG_DZ_PIECES = WG_TR * WG_TW * 4, WG_A_PIECES = (WG_TR + 2) * WG_AW * 4;
+// words of LDS: the staged tile, then (reused) the sums of two of four row
+// groups, three kernel rows of 56 accumulators per lane each
+constexpr int WG_LDS = std::max((WG_DZ_PIECES + WG_A_PIECES) * 4, 2 * 3 * 56 * 64);
+
+__host__ __device__ inline int wg_tiles(int B, int H, int W) {
+    return B * ((H + WG_TR - 1) / WG_TR) * (W / WG_TW);
+}
+
+// operands of the even and the odd channels from eight channel-pair words
+__device__ __forceinline__ void split_pairs(const uint32_t (&d)[8], bf16x8 &even, bf16x8 &odd) {
+    u32x4 e, o;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        e[k] = __builtin_amdgcn_perm(d[2 * k + 1], d[2 * k], 0x05040100u);
+        o[k] = __builtin_amdgcn_perm(d[2 * k + 1], d[2 * k], 0x07060302u);
+    }
+    even = __builtin_bit_cast(bf16x8, e);
+    odd = __builtin_bit_cast(bf16x8, o);
+}
+
+// C -> C layer.  A block of 12 waves marches over tiles of 16 rows x 32
+// columns; wave (ky, pg) takes the three taps of kernel row ky over the tile's
+// rows 4pg .. 4pg + 3 (12 MFMAs per 32 pixels), which keeps its accumulators at
+// 48 registers.  The next tile is on its way in registers while this one is
+// multiplied.  Bounds at 32 images of 128^2: 67 MB of operands, 11 us at the
+// card's copy rate, and 9.7 GFLOP.  Measured 23.4 us; staging transposed
+// copies with 2-byte LDS stores and adding 9216 atomics per block took 527 us.
+// element e of a block's partial result: ((t * 4 + 2 mt + nt) * 4 + r) * 64 + lane
+// for dW[2 (4g + r) + mt][2 (lane % 16) + nt][t], then the 32 biases.
+__global__ void __launch_bounds__(768) k_mid_wgrad(const bf16 *__restrict__ dz,
                                                    const bf16 *__restrict__ ain, int B, int H,
-                                                   int W, float *__restrict__ dw,
-                                                   float *__restrict__ db) {
-    __shared__ __attribute__((aligned(16))) bf16 sdz[SC][WPAD];
-    __shared__ __attribute__((aligned(16))) bf16 sa[3][3][SC][WPAD];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+                                                   int W, float *__restrict__ part) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[WG_LDS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int r16 = lane & 15, g = lane >> 4;
-    f32x4 acc[3][2][2];
+    const int ky = wave % 3, pg = wave / 3;
+    const int txs = W / WG_TW, tys = (H + WG_TR - 1) / WG_TR;
+    const int tiles = wg_tiles(B, H, W);
+    constexpr int PRE = (WG_DZ_PIECES + WG_A_PIECES + 767) / 768;
+    u32x4 pre[PRE];
+    auto fetch = [&](int tile) {
+        const int x0 = (tile % txs) * WG_TW, t1 = tile / txs;
+        const int y0 = (t1 % tys) * WG_TR, n = t1 / tys;
 #pragma unroll
-    for (int s = 0; s < 3; ++s)
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) acc[s][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bacc = 0.f;
-    const int nseg = (B * H * W) / WSEG;
-    for (int seg = blockIdx.x; seg < nseg; seg += gridDim.x) {
-        const int p0 = seg * WSEG;
-        const int x0 = p0 % W, t2 = p0 / W, y = t2 % H, n = t2 / H;
-        __syncthreads();
-        // dZ tile: 32 pixels x 32 channels, 4 values per thread
-        {
-            const int e = tid * 4;
-            const int j = e / SC, c = e % SC;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) sdz[c + k][j] = dz[size_t(p0 + j) * SC + c + k];
-        }
-        // shifted activation tiles
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky) {
-            const int rowbase = (n * H + wrapi(y + ky - 1, H)) * W;
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx) {
-                const int e = tid * 4;
-                const int j = e / SC, c = e % SC;
-                const size_t q = size_t(rowbase + wrapi(x0 + j + kx - 1, W));
-#pragma unroll
-                for (int k = 0; k < 4; ++k) sa[kx][ky][c + k][j] = ain[q * SC + c + k];
+        for (int i = 0; i < PRE; ++i) {
+            const int k = tid + i * 768;
+            pre[i] = u32x4{0u, 0u, 0u, 0u};
+            if (k < WG_DZ_PIECES) {
+                const int px = k >> 2, y = y0 + px / WG_TW, x = x0 + px % WG_TW;
+                if (y < H)
+                    pre[i] = *reinterpret_cast<const u32x4 *>(dz + size_t((n * H + y) * W + x) * SC + (k & 3) * 8);
+            } else if (k < WG_DZ_PIECES + WG_A_PIECES) {
+                const int k2 = k - WG_DZ_PIECES, px = k2 >> 2;
+                const int r = px / WG_AW, c = px % WG_AW;
+                // rows past the image's end and its halo are not used: any valid row
+                const int y = wrapi(min(y0 - 1 + r, H), H), x = wrapi(x0 - 1 + c, W);
+                pre[i] = *reinterpret_cast<const u32x4 *>(ain + size_t((n * H + y) * W + x) * SC + (k2 & 3) * 8);
             }
         }
-        __syncthreads();
-        if (tid < SC) {
-            float s = 0.f;
+    };
+    f32x4 acc[3][2][2], accb[2];
 #pragma unroll
-            for (int j = 0; j < WSEG; ++j) s += float(sdz[tid][j]);
-            bacc += s;
-        }
-        bf16x8 aop[2];
+    for (int k = 0; k < 3; ++k)
 #pragma unroll
         for (int mt = 0; mt < 2; ++mt)
-            aop[mt] = *reinterpret_cast<const bf16x8 *>(&sdz[mt * 16 + r16][8 * g]);
 #pragma unroll
-        for (int s = 0; s < 3; ++s) {
-            const int t = wave + 4 * s;
-            if (t < 9) {
-                const int ky = t / 3, kx = t % 3;
+            for (int nt = 0; nt < 2; ++nt) acc[k][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    accb[0] = accb[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const u32x4 one4 = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, one4);
+    fetch(blockIdx.x);
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        __syncthreads();
 #pragma unroll
-                for (int nt = 0; nt < 2; ++nt) {
-                    const bf16x8 bop =
-                        *reinterpret_cast<const bf16x8 *>(&sa[kx][ky][nt * 16 + r16][8 * g]);
+        for (int i = 0; i < PRE; ++i) {
+            const int k = tid + i * 768;
+            if (k < WG_DZ_PIECES + WG_A_PIECES) *reinterpret_cast<u32x4 *>(lds + k * 4) = pre[i];
+        }
+        __syncthreads();
+        if (tile + int(gridDim.x) < tiles) fetch(tile + gridDim.x);
+        const int y0 = ((tile / txs) % tys) * WG_TR;
 #pragma unroll
-                    for (int mt = 0; mt < 2; ++mt) acc[s][mt][nt] = mfma16(aop[mt], bop, acc[s][mt][nt]);
-                }
+        for (int rr = 0; rr < 4; ++rr) {
+            const int row = pg * 4 + rr;
+            if (y0 + row >= H) break;  // wave-uniform
+            uint32_t d[8];
+            bf16x8 aop[2];
+            const uint32_t *dp = lds + (row * WG_TW + g) * 16 + r16;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) d[j] = dp[j * 64];
+            split_pairs(d, aop[0], aop[1]);
+            if (ky == 0) {
+                accb[0] = mfma16(aop[0], ones, accb[0]);
+                accb[1] = mfma16(aop[1], ones, accb[1]);
+            }
+            const uint32_t *ap = lds + WG_DZ_PIECES * 4 + ((row + ky) * WG_AW + g) * 16 + r16;
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+                bf16x8 bop[2];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) d[j] = ap[kx * 16 + j * 64];
+                split_pairs(d, bop[0], bop[1]);
+#pragma unroll
+                for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < 2; ++nt) acc[kx][mt][nt] = mfma16(aop[mt], bop[nt], acc[kx][mt][nt]);
             }
         }
     }
+    // the four row groups of each kernel row: 2, 3 into 0, 1, then 1 into 0
+    float *red = reinterpret_cast<float *>(lds);  // [2][3][56][64]
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        const int t = wave + 4 * s;
-        if (t < 9) {
+    for (int half = 2; half >= 1; half >>= 1) {
+        __syncthreads();
+        if (pg >= half && pg < 2 * half) {
+            float *q = red + ((pg - half) * 3 + ky) * 56 * 64 + lane;
+#pragma unroll
+            for (int k = 0; k < 12; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) q[(k * 4 + r) * 64] = acc[k >> 2][(k >> 1) & 1][k & 1][r];
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-                for (int nt = 0; nt < 2; ++nt)
+                for (int r = 0; r < 4; ++r) q[(48 + mt * 4 + r) * 64] = accb[mt][r];
+        }
+        __syncthreads();
+        if (pg < half) {
+            const float *q = red + (pg * 3 + ky) * 56 * 64 + lane;
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int co = mt * 16 + 4 * g + r, ci = nt * 16 + r16;
-                        atomicAdd(&dw[(co * SC + ci) * 9 + t], acc[s][mt][nt][r]);
-                    }
+            for (int k = 0; k < 12; ++k)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[k >> 2][(k >> 1) & 1][k & 1][r] += q[(k * 4 + r) * 64];
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) accb[mt][r] += q[(48 + mt * 4 + r) * 64];
         }
     }
-    if (tid < SC) atomicAdd(&db[tid], bacc);
+    if (pg != 0) return;
+    float *out = part + size_t(blockIdx.x) * WG_LEN;
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            out[(((ky * 3 + (k >> 2)) * 4 + (k & 3)) * 4 + r) * 64 + lane] = acc[k >> 2][(k >> 1) & 1][k & 1][r];
+    if (ky == 0 && r16 == 0) {
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) out[9 * SC * SC + 2 * (4 * g + r) + mt] = accb[mt][r];
+    }
+}
+
+// First (LAST = false) and last layer: one operand is the BF16 activation
+// gradient (activation) of the 32 channels, the other an FP32 field per input
+// channel, the network input X formed from the fields (or dy = g - <g>).  Each
+// FP32 value enters as three BF16 parts that sum to it exactly, so that the
+// products are exact and the sums FP32, as with FP32 factors: columns (part,
+// ci, tap) of the second operand, 27 per input channel, then one of ones
+// (sum_p dZ[p][co], the first layer's bias).  Four waves, four rows of the
+// tile each.  It reads 64 + 4K B per pixel.  Measured at 32 images of 128^2:
+// 21.1 us (first, K = 2) and 14.9 us (last); one lane per channel
+// with FP32 FMAs and atomics took 251 and 178 us.
+// Element of a block's partial result: (nt * 2 + mt) * 256 + r * 64 + lane for
+// channel 2 (4g + r) + mt and column 16 nt + lane % 16, then sum_p of the field.
+template <int K>
+constexpr int wg_edge_tiles() { return K == 1 ? 2 : 4; }  // columns / 16
+template <int K>
+constexpr int wg_edge_len() { return wg_edge_tiles<K>() * 512 + 1; }
+
+template <int K, bool LAST>
+__global__ void __launch_bounds__(256) k_edge_wgrad(const bf16 *__restrict__ act, const float *__restrict__ cur,
+                                                    const float *__restrict__ prev, float mean, float inv_in,
+                                                    float inv_out, const double *__restrict__ gsum, int B,
+                                                    int H, int W, float *__restrict__ part) {
+    static_assert(!LAST || K == 1, "the last layer has one output");
+    constexpr int NT = wg_edge_tiles<K>();
+    constexpr int PL = (WG_TR + 2) * WG_AW;  // values per part plane
+    __shared__ __attribute__((aligned(16))) uint32_t sact[WG_DZ_PIECES * 4];
+    __shared__ uint16_t sx[K * 3 * PL + 2];  // planes [ci][part], then 1 and 0
+    __shared__ float red[3][NT * 2 * 4 * 64];
+    __shared__ double dred[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int r16 = lane & 15, g = lane >> 4;
+    const int txs = W / WG_TW, tys = (H + WG_TR - 1) / WG_TR;
+    const int tiles = wg_tiles(B, H, W);
+    // this lane's columns: offset of pixel (row 0, column g) and the step of four pixels
+    int base[NT], hop[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int q = nt * 16 + r16;
+        if (q < 27 * K) {
+            const int pt = q / (9 * K), ci = (q / 9) % K, tap = q % 9;
+            const int ky = LAST ? 2 - tap / 3 : tap / 3, kx = LAST ? 2 - tap % 3 : tap % 3;
+            base[nt] = (ci * 3 + pt) * PL + ky * WG_AW + kx + g;
+            hop[nt] = 1;
+        } else {
+            base[nt] = K * 3 * PL + (q == 27 * K ? 0 : 1);
+            hop[nt] = 0;
+        }
+    }
+    if (tid == 0) {
+        sx[K * 3 * PL] = 0x3F80u;  // 1
+        sx[K * 3 * PL + 1] = 0u;
+    }
+    f32x4 acc[NT][2];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) acc[nt][0] = acc[nt][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    double fsum = 0.0;
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        const int x0 = (tile % txs) * WG_TW, t1 = tile / txs;
+        const int y0 = (t1 % tys) * WG_TR, n = t1 / tys;
+        const float gm = LAST ? float(gsum[n] / (H * W)) : 0.f;
+        __syncthreads();
+        for (int k = tid; k < WG_DZ_PIECES; k += 256) {
+            const int px = k >> 2, y = y0 + px / WG_TW, x = x0 + px % WG_TW;
+            if (y < H)
+                *reinterpret_cast<u32x4 *>(sact + k * 4) =
+                    *reinterpret_cast<const u32x4 *>(act + size_t((n * H + y) * W + x) * SC + (k & 3) * 8);
+        }
+        for (int k = tid; k < PL; k += 256) {
+            const int r = k / WG_AW, c = k % WG_AW;
+            const int y = wrapi(min(y0 - 1 + r, H), H), x = wrapi(x0 - 1 + c, W);
+            const size_t q = size_t(n * H + y) * W + x;
+            const float v0 = cur[q];
+            float v[2] = {LAST ? v0 - gm : (v0 - mean) * inv_in, 0.f};
+            if constexpr (K == 2) v[1] = (v0 - prev[q]) * inv_out;
+            if (LAST && r >= 1 && r <= WG_TR && c >= 1 && c <= WG_TW && y0 - 1 + r < H) fsum += double(v[0]);
+#pragma unroll
+            for (int ci = 0; ci < K; ++ci) {
+                const bf16 hi = bf16(v[ci]);
+                const float r1 = v[ci] - float(hi);
+                const bf16 mid = bf16(r1);
+                const bf16 lo = bf16(r1 - float(mid));
+                sx[(ci * 3 + 0) * PL + k] = __builtin_bit_cast(uint16_t, hi);
+                sx[(ci * 3 + 1) * PL + k] = __builtin_bit_cast(uint16_t, mid);
+                sx[(ci * 3 + 2) * PL + k] = __builtin_bit_cast(uint16_t, lo);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int rr = 0; rr < WG_TR / 4; ++rr) {
+            const int row = wave * (WG_TR / 4) + rr;
+            if (y0 + row >= H) break;  // wave-uniform
+            uint32_t d[8];
+            bf16x8 aop[2];
+            const uint32_t *dp = sact + (row * WG_TW + g) * 16 + r16;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) d[j] = dp[j * 64];
+            split_pairs(d, aop[0], aop[1]);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const uint16_t *xp = sx + base[nt] + hop[nt] * row * WG_AW;
+                u32x4 b4;
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    b4[k] = uint32_t(xp[hop[nt] * 8 * k]) | (uint32_t(xp[hop[nt] * (8 * k + 4)]) << 16);
+                const bf16x8 bop = __builtin_bit_cast(bf16x8, b4);
+                acc[nt][0] = mfma16(aop[0], bop, acc[nt][0]);
+                acc[nt][1] = mfma16(aop[1], bop, acc[nt][1]);
+            }
+        }
+    }
+    if (LAST) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) fsum += __shfl_xor(fsum, o, 64);
+        if (lane == 0) dred[wave] = fsum;
+    }
+    if (wave > 0) {
+#pragma unroll
+        for (int k = 0; k < NT * 2; ++k)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) red[wave - 1][k * 256 + r * 64 + lane] = acc[k >> 1][k & 1][r];
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    float *out = part + size_t(blockIdx.x) * wg_edge_len<K>();
+#pragma unroll
+    for (int k = 0; k < NT * 2; ++k)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int e = k * 256 + r * 64 + lane;
+            out[e] = (acc[k >> 1][k & 1][r] + red[0][e]) + (red[1][e] + red[2][e]);
+        }
+    if (lane == 0) out[NT * 512] = LAST ? float((dred[0] + dred[1]) + (dred[2] + dred[3])) : 0.f;
+}
+
+// Sums the blocks' partial results of every layer into the gradient vector
+// (each partial once, in FP64, in a fixed order): a block takes 64 elements
+// of one layer, its four waves a quarter of the partials each.
+struct WgradSum {
+    int nmid, mid_blocks, edge_blocks, in_ch;
+    const float *mid, *first, *last;  // [layer][block][WG_LEN], [block][len]
+    int woff0, boff0, woff1, mid_stride, woffl, boffl;  // offsets in the gradient vector
+};
+constexpr int WG_MID_GROUPS = (WG_LEN + 63) / 64;
+
+__device__ inline double wg_column(const float *__restrict__ part, int blocks, int len, int e) {
+    double s = 0.0;
+    for (int b = threadIdx.x >> 6; b < blocks; b += 4) s += double(part[size_t(b) * len + e]);
+    return s;
+}
+
+template <int K>
+__device__ inline double wg_edge_value(const float *__restrict__ part, int blocks, int ch, int col) {
+    const int mt = ch & 1, row = ch >> 1;  // channel 2 (4g + r) + mt
+    const int e = ((col >> 4) * 2 + mt) * 256 + (row & 3) * 64 + (row >> 2) * 16 + (col & 15);
+    return wg_column(part, blocks, wg_edge_len<K>(), e);
+}
+
+__global__ void __launch_bounds__(256) k_wgrad_sum(WgradSum a, float *__restrict__ grads) {
+    __shared__ double sh[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int mid_groups = a.nmid * WG_MID_GROUPS;
+    double s = 0.0;
+    int dst = -1;
+    if (int(blockIdx.x) < mid_groups) {
+        const int l = blockIdx.x / WG_MID_GROUPS, e = (blockIdx.x % WG_MID_GROUPS) * 64 + lane;
+        if (e < WG_LEN) {
+            s = wg_column(a.mid + size_t(l) * a.mid_blocks * WG_LEN, a.mid_blocks, WG_LEN, e);
+            const int base = a.woff1 + l * a.mid_stride;
+            if (e < 9 * SC * SC) {
+                const int q = e >> 6, el = e & 63;
+                const int r = q & 3, nt = (q >> 2) & 1, mt = (q >> 3) & 1, t = q >> 4;
+                const int co = 2 * (4 * (el >> 4) + r) + mt, ci = 2 * (el & 15) + nt;
+                dst = base + (co * SC + ci) * 9 + t;
+            } else {
+                dst = base + e;  // the biases follow the weights
+            }
+        }
+    } else {
+        const int e = (int(blockIdx.x) - mid_groups) * 64 + lane;
+        const int n0 = SC * (9 * a.in_ch + 1), nl = SC * 9 + 1;  // first layer, last layer
+        if (e < n0) {
+            const int ch = e / (9 * a.in_ch + 1), k = e % (9 * a.in_ch + 1);
+            const bool bias = k == 9 * a.in_ch;  // the column of ones
+            dst = bias ? a.boff0 + ch : a.woff0 + ch * 9 * a.in_ch + k;
+            for (int pt = 0; pt < (bias ? 1 : 3); ++pt) {
+                const int col = (bias ? 27 * a.in_ch : pt * 9 * a.in_ch + k);
+                s += a.in_ch == 2 ? wg_edge_value<2>(a.first, a.edge_blocks, ch, col)
+                                  : wg_edge_value<1>(a.first, a.edge_blocks, ch, col);
+            }
+        } else if (e < n0 + nl) {
+            const int k = e - n0;
+            if (k < SC * 9) {
+                dst = a.woffl + k;
+                for (int pt = 0; pt < 3; ++pt)
+                    s += wg_edge_value<1>(a.last, a.edge_blocks, k / 9, pt * 9 + k % 9);
+            } else {
+                dst = a.boffl;
+                s = wg_column(a.last, a.edge_blocks, wg_edge_len<1>(), wg_edge_len<1>() - 1);
+            }
+        }
+    }
+    sh[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && dst >= 0)
+        grads[dst] = float((sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]));
 }
 
 // BF16 packings of a C -> C layer: forward wf[t][co][ci], adjoint wb[t][ci][co]
@@ -974,7 +1183,9 @@ struct fsc_sur {
     std::vector<float *> z;            // [layers - 1] of P x 32
     std::vector<bf16 *> a;             // [layers - 1] of P x 32
     bf16 *dzA = nullptr, *dzB = nullptr;
-    float *y = nullptr, *gbuf = nullptr, *X = nullptr;
+    float *y = nullptr, *gbuf = nullptr;
+    float *wpart = nullptr;  // blocks' partial weight gradients: C -> C layers, first, last
+    int wblocks = 0, eblocks = 0;  // blocks of a weight-gradient launch at max_batch
     double *ysum = nullptr, *gsum = nullptr, *loss = nullptr;
     double *part = nullptr;  // [maxB][IMG_PARTS] segment sums
     int64_t adam_t = 0;
@@ -1011,7 +1222,7 @@ void sur_free(fsc_sur *s) {
     if (!s) return;
     (void)hipStreamSynchronize(s->stream);
     void *ptrs[] = {s->params, s->grads, s->m,    s->v,    s->wf,   s->wb, s->wl3, s->dzA,
-                    s->dzB,    s->y,     s->gbuf, s->ysum, s->gsum, s->loss, s->X, s->part};
+                    s->dzB,    s->y,     s->gbuf, s->ysum, s->gsum, s->loss, s->wpart, s->part};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto p : s->z)
@@ -1086,30 +1297,18 @@ int img_sums(fsc_sur *s, const float *v, int B, double *out) {
 }
 
 // forward pass up to y (and the per-image sums of y); `train` keeps what the
-// backward pass needs (the FP32 pre-activations and the input X)
+// backward pass needs (the FP32 pre-activations)
 int sur_forward_core(fsc_sur *s, const float *prev, const float *cur, int B, bool train) {
     const int P = B * s->H * s->W;
     const unsigned nb = unsigned((P + 255) / 256);
     const float ii = 1.f / s->in_scale, io = 1.f / s->out_scale;
     const float *w0 = s->params + s->woff[0], *b0 = s->params + s->boff[0];
-    if (train) {
-        hipLaunchKernelGGL(k_input, dim3(nb), dim3(256), 0, s->stream, cur, prev, P, s->in_ch, s->mean,
-                           ii, io, s->X);
-        SCHK(s, hipGetLastError());
-        if (s->in_ch == 2)
-            hipLaunchKernelGGL((k_first<2, true, false>), dim3(nb), dim3(256), 0, s->stream, s->X, cur,
-                               prev, s->mean, ii, io, B, s->H, s->W, w0, b0, s->z[0], s->a[0]);
-        else
-            hipLaunchKernelGGL((k_first<1, true, false>), dim3(nb), dim3(256), 0, s->stream, s->X, cur,
-                               prev, s->mean, ii, io, B, s->H, s->W, w0, b0, s->z[0], s->a[0]);
-    } else {
-        if (s->in_ch == 2)
-            hipLaunchKernelGGL((k_first<2, false, true>), dim3(nb), dim3(256), 0, s->stream, s->X, cur,
-                               prev, s->mean, ii, io, B, s->H, s->W, w0, b0, s->z[0], s->a[0]);
-        else
-            hipLaunchKernelGGL((k_first<1, false, true>), dim3(nb), dim3(256), 0, s->stream, s->X, cur,
-                               prev, s->mean, ii, io, B, s->H, s->W, w0, b0, s->z[0], s->a[0]);
-    }
+    auto first = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(nb), dim3(256), 0, s->stream, cur, prev, s->mean, ii, io, B, s->H,
+                           s->W, w0, b0, s->z[0], s->a[0]);
+    };
+    if (s->in_ch == 2) train ? first(k_first<2, true>) : first(k_first<2, false>);
+    else train ? first(k_first<1, true>) : first(k_first<1, false>);
     SCHK(s, hipGetLastError());
     const int tiles = P / 16;
     const unsigned mb = unsigned(std::min(2048, std::max(1, tiles / 16)));
@@ -1155,35 +1354,50 @@ int sur_forward_core(fsc_sur *s, const float *prev, const float *cur, int B, boo
     return FSC_OK;
 }
 
-int sur_backward(fsc_sur *s, const float *in, const float *tgt, int B) {
+int sur_backward(fsc_sur *s, const float *prev, const float *in, const float *tgt, int B) {
     const int H = s->H, W = s->W, P = B * H * W;
     const unsigned nb = unsigned((P + 255) / 256);
-    SCHK(s, hipMemsetAsync(s->grads, 0, sizeof(float) * s->nparams, s->stream));
+    const float ii = 1.f / s->in_scale, io = 1.f / s->out_scale;
     SCHK(s, hipMemsetAsync(s->loss, 0, sizeof(double), s->stream));
-    hipLaunchKernelGGL(k_loss, dim3(nb), dim3(256), 0, s->stream, in, tgt, s->y, s->ysum, P, H * W,
-                       1.f / s->out_scale, 1.f / float(P), s->gbuf, s->loss);
+    hipLaunchKernelGGL(k_loss, dim3(nb), dim3(256), 0, s->stream, in, tgt, s->y, s->ysum, P, H * W, io,
+                       1.f / float(P), s->gbuf, s->loss);
     SCHK(s, hipGetLastError());
     {
         int rc = img_sums(s, s->gbuf, B, s->gsum);
         if (rc) return rc;
     }
     const int last = s->layers - 1;
-    const int chunk = 2048;
-    const unsigned cb = unsigned((P + chunk - 1) / chunk);
-    hipLaunchKernelGGL(k_last_wgrad, dim3(cb), dim3(256), 0, s->stream, s->gbuf, s->gsum, B, H, W,
-                       s->a[last - 1], s->grads + s->woff[last], s->grads + s->boff[last], chunk);
+    const int wtiles = wg_tiles(B, H, W);
+    WgradSum ws{};
+    ws.nmid = nmid(s);
+    ws.in_ch = s->in_ch;
+    ws.mid_blocks = std::min(wtiles, WG_MAX_BLOCKS);
+    ws.edge_blocks = std::min(wtiles, WG_EDGE_BLOCKS);
+    float *pmid = s->wpart, *pfirst = pmid + size_t(nmid(s)) * s->wblocks * WG_LEN;
+    float *plast = pfirst + size_t(s->eblocks) * wg_edge_len<2>();
+    ws.mid = pmid;
+    ws.first = pfirst;
+    ws.last = plast;
+    ws.woff0 = int(s->woff[0]);
+    ws.boff0 = int(s->boff[0]);
+    ws.woff1 = int(s->woff[1]);
+    ws.mid_stride = WG_LEN;
+    ws.woffl = int(s->woff[last]);
+    ws.boffl = int(s->boff[last]);
+    const dim3 eb(unsigned(ws.edge_blocks));
+    hipLaunchKernelGGL((k_edge_wgrad<1, true>), eb, dim3(256), 0, s->stream, s->a[last - 1], s->gbuf, nullptr,
+                       0.f, 0.f, 0.f, s->gsum, B, H, W, plast);
     SCHK(s, hipGetLastError());
     bf16 *dz = s->dzA, *dzn = s->dzB;
-    hipLaunchKernelGGL(k_last_bwd, dim3(nb), dim3(256), 0, s->stream, s->gbuf, s->gsum, B, H, W,
-                       s->params + s->woff[last], s->z[last - 1], dz);
+    hipLaunchKernelGGL(k_last_bwd, dim3(unsigned((P + 63) / 64)), dim3(256), 0, s->stream, s->gbuf, s->gsum, B,
+                       H, W, s->params + s->woff[last], s->z[last - 1], dz);
     SCHK(s, hipGetLastError());
     const int tiles = P / 16;
     const unsigned mb = unsigned(std::min(2048, std::max(1, tiles / 16)));
-    const unsigned wgb = unsigned(std::min(1024, std::max(1, P / WSEG / 8)));
     for (int l = nmid(s); l >= 1; --l) {
         // dz holds dL/dz_l; weight gradient, then dL/dz_{l-1}
-        hipLaunchKernelGGL(k_mid_wgrad, dim3(wgb), dim3(256), 0, s->stream, dz, s->a[l - 1], B, H,
-                           W, s->grads + s->woff[l], s->grads + s->boff[l]);
+        hipLaunchKernelGGL(k_mid_wgrad, dim3(unsigned(ws.mid_blocks)), dim3(768), 0, s->stream, dz, s->a[l - 1],
+                           B, H, W, pmid + size_t(l - 1) * ws.mid_blocks * WG_LEN);
         SCHK(s, hipGetLastError());
         const size_t off = size_t(l - 1) * 9 * SC * SC;
         if (lds_tiles(s))
@@ -1196,11 +1410,15 @@ int sur_backward(fsc_sur *s, const float *in, const float *tgt, int B) {
         std::swap(dz, dzn);
     }
     if (s->in_ch == 2)
-        hipLaunchKernelGGL(k_first_wgrad<2>, dim3(cb), dim3(256), 0, s->stream, dz, s->X, B, H, W,
-                           s->grads + s->woff[0], s->grads + s->boff[0], chunk);
+        hipLaunchKernelGGL((k_edge_wgrad<2, false>), eb, dim3(256), 0, s->stream, dz, in, prev, s->mean, ii, io,
+                           nullptr, B, H, W, pfirst);
     else
-        hipLaunchKernelGGL(k_first_wgrad<1>, dim3(cb), dim3(256), 0, s->stream, dz, s->X, B, H, W,
-                           s->grads + s->woff[0], s->grads + s->boff[0], chunk);
+        hipLaunchKernelGGL((k_edge_wgrad<1, false>), eb, dim3(256), 0, s->stream, dz, in, prev, s->mean, ii, io,
+                           nullptr, B, H, W, pfirst);
+    SCHK(s, hipGetLastError());
+    const int edge = SC * (9 * s->in_ch + 1) + SC * 9 + 1;
+    hipLaunchKernelGGL(k_wgrad_sum, dim3(unsigned(ws.nmid * WG_MID_GROUPS + (edge + 63) / 64)), dim3(256), 0,
+                       s->stream, ws, s->grads);
     SCHK(s, hipGetLastError());
     return FSC_OK;
 }
@@ -1258,6 +1476,10 @@ int fsc_sur_create(int layers, int in_ch, int H, int W, int max_batch, uint64_t 
     }
     s->nparams = o;
     const size_t P = size_t(max_batch) * H * W;
+    s->wblocks = std::min(wg_tiles(max_batch, H, W), WG_MAX_BLOCKS);
+    s->eblocks = std::min(wg_tiles(max_batch, H, W), WG_EDGE_BLOCKS);
+    const size_t wlen = size_t(layers - 2) * s->wblocks * WG_LEN +
+                        size_t(s->eblocks) * (wg_edge_len<2>() + wg_edge_len<1>());
     bool ok = hipMalloc(&s->params, sizeof(float) * o) == hipSuccess &&
               hipMalloc(&s->grads, sizeof(float) * o) == hipSuccess &&
               hipMalloc(&s->m, sizeof(float) * o) == hipSuccess &&
@@ -1269,7 +1491,7 @@ int fsc_sur_create(int layers, int in_ch, int H, int W, int max_batch, uint64_t 
               hipMalloc(&s->dzB, sizeof(bf16) * P * SC) == hipSuccess &&
               hipMalloc(&s->y, sizeof(float) * P) == hipSuccess &&
               hipMalloc(&s->gbuf, sizeof(float) * P) == hipSuccess &&
-              hipMalloc(&s->X, sizeof(float) * P * in_ch) == hipSuccess &&
+              hipMalloc(&s->wpart, sizeof(float) * wlen) == hipSuccess &&
               hipMalloc(&s->ysum, sizeof(double) * max_batch) == hipSuccess &&
               hipMalloc(&s->part, sizeof(double) * IMG_PARTS * max_batch) == hipSuccess &&
               hipMalloc(&s->gsum, sizeof(double) * max_batch) == hipSuccess &&
@@ -1379,7 +1601,7 @@ int fsc_sur_grad(fsc_sur *s, const float *dev_prev, const float *dev_in, const f
     if (rc) return rc;
     rc = sur_forward_core(s, dev_prev, dev_in, batch, true);
     if (rc) return rc;
-    rc = sur_backward(s, dev_in, dev_target, batch);
+    rc = sur_backward(s, dev_prev, dev_in, dev_target, batch);
     if (rc) return rc;
     if (host_grad)
         SCHK(s, hipMemcpyAsync(host_grad, s->grads, sizeof(float) * s->nparams,
@@ -1401,7 +1623,7 @@ int fsc_sur_train_step(fsc_sur *s, const float *dev_prev, const float *dev_in,
     if (rc) return rc;
     rc = sur_forward_core(s, dev_prev, dev_in, batch, true);
     if (rc) return rc;
-    rc = sur_backward(s, dev_in, dev_target, batch);
+    rc = sur_backward(s, dev_prev, dev_in, dev_target, batch);
     if (rc) return rc;
     s->adam_t += 1;
     const float b1 = 0.9f, b2 = 0.999f;
