@@ -99,9 +99,12 @@ __device__ __forceinline__ void mid_epilogue(const f32x4 (&acc)[2], size_t pix, 
             for (int r = 0; r < 4; ++r) out[4 * nt + r] = bf16(silu(acc[nt][r]));
         }
     }
-    // non-temporal: the next layer reads the records from memory anyway
-    // (3% per rollout pass against the default policy)
-    __builtin_nontemporal_store(out, reinterpret_cast<bf16x8 *>(aout + o));
+    // inference: non-temporal, the next layer reads the records from memory
+    // anyway (3% per rollout pass against the default policy).  Training keeps
+    // them cached: the launch after this one reads them (an Adam step of the
+    // nine-layer network on 32 images of 128^2: 876 against 920 us).
+    if (BWD || ZOUT) *reinterpret_cast<bf16x8 *>(aout + o) = out;
+    else __builtin_nontemporal_store(out, reinterpret_cast<bf16x8 *>(aout + o));
 }
 
 __global__ void k_mfma_probe(const float *A, const float *B, float *Cm) {
@@ -122,7 +125,11 @@ __global__ void k_mfma_probe(const float *A, const float *B, float *Cm) {
 // read through the scalar cache and enter the FMAs as scalar operands.  ZOUT
 // keeps the FP32 pre-activations for the backward pass (training).  The
 // network input is formed from the fields on the fly.  A pixel's 32 BF16
-// activations go out as four 16-byte stores.
+// activations go out as four 16-byte stores.  In training the pre-activations
+// are twice as many bytes as those, and lane-strided 16-byte pieces of 128-byte
+// records took 44 us at 32 images of 128^2 (100 MB written): there a wave
+// passes them through LDS and stores 1 KB of consecutive bytes at a time
+// (31.3 us).
 // ---------------------------------------------------------------------------
 template <int K, bool ZOUT>
 __global__ void __launch_bounds__(256) k_first(const float *__restrict__ cur,
@@ -132,9 +139,14 @@ __global__ void __launch_bounds__(256) k_first(const float *__restrict__ cur,
                                                const float *__restrict__ b, float *__restrict__ z,
                                                bf16 *__restrict__ a) {
     const int P = B * H * W;
+    [[maybe_unused]] const int wave = threadIdx.x >> 6;
+    // training: a wave's pre-activations, pieces of four channels, pixel l's at
+    // 8 l + (piece ^ (l % 8)), so that neither side meets a bank conflict
+    __shared__ __attribute__((aligned(16))) f32x4 zt[ZOUT ? 4 : 1][ZOUT ? 64 * 8 : 1];
     const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= P) return;
-    const int x = p % W, t = p / W, y = t % H, n = t / H;
+    if (!ZOUT && p >= P) return;
+    const int pc = min(p, P - 1);  // lanes past the end repeat the last pixel
+    const int x = pc % W, t = pc / W, y = t % H, n = t / H;
     float xi[K][9];
 #pragma unroll
     for (int ky = 0; ky < 3; ++ky)
@@ -145,6 +157,7 @@ __global__ void __launch_bounds__(256) k_first(const float *__restrict__ cur,
             xi[0][ky * 3 + kx] = (c - mean) * inv_in;
             if constexpr (K == 2) xi[1][ky * 3 + kx] = (c - prev[q]) * inv_out;
         }
+    [[maybe_unused]] const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int c8 = 0; c8 < SC / 8; ++c8) {
         bf16x8 out;
@@ -158,13 +171,30 @@ __global__ void __launch_bounds__(256) k_first(const float *__restrict__ cur,
 #pragma unroll
                 for (int k = 0; k < 9; ++k) acc += w[(co * K + ci) * 9 + k] * xi[ci][k];
             zq[j >> 2][j & 3] = acc;
-            out[j] = bf16(silu(acc));
+            if constexpr (!ZOUT) out[j] = bf16(silu(acc));
         }
         if constexpr (ZOUT) {
-            *reinterpret_cast<f32x4 *>(z + size_t(p) * SC + c8 * 8) = zq[0];
-            *reinterpret_cast<f32x4 *>(z + size_t(p) * SC + c8 * 8 + 4) = zq[1];
+            zt[wave][lane * 8 + ((2 * c8) ^ (lane & 7))] = zq[0];
+            zt[wave][lane * 8 + ((2 * c8 + 1) ^ (lane & 7))] = zq[1];
+        } else {
+            *reinterpret_cast<bf16x8 *>(a + size_t(p) * SC + c8 * 8) = out;
         }
-        *reinterpret_cast<bf16x8 *>(a + size_t(p) * SC + c8 * 8) = out;
+    }
+    if constexpr (ZOUT) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // a wave reads what its own lanes wrote
+        __builtin_amdgcn_wave_barrier();
+        const int p0 = p - lane;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int px = i * 8 + (lane >> 3), q = lane & 7;
+            if (p0 + px >= P) break;
+            const f32x4 v = zt[wave][px * 8 + (q ^ (px & 7))];
+            bf16x4 o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] = bf16(silu(v[r]));
+            *reinterpret_cast<f32x4 *>(z + size_t(p0 + px) * SC + q * 4) = v;
+            *reinterpret_cast<bf16x4 *>(a + size_t(p0 + px) * SC + q * 4) = o;
+        }
     }
 }
 
@@ -480,24 +510,6 @@ __global__ void __launch_bounds__(256) k_last(const bf16 *__restrict__ a, int B,
     if (lane == 0) part[sg] = s;
 }
 
-// Per-image sums of a field in FP64, in a fixed order: stage 1 sums each of
-// IMG_PARTS contiguous segments of an image (one block each, a block-wide tree),
-// stage 2 sums an image's segment sums (one block per image).
-__global__ void __launch_bounds__(256) k_img_part(const float *__restrict__ v, int HW,
-                                                  double *__restrict__ part) {
-    __shared__ double sh[4];
-    const int img = blockIdx.x / IMG_PARTS, seg = blockIdx.x % IMG_PARTS;
-    const int len = (HW + IMG_PARTS - 1) / IMG_PARTS;
-    const int lo = seg * len, hi = min(HW, lo + len);
-    const float *row = v + size_t(img) * HW;
-    double s = 0.0;
-    for (int i = lo + threadIdx.x; i < hi; i += 256) s += double(row[i]);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
-}
 // sum of an image's IMG_PARTS segment sums by one wave, in a fixed order
 __device__ inline double image_total(const double *__restrict__ part, int img) {
     const int lane = threadIdx.x & 63;
@@ -508,15 +520,10 @@ __device__ inline double image_total(const double *__restrict__ part, int img) {
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     return s;
 }
-__global__ void __launch_bounds__(64) k_img_total(const double *__restrict__ part,
-                                                  double *__restrict__ out) {
-    const double s = image_total(part, blockIdx.x);
-    if (threadIdx.x == 0) out[blockIdx.x] = s;
-}
 static_assert(IMG_PARTS % 64 == 0, "a wave sums the segment sums (and k_last's blocks of four)");
 
 // prediction rho_t + out_scale (y - <y>_image); block (image, segment), the
-// image's mean from its IMG_PARTS segment sums (summed as k_img_total does)
+// image's mean from its IMG_PARTS segment sums
 __global__ void __launch_bounds__(256) k_pred(const float *__restrict__ in,
                                               const float *__restrict__ y,
                                               const double *__restrict__ part, int HW,
@@ -537,27 +544,71 @@ __global__ void __launch_bounds__(256) k_pred(const float *__restrict__ in,
     }
 }
 
-// loss terms and dL/dyhat; loss accumulated in FP64
+// Loss terms and dL/dyhat; block (image, segment) as k_pred, the image's mean
+// of y from its segment sums.  Every block leaves the FP64 sums of its
+// segment's dL/dyhat and of its squared errors (fixed order, no atomics: 2048
+// blocks adding to one double took 27 us at 32 images of 128^2).
 __global__ void __launch_bounds__(256) k_loss(const float *__restrict__ in,
                                               const float *__restrict__ tgt,
                                               const float *__restrict__ y,
-                                              const double *__restrict__ ysum, int P, int HW,
+                                              const double *__restrict__ ypart, int HW,
                                               float inv_out_scale, float invM,
-                                              float *__restrict__ gout, double *__restrict__ loss) {
-    __shared__ double sh[4];
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    double e2 = 0.0;
-    if (p < P) {
-        const float yhat = y[p] - float(ysum[p / HW] / HW);
-        const float e = yhat - (tgt[p] - in[p]) * inv_out_scale;
-        gout[p] = 2.f * e * invM;
-        e2 = double(e) * double(e);
+                                              float *__restrict__ gout, double *__restrict__ gpart,
+                                              double *__restrict__ epart) {
+    __shared__ float mean_sh;
+    __shared__ double sh[2][4];
+    const int img = blockIdx.x / IMG_PARTS, seg = blockIdx.x % IMG_PARTS;
+    if (threadIdx.x < 64) {
+        const double t = image_total(ypart, img);
+        if (threadIdx.x == 0) mean_sh = float(t / HW);
+    }
+    __syncthreads();
+    const float mean = mean_sh;
+    const int len = (HW + IMG_PARTS - 1) / IMG_PARTS;
+    const int lo = seg * len, hi = min(HW, lo + len);
+    double gs = 0.0, e2 = 0.0;
+    for (int i = lo + threadIdx.x; i < hi; i += 256) {
+        const size_t p = size_t(img) * HW + i;
+        const float e = (y[p] - mean) - (tgt[p] - in[p]) * inv_out_scale;
+        const float gv = 2.f * e * invM;
+        gout[p] = gv;
+        gs += double(gv);
+        e2 += double(e) * double(e);
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) e2 += __shfl_xor(e2, o, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = e2;
+    for (int o = 32; o > 0; o >>= 1) {
+        gs += __shfl_xor(gs, o, 64);
+        e2 += __shfl_xor(e2, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][threadIdx.x >> 6] = gs;
+        sh[1][threadIdx.x >> 6] = e2;
+    }
     __syncthreads();
-    if (threadIdx.x == 0) unsafeAtomicAdd(loss, sh[0] + sh[1] + sh[2] + sh[3]);
+    if (threadIdx.x == 0) {
+        gpart[blockIdx.x] = sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3];
+        epart[blockIdx.x] = sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3];
+    }
+}
+
+// Per-image sums of dL/dyhat (one block each) and, in one more block, the
+// loss, from the segment sums in a fixed order.
+__global__ void __launch_bounds__(256) k_loss_total(const double *__restrict__ gpart,
+                                                    const double *__restrict__ epart, int B,
+                                                    double *__restrict__ gsum,
+                                                    double *__restrict__ loss) {
+    __shared__ double sh[4];
+    const bool all = int(blockIdx.x) == B;
+    const double *v = all ? epart : gpart + blockIdx.x * IMG_PARTS;
+    const int n = all ? B * IMG_PARTS : IMG_PARTS;
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = threadIdx.x; k < n; k += 256) s += v[k];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) (all ? loss[0] : gsum[blockIdx.x]) = (sh[0] + sh[1]) + (sh[2] + sh[3]);
 }
 
 // Last layer backward-data: dZ_{L-2}[p][c] = SiLU'(z) sum_t dy[p - off(t)] W[c][t]
@@ -930,8 +981,19 @@ struct WgradSum {
 constexpr int WG_MID_GROUPS = (WG_LEN + 63) / 64;
 
 __device__ inline double wg_column(const float *__restrict__ part, int blocks, int len, int e) {
+    // sixteen loads in flight: one at a time the sum is a chain of memory
+    // latencies (258 us for the nine-layer network, 44 us like this)
+    const float *p = part + e;
     double s = 0.0;
-    for (int b = threadIdx.x >> 6; b < blocks; b += 4) s += double(part[size_t(b) * len + e]);
+    int b = threadIdx.x >> 6;
+    for (; b + 60 < blocks; b += 64) {
+        float v[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = p[size_t(b + 4 * k) * len];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) s += double(v[k]);
+    }
+    for (; b < blocks; b += 4) s += double(p[size_t(b) * len]);
     return s;
 }
 
@@ -992,46 +1054,52 @@ __global__ void __launch_bounds__(256) k_wgrad_sum(WgradSum a, float *__restrict
         grads[dst] = float((sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]));
 }
 
-// BF16 packings of a C -> C layer: forward wf[t][co][ci], adjoint wb[t][ci][co]
-// = W[co][ci][8 - t] (tap flip).
-__global__ void k_pack(const float *__restrict__ w, bf16 *__restrict__ wf, bf16 *__restrict__ wb) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= SC * SC * 9) return;
-    const int t = k % 9, ci = (k / 9) % SC, co = k / (9 * SC);
-    const bf16 v = bf16(w[k]);
-    wf[(t * SC + co) * SC + ci] = v;
-    wb[((8 - t) * SC + ci) * SC + co] = v;
-}
-
-// The last layer's FP32 weights w[c][t] (C -> 1) as three BF16 parts for the
-// matrix cores, wl3[t][part][c]: hi = bf16(w), mid = bf16(w - hi), lo =
-// bf16(w - hi - mid).  Each difference is exact in FP32, and what lo leaves
-// is zero for normal FP32 weights, so hi + mid + lo = w.
-__global__ void k_pack_last(const float *__restrict__ w, bf16 *__restrict__ wl3) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= SC * 9) return;
-    const int t = k % 9, c = k / 9;
-    const float v = w[k];
-    const bf16 hi = bf16(v);
-    const float r1 = v - float(hi);
-    const bf16 mid = bf16(r1);
-    const bf16 lo = bf16(r1 - float(mid));
-    wl3[(t * 3 + 0) * SC + c] = hi;
-    wl3[(t * 3 + 1) * SC + c] = mid;
-    wl3[(t * 3 + 2) * SC + c] = lo;
-}
-
-__global__ void k_adam(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
-                       float *__restrict__ v, int n, float lr, float b1, float b2, float eps,
-                       float bc1, float bc2) {
+// Packed copies of the parameters for the matrix cores, one parameter per
+// thread, every layer in one launch, after an Adam step (ADAM) or a plain
+// change of the parameters:
+//   C -> C layers: forward wf[t][co][ci], adjoint wb[t][ci][co] = W[co][ci][8 - t]
+//   (tap flip);
+//   last layer: its FP32 weights w[c][t] as three BF16 parts wl3[t][part][c]: hi =
+//   bf16(w), mid = bf16(w - hi), lo = bf16(w - hi - mid).  Each difference is exact
+//   in FP32, and what lo leaves is zero for normal FP32 weights, so hi + mid + lo = w.
+struct AdamArgs {
+    const float *g;
+    float *m, *v;
+    float lr, b1, b2, eps, bc1, bc2;
+};
+template <bool ADAM>
+__global__ void __launch_bounds__(256) k_update(float *__restrict__ p, int n, int mid0, int last0, AdamArgs o,
+                                                bf16 *__restrict__ wf, bf16 *__restrict__ wb,
+                                                bf16 *__restrict__ wl3) {
     const int k = blockIdx.x * 256 + threadIdx.x;
     if (k >= n) return;
-    const float gk = g[k];
-    const float mk = b1 * m[k] + (1.f - b1) * gk;
-    const float vk = b2 * v[k] + (1.f - b2) * gk * gk;
-    m[k] = mk;
-    v[k] = vk;
-    p[k] -= lr * (mk / bc1) / (sqrtf(vk / bc2) + eps);
+    float w = p[k];
+    if constexpr (ADAM) {
+        const float gk = o.g[k];
+        const float mk = o.b1 * o.m[k] + (1.f - o.b1) * gk;
+        const float vk = o.b2 * o.v[k] + (1.f - o.b2) * gk * gk;
+        o.m[k] = mk;
+        o.v[k] = vk;
+        w -= o.lr * (mk / o.bc1) / (sqrtf(vk / o.bc2) + o.eps);
+        p[k] = w;
+    }
+    if (k >= last0) {
+        const int e = k - last0, t = e % 9, c = e / 9;
+        if (c >= SC) return;  // the bias
+        const bf16 hi = bf16(w);
+        const float r1 = w - float(hi);
+        const bf16 mid = bf16(r1);
+        wl3[(t * 3 + 0) * SC + c] = hi;
+        wl3[(t * 3 + 1) * SC + c] = mid;
+        wl3[(t * 3 + 2) * SC + c] = bf16(r1 - float(mid));
+    } else if (k >= mid0) {
+        const int l = (k - mid0) / WG_LEN, e = (k - mid0) % WG_LEN;
+        if (e >= 9 * SC * SC) return;  // the biases
+        const int t = e % 9, ci = (e / 9) % SC, co = e / (9 * SC);
+        const size_t off = size_t(l) * 9 * SC * SC;
+        wf[off + (t * SC + co) * SC + ci] = bf16(w);
+        wb[off + ((8 - t) * SC + ci) * SC + co] = bf16(w);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1186,8 +1254,8 @@ struct fsc_sur {
     float *y = nullptr, *gbuf = nullptr;
     float *wpart = nullptr;  // blocks' partial weight gradients: C -> C layers, first, last
     int wblocks = 0, eblocks = 0;  // blocks of a weight-gradient launch at max_batch
-    double *ysum = nullptr, *gsum = nullptr, *loss = nullptr;
-    double *part = nullptr;  // [maxB][IMG_PARTS] segment sums
+    double *gsum = nullptr, *loss = nullptr;
+    double *part = nullptr;  // [3][maxB][IMG_PARTS] segment sums of y, dL/dy and the squared errors
     int64_t adam_t = 0;
     // captured rollouts: (prev, traj, batch, passes) -> graph, replayed on a
     // stream of the surrogate's own that is ordered after and before `stream`
@@ -1222,7 +1290,7 @@ void sur_free(fsc_sur *s) {
     if (!s) return;
     (void)hipStreamSynchronize(s->stream);
     void *ptrs[] = {s->params, s->grads, s->m,    s->v,    s->wf,   s->wb, s->wl3, s->dzA,
-                    s->dzB,    s->y,     s->gbuf, s->ysum, s->gsum, s->loss, s->wpart, s->part};
+                    s->dzB,    s->y,     s->gbuf, s->gsum, s->loss, s->wpart, s->part};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     for (auto p : s->z)
@@ -1266,15 +1334,16 @@ int drop_rollouts(fsc_sur *s) {
 // grow the cache without bound).
 constexpr size_t ROLLOUT_CACHE_MAX = 8;
 
-int pack_weights(fsc_sur *s) {
-    for (int l = 1; l <= nmid(s); ++l) {
-        const size_t off = size_t(l - 1) * 9 * SC * SC;
-        hipLaunchKernelGGL(k_pack, dim3((SC * SC * 9 + 255) / 256), dim3(256), 0, s->stream,
-                           s->params + s->woff[l], s->wf + off, s->wb + off);
-        SCHK(s, hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_pack_last, dim3((SC * 9 + 255) / 256), dim3(256), 0, s->stream,
-                       s->params + s->woff[s->layers - 1], s->wl3);
+// packs the current parameters, after one Adam step on them if `o` is given
+int update_params(fsc_sur *s, const AdamArgs *o) {
+    const dim3 nb(unsigned((s->nparams + 255) / 256));
+    const int n = int(s->nparams), mid0 = int(s->woff[1]), last0 = int(s->woff[s->layers - 1]);
+    if (o)
+        hipLaunchKernelGGL(k_update<true>, nb, dim3(256), 0, s->stream, s->params, n, mid0, last0, *o, s->wf,
+                           s->wb, s->wl3);
+    else
+        hipLaunchKernelGGL(k_update<false>, nb, dim3(256), 0, s->stream, s->params, n, mid0, last0, AdamArgs{},
+                           s->wf, s->wb, s->wl3);
     SCHK(s, hipGetLastError());
     return FSC_OK;
 }
@@ -1287,16 +1356,7 @@ int check_batch(fsc_sur *s, int batch) {
 // the LDS-staged C -> C layer applies when its tiles divide the image
 bool lds_tiles(const fsc_sur *s) { return s->H % MR == 0 && s->W % MW == 0; }
 
-int img_sums(fsc_sur *s, const float *v, int B, double *out) {
-    hipLaunchKernelGGL(k_img_part, dim3(unsigned(B * IMG_PARTS)), dim3(256), 0, s->stream, v,
-                       s->H * s->W, s->part);
-    SCHK(s, hipGetLastError());
-    hipLaunchKernelGGL(k_img_total, dim3(unsigned(B)), dim3(64), 0, s->stream, s->part, out);
-    SCHK(s, hipGetLastError());
-    return FSC_OK;
-}
-
-// forward pass up to y (and the per-image sums of y); `train` keeps what the
+// forward pass up to y (and its sums over the segments of every image); `train` keeps what the
 // backward pass needs (the FP32 pre-activations)
 int sur_forward_core(fsc_sur *s, const float *prev, const float *cur, int B, bool train) {
     const int P = B * s->H * s->W;
@@ -1347,25 +1407,19 @@ int sur_forward_core(fsc_sur *s, const float *prev, const float *cur, int B, boo
     hipLaunchKernelGGL(k_last, dim3(unsigned(B * IMG_PARTS / 4)), dim3(256), 0, s->stream, s->a[last - 1], B,
                        s->H, s->W, s->wl3, s->params + s->boff[last], s->y, s->part);
     SCHK(s, hipGetLastError());
-    if (train) {  // the loss needs the per-image sums of y
-        hipLaunchKernelGGL(k_img_total, dim3(unsigned(B)), dim3(64), 0, s->stream, s->part, s->ysum);
-        SCHK(s, hipGetLastError());
-    }
     return FSC_OK;
 }
 
 int sur_backward(fsc_sur *s, const float *prev, const float *in, const float *tgt, int B) {
     const int H = s->H, W = s->W, P = B * H * W;
-    const unsigned nb = unsigned((P + 255) / 256);
     const float ii = 1.f / s->in_scale, io = 1.f / s->out_scale;
-    SCHK(s, hipMemsetAsync(s->loss, 0, sizeof(double), s->stream));
-    hipLaunchKernelGGL(k_loss, dim3(nb), dim3(256), 0, s->stream, in, tgt, s->y, s->ysum, P, H * W, io,
-                       1.f / float(P), s->gbuf, s->loss);
+    double *gpart = s->part + size_t(IMG_PARTS) * s->maxB, *epart = gpart + size_t(IMG_PARTS) * s->maxB;
+    hipLaunchKernelGGL(k_loss, dim3(unsigned(B * IMG_PARTS)), dim3(256), 0, s->stream, in, tgt, s->y, s->part,
+                       H * W, io, 1.f / float(P), s->gbuf, gpart, epart);
     SCHK(s, hipGetLastError());
-    {
-        int rc = img_sums(s, s->gbuf, B, s->gsum);
-        if (rc) return rc;
-    }
+    hipLaunchKernelGGL(k_loss_total, dim3(unsigned(B + 1)), dim3(256), 0, s->stream, gpart, epart, B, s->gsum,
+                       s->loss);
+    SCHK(s, hipGetLastError());
     const int last = s->layers - 1;
     const int wtiles = wg_tiles(B, H, W);
     WgradSum ws{};
@@ -1492,8 +1546,7 @@ int fsc_sur_create(int layers, int in_ch, int H, int W, int max_batch, uint64_t 
               hipMalloc(&s->y, sizeof(float) * P) == hipSuccess &&
               hipMalloc(&s->gbuf, sizeof(float) * P) == hipSuccess &&
               hipMalloc(&s->wpart, sizeof(float) * wlen) == hipSuccess &&
-              hipMalloc(&s->ysum, sizeof(double) * max_batch) == hipSuccess &&
-              hipMalloc(&s->part, sizeof(double) * IMG_PARTS * max_batch) == hipSuccess &&
+              hipMalloc(&s->part, sizeof(double) * 3 * IMG_PARTS * max_batch) == hipSuccess &&
               hipMalloc(&s->gsum, sizeof(double) * max_batch) == hipSuccess &&
               hipMalloc(&s->loss, sizeof(double)) == hipSuccess;
     for (int l = 0; ok && l < layers - 1; ++l) {
@@ -1511,7 +1564,7 @@ int fsc_sur_create(int layers, int in_ch, int H, int W, int max_batch, uint64_t 
     }
     if (hipMemcpy(s->params, host.data(), sizeof(float) * o, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemset(s->m, 0, sizeof(float) * o) != hipSuccess ||
-        hipMemset(s->v, 0, sizeof(float) * o) != hipSuccess || pack_weights(s) != FSC_OK ||
+        hipMemset(s->v, 0, sizeof(float) * o) != hipSuccess || update_params(s, nullptr) != FSC_OK ||
         hipStreamSynchronize(s->stream) != hipSuccess) {
         sur_free(s);
         return sur_fail(nullptr, FSC_E_HIP, "surrogate initialisation failed");
@@ -1537,7 +1590,7 @@ int fsc_sur_nparams(const fsc_sur *s, int64_t *n) {
 int fsc_sur_set_params(fsc_sur *s, const float *host, int64_t n) {
     if (!s || !host || n != s->nparams) return FSC_E_INVAL;
     SCHK(s, hipMemcpyAsync(s->params, host, sizeof(float) * n, hipMemcpyHostToDevice, s->stream));
-    int rc = pack_weights(s);
+    int rc = update_params(s, nullptr);
     if (rc) return rc;
     SCHK(s, hipMemsetAsync(s->m, 0, sizeof(float) * n, s->stream));
     SCHK(s, hipMemsetAsync(s->v, 0, sizeof(float) * n, s->stream));
@@ -1629,11 +1682,8 @@ int fsc_sur_train_step(fsc_sur *s, const float *dev_prev, const float *dev_in,
     const float b1 = 0.9f, b2 = 0.999f;
     const float bc1 = 1.f - std::pow(b1, float(s->adam_t));
     const float bc2 = 1.f - std::pow(b2, float(s->adam_t));
-    hipLaunchKernelGGL(k_adam, dim3(unsigned((s->nparams + 255) / 256)), dim3(256), 0, s->stream,
-                       s->params, s->grads, s->m, s->v, int(s->nparams), lr, b1, b2, 1e-8f, bc1,
-                       bc2);
-    SCHK(s, hipGetLastError());
-    rc = pack_weights(s);
+    const AdamArgs o{s->grads, s->m, s->v, lr, b1, b2, 1e-8f, bc1, bc2};
+    rc = update_params(s, &o);
     if (rc) return rc;
     if (loss) {
         double l = 0.0;
