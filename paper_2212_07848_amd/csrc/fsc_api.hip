@@ -56,7 +56,7 @@ struct Rep {
     int64_t nsamples = 0;
     double *d_sk = nullptr;  // axis_sum, axis_sq, rad_sum, rad_sq
     void *cbuf = nullptr, *ctmp = nullptr;
-    void *tw[3] = {nullptr, nullptr, nullptr};
+    int *d_done = nullptr;  // blocks of a sample that have finished
     double *d_stats = nullptr, *d_partials = nullptr;
     // time series of samples: rows (step, L, per-shell mean S) -- see fsc_series_enable
     double *d_mom = nullptr, *d_series = nullptr;
@@ -100,6 +100,7 @@ struct fsc_ens {
     std::vector<MeasRep> meas;
     MeasPlan mplan;
     MeasRep *d_meas = nullptr;
+    std::map<int, void *> tabs;  // transform tables by line length
     int *d_mpre = nullptr;
     std::string err;
     std::map<std::pair<int, std::pair<int64_t, int64_t>>, GraphEntry> graphs;
@@ -170,6 +171,34 @@ int resolve_params(const fsc_params &in, fsc_params &out, std::string &err) {
     return FSC_OK;
 }
 
+// Shell index round(sqrt(m)) of a squared mode number, in integer arithmetic.
+int round_sqrt(int64_t m) {
+    int64_t b = int64_t(std::sqrt(double(m)));
+    while (b * b > m) --b;
+    while ((b + 1) * (b + 1) <= m) ++b;
+    if (m - b * b > b) ++b;
+    return int(b);
+}
+
+// Modes of each shell of an L x L (D = 2) or L x L x L box, k = 0 excluded: the
+// shell grows along a line of modes, so it is followed, not looked up.
+void count_shells(int D, int L, int nrad, int64_t *modes) {
+    for (int b = 0; b < nrad; ++b) modes[b] = 0;
+    const int h = L / 2;
+    auto signs = [&](int v) { return int64_t(v == 0 || 2 * v == L ? 1 : 2); };
+    for (int z = 0; z <= (D == 3 ? h : 0); ++z)
+        for (int y = 0; y <= h; ++y) {
+            const int64_t base = int64_t(y) * y + int64_t(z) * z;
+            const int64_t w = signs(y) * (D == 3 ? signs(z) : 1);
+            int64_t b = round_sqrt(base);
+            for (int x = 0; x <= h; ++x) {
+                while (base + int64_t(x) * x > b * b + b) ++b;
+                modes[b] += w * signs(x);
+            }
+        }
+    modes[0] -= 1;
+}
+
 int init_rep(Rep &r, const fsc_params &p, void *ext_a, void *ext_b, fsc_ens *e) {
     r.p = p;
     r.Q = q_of(p.D);
@@ -195,13 +224,6 @@ int init_rep(Rep &r, const fsc_params &p, void *ext_a, void *ext_b, fsc_ens *e) 
     const int nmax = std::max(p.nx, std::max(p.ny, p.nz));
     r.n_axis = nmax / 2 + 1;
     const bool cubic = p.nx == p.ny && (D == 2 || p.ny == p.nz);
-    auto round_sqrt = [](int64_t m) {
-        int64_t b = int64_t(std::sqrt(double(m)));
-        while (b * b > m) --b;
-        while ((b + 1) * (b + 1) <= m) ++b;
-        if (m - b * b > b) ++b;
-        return int(b);
-    };
     r.n_rad = cubic ? round_sqrt(int64_t(D) * (p.nx / 2) * (p.nx / 2)) + 1 : 0;
     r.axis_modes.assign(size_t(D) * r.n_axis, 0);
     r.rad_modes.assign(size_t(r.n_rad), 0);
@@ -211,21 +233,7 @@ int init_rep(Rep &r, const fsc_params &p, void *ext_a, void *ext_b, fsc_ens *e) 
             const int m = q <= sides[d] / 2 ? q : sides[d] - q;
             r.axis_modes[size_t(d) * r.n_axis + m] += 1;
         }
-    if (cubic) {
-        const int L = p.nx;
-        std::vector<int64_t> sq(L);
-        for (int q = 0; q < L; ++q) {
-            const int64_t m = q <= L / 2 ? q : q - L;
-            sq[q] = m * m;
-        }
-        const int zmax = D == 3 ? L : 1;
-        for (int z = 0; z < zmax; ++z)
-            for (int y = 0; y < L; ++y)
-                for (int x = 0; x < L; ++x) {
-                    const int64_t m2 = sq[x] + sq[y] + (D == 3 ? sq[z] : 0);
-                    if (m2) r.rad_modes[round_sqrt(m2)] += 1;
-                }
-    }
+    if (cubic) count_shells(D, p.nx, r.n_rad, r.rad_modes.data());
     const size_t nsk = 2 * size_t(D) * r.n_axis + 2 * size_t(r.n_rad);
     if (hipMalloc(&r.d_sk, sizeof(double) * nsk) != hipSuccess ||
         hipMalloc(&r.d_mom, sizeof(double) * 2) != hipSuccess ||
@@ -241,35 +249,40 @@ int init_rep(Rep &r, const fsc_params &p, void *ext_a, void *ext_b, fsc_ens *e) 
     return FSC_OK;
 }
 
-// Buffers of the S(k) sample: complex field, scratch and twiddle tables.  The
+// Buffers of the S(k) sample: half spectra, the counter of finished blocks and,
+// shared by the replicas of an ensemble, a transform table per side length.  The
 // set counts as ready only when every part exists, so that a call that failed
 // half way is completed (or fails again) on the next request.
 int ensure_fft(Rep &r, fsc_ens *e) {
     const int sides[3] = {r.p.nx, r.p.ny, r.p.nz};
-    bool ready = r.cbuf && r.ctmp;
-    for (int d = 0; d < r.p.D; ++d) ready = ready && r.tw[d];
+    bool ready = r.cbuf && r.d_done && (r.p.D == 2 || r.ctmp);
+    for (int d = 0; d < r.p.D; ++d) ready = ready && e->tabs.count(sides[d]);
     if (ready) return FSC_OK;
     for (int d = 0; d < r.p.D; ++d)
         if (sides[d] > 8192) return fail(e, FSC_E_NOTSUP, "S(k) needs sides <= 8192");
-    const size_t csz = 2 * r.esz * size_t(r.N);
+    const size_t csz = 2 * r.esz * size_t(r.p.nx / 2 + 1) * size_t(r.p.ny) * size_t(r.p.nz);
+    const bool counter = r.d_done != nullptr;
     if ((!r.cbuf && hipMalloc(&r.cbuf, csz) != hipSuccess) ||
-        (!r.ctmp && hipMalloc(&r.ctmp, csz) != hipSuccess)) {
+        (r.p.D == 3 && !r.ctmp && hipMalloc(&r.ctmp, csz) != hipSuccess) ||
+        (!r.d_done && hipMalloc(&r.d_done, sizeof(int)) != hipSuccess)) {
         (void)hipGetLastError();
         return fail(e, FSC_E_OOM, "FFT buffer allocation failed");
     }
+    if (!counter) HIPCHK(e, hipMemsetAsync(r.d_done, 0, sizeof(int), e->stream));
     for (int d = 0; d < r.p.D; ++d) {
-        if (r.tw[d]) continue;
-        void *tw = nullptr;
-        if (hipMalloc(&tw, 2 * r.esz * twiddle_len(sides[d])) != hipSuccess) {
+        if (e->tabs.count(sides[d])) continue;
+        const SkAxis x = sk_axis(sides[d], r.p.precision);
+        void *tab = nullptr;
+        if (hipMalloc(&tab, 2 * r.esz * sk_table_len(x)) != hipSuccess) {
             (void)hipGetLastError();
-            return fail(e, FSC_E_OOM, "twiddle allocation failed");
+            return fail(e, FSC_E_OOM, "transform table allocation failed");
         }
-        const hipError_t ec = launch_twiddles(r.p.precision, tw, sides[d], e->stream);
+        const hipError_t ec = sk_table(r.p.precision, x, tab, nullptr, 0, e->stream);
         if (ec != hipSuccess) {
-            (void)hipFree(tw);
-            return fail(e, FSC_E_HIP, std::string("twiddles: ") + hipGetErrorString(ec));
+            (void)hipFree(tab);
+            return fail(e, FSC_E_HIP, std::string("transform table: ") + hipGetErrorString(ec));
         }
-        r.tw[d] = tw;
+        e->tabs[sides[d]] = tab;
     }
     return FSC_OK;
 }
@@ -288,12 +301,14 @@ int ensure_measure_plan(fsc_ens *e) {
         const Rep &r = e->reps[k];
         MeasRep &x = m[size_t(k)];
         std::memset(&x, 0, sizeof(MeasRep));
-        if (!r.cbuf) return fail(e, FSC_E_STATE, "S(k) buffers missing");
+        if (!r.cbuf || !r.d_done) return fail(e, FSC_E_STATE, "S(k) buffers missing");
         x.buf[0] = r.buf[0];
         x.buf[1] = r.buf[1];
         x.cbuf = r.cbuf;
         x.ctmp = r.ctmp;
-        for (int d = 0; d < 3; ++d) x.tw[d] = r.tw[d];
+        x.done = r.d_done;
+        const int sides[3] = {r.p.nx, r.p.ny, r.p.nz};
+        for (int d = 0; d < r.p.D; ++d) x.tab[d] = e->tabs.at(sides[d]);
         x.g = r.geom();
         const size_t na = size_t(r.p.D) * r.n_axis;
         x.t.axis_sum = r.d_sk;
@@ -316,12 +331,12 @@ int ensure_measure_plan(fsc_ens *e) {
             x.modes_cap = r.modes_cap;
         }
     }
-    if (e->d_meas && m.size() == e->meas.size() &&
-        std::memcmp(m.data(), e->meas.data(), sizeof(MeasRep) * m.size()) == 0)
-        return FSC_OK;
     MeasPlan P;
     P.esz = e->reps[0].esz;
     if (measure_plan(m.data(), n, P)) return fail(e, FSC_E_NOTSUP, "S(k) sample sizes out of range");
+    if (e->d_meas && m.size() == e->meas.size() &&
+        std::memcmp(m.data(), e->meas.data(), sizeof(MeasRep) * m.size()) == 0)
+        return FSC_OK;
     HIPCHK(e, hipStreamSynchronize(e->stream));
     if (!e->d_meas) {
         if (hipMalloc(&e->d_meas, sizeof(MeasRep) * size_t(n)) != hipSuccess ||
@@ -339,9 +354,10 @@ int ensure_measure_plan(fsc_ens *e) {
 }
 
 // enqueues one S(k) sample of every replica from buffer `par`; the sampled
-// state is `step_off` steps past the device step counter
-int enqueue_measure(fsc_ens *e, int par, uint32_t step_off) {
-    HIPCHK(e, launch_measure(e->mplan, e->d_meas, e->d_mpre, e->precision, par, e->d_step, step_off,
+// state is `step_off` steps past the device step counter, to which `advance` is
+// added first
+int enqueue_measure(fsc_ens *e, int par, uint32_t step_off, uint64_t advance = 0) {
+    HIPCHK(e, launch_measure(e->mplan, e->d_meas, e->d_mpre, e->precision, par, e->d_step, advance, step_off,
                              e->stream));
     return FSC_OK;
 }
@@ -583,6 +599,7 @@ int64_t count_launches(const fsc_ens *e, int64_t n, int64_t sk_every) {
 
 int enqueue_steps(fsc_ens *e, int cur, int64_t n, int64_t sk_every, int64_t *samples, int *flips) {
     int c = cur, launches = 0;
+    bool advanced = false;
     for (int64_t k = 0; k < n;) {
         const bool two = pair_from(e, k, n, sk_every);
         StepLaunch L = make_launch(e, c, uint32_t(k));
@@ -592,12 +609,15 @@ int enqueue_steps(fsc_ens *e, int cur, int64_t n, int64_t sk_every, int64_t *sam
         ++launches;
         k += two ? 2 : 1;
         if (sk_every > 0 && k % sk_every == 0) {
-            int rc = enqueue_measure(e, c, uint32_t(k));
+            // a sample after the last step moves the step counter on as well
+            // (a launch of its own for one addition takes 4 us)
+            int rc = k == n ? enqueue_measure(e, c, 0, uint64_t(n)) : enqueue_measure(e, c, uint32_t(k));
             if (rc) return rc;
             if (samples) ++*samples;
+            if (k == n) advanced = true;
         }
     }
-    HIPCHK(e, launch_step_advance(e->d_step, uint64_t(n), e->stream));
+    if (!advanced) HIPCHK(e, launch_step_advance(e->d_step, uint64_t(n), e->stream));
     if (flips) *flips = launches & 1;
     return FSC_OK;
 }
@@ -906,12 +926,12 @@ void ens_free(fsc_ens *e) {
             if (r.buf[0]) (void)hipFree(r.buf[0]);
             if (r.buf[1]) (void)hipFree(r.buf[1]);
         }
-        void *ptrs[] = {r.d_sk,     r.cbuf,       r.ctmp,  r.tw[0],     r.tw[1],      r.tw[2],
-                        r.d_stats,  r.d_partials, r.d_mom, r.d_series, r.d_series_n, r.d_modes,
-                        r.d_modes_n};
+        void *ptrs[] = {r.d_sk,  r.cbuf,     r.ctmp,       r.d_done,  r.d_stats,  r.d_partials,
+                        r.d_mom, r.d_series, r.d_series_n, r.d_modes, r.d_modes_n};
         for (void *p : ptrs)
             if (p) (void)hipFree(p);
     }
+    for (auto &kv : e->tabs) (void)hipFree(kv.second);
     if (e->d_desc) (void)hipFree(e->d_desc);
     if (e->d_tile_begin) (void)hipFree(e->d_tile_begin);
     if (e->d_step) (void)hipFree(e->d_step);
@@ -1495,98 +1515,54 @@ int fsc_ens_coarsen(fsc_ens *ens, int replica, int factor, float *dev_out) {
 
 namespace {
 
-// Shell index round(sqrt(m)) of a squared mode number, in integer arithmetic.
-int round_sqrt_shell(int64_t m) {
-    int64_t b = int64_t(std::sqrt(double(m)));
-    while (b * b > m) --b;
-    while ((b + 1) * (b + 1) <= m) ++b;
-    if (m - b * b > b) ++b;
-    return int(b);
+// S(k) of `batch` fields [batch][L][L] (float) on stream st, up to `chunk` fields
+// at a time through the work areas (the transform table, spectra and sums of a
+// chunk, contiguous from `work`): the table and cleared sums in one launch, two
+// passes over the chunk, one copy of its sums to the host.  Shared by
+// fsc_field_sk (which allocates the areas per call) and fsc_field_sk_noalloc
+// (which uses the library's static scratch).
+size_t field_tab_bytes(int L) { return (8 * sk_table_len(sk_axis(L, 0)) + 255) & ~size_t(255); }
+size_t field_spec_bytes(int L) { return 8 * size_t(L / 2 + 1) * L; }
+size_t field_work_bytes(int L, int nrad, int chunk) {
+    return field_tab_bytes(L) + size_t(chunk) * (field_spec_bytes(L) + sizeof(double) * field_acc_len(nrad));
 }
 
-// Mode count of each radial shell of an L x L box (k = 0 excluded).
-void field_shell_modes(int L, int nrad, int64_t *modes) {
-    for (int k = 0; k < nrad; ++k) modes[k] = 0;
-    for (int y = 0; y < L; ++y)
-        for (int x = 0; x < L; ++x) {
-            const int64_t mx = x <= L / 2 ? x : x - L, my = y <= L / 2 ? y : y - L;
-            if (mx || my) modes[round_sqrt_shell(mx * mx + my * my)] += 1;
-        }
-}
-
-// Device work areas of one field S(k): two complex lines of N points, the
-// twiddles, the FP64 bin accumulators and the series counter.
-struct FieldWork {
-    void *ca, *cb, *tw;
-    double *acc;
-    int *cnt;
-};
-
-size_t field_acc_len(int L, int nrad) {
-    return 2 * size_t(2 * (L / 2 + 1)) + 2 * size_t(nrad) + 2 + size_t(2 + nrad);
-}
-
-// S(k) of `batch` fields [batch][L][L] (float) on stream st, one field after
-// the other through the work areas w: density to complex, FFT along x then
-// y, radial binning with the first moment, then the shell sums and the moment
-// pair are copied to the host.  Shared by fsc_field_sk (which allocates w per
-// call) and fsc_field_sk_noalloc (which uses the library's static scratch).
-hipError_t field_sk_batches(const float *dev_fields, int batch, int L, hipStream_t st,
-                            const FieldWork &w, const int64_t *modes, int nrad,
-                            double *host_shell_mean, double *host_L) {
-    const int64_t N = int64_t(L) * L;
-    const int na = L / 2 + 1;
-    const size_t nacc = field_acc_len(L, nrad);
-    hipError_t ec = launch_twiddles(0, w.tw, L, st);
-    const Geometry g{2, L, L, 1, N};
-    for (int b = 0; b < batch && ec == hipSuccess; ++b) {
-        // the accumulators and the series counter start at zero for every field
-        ec = launch_zero_words(w.acc, int64_t(2 * nacc), st);
-        if (ec == hipSuccess) ec = launch_zero_words(w.cnt, 1, st);
-        if (ec == hipSuccess) ec = launch_field_cplx(dev_fields + size_t(b) * N, int(N), w.ca, st);
-        if (ec == hipSuccess) ec = launch_fft_axis(0, w.ca, w.cb, w.tw, L, L, 1, st);
-        if (ec == hipSuccess) ec = launch_fft_axis(0, w.cb, w.ca, w.tw, L, L, 1, st);
-        BinTargets t;
-        t.axis_sum = w.acc;
-        t.axis_sq = w.acc + 2 * na;
-        t.rad_sum = w.acc + 4 * na;
-        t.rad_sq = w.acc + 4 * na + nrad;
-        t.n_axis = na;
-        t.n_rad = nrad;
-        t.mom = w.acc + 4 * na + 2 * nrad;
-        t.series = w.acc + 4 * na + 2 * nrad + 2;
-        t.series_n = w.cnt;
-        t.series_cap = 1;
-        if (ec == hipSuccess) ec = launch_bin(g, 0, w.ca, t, st);
-        double mom[2] = {0.0, 0.0};
-        double *shell = host_shell_mean ? host_shell_mean + size_t(b) * nrad : nullptr;
-        if (ec == hipSuccess && shell)
-            ec = hipMemcpyAsync(shell, t.rad_sum, sizeof(double) * nrad, hipMemcpyDeviceToHost, st);
+hipError_t field_sk_batches(const float *dev_fields, int batch, int L, hipStream_t st, void *work, int chunk,
+                            int nrad, double *host_shell_mean, double *host_L) {
+    std::vector<int64_t> modes(size_t(nrad), 0);
+    count_shells(2, L, nrad, modes.data());
+    const size_t N = size_t(L) * L, len = field_acc_len(nrad);
+    unsigned char *tab = static_cast<unsigned char *>(work);
+    unsigned char *spec = tab + field_tab_bytes(L);
+    std::vector<double> h(len * size_t(std::min(batch, chunk)));
+    hipError_t ec = hipSuccess;
+    for (int b = 0; b < batch && ec == hipSuccess; b += chunk) {
+        const int nb = std::min(chunk, batch - b);
+        double *acc = reinterpret_cast<double *>(spec + size_t(nb) * field_spec_bytes(L));
+        ec = sk_table(0, sk_axis(L, 0), tab, acc, int64_t(2 * len) * nb, st);
+        if (ec == hipSuccess) ec = launch_field_sk(dev_fields + size_t(b) * N, nb, L, nrad, spec, tab, acc, st);
         if (ec == hipSuccess)
-            ec = hipMemcpyAsync(mom, t.mom, sizeof(mom), hipMemcpyDeviceToHost, st);
-        if (ec == hipSuccess) ec = hipStreamSynchronize(st);
+            ec = hipMemcpyAsync(h.data(), acc, sizeof(double) * len * nb, hipMemcpyDeviceToHost, st);
+        const hipError_t es = hipStreamSynchronize(st);
+        if (ec == hipSuccess) ec = es;
         if (ec != hipSuccess) break;
-        if (shell)
-            for (int k = 0; k < nrad; ++k) shell[k] = modes[k] ? shell[k] / double(modes[k]) : 0.0;
-        if (host_L) host_L[b] = mom[1] > 0.0 ? 2.0 * M_PI * mom[0] / mom[1] : 0.0;
+        for (int f = 0; f < nb; ++f) {
+            const double *q = h.data() + len * size_t(f), *mom = q + nrad;
+            if (host_shell_mean)
+                for (int k = 0; k < nrad; ++k)
+                    host_shell_mean[size_t(b + f) * nrad + k] = modes[size_t(k)] ? q[k] / double(modes[size_t(k)]) : 0.0;
+            if (host_L) host_L[b + f] = mom[1] > 0.0 ? 2.0 * M_PI * mom[0] / mom[1] : 0.0;
+        }
     }
     return ec;
 }
 
 // ---- fixed-size scratch of the allocation-free field S(k) ----------------
-// Sized for fields up to FIELD_STATIC_MAX_SIDE^2: two complex work lines of
-// 8 B per point, the twiddles, the accumulators and the counter, each at a
-// 256-byte boundary.  Every device the library runs on holds one copy for the
-// life of the process.
+// 16 MiB and some: at least one field of FIELD_STATIC_MAX_SIDE^2 at a time (its
+// half spectrum takes 4.2 MB), many smaller ones.  Every device the library runs
+// on holds one copy for the life of the process.
 constexpr int FIELD_STATIC_MAX_SIDE = 1024;
-constexpr int FIELD_STATIC_MAX_NRAD = 726;  // round(sqrt(2) * 512) + 1
-constexpr size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
-constexpr size_t FS_CPLX = 8 * size_t(FIELD_STATIC_MAX_SIDE) * FIELD_STATIC_MAX_SIDE;
-constexpr size_t FS_TW = align256(8 * size_t(FIELD_STATIC_MAX_SIDE));
-constexpr size_t FS_ACC = align256(8 * (2 * size_t(2 * (FIELD_STATIC_MAX_SIDE / 2 + 1)) +
-                                        2 * size_t(FIELD_STATIC_MAX_NRAD) + 2 +
-                                        size_t(2 + FIELD_STATIC_MAX_NRAD)));
-constexpr size_t FS_BYTES = 2 * FS_CPLX + FS_TW + FS_ACC + 256;
+constexpr size_t FS_BYTES = (size_t(16) << 20) + (size_t(64) << 10);
 
 __device__ __align__(256) unsigned char scratch[FS_BYTES];
 
@@ -1617,7 +1593,7 @@ hipError_t scratch_on(int dev, void **out) {
 
 int field_args(const float *dev_fields, int batch, int ny, int nx, int nbins, int *nrad) {
     if (!dev_fields || batch < 1 || nx < 2 || ny < 2 || nx != ny || nx > 8192) return FSC_E_INVAL;
-    *nrad = round_sqrt_shell(2 * int64_t(nx / 2) * (nx / 2)) + 1;
+    *nrad = round_sqrt(2 * int64_t(nx / 2) * (nx / 2)) + 1;
     return nbins == *nrad ? FSC_OK : FSC_E_INVAL;
 }
 
@@ -1629,27 +1605,15 @@ int fsc_field_sk(const float *dev_fields, int batch, int ny, int nx, void *strea
     int rc = field_args(dev_fields, batch, ny, nx, nbins, &nrad);
     if (rc) return rc;
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    const int L = nx;
-    std::vector<int64_t> modes(nrad, 0);
-    field_shell_modes(L, nrad, modes.data());
-    const int64_t N = int64_t(L) * L;
-    void *ca = nullptr, *cb = nullptr, *tw = nullptr;
-    double *acc = nullptr;
-    int *cnt = nullptr;
-    const size_t nacc = field_acc_len(L, nrad);
-    if (hipMalloc(&ca, 8 * N) != hipSuccess || hipMalloc(&cb, 8 * N) != hipSuccess ||
-        hipMalloc(&tw, 8 * twiddle_len(L)) != hipSuccess ||
-        hipMalloc(&acc, sizeof(double) * nacc) != hipSuccess ||
-        hipMalloc(&cnt, sizeof(int)) != hipSuccess) {
+    // the spectra of a chunk stay within 1 GiB
+    const int chunk = int(std::min<int64_t>(batch, std::max<int64_t>(1, (int64_t(1) << 30) / int64_t(field_spec_bytes(nx)))));
+    void *work = nullptr;
+    if (hipMalloc(&work, field_work_bytes(nx, nrad, chunk)) != hipSuccess) {
         (void)hipGetLastError();
-        for (void *p : {ca, cb, tw, (void *)acc, (void *)cnt})
-            if (p) (void)hipFree(p);
         return FSC_E_OOM;
     }
-    const FieldWork w{ca, cb, tw, acc, cnt};
-    hipError_t ec = field_sk_batches(dev_fields, batch, L, st, w, modes.data(), nrad,
-                                     host_shell_mean, host_L);
-    for (void *p : {ca, cb, tw, (void *)acc, (void *)cnt}) (void)hipFree(p);
+    const hipError_t ec = field_sk_batches(dev_fields, batch, nx, st, work, chunk, nrad, host_shell_mean, host_L);
+    (void)hipFree(work);
     return ec == hipSuccess ? FSC_OK : FSC_E_HIP;
 }
 
@@ -1665,24 +1629,15 @@ int fsc_field_sk_noalloc(const float *dev_fields, int batch, int ny, int nx, voi
     if (ec != hipSuccess) return FSC_E_HIP;
     void *base = nullptr;
     if (scratch_on(dev, &base) != hipSuccess) return FSC_E_HIP;
-    unsigned char *p = static_cast<unsigned char *>(base);
-    const FieldWork w{p, p + FS_CPLX, p + 2 * FS_CPLX,
-                      reinterpret_cast<double *>(p + 2 * FS_CPLX + FS_TW),
-                      reinterpret_cast<int *>(p + 2 * FS_CPLX + FS_TW + FS_ACC)};
-    int64_t modes[FIELD_STATIC_MAX_NRAD];
-    field_shell_modes(nx, nrad, modes);
-    ec = field_sk_batches(dev_fields, batch, nx, st, w, modes, nrad, host_shell_mean, host_L);
+    int chunk = 1;
+    while (chunk < batch && field_work_bytes(nx, nrad, chunk + 1) <= FS_BYTES) ++chunk;
+    ec = field_sk_batches(dev_fields, batch, nx, st, base, chunk, nrad, host_shell_mean, host_L);
     return ec == hipSuccess ? FSC_OK : FSC_E_HIP;
 }
 
 int fsc_field_nbins(int n, int *nbins) {
     if (n < 2 || !nbins) return FSC_E_INVAL;
-    int64_t m = 2 * int64_t(n / 2) * (n / 2);
-    int64_t b = int64_t(std::sqrt(double(m)));
-    while (b * b > m) --b;
-    while ((b + 1) * (b + 1) <= m) ++b;
-    if (m - b * b > b) ++b;
-    *nbins = int(b) + 1;
+    *nbins = round_sqrt(2 * int64_t(n / 2) * (n / 2)) + 1;
     return FSC_OK;
 }
 

@@ -70,20 +70,27 @@ size_t stats_partials_len();
 hipError_t launch_stats(const Geometry &g, int precision, const void *buf, double rho0,
                         double *partials, double *out, hipStream_t s);
 
-// In-place complex FFT of every line along the contiguous axis of a
-// [n2][n1][n0] array, then a rotation to [n0][n2][n1]; after D calls the
-// array is back in its original axis order and transformed along every axis.
-// `twiddle` holds n0/2 complex values exp(-2 pi i k / n0) (power-of-two n0)
-// or n0 values (other n0).  `tmp` is a second complex buffer of equal size.
-hipError_t launch_fft_axis(int precision, void *data, void *tmp, const void *twiddle, int n0,
-                           int n1, int n2, hipStream_t s);
-hipError_t launch_twiddles(int precision, void *tw, int n, hipStream_t s);
-size_t twiddle_len(int n);
+// Transform of one axis: lines of n values over m points, m = 2^logm (n itself,
+// or at least 2n - 1 for the chirp form), or m = n and logm = -1 (direct sum).
+struct SkAxis {
+    int n, m, logm;
+};
+SkAxis sk_axis(int n, int precision);
+// complex values of an axis' table: the m-th roots of unity, and for the chirp
+// form the chirp and its spectrum
+size_t sk_table_len(const SkAxis &x);
+// Fills a table; the same launch clears `zero_words` 32-bit words at `zero`.
+// Synchronises the stream for the chirp form.
+hipError_t sk_table(int precision, const SkAxis &x, void *tab, void *zero, int64_t zero_words, hipStream_t s);
+// LDS of `lines` lines of m complex values of csz bytes (see sk_stride)
+__host__ __device__ inline size_t sk_line_bytes(size_t csz, int lines, int m) {
+    return (csz * size_t(lines) * size_t(m + (m >> 3) + 1) + 15) & ~size_t(15);
+}
 
-// Adds |X(k)|^2 / N of one spectrum to the FP64 axis and radial accumulators.
+// Where the |X(k)|^2 / N of one spectrum go: FP64 axis and radial accumulators.
 struct BinTargets {
-    double *axis_sum, *axis_sq;  // [D][n_axis]
-    double *rad_sum, *rad_sq;    // [n_rad] or null
+    double *axis_sum, *axis_sq;  // [D][n_axis], or null
+    double *rad_sum, *rad_sq;    // [n_rad] (rad_sq may be null)
     int n_axis, n_rad;
     // time series (null when disabled): per-sample sum P and sum |k| P, and
     // rows [cap][2 + n_rad] = (step, L, per-shell sums of P) at row *series_n
@@ -92,15 +99,15 @@ struct BinTargets {
     const int *series_n;
     int series_cap;
 };
-hipError_t launch_bin(const Geometry &g, int precision, const void *spec, const BinTargets &t,
-                      hipStream_t s);
 // One replica's part of a batched S(k) sample: a device table filled by the
 // host.  The sampled density is dn(x) = sum_i f_i(x) - rho0 of the streamed
 // state, gathered from the stored post-collision buffer buf[parity].
 struct MeasRep {
     const void *buf[2];   // population buffers
-    void *cbuf, *ctmp;    // complex work buffers of N elements each
-    const void *tw[3];    // twiddles per axis (see launch_twiddles)
+    void *cbuf, *ctmp;    // half spectra, (nx/2 + 1) ny nz complex values (ctmp: 3D only)
+    const void *tab[3];   // transform tables per axis (see sk_table)
+    SkAxis ax[3];         // set by measure_plan, as are
+    int lc[3];            // lines per block of the row, mid and last launches
     Geometry g;
     BinTargets t;         // accumulators; t.mom == nullptr: no time series
     double invN;
@@ -108,33 +115,38 @@ struct MeasRep {
     double *modes;        // mode recorder rows [cap][D][nm][2], or null
     int *modes_n;
     int modes_nm, modes_cap;
+    int *done;            // blocks of the last launch that have finished (0 between samples)
 };
-// kinds of work in one sample; MK_FFT + d and MK_ROT + d for axis pass d
-constexpr int MK_DENSITY = 0, MK_FFT = 1, MK_ROT = 4, MK_BIN = 7, MK_MODES = 8, MK_COUNT = 9;
+// kinds of work in one sample
+constexpr int MK_ROWS = 0, MK_MID = 1, MK_LAST = 2, MK_COUNT = 3;
 struct MeasPlan {
     int nrep = 0, D = 2;
     size_t esz = 4;          // bytes of one real (set by the caller)
     std::vector<int> pre;    // [MK_COUNT][nrep + 1]: first block of each replica per kind
-    size_t shm_fft[3] = {0, 0, 0}, shm_bin = 0;
-    bool any_series = false;
+    size_t shm[MK_COUNT] = {};
+    int threads[MK_COUNT] = {};
 };
-// Fills the block prefixes and LDS sizes of P from the host copy of the
-// replica table; -1 if a side exceeds 8192 or a grid exceeds 2^31 blocks.
-int measure_plan(const MeasRep *reps, int nrep, MeasPlan &P);
-// One S(k) sample of every replica in P (density, FFT passes, binning, mode
-// records, series rows), in at most 4 + 2 D launches.  The sampled state is
-// step_base[0] + step_off.
+// Fills the block prefixes, block sizes and LDS sizes of P, and the transforms
+// of the host copy of the replica table; -1 if a side exceeds 8192 or a grid
+// exceeds 2^31 blocks.
+int measure_plan(MeasRep *reps, int nrep, MeasPlan &P);
+// One S(k) sample of every replica in P (bins, mode records, series rows), in
+// two (2D) or three launches.  Adds `advance` to the step counter step_base[0]
+// first (the steps enqueued before the sample, once none of their launches is
+// still to read it); the sampled state is step_base[0] + step_off after that.
 hipError_t launch_measure(const MeasPlan &P, const MeasRep *dev_reps, const int *dev_pre, int precision,
-                          int parity, const uint64_t *step_base, uint32_t step_off, hipStream_t s);
+                          int parity, uint64_t *step_base, uint64_t advance, uint32_t step_off, hipStream_t s);
+
+// S(k) of `batch` device fields [n][n]: adds every field's shell sums of |X|^2 /
+// n^2 and its sum P and sum |k| P to acc + f field_acc_len(n_rad).  spec:
+// batch (n/2 + 1) n complex floats; tab: the table of sk_axis(n, 0).
+__host__ __device__ inline size_t field_acc_len(int n_rad) { return size_t(n_rad) + 2; }
+hipError_t launch_field_sk(const float *fields, int batch, int n, int n_rad, void *spec, const void *tab,
+                           double *acc, hipStream_t s);
 
 // Block means of the density over f x f blocks (2D) into out[(ny/f) x (nx/f)].
 hipError_t launch_coarsen(const Geometry &g, int precision, const void *buf, double rho0, int f,
                           float *out, hipStream_t s);
-// Real field -> interleaved complex float.
-hipError_t launch_field_cplx(const float *f, int n, void *c, hipStream_t s);
-// Zeroes `words` 32-bit words of device memory with a fill kernel.
-hipError_t launch_zero_words(void *p, int64_t words, hipStream_t s);
-
 // Plain copy of `bytes` (multiple of 16) bytes.
 hipError_t launch_copy(const void *src, void *dst, int64_t bytes, hipStream_t s);
 

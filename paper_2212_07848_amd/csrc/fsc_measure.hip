@@ -1,10 +1,13 @@
 // fsc_measure.hip -- density gathers, FP64 state reductions, and the
 // structure-factor pipeline S(k) = <|dn(k)|^2> / N of Lulli et al.
-// (arXiv:2212.07848, the quantity compared with Eq. 16):
-//   density gather -> complex FFT along each axis (LDS radix-2 Cooley-Tukey
-//   per line, or a direct DFT for other lengths) with axis rotations between
-//   passes -> per-line binning with an LDS window of radial shells and FP64
-//   accumulation.
+// (arXiv:2212.07848, the quantity compared with Eq. 16): real transforms of the
+// gathered density, line by line in LDS, and binning of the last transform
+// where it lies, with FP64 accumulation.
+#include <algorithm>
+#include <cmath>
+#include <utility>
+#include <vector>
+
 #include "fsc_internal.h"
 
 namespace fsc {
@@ -35,61 +38,38 @@ __device__ inline void gather_node(const real *src, const Geometry &g, int x, in
     }
 }
 
-template <class L, typename real, bool CPLX>
-__device__ inline void density_block(const Geometry &g, const real *__restrict__ src,
-                                     real *__restrict__ out, int blk) {
+template <class L, typename real>
+__global__ void __launch_bounds__(256) k_density(Geometry g, const real *__restrict__ src,
+                                                 real *__restrict__ out) {
     const int strips = (g.nx + 255) / 256;
-    const int row = blk / strips;
-    const int x = (blk % strips) * 256 + threadIdx.x;
+    const int row = int(blockIdx.x) / strips;
+    const int x = (int(blockIdx.x) % strips) * 256 + threadIdx.x;
     if (x >= g.nx) return;
-    const int y = row % g.ny, z = row / g.ny;
     real f[L::Q];
-    gather_node<L, real>(src, g, x, y, z, f);
+    gather_node<L, real>(src, g, x, row % g.ny, row / g.ny, f);
     real dn = real(0);
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) dn += f[i];
-    const int64_t s = int64_t(row) * g.nx + x;
-    if (CPLX) {
-        out[2 * s] = dn;
-        out[2 * s + 1] = real(0);
-    } else {
-        out[s] = dn;
-    }
-}
-
-template <class L, typename real, bool CPLX>
-__global__ void __launch_bounds__(256) k_density(Geometry g, const real *__restrict__ src,
-                                                 real *__restrict__ out) {
-    density_block<L, real, CPLX>(g, src, out, int(blockIdx.x));
+    out[int64_t(row) * g.nx + x] = dn;
 }
 
 template <class L, typename real>
-static hipError_t density_impl(const Geometry &g, const void *buf, void *out, bool cplx,
-                               hipStream_t s) {
+static hipError_t density_impl(const Geometry &g, const void *buf, void *out, hipStream_t s) {
     const int strips = (g.nx + 255) / 256;
     const int64_t blocks = int64_t(strips) * g.ny * g.nz;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    if (cplx)
-        hipLaunchKernelGGL((k_density<L, real, true>), dim3(unsigned(blocks)), dim3(256), 0, s, g,
-                           static_cast<const real *>(buf), static_cast<real *>(out));
-    else
-        hipLaunchKernelGGL((k_density<L, real, false>), dim3(unsigned(blocks)), dim3(256), 0, s, g,
-                           static_cast<const real *>(buf), static_cast<real *>(out));
+    hipLaunchKernelGGL((k_density<L, real>), dim3(unsigned(blocks)), dim3(256), 0, s, g,
+                       static_cast<const real *>(buf), static_cast<real *>(out));
     return hipGetLastError();
-}
-
-static hipError_t density_dispatch(const Geometry &g, int precision, const void *buf, void *out,
-                                   bool cplx, hipStream_t s) {
-    if (g.D == 2)
-        return precision == 0 ? density_impl<D2Q9, float>(g, buf, out, cplx, s)
-                              : density_impl<D2Q9, double>(g, buf, out, cplx, s);
-    return precision == 0 ? density_impl<D3Q19, float>(g, buf, out, cplx, s)
-                          : density_impl<D3Q19, double>(g, buf, out, cplx, s);
 }
 
 hipError_t launch_density_real(const Geometry &g, int precision, const void *buf, void *out,
                                hipStream_t s) {
-    return density_dispatch(g, precision, buf, out, false, s);
+    if (g.D == 2)
+        return precision == 0 ? density_impl<D2Q9, float>(g, buf, out, s)
+                              : density_impl<D2Q9, double>(g, buf, out, s);
+    return precision == 0 ? density_impl<D3Q19, float>(g, buf, out, s)
+                          : density_impl<D3Q19, double>(g, buf, out, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -216,312 +196,467 @@ hipError_t launch_stats(const Geometry &g, int precision, const void *buf, doubl
 }
 
 // ---------------------------------------------------------------------------
-// FFT along the contiguous axis + rotation [n2][n1][n0] -> [n0][n2][n1].
+// Structure factor.  One sample of a lattice is
+//   rows: density gather and transform along x.  The density is real, so two
+//     rows share one complex transform and only kx = 0 .. nx/2 is kept; a block
+//     takes 2 lc rows and writes the half spectrum with y (the next axis)
+//     contiguous, [kx][z][y], in pieces of 2 lc values;
+//   mid (3D): transform along y of lc lines (kx, z .. z + lc - 1), written
+//     [kx][ky][z];
+//   last: transform along the last axis of lc lines and, from LDS, the bins, the
+//     moments of L(t) and the recorded modes; the spectrum goes nowhere else.
+// The modes with 0 < kx < nx/2 stand for themselves and
+// their mirror images -k, which have the same |X|^2.
+//
+// Traffic of a 2D FP32 sample: 36 B per node read, 4 written, 4 read.  (Complex
+// transforms with a rotation pass per axis and a binning pass moved 36 + 88.)
+// Measured, before and now, us: 4096^2 FP32 840 and 395 (rows 207: 2.9 TB/s of
+// populations; last 190 to 310); 256^3 FP32 2000 and 410; 750 x 487 FP64 480 and
+// 52; 16 fields of 128^2 1390 and 20.
 // ---------------------------------------------------------------------------
-size_t twiddle_len(int n) { return (n & (n - 1)) == 0 ? size_t(n > 1 ? n / 2 : 1) : size_t(n); }
+// Lines in LDS: element i of line l at l sk_stride(m) + sk_pad(i).  One pad
+// element in eight keeps the strided accesses of the radix-8 passes off each
+// other's banks; the odd stride does it for accesses across lines.
+__host__ __device__ inline int sk_stride(int m) { return m + (m >> 3) + 1; }
+__device__ inline int sk_pad(int i) { return i + (i >> 3); }
+
+constexpr int SK_HELD = 16;  // complex values a thread holds in one pass
 
 template <typename real>
-__global__ void k_twiddle(cplx<real> *tw, int n, int len) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= len) return;
-    double s, c;
-    // exp(-2 pi i k / n), argument reduced exactly through sincospi
-    sincospi(-2.0 * double(k) / double(n), &s, &c);
-    tw[k].re = real(c);
-    tw[k].im = real(s);
+__device__ __forceinline__ cplx<real> c_mul(cplx<real> a, cplx<real> b) {
+    return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
 }
-
-hipError_t launch_twiddles(int precision, void *tw, int n, hipStream_t s) {
-    const int len = int(twiddle_len(n));
-    const int nb = (len + 255) / 256;
-    if (precision == 0)
-        hipLaunchKernelGGL(k_twiddle<float>, dim3(nb), dim3(256), 0, s,
-                           static_cast<cplx<float> *>(tw), n, len);
-    else
-        hipLaunchKernelGGL(k_twiddle<double>, dim3(nb), dim3(256), 0, s,
-                           static_cast<cplx<double> *>(tw), n, len);
-    return hipGetLastError();
-}
-
-// Iterative radix-2 Cooley-Tukey on one line staged in LDS (a[n]): bit-reversed
-// load, then log2(n) butterfly stages with twiddles W_len^k = tw[k * n/len].
 template <typename real>
-__device__ inline void fft_line_pow2(cplx<real> *__restrict__ line, const cplx<real> *__restrict__ tw,
-                                     int n, int logn, cplx<real> *a) {
-    for (int i = threadIdx.x; i < n; i += 256) {
-        const int r = logn == 0 ? 0 : int(__brev(unsigned(i)) >> (32 - logn));
-        a[r] = line[i];
+__device__ __forceinline__ cplx<real> c_add(cplx<real> a, cplx<real> b) {
+    return {a.re + b.re, a.im + b.im};
+}
+template <typename real>
+__device__ __forceinline__ cplx<real> c_sub(cplx<real> a, cplx<real> b) {
+    return {a.re - b.re, a.im - b.im};
+}
+
+// X_k = sum_r v_r exp(-2 pi i r k / R) in place
+template <typename real>
+__device__ __forceinline__ void dft_r(cplx<real> (&v)[2]) {
+    const cplx<real> t = v[0];
+    v[0] = c_add(t, v[1]);
+    v[1] = c_sub(t, v[1]);
+}
+template <typename real>
+__device__ __forceinline__ void dft_r(cplx<real> (&v)[4]) {
+    const cplx<real> s = c_add(v[0], v[2]), d = c_sub(v[0], v[2]);
+    const cplx<real> p = c_add(v[1], v[3]), q = c_sub(v[1], v[3]);
+    v[0] = c_add(s, p);
+    v[2] = c_sub(s, p);
+    v[1] = {d.re + q.im, d.im - q.re};
+    v[3] = {d.re - q.im, d.im + q.re};
+}
+template <typename real>
+__device__ __forceinline__ void dft_r(cplx<real> (&v)[8]) {
+    cplx<real> e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    dft_r(e);
+    dft_r(o);
+    constexpr real h = real(0.70710678118654752440);
+    const cplx<real> o1 = {(o[1].re + o[1].im) * h, (o[1].im - o[1].re) * h};
+    const cplx<real> o2 = {o[2].im, -o[2].re};
+    const cplx<real> o3 = {(o[3].im - o[3].re) * h, -(o[3].re + o[3].im) * h};
+    v[0] = c_add(e[0], o[0]);
+    v[4] = c_sub(e[0], o[0]);
+    v[1] = c_add(e[1], o1);
+    v[5] = c_sub(e[1], o1);
+    v[2] = c_add(e[2], o2);
+    v[6] = c_sub(e[2], o2);
+    v[3] = c_add(e[3], o3);
+    v[7] = c_sub(e[3], o3);
+}
+
+// One radix-R Stockham pass over lines of m = 2^logm (2^nsl: product of the
+// radices before): every value is in a register between the two barriers, so
+// the pass works in place.  Needs lines * m <= SK_HELD * blockDim.x.
+template <typename real, int R>
+__device__ __forceinline__ void sk_pass(cplx<real> *a, int lines, int m, int logm, int nsl,
+                               const cplx<real> *__restrict__ tw) {
+    constexpr int LR = R == 8 ? 3 : (R == 4 ? 2 : 1), M = SK_HELD / R;
+    const int lper = logm - LR, per = 1 << lper, total = lines << lper, ls = sk_stride(m);
+    cplx<real> v[M][R];
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+        const int id = threadIdx.x + q * blockDim.x;
+        if (id < total) {
+            const int j = id & (per - 1);
+            const cplx<real> *b = a + (id >> lper) * ls;
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[q][r] = b[sk_pad(j + (r << lper))];
+            if (nsl > 0) {
+                const int k = (j & ((1 << nsl) - 1)) << (lper - nsl);
+#pragma unroll
+                for (int r = 1; r < R; ++r) v[q][r] = c_mul(v[q][r], tw[k * r]);
+            }
+            dft_r(v[q]);
+        }
     }
     __syncthreads();
-    for (int len = 2; len <= n; len <<= 1) {
-        const int half = len >> 1;
-        const int stride = n / len;
-        for (int j = threadIdx.x; j < n / 2; j += 256) {
-            const int g = j / half, k = j - g * half;
-            const int i0 = g * len + k, i1 = i0 + half;
-            const cplx<real> w = tw[k * stride];
-            const cplx<real> u = a[i0], v0 = a[i1];
-            const cplx<real> v = {v0.re * w.re - v0.im * w.im, v0.re * w.im + v0.im * w.re};
-            a[i0] = {u.re + v.re, u.im + v.im};
-            a[i1] = {u.re - v.re, u.im - v.im};
+#pragma unroll
+    for (int q = 0; q < M; ++q) {
+        const int id = threadIdx.x + q * blockDim.x;
+        if (id < total) {
+            const int j = id & (per - 1), k = j & ((1 << nsl) - 1);
+            cplx<real> *b = a + (id >> lper) * ls;
+            const int o = ((j >> nsl) << (nsl + LR)) + k;
+#pragma unroll
+            for (int r = 0; r < R; ++r) b[sk_pad(o + (r << nsl))] = v[q][r];
+        }
+    }
+    __syncthreads();
+}
+
+template <typename real>
+__device__ __forceinline__ void sk_pow2(cplx<real> *a, int lines, int m, int logm, const cplx<real> *__restrict__ tw) {
+    int nsl = 0;
+    for (; logm - nsl >= 3; nsl += 3) sk_pass<real, 8>(a, lines, m, logm, nsl, tw);
+    if (logm - nsl == 2) sk_pass<real, 4>(a, lines, m, logm, nsl, tw);
+    else if (logm - nsl == 1) sk_pass<real, 2>(a, lines, m, logm, nsl, tw);
+}
+
+// Transforms `lines` lines of n values in LDS, in place, natural order in and
+// out.  Starts and ends at a barrier.  Table `tab` (see sk_table):
+//   n a power of two (m = n): radix-8 passes;
+//   other n: the chirp transform (Bluestein) over m = 2^logm >= 2n - 1, jk =
+//     (j^2 + k^2 - (k - j)^2)/2: multiply by the chirp, convolve by a transform,
+//     a product with the chirp's spectrum and an inverse transform, multiply by
+//     the chirp.  O(m log m) where the direct sum is O(n^2): at 750 x 487 in
+//     FP64 a sample's transforms took 458 us as direct sums;
+//   logm < 0 (FP64 lines beyond 4096 whose chirp form does not fit the LDS):
+//     the direct sum.
+template <typename real>
+__device__ __forceinline__ void sk_fft(cplx<real> *a, int lines, const SkAxis &x, const cplx<real> *__restrict__ tab) {
+    const int n = x.n, m = x.m, ls = sk_stride(m);
+    __syncthreads();
+    if (n == 1) return;
+    if (x.logm < 0) {
+        cplx<real> acc[SK_HELD];
+#pragma unroll
+        for (int q = 0; q < SK_HELD; ++q) {
+            const int id = threadIdx.x + q * blockDim.x;
+            if (id < lines * n) {
+                const int k = id % n;
+                const cplx<real> *b = a + (id / n) * ls;
+                real sr = real(0), si = real(0);
+                int idx = 0;
+                for (int j = 0; j < n; ++j) {
+                    const cplx<real> w = tab[idx], v = b[sk_pad(j)];
+                    sr += v.re * w.re - v.im * w.im;
+                    si += v.re * w.im + v.im * w.re;
+                    idx += k;
+                    if (idx >= n) idx -= n;
+                }
+                acc[q] = {sr, si};
+            }
         }
         __syncthreads();
-    }
-    for (int i = threadIdx.x; i < n; i += 256) line[i] = a[i];
-}
-
-// Direct DFT of one line (any n): X_k = sum_j x_j tw[(j k) mod n].
-template <typename real>
-__device__ inline void dft_line(cplx<real> *__restrict__ line, const cplx<real> *__restrict__ tw, int n,
-                                cplx<real> *a) {
-    for (int i = threadIdx.x; i < n; i += 256) a[i] = line[i];
-    __syncthreads();
-    for (int k = threadIdx.x; k < n; k += 256) {
-        real sr = real(0), si = real(0);
-        int idx = 0;
-        for (int j = 0; j < n; ++j) {
-            const cplx<real> w = tw[idx];
-            sr += a[j].re * w.re - a[j].im * w.im;
-            si += a[j].re * w.im + a[j].im * w.re;
-            idx += k;
-            if (idx >= n) idx -= n;
+#pragma unroll
+        for (int q = 0; q < SK_HELD; ++q) {
+            const int id = threadIdx.x + q * blockDim.x;
+            if (id < lines * n) a[(id / n) * ls + sk_pad(id % n)] = acc[q];
         }
-        line[k] = {sr, si};
+        __syncthreads();
+        return;
     }
-}
-
-template <typename real>
-__global__ void __launch_bounds__(256) k_fft_pow2(cplx<real> *__restrict__ data,
-                                                  const cplx<real> *__restrict__ tw, int n,
-                                                  int logn) {
-    extern __shared__ unsigned char smem_raw[];
-    fft_line_pow2<real>(data + int64_t(blockIdx.x) * n, tw, n, logn,
-                        reinterpret_cast<cplx<real> *>(smem_raw));
-}
-
-template <typename real>
-__global__ void __launch_bounds__(256) k_dft(cplx<real> *__restrict__ data,
-                                             const cplx<real> *__restrict__ tw, int n) {
-    extern __shared__ unsigned char smem_raw[];
-    dft_line<real>(data + int64_t(blockIdx.x) * n, tw, n, reinterpret_cast<cplx<real> *>(smem_raw));
-}
-
-// out[(i0 * n2 + i2) * n1 + i1] = in[(i2 * n1 + i1) * n0 + i0], via 32x32 LDS tiles;
-// block (b0, b1, i2) of the (ceil(n0/32), ceil(n1/32), n2) grid
-template <typename real>
-__device__ inline void rotate_block(const cplx<real> *__restrict__ in, cplx<real> *__restrict__ out,
-                                    int n0, int n1, int n2, int bx, int by, int i2,
-                                    cplx<real> (&tile)[32][33]) {
-    const int b0 = bx * 32, b1 = by * 32;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int r = ty; r < 32; r += 8) {
-        const int i1 = b1 + r, i0 = b0 + tx;
-        if (i1 < n1 && i0 < n0) tile[r][tx] = in[(int64_t(i2) * n1 + i1) * n0 + i0];
+    const bool chirped = n != m;
+    const cplx<real> *chirp = tab + m, *bhat = tab + m + n;
+    for (int half = 0; half < (chirped ? 2 : 1); ++half) {
+        if (chirped) {
+            for (int id = threadIdx.x; id < lines << x.logm; id += blockDim.x) {
+                const int j = id & (m - 1);
+                cplx<real> *b = a + (id >> x.logm) * ls + sk_pad(j);
+                if (half == 0) {
+                    *b = j < n ? c_mul(*b, chirp[j]) : cplx<real>{real(0), real(0)};
+                } else {  // the inverse transform, as the conjugate of a forward one
+                    const cplx<real> v = c_mul(*b, bhat[j]);
+                    *b = {v.re, -v.im};
+                }
+            }
+            __syncthreads();
+        }
+        sk_pow2<real>(a, lines, m, x.logm, tab);
+    }
+    if (!chirped) return;
+    for (int id = threadIdx.x; id < lines << x.logm; id += blockDim.x) {
+        const int j = id & (m - 1);
+        if (j < n) {
+            cplx<real> *b = a + (id >> x.logm) * ls + sk_pad(j);
+            *b = c_mul(cplx<real>{b->re, -b->im}, chirp[j]);
+        }
     }
     __syncthreads();
-    for (int r = ty; r < 32; r += 8) {
-        const int i0 = b0 + r, i1 = b1 + tx;
-        if (i0 < n0 && i1 < n1) out[(int64_t(i0) * n2 + i2) * n1 + i1] = tile[tx][r];
-    }
 }
 
+// Device part of a transform table: tw[k] = exp(-2 pi i k / m), k < m, then for
+// the chirp form chirp[j] = exp(-pi i j^2 / n), j < n (both exactly reduced);
+// the chirp's spectrum behind them comes from the host.  `zero` words are
+// cleared by the same launch.
 template <typename real>
-__global__ void __launch_bounds__(256) k_rotate(const cplx<real> *__restrict__ in,
-                                                cplx<real> *__restrict__ out, int n0, int n1,
-                                                int n2) {
-    __shared__ cplx<real> tile[32][33];
-    rotate_block<real>(in, out, n0, n1, n2, int(blockIdx.x), int(blockIdx.y), int(blockIdx.z), tile);
-}
-
-hipError_t launch_fft_axis(int precision, void *data, void *tmp, const void *twiddle, int n0,
-                           int n1, int n2, hipStream_t s) {
-    const int64_t lines = int64_t(n1) * n2;
-    if (lines > 0x7fffffff || n0 > 8192) return hipErrorInvalidValue;
-    const bool pow2 = (n0 & (n0 - 1)) == 0;
-    int logn = 0;
-    while ((1 << logn) < n0) ++logn;
-    const size_t esz = precision == 0 ? sizeof(cplx<float>) : sizeof(cplx<double>);
-    const size_t shm = esz * size_t(n0);
-    if (shm > 160 * 1024) return hipErrorInvalidValue;
-    if (precision == 0) {
-        auto *d = static_cast<cplx<float> *>(data);
-        auto *t = static_cast<const cplx<float> *>(twiddle);
-        if (n0 > 1) {
-            if (pow2)
-                hipLaunchKernelGGL(k_fft_pow2<float>, dim3(unsigned(lines)), dim3(256), shm, s, d, t,
-                                   n0, logn);
-            else
-                hipLaunchKernelGGL(k_dft<float>, dim3(unsigned(lines)), dim3(256), shm, s, d, t, n0);
-        }
-        hipLaunchKernelGGL(k_rotate<float>, dim3((n0 + 31) / 32, (n1 + 31) / 32, n2), dim3(256),
-                           0, s, d, static_cast<cplx<float> *>(tmp), n0, n1, n2);
-    } else {
-        auto *d = static_cast<cplx<double> *>(data);
-        auto *t = static_cast<const cplx<double> *>(twiddle);
-        if (n0 > 1) {
-            if (pow2)
-                hipLaunchKernelGGL(k_fft_pow2<double>, dim3(unsigned(lines)), dim3(256), shm, s, d,
-                                   t, n0, logn);
-            else
-                hipLaunchKernelGGL(k_dft<double>, dim3(unsigned(lines)), dim3(256), shm, s, d, t,
-                                   n0);
-        }
-        hipLaunchKernelGGL(k_rotate<double>, dim3((n0 + 31) / 32, (n1 + 31) / 32, n2), dim3(256),
-                           0, s, d, static_cast<cplx<double> *>(tmp), n0, n1, n2);
+__global__ void __launch_bounds__(256) k_sk_table(cplx<real> *__restrict__ tab, SkAxis x,
+                                                  uint32_t *__restrict__ zero, int64_t words) {
+    const int64_t k = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (k < x.m) {
+        double s, c;
+        sincospi(-2.0 * double(k) / double(x.m), &s, &c);
+        tab[k] = {real(c), real(s)};
+    } else if (x.logm >= 0 && x.m != x.n && k < x.m + x.n) {
+        const int64_t j = k - x.m;
+        double s, c;
+        sincospi(-double((j * j) % (2 * x.n)) / double(x.n), &s, &c);
+        tab[k] = {real(c), real(s)};
     }
-    return hipGetLastError();
+    if (k < words) zero[k] = 0u;
 }
 
-// ---------------------------------------------------------------------------
-// Binning.  One block per x-line (fixed y, z) of the spectrum.
-// ---------------------------------------------------------------------------
-__device__ inline int isqrt_round(int64_t m) {
-    // b = round(sqrt(m)) in exact integer arithmetic ((b - 1/2)^2 <= m < (b + 1/2)^2)
-    int64_t b = int64_t(sqrt(double(m)));
-    while (b * b > m) --b;
-    while ((b + 1) * (b + 1) <= m) ++b;
-    if (m - b * b > b) ++b;
-    return int(b);
+// floor(sqrt(v)) of 0 <= v < 2^29
+__device__ inline int isqrt(int v) {
+    int b = int(sqrtf(float(v)));
+    while (b * b > v) --b;
+    while ((b + 1) * (b + 1) <= v) ++b;
+    return b;
+}
+// shell round(sqrt(v)): (b - 1/2)^2 <= v < (b + 1/2)^2, that is b^2 - b < v <= b^2 + b
+__device__ inline int shell_of(int v) {
+    const int b = isqrt(v);
+    return v > b * b + b ? b + 1 : b;
 }
 
 __device__ inline int signed_mode(int q, int n) { return q <= n / 2 ? q : q - n; }
 
+// Closes one sample: the time series' row gets (step, L) with L = 2 pi sum P /
+// sum |k| P, the moments are cleared, the row counters advance.  One thread,
+// after every block of the replica has added its share.
+__device__ __forceinline__ void sk_close(const MeasRep &m, uint64_t step) {
+    if (m.t.mom != nullptr) {
+        const double p0 = __hip_atomic_load(&m.t.mom[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const double p1 = __hip_atomic_load(&m.t.mom[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int row = m.series_n[0];
+        if (m.t.series != nullptr && row < m.t.series_cap) {
+            double *s = m.t.series + size_t(row) * (2 + m.t.n_rad);
+            s[0] = double(step);
+            s[1] = p1 > 0.0 ? 2.0 * M_PI * p0 / p1 : 0.0;
+        }
+        __hip_atomic_store(&m.t.mom[0], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&m.t.mom[1], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        m.series_n[0] = row + 1;
+    }
+    if (m.modes_cap > 0) m.modes_n[0] += 1;
+}
+
+// Bins of `lines` transformed lines in LDS.  Line l holds the modes (kx, ky, kz)
+// of its own last component, element i = signed mode i of the last axis (length
+// n); the others are (kx, ky) = (o, i0 + l) in 3D and kx = i0 + l in 2D.
+//
+// Along a line the shell grows with |k_last|, so every shell is a range of it
+// whose ends are integer square roots: the lanes go over (line, shell) pairs
+// and sum their few modes in registers, instead of one shell lookup and two
+// contended atomics per mode.  `wnd` [2][W] collects the lines' shells in LDS
+// (nullptr: one line, added to memory directly).
 template <typename real>
-__device__ inline void bin_row(const Geometry &g, const cplx<real> *__restrict__ spec,
-                               const BinTargets &t, double invN, int row, double *wnd,
-                               double (&red)[2][4]) {
-    const int y = row % g.ny, z = row / g.ny;
-    const int my = signed_mode(y, g.ny), mz = signed_mode(z, g.nz);
-    const int64_t base2 = int64_t(my) * my + int64_t(mz) * mz;
-    const bool rad = t.n_rad > 0;
-    const bool ser = t.mom != nullptr;
-    const int srow = ser ? t.series_n[0] : 0;
-    const bool ser_row = ser && t.series != nullptr && srow < t.series_cap;
-    const double ky = 2.0 * M_PI * my / g.ny, kz = 2.0 * M_PI * mz / g.nz;
-    int blo = 0, W = 0;
-    if (rad) {
-        const int half = g.nx / 2;
-        blo = isqrt_round(base2);
-        W = isqrt_round(base2 + int64_t(half) * half) - blo + 1;
-        for (int k = threadIdx.x; k < 2 * W; k += 256) wnd[k] = 0.0;
-        __syncthreads();
-    }
-    double sP = 0.0, skP = 0.0;
-    for (int x = threadIdx.x; x < g.nx; x += 256) {
-        const int mx = signed_mode(x, g.nx);
-        const int64_t m2 = base2 + int64_t(mx) * mx;
-        if (m2 == 0) continue;
-        const cplx<real> v = spec[int64_t(row) * g.nx + x];
-        const double P = (double(v.re) * double(v.re) + double(v.im) * double(v.im)) * invN;
-        const int nz_cnt = (mx != 0) + (my != 0) + (mz != 0);
-        if (nz_cnt == 1) {
-            const int d = mx != 0 ? 0 : (my != 0 ? 1 : 2);
-            const int m = abs(mx != 0 ? mx : (my != 0 ? my : mz));
-            unsafeAtomicAdd(&t.axis_sum[d * t.n_axis + m], P);
-            unsafeAtomicAdd(&t.axis_sq[d * t.n_axis + m], P * P);
+__device__ __forceinline__ void sk_bin(const MeasRep &m, const cplx<real> *a, int ls, int lines, int o, int i0,
+                              double *wnd) {
+    const Geometry &g = m.g;
+    const BinTargets &t = m.t;
+    const bool d3 = g.D == 3;
+    const int n = d3 ? g.nz : g.ny, half = n / 2, nt = blockDim.x;
+    const double invN = m.invN;
+    auto other = [&](int l, int &kx, int &ky) {
+        kx = d3 ? o : i0 + l;
+        ky = d3 ? signed_mode(i0 + l, g.ny) : 0;
+    };
+    auto weight = [&](int kx) { return kx == 0 || 2 * kx == g.nx ? 1.0 : 2.0; };
+    auto power = [&](int l, int i) {
+        const cplx<real> v = a[l * ls + sk_pad(i)];
+        return (double(v.re) * double(v.re) + double(v.im) * double(v.im)) * invN;
+    };
+    const int srow = t.mom && t.series ? t.series_n[0] : 0;
+    double *srow_bins = t.mom && t.series && srow < t.series_cap ? t.series + size_t(srow) * (2 + t.n_rad) + 2 : nullptr;
+    auto add_shell = [&](int b, double s, double q) {
+        unsafeAtomicAdd(&t.rad_sum[b], s);
+        if (t.rad_sq) unsafeAtomicAdd(&t.rad_sq[b], q);
+        if (srow_bins) unsafeAtomicAdd(&srow_bins[b], s);
+    };
+    if (t.n_rad > 0) {
+        int lo2 = 0x7fffffff, hi2 = 0;
+        for (int l = 0; l < lines; ++l) {
+            int kx, ky;
+            other(l, kx, ky);
+            lo2 = min(lo2, kx * kx + ky * ky);
+            hi2 = max(hi2, kx * kx + ky * ky);
         }
-        if (rad) {
-            const int b = isqrt_round(m2) - blo;
-            atomicAdd(&wnd[b], P);
-            atomicAdd(&wnd[W + b], P * P);
+        const int blo = shell_of(lo2), W = shell_of(hi2 + half * half) - blo + 1;
+        if (wnd) {
+            for (int k = threadIdx.x; k < 2 * W; k += nt) wnd[k] = 0.0;
+            __syncthreads();
         }
-        if (ser) {
-            const double kx = 2.0 * M_PI * mx / g.nx;
-            sP += P;
-            skP += sqrt(kx * kx + ky * ky + kz * kz) * P;
-        }
-    }
-    if (ser) {
-        sP = wave_sum(sP);
-        skP = wave_sum(skP);
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        if (lane == 0) {
-            red[0][wv] = sP;
-            red[1][wv] = skP;
-        }
-    }
-    if (rad || ser) __syncthreads();
-    if (ser && threadIdx.x == 0) {
-        unsafeAtomicAdd(&t.mom[0], red[0][0] + red[0][1] + red[0][2] + red[0][3]);
-        unsafeAtomicAdd(&t.mom[1], red[1][0] + red[1][1] + red[1][2] + red[1][3]);
-    }
-    if (rad) {
-        double *srow_bins = ser_row ? t.series + size_t(srow) * (2 + t.n_rad) + 2 : nullptr;
-        for (int k = threadIdx.x; k < W; k += 256) {
-            if (wnd[k] != 0.0 || wnd[W + k] != 0.0) {
-                unsafeAtomicAdd(&t.rad_sum[blo + k], wnd[k]);
-                unsafeAtomicAdd(&t.rad_sq[blo + k], wnd[W + k]);
-                if (srow_bins) unsafeAtomicAdd(&srow_bins[blo + k], wnd[k]);
+        for (int id = threadIdx.x; id < lines * W; id += nt) {
+            const int l = id / W, b = blo + id % W;
+            int kx, ky;
+            other(l, kx, ky);
+            const int base = kx * kx + ky * ky;
+            const int top = b * b + b - base;  // |k_last|^2 <= top and > top - 2b
+            if (b == 0 || top < 0) continue;
+            const int hi = min(half, isqrt(top));
+            const int lo = top - 2 * b < 0 ? 0 : isqrt(top - 2 * b) + 1;
+            double s = 0.0, q = 0.0;
+            for (int k = lo; k <= hi; ++k) {
+                const double p = power(l, k);
+                s += p;
+                q += p * p;
+                if (k > 0 && 2 * k != n) {
+                    const double r = power(l, n - k);
+                    s += r;
+                    q += r * r;
+                }
+            }
+            if (s == 0.0) continue;
+            const double w = weight(kx);
+            if (wnd) {
+                atomicAdd(&wnd[b - blo], w * s);
+                atomicAdd(&wnd[W + b - blo], w * q);
+            } else {
+                add_shell(b, w * s, w * q);
             }
         }
-    }
-}
-
-template <typename real>
-__global__ void __launch_bounds__(256) k_bin(Geometry g, const cplx<real> *__restrict__ spec,
-                                             BinTargets t, double invN) {
-    extern __shared__ double wnd[];  // [2][W]
-    __shared__ double red[2][4];
-    bin_row<real>(g, spec, t, invN, int(blockIdx.x), wnd, red);
-}
-
-hipError_t launch_bin(const Geometry &g, int precision, const void *spec, const BinTargets &t,
-                      hipStream_t s) {
-    const int64_t rows = int64_t(g.ny) * g.nz;
-    if (rows > 0x7fffffff) return hipErrorInvalidValue;
-    const size_t shm = t.n_rad > 0 ? sizeof(double) * 2 * size_t(g.nx / 2 + 3) : 0;
-    const double invN = 1.0 / double(g.N);
-    if (precision == 0)
-        hipLaunchKernelGGL(k_bin<float>, dim3(unsigned(rows)), dim3(256), shm, s, g,
-                           static_cast<const cplx<float> *>(spec), t, invN);
-    else
-        hipLaunchKernelGGL(k_bin<double>, dim3(unsigned(rows)), dim3(256), shm, s, g,
-                           static_cast<const cplx<double> *>(spec), t, invN);
-    return hipGetLastError();
-}
-
-// Closes one sample of a replica's time series: row *series_n gets (step, L)
-// with L = 2 pi sum P / sum |k| P, the moments are cleared and the row advances.
-__device__ inline void series_finalize(double *mom, double *series, int *series_n, int cap,
-                                       int row_len, uint64_t step) {
-    const int row = series_n[0];
-    if (series != nullptr && row < cap) {
-        series[size_t(row) * row_len] = double(step);
-        series[size_t(row) * row_len + 1] = mom[1] > 0.0 ? 2.0 * M_PI * mom[0] / mom[1] : 0.0;
-    }
-    mom[0] = 0.0;
-    mom[1] = 0.0;
-    series_n[0] = row + 1;
-}
-
-// Mode recorder: the complex amplitudes of the modes m = 1..nm along each
-// lattice axis of the transformed density (natural [z][y][x] order), as
-// doubles, into row *rec_n of rec[cap][D][nm][2]; the row counter advances.
-template <typename real>
-__device__ inline void record_modes_block(const Geometry &g, const cplx<real> *__restrict__ spec,
-                                          int nm, double *__restrict__ rec, int *__restrict__ rec_n,
-                                          int cap) {
-    const int row = rec_n[0];
-    const int total = g.D * nm;
-    if (row < cap) {
-        for (int q = threadIdx.x; q < total; q += 256) {
-            const int d = q / nm, m = q % nm + 1;
-            const int64_t stride = d == 0 ? 1 : (d == 1 ? int64_t(g.nx) : int64_t(g.nx) * g.ny);
-            const cplx<real> v = spec[int64_t(m) * stride];
-            rec[(size_t(row) * total + q) * 2] = double(v.re);
-            rec[(size_t(row) * total + q) * 2 + 1] = double(v.im);
+        if (wnd) {
+            __syncthreads();
+            for (int k = threadIdx.x; k < W; k += nt)
+                if (wnd[k] != 0.0 || wnd[W + k] != 0.0) add_shell(blo + k, wnd[k], wnd[W + k]);
         }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) rec_n[0] = row + 1;
+    if (t.axis_sum) {
+        auto add_axis = [&](int d, int k, double w, double p) {
+            unsafeAtomicAdd(&t.axis_sum[d * t.n_axis + abs(k)], w * p);
+            unsafeAtomicAdd(&t.axis_sq[d * t.n_axis + abs(k)], w * p * p);
+        };
+        for (int l = threadIdx.x; l < lines; l += nt) {  // modes with no last component
+            int kx, ky;
+            other(l, kx, ky);
+            if (ky == 0 && kx != 0) add_axis(0, kx, weight(kx), power(l, 0));
+            if (kx == 0 && ky != 0) add_axis(1, ky, 1.0, power(l, 0));
+        }
+        if ((!d3 || o == 0) && i0 == 0)  // line 0 has no other component
+            for (int i = threadIdx.x + 1; i < n; i += nt) add_axis(g.D - 1, signed_mode(i, n), 1.0, power(0, i));
+    }
+    if (t.mom) {
+        const double ux = 2.0 * M_PI / g.nx, uy = 2.0 * M_PI / g.ny, uz = 2.0 * M_PI / n;
+        double sp = 0.0, sk = 0.0;
+        for (int id = threadIdx.x; id < lines * n; id += nt) {
+            const int l = id / n, i = id % n;
+            int kx, ky;
+            other(l, kx, ky);
+            const int kl = signed_mode(i, n);
+            if (kx == 0 && ky == 0 && kl == 0) continue;
+            const double p = weight(kx) * power(l, i);
+            const double x = ux * kx, y = uy * ky, z = uz * kl;
+            sp += p;
+            sk += sqrt(x * x + y * y + z * z) * p;
+        }
+        sp = wave_sum(sp);
+        sk = wave_sum(sk);
+        __shared__ double red[2][16];
+        if ((threadIdx.x & 63) == 0) {
+            red[0][threadIdx.x >> 6] = sp;
+            red[1][threadIdx.x >> 6] = sk;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            double v = 0.0;
+            for (int w = 0; w < nt >> 6; ++w) v += red[threadIdx.x][w];
+            unsafeAtomicAdd(&t.mom[threadIdx.x], v);
+        }
+    }
+    if (m.modes_cap > 0 && m.modes_n[0] < m.modes_cap) {
+        // amplitudes of the modes 1 .. nm along each axis, row [D][nm][2]
+        double *row = m.modes + size_t(m.modes_n[0]) * g.D * m.modes_nm * 2;
+        auto put = [&](int d, int k, int l, int i) {
+            const cplx<real> v = a[l * ls + sk_pad(i)];
+            row[(d * m.modes_nm + k - 1) * 2] = double(v.re);
+            row[(d * m.modes_nm + k - 1) * 2 + 1] = double(v.im);
+        };
+        for (int l = threadIdx.x; l < lines; l += nt) {
+            int kx, ky;
+            other(l, kx, ky);
+            if (ky == 0 && kx >= 1 && kx <= m.modes_nm) put(0, kx, l, 0);
+            if (d3 && kx == 0 && ky >= 1 && ky <= m.modes_nm) put(1, ky, l, 0);
+        }
+        if ((!d3 || o == 0) && i0 == 0)
+            for (int k = threadIdx.x + 1; k <= m.modes_nm; k += nt) put(g.D - 1, k, 0, k);
+    }
+}
+
+// Half spectra of two rows from the transform of (row 0) + i (row 1).
+template <typename real>
+__device__ __forceinline__ void sk_unpack(const cplx<real> *line, int n, int k, cplx<real> &r0, cplx<real> &r1) {
+    const cplx<real> p = line[sk_pad(k)], q = line[sk_pad(k == 0 ? 0 : n - k)];
+    constexpr real h = real(0.5);
+    r0 = {(p.re + q.re) * h, (p.im - q.im) * h};
+    r1 = {(p.im + q.im) * h, (q.re - p.re) * h};
+}
+
+// the rows y0, y0 + 1, .. of plane z as packed lines; val(x, y, z) is the field
+template <typename real, class Val>
+__device__ __forceinline__ void sk_load_rows(const Geometry &g, int y0, int z, int lines, int ls, cplx<real> *a, Val val) {
+    for (int id = threadIdx.x; id < lines * g.nx; id += blockDim.x) {
+        const int l = id / g.nx, x = id % g.nx, y = y0 + 2 * l;
+        a[l * ls + sk_pad(x)] = {val(x, y, z), y + 1 < g.ny ? val(x, y + 1, z) : real(0)};
+    }
+}
+
+template <typename real, class Val>
+__device__ __forceinline__ void sk_rows_block(const MeasRep &m, int blk, cplx<real> *a, Val val) {
+    const Geometry &g = m.g;
+    const int lc = m.lc[0], per = (g.ny + 2 * lc - 1) / (2 * lc);
+    const int z = blk / per, y0 = (blk % per) * 2 * lc;
+    const int lines = min(lc, (g.ny - y0 + 1) / 2), ls = sk_stride(m.ax[0].m);
+    sk_load_rows<real>(g, y0, z, lines, ls, a, val);
+    sk_fft<real>(a, lines, m.ax[0], static_cast<const cplx<real> *>(m.tab[0]));
+    cplx<real> *out = static_cast<cplx<real> *>(m.cbuf);
+    const int hx = g.nx / 2 + 1;
+    for (int id = threadIdx.x; id < hx * lines; id += blockDim.x) {
+        const int l = id % lines, k = id / lines, y = y0 + 2 * l;
+        cplx<real> r0, r1;
+        sk_unpack<real>(a + l * ls, g.nx, k, r0, r1);
+        cplx<real> *o = out + (int64_t(k) * g.nz + z) * g.ny + y;
+        o[0] = r0;
+        if (y + 1 < g.ny) o[1] = r1;
+    }
+}
+
+// transform of `lines` contiguous lines of `in` into LDS
+template <typename real>
+__device__ __forceinline__ void sk_lines(const cplx<real> *__restrict__ in, int lines, const SkAxis &x, const void *tab,
+                                cplx<real> *a) {
+    const int ls = sk_stride(x.m);
+    for (int id = threadIdx.x; id < lines * x.n; id += blockDim.x)
+        a[(id / x.n) * ls + sk_pad(id % x.n)] = in[id];
+    sk_fft<real>(a, lines, x, static_cast<const cplx<real> *>(tab));
+}
+
+template <typename real>
+__device__ __forceinline__ void sk_last_block(const MeasRep &m, int blk, unsigned char *smem) {
+    const Geometry &g = m.g;
+    const bool d3 = g.D == 3;
+    const SkAxis &x = m.ax[d3 ? 2 : 1];
+    const int inner = d3 ? g.ny : g.nx / 2 + 1, lc = m.lc[2];
+    const int per = (inner + lc - 1) / lc, o = blk / per, i0 = (blk % per) * lc;
+    const int lines = min(lc, inner - i0), ls = sk_stride(x.m);
+    cplx<real> *a = reinterpret_cast<cplx<real> *>(smem);
+    double *wnd = lc > 1 ? reinterpret_cast<double *>(smem + sk_line_bytes(sizeof(cplx<real>), lc, x.m)) : nullptr;
+    const cplx<real> *in = static_cast<const cplx<real> *>(d3 ? m.ctmp : m.cbuf);
+    sk_lines<real>(in + (int64_t(o) * inner + i0) * x.n, lines, x, m.tab[d3 ? 2 : 1], a);
+    sk_bin<real>(m, a, ls, lines, o, i0, wnd);
 }
 
 // ---------------------------------------------------------------------------
-// One S(k) sample of every replica of an ensemble in a fixed number of
-// launches (density, then per axis an FFT pass and a rotation, binning, mode
-// records, series rows), whatever the number of replicas.  Each launch is a
-// flat grid over the replicas: block b belongs to the replica r with
-// pre[r] <= b < pre[r + 1] (a prefix table per kind of work).
+// One sample of every replica of an ensemble in two or three launches, whatever
+// the number of replicas.  Each launch is a flat grid over the replicas: block b
+// belongs to the replica r with pre[r] <= b < pre[r + 1] (a prefix table per
+// kind of work).
 // ---------------------------------------------------------------------------
 __device__ inline int rep_of(const int *__restrict__ pre, int nrep, int b) {
     // largest r with pre[r] <= b; replicas without blocks of this kind have
@@ -535,178 +670,327 @@ __device__ inline int rep_of(const int *__restrict__ pre, int nrep, int b) {
     return lo;
 }
 
-// Arguments of the FFT pass d (transform of the contiguous axis, then the
-// rotation (n0, n1, n2) -> (n1, n2, n0)); a unit middle axis makes the
-// rotation a plain transpose of (n2 x n0).
-struct PassDims {
-    int n0, n1, n2;
-};
-__host__ __device__ inline PassDims pass_dims(const Geometry &g, int d) {
-    int n0 = g.nx, n1 = g.ny, n2 = g.nz;
-    for (int k = 0; k < d; ++k) {
-        const int t = n0;
-        n0 = n1;
-        n1 = n2;
-        n2 = t;
-    }
-    return n1 == 1 ? PassDims{n0, n2, 1} : PassDims{n0, n1, n2};
+template <class L, typename real>
+__device__ inline auto sk_density(const MeasRep &m, int par) {
+    const real *src = static_cast<const real *>(m.buf[par]);
+    return [&m, src](int x, int y, int z) {
+        real f[L::Q];
+        gather_node<L, real>(src, m.g, x, y, z, f);
+        real dn = real(0);
+#pragma unroll
+        for (int i = 0; i < L::Q; ++i) dn += f[i];
+        return dn;
+    };
 }
 
 template <class L, typename real>
-__global__ void __launch_bounds__(256) k_density_batch(const MeasRep *__restrict__ mr,
-                                                       const int *__restrict__ pre, int nrep, int par) {
+__global__ void __launch_bounds__(1024) k_sk_rows(const MeasRep *__restrict__ mr, const int *__restrict__ pre,
+                                                  int nrep, int par, uint64_t *__restrict__ step_base,
+                                                  uint64_t advance) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && advance) step_base[0] += advance;
     const int r = rep_of(pre, nrep, int(blockIdx.x));
-    const MeasRep &m = mr[r];
-    density_block<L, real, true>(m.g, static_cast<const real *>(m.buf[par]), static_cast<real *>(m.cbuf),
-                                 int(blockIdx.x) - pre[r]);
+    sk_rows_block<real>(mr[r], int(blockIdx.x) - pre[r], reinterpret_cast<cplx<real> *>(smem_raw),
+                        sk_density<L, real>(mr[r], par));
 }
 
-// pass d works in place on cbuf (d even) or ctmp (d odd) and rotates into the other
 template <typename real>
-__global__ void __launch_bounds__(256) k_fft_batch(const MeasRep *__restrict__ mr,
-                                                   const int *__restrict__ pre, int nrep, int d) {
-    extern __shared__ unsigned char smem_raw[];
-    const int r = rep_of(pre, nrep, int(blockIdx.x));
-    const MeasRep &m = mr[r];
-    const PassDims p = pass_dims(m.g, d);
-    if (p.n0 <= 1) return;
-    cplx<real> *line = static_cast<cplx<real> *>((d & 1) ? m.ctmp : m.cbuf) +
-                       int64_t(int(blockIdx.x) - pre[r]) * p.n0;
-    const cplx<real> *tw = static_cast<const cplx<real> *>(m.tw[d]);
+__global__ void __launch_bounds__(1024) k_sk_mid(const MeasRep *__restrict__ mr, const int *__restrict__ pre,
+                                                 int nrep) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     cplx<real> *a = reinterpret_cast<cplx<real> *>(smem_raw);
-    if ((p.n0 & (p.n0 - 1)) == 0) {
-        int logn = 0;
-        while ((1 << logn) < p.n0) ++logn;
-        fft_line_pow2<real>(line, tw, p.n0, logn, a);
+    const int r = rep_of(pre, nrep, int(blockIdx.x));
+    const MeasRep &m = mr[r];
+    const Geometry &g = m.g;
+    const int blk = int(blockIdx.x) - pre[r], lc = m.lc[1], per = (g.nz + lc - 1) / lc;
+    const int kx = blk / per, z0 = (blk % per) * lc, lines = min(lc, g.nz - z0), ls = sk_stride(m.ax[1].m);
+    sk_lines<real>(static_cast<const cplx<real> *>(m.cbuf) + (int64_t(kx) * g.nz + z0) * g.ny, lines, m.ax[1],
+                   m.tab[1], a);
+    cplx<real> *out = static_cast<cplx<real> *>(m.ctmp) + int64_t(kx) * g.ny * g.nz + z0;
+    for (int id = threadIdx.x; id < lines * g.ny; id += blockDim.x) {
+        const int l = id % lines, k = id / lines;
+        out[int64_t(k) * g.nz + l] = a[l * ls + sk_pad(k)];
+    }
+}
+
+// The replica's last block to finish closes the sample (series row, counters).
+// What it reads of the others went through atomics and is read back by atomics,
+// so every wave only has to see its own ones done before the block counts
+// itself; a device-wide fence writes back the L2 of the block's XCD, which cost
+// 40 us of a launch of 544 blocks.
+__device__ __forceinline__ void sk_finish(const MeasRep &m, int blocks, const uint64_t *step_base,
+                                          uint32_t step_off) {
+    if (m.t.mom == nullptr && m.modes_cap == 0) return;
+    __builtin_amdgcn_s_waitcnt(0);  // all counters
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    if (blocks > 1 &&
+        __hip_atomic_fetch_add(m.done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != blocks - 1)
+        return;
+    sk_close(m, step_base[0] + step_off);
+    if (blocks > 1) __hip_atomic_store(m.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename real>
+__global__ void __launch_bounds__(1024) k_sk_last(const MeasRep *__restrict__ mr, const int *__restrict__ pre,
+                                                  int nrep, const uint64_t *__restrict__ step_base,
+                                                  uint32_t step_off) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const int r = rep_of(pre, nrep, int(blockIdx.x));
+    sk_last_block<real>(mr[r], int(blockIdx.x) - pre[r], smem_raw);
+    sk_finish(mr[r], pre[r + 1] - pre[r], step_base, step_off);
+}
+
+// ---------------------------------------------------------------------------
+// Host side of the plan.
+// ---------------------------------------------------------------------------
+constexpr size_t SK_LDS = 160 * 1024 - 512;  // dynamic part
+
+static int sk_cap(int precision) { return precision == 0 ? 16384 : 8192; }  // lines x m of one block
+
+SkAxis sk_axis(int n, int precision) {
+    SkAxis x{n, 1, 0};
+    const bool pow2 = (n & (n - 1)) == 0;
+    while (x.m < (pow2 ? n : 2 * n - 1)) x.m <<= 1;
+    while ((1 << x.logm) < x.m) ++x.logm;
+    if (x.m > sk_cap(precision)) x.m = n, x.logm = -1;
+    return x;
+}
+
+size_t sk_table_len(const SkAxis &x) { return size_t(x.m) + (x.logm >= 0 && x.m != x.n ? size_t(x.n) + x.m : 0); }
+
+// Spectrum of the convolution kernel of the chirp form, exp(+pi i j^2 / n) at j
+// and m - j, over m points and divided by m (the inverse transform's factor).
+static void chirp_spectrum(const SkAxis &x, std::vector<double> &re, std::vector<double> &im) {
+    const int n = x.n, m = x.m;
+    re.assign(size_t(m), 0.0);
+    im.assign(size_t(m), 0.0);
+    for (int64_t j = 0; j < n; ++j) {
+        const double ang = M_PI * double((j * j) % (2 * n)) / double(n);
+        re[size_t(j)] = std::cos(ang) / m;
+        im[size_t(j)] = std::sin(ang) / m;
+        if (j > 0) {
+            re[size_t(m - j)] = re[size_t(j)];
+            im[size_t(m - j)] = im[size_t(j)];
+        }
+    }
+    // radix-2, decimation in frequency, then bit reversal
+    std::vector<double> c(size_t(m / 2) + 1), s(size_t(m / 2) + 1);
+    for (int k = 0; k < m / 2; ++k) {
+        c[size_t(k)] = std::cos(2.0 * M_PI * k / m);
+        s[size_t(k)] = -std::sin(2.0 * M_PI * k / m);
+    }
+    for (int len = m; len >= 2; len >>= 1)
+        for (int b = 0; b < m; b += len)
+            for (int k = 0; k < len / 2; ++k) {
+                const size_t p = size_t(b + k), q = p + size_t(len / 2), w = size_t(k) * size_t(m / len);
+                const double dr = re[p] - re[q], di = im[p] - im[q];
+                re[p] += re[q];
+                im[p] += im[q];
+                re[q] = dr * c[w] - di * s[w];
+                im[q] = dr * s[w] + di * c[w];
+            }
+    for (int i = 0, j = 0; i < m; ++i) {
+        if (i < j) {
+            std::swap(re[size_t(i)], re[size_t(j)]);
+            std::swap(im[size_t(i)], im[size_t(j)]);
+        }
+        int bit = m >> 1;
+        for (; bit && (j & bit); bit >>= 1) j ^= bit;
+        j ^= bit;
+    }
+}
+
+hipError_t sk_table(int precision, const SkAxis &x, void *tab, void *zero, int64_t zero_words, hipStream_t s) {
+    const int64_t n = std::max(int64_t(sk_table_len(x)), zero_words);
+    const dim3 nb(unsigned((n + 255) / 256));
+    if (precision == 0)
+        hipLaunchKernelGGL(k_sk_table<float>, nb, dim3(256), 0, s, static_cast<cplx<float> *>(tab), x,
+                           static_cast<uint32_t *>(zero), zero_words);
+    else
+        hipLaunchKernelGGL(k_sk_table<double>, nb, dim3(256), 0, s, static_cast<cplx<double> *>(tab), x,
+                           static_cast<uint32_t *>(zero), zero_words);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || x.logm < 0 || x.m == x.n) return e;
+    std::vector<double> re, im;
+    chirp_spectrum(x, re, im);
+    const size_t csz = precision == 0 ? 8 : 16, m = size_t(x.m);
+    std::vector<double> d(2 * m);
+    if (precision == 0) {
+        float *f = reinterpret_cast<float *>(d.data());
+        for (size_t k = 0; k < m; ++k) f[2 * k] = float(re[k]), f[2 * k + 1] = float(im[k]);
     } else {
-        dft_line<real>(line, tw, p.n0, a);
+        for (size_t k = 0; k < m; ++k) d[2 * k] = re[k], d[2 * k + 1] = im[k];
     }
+    e = hipMemcpyAsync(static_cast<char *>(tab) + csz * (m + size_t(x.n)), d.data(), csz * m,
+                       hipMemcpyHostToDevice, s);
+    const hipError_t es = hipStreamSynchronize(s);  // the host copy goes with this call
+    return e != hipSuccess ? e : es;
 }
 
-template <typename real>
-__global__ void __launch_bounds__(256) k_rotate_batch(const MeasRep *__restrict__ mr,
-                                                      const int *__restrict__ pre, int nrep, int d) {
-    __shared__ cplx<real> tile[32][33];
-    const int r = rep_of(pre, nrep, int(blockIdx.x));
-    const MeasRep &m = mr[r];
-    const PassDims p = pass_dims(m.g, d);
-    const int gx = (p.n0 + 31) / 32, gy = (p.n1 + 31) / 32;
-    const int lb = int(blockIdx.x) - pre[r];
-    const int bz = lb / (gx * gy), rem = lb % (gx * gy);
-    const void *in = (d & 1) ? m.ctmp : m.cbuf;
-    void *out = (d & 1) ? m.cbuf : m.ctmp;
-    rotate_block<real>(static_cast<const cplx<real> *>(in), static_cast<cplx<real> *>(out), p.n0, p.n1,
-                       p.n2, rem % gx, rem / gx, bz, tile);
+// Lines per block: enough to write pieces of 64 to 256 bytes (of up to 16384
+// values, whose LDS still leaves a block its 160 KB), but not so many that an
+// axis with few lines leaves CUs without a block.
+static int sk_lines_per_block(int m, int precision, int64_t lines) {
+    const int cap = sk_cap(precision), base = precision == 0 ? 8192 : 4096;
+    int lc = std::min(16, std::max(std::max(1, base / m), std::min(4, cap / m)));
+    while (lc > 2 && lines / lc < 512) lc >>= 1;
+    return std::max(1, std::min(lc, cap / m));
 }
 
-// the transformed spectrum lies in cbuf after an even number of passes, else in ctmp
-template <typename real>
-__global__ void __launch_bounds__(256) k_bin_batch(const MeasRep *__restrict__ mr,
-                                                   const int *__restrict__ pre, int nrep) {
-    extern __shared__ double wnd[];
-    __shared__ double red[2][4];
-    const int r = rep_of(pre, nrep, int(blockIdx.x));
-    const MeasRep &m = mr[r];
-    const void *spec = (m.g.D & 1) ? m.ctmp : m.cbuf;
-    bin_row<real>(m.g, static_cast<const cplx<real> *>(spec), m.t, m.invN, int(blockIdx.x) - pre[r], wnd,
-                  red);
+static int sk_threads(int lines, int m) {
+    const int t = (lines * m + SK_HELD - 1) / SK_HELD;
+    return t <= 256 ? 256 : (t <= 512 ? 512 : 1024);
 }
 
-template <typename real>
-__global__ void __launch_bounds__(256) k_modes_batch(const MeasRep *__restrict__ mr,
-                                                     const int *__restrict__ pre, int nrep) {
-    const int r = rep_of(pre, nrep, int(blockIdx.x));
-    const MeasRep &m = mr[r];
-    const void *spec = (m.g.D & 1) ? m.ctmp : m.cbuf;
-    record_modes_block<real>(m.g, static_cast<const cplx<real> *>(spec), m.modes_nm, m.modes, m.modes_n,
-                             m.modes_cap);
+static size_t sk_window(const Geometry &g, int lc) {
+    return sizeof(double) * 2 * size_t((g.D == 3 ? g.nz : g.ny) / 2 + lc + 4);
 }
 
-__global__ void __launch_bounds__(64) k_series_batch(const MeasRep *__restrict__ mr, int nrep,
-                                                     const uint64_t *__restrict__ step_base,
-                                                     uint32_t step_off) {
-    for (int r = threadIdx.x; r < nrep; r += 64) {
-        const MeasRep &m = mr[r];
-        if (m.t.mom != nullptr)
-            series_finalize(m.t.mom, m.t.series, m.series_n, m.t.series_cap, 2 + m.t.n_rad,
-                            step_base[0] + step_off);
-    }
-}
-
-int measure_plan(const MeasRep *reps, int nrep, MeasPlan &P) {
+int measure_plan(MeasRep *reps, int nrep, MeasPlan &P) {
     P.nrep = nrep;
     P.pre.assign(size_t(MK_COUNT) * (nrep + 1), 0);
-    for (int k = 0; k < 3; ++k) P.shm_fft[k] = 0;
-    P.shm_bin = 0;
-    P.any_series = false;
+    for (int k = 0; k < MK_COUNT; ++k) P.shm[k] = 0, P.threads[k] = 256;
     if (nrep < 1) return -1;
-    const int D = reps[0].g.D;
+    const int D = reps[0].g.D, prec = P.esz == 4 ? 0 : 1;
+    const size_t csz = 2 * P.esz;
     P.D = D;
+    int64_t nlines[3] = {};
+    for (int r = 0; r < nrep; ++r) {
+        const Geometry &g = reps[r].g;
+        const int64_t hx = g.nx / 2 + 1;
+        if (g.D != D) return -1;
+        nlines[0] += int64_t((g.ny + 1) / 2) * g.nz;
+        nlines[1] += hx * g.nz;
+        nlines[2] += D == 3 ? hx * g.ny : hx;
+    }
     int64_t tot[MK_COUNT] = {};
     for (int r = 0; r < nrep; ++r) {
-        const MeasRep &m = reps[r];
+        MeasRep &m = reps[r];
         const Geometry &g = m.g;
-        if (g.D != D) return -1;
-        int64_t n[MK_COUNT] = {};
-        n[MK_DENSITY] = int64_t((g.nx + 255) / 256) * g.ny * g.nz;
+        const int side[3] = {g.nx, g.ny, g.nz}, hx = g.nx / 2 + 1;
         for (int d = 0; d < D; ++d) {
-            const PassDims p = pass_dims(g, d);
-            if (p.n0 > 8192) return -1;
-            n[MK_FFT + d] = int64_t(p.n1) * p.n2;
-            n[MK_ROT + d] = int64_t((p.n0 + 31) / 32) * ((p.n1 + 31) / 32) * p.n2;
-            const size_t sh = P.esz * 2 * size_t(p.n0);
-            if (sh > P.shm_fft[d]) P.shm_fft[d] = sh;
+            if (side[d] > 8192) return -1;
+            m.ax[d] = sk_axis(side[d], prec);
         }
-        n[MK_BIN] = int64_t(g.ny) * g.nz;
-        n[MK_MODES] = m.modes_cap > 0 ? 1 : 0;
-        if (m.t.n_rad > 0) {
-            const size_t sh = sizeof(double) * 2 * size_t(g.nx / 2 + 3);
-            if (sh > P.shm_bin) P.shm_bin = sh;
+        for (int k = 0; k < 3; ++k) {
+            const int d = k == 2 ? D - 1 : k;
+            if (k == 1 && D == 2) continue;
+            m.lc[k] = sk_lines_per_block(m.ax[d].m, prec, nlines[k]);
         }
-        if (m.t.mom != nullptr) P.any_series = true;
+        const SkAxis &last = m.ax[D - 1];
+        while (m.lc[2] > 1 && sk_line_bytes(csz, m.lc[2], last.m) + sk_window(g, m.lc[2]) > SK_LDS) m.lc[2] >>= 1;
+        int64_t n[MK_COUNT] = {};
+        auto need = [&](int k, size_t shm, int threads) {
+            P.shm[k] = std::max(P.shm[k], shm);
+            P.threads[k] = std::max(P.threads[k], threads);
+        };
+        n[MK_ROWS] = int64_t((g.ny + 2 * m.lc[0] - 1) / (2 * m.lc[0])) * g.nz;
+        need(MK_ROWS, sk_line_bytes(csz, m.lc[0], m.ax[0].m), sk_threads(m.lc[0], m.ax[0].m));
+        if (D == 3) {
+            n[MK_MID] = int64_t(hx) * ((g.nz + m.lc[1] - 1) / m.lc[1]);
+            need(MK_MID, sk_line_bytes(csz, m.lc[1], m.ax[1].m), sk_threads(m.lc[1], m.ax[1].m));
+        }
+        const int inner = D == 3 ? g.ny : hx;
+        n[MK_LAST] = int64_t((inner + m.lc[2] - 1) / m.lc[2]) * (D == 3 ? hx : 1);
+        need(MK_LAST, sk_line_bytes(csz, m.lc[2], last.m) + (m.lc[2] > 1 ? sk_window(g, m.lc[2]) : 0),
+             sk_threads(m.lc[2], last.m));
         for (int k = 0; k < MK_COUNT; ++k) {
             P.pre[size_t(k) * (nrep + 1) + r] = int(tot[k]);
             tot[k] += n[k];
             if (tot[k] > 0x7fffffff) return -1;
         }
     }
-    for (int k = 0; k < MK_COUNT; ++k) P.pre[size_t(k) * (nrep + 1) + nrep] = int(tot[k]);
-    if (P.shm_fft[0] > 160 * 1024 || P.shm_bin > 160 * 1024) return -1;
+    for (int k = 0; k < MK_COUNT; ++k) {
+        P.pre[size_t(k) * (nrep + 1) + nrep] = int(tot[k]);
+        if (P.shm[k] > SK_LDS) return -1;
+    }
     return 0;
 }
 
 template <class L, typename real>
 static hipError_t measure_impl(const MeasPlan &P, const MeasRep *mr, const int *pre, int par,
-                               const uint64_t *step_base, uint32_t step_off, hipStream_t s) {
+                               uint64_t *step_base, uint64_t advance, uint32_t step_off, hipStream_t s) {
     const int nrep = P.nrep;
-    auto total = [&](int k) { return unsigned(P.pre[size_t(k) * (nrep + 1) + nrep]); };
+    auto grid = [&](int k) { return dim3(unsigned(P.pre[size_t(k) * (nrep + 1) + nrep])); };
     auto pk = [&](int k) { return pre + size_t(k) * (nrep + 1); };
-    hipLaunchKernelGGL((k_density_batch<L, real>), dim3(total(MK_DENSITY)), dim3(256), 0, s, mr,
-                       pk(MK_DENSITY), nrep, par);
-    for (int d = 0; d < L::D; ++d) {
-        hipLaunchKernelGGL(k_fft_batch<real>, dim3(total(MK_FFT + d)), dim3(256), P.shm_fft[d], s, mr,
-                           pk(MK_FFT + d), nrep, d);
-        hipLaunchKernelGGL(k_rotate_batch<real>, dim3(total(MK_ROT + d)), dim3(256), 0, s, mr,
-                           pk(MK_ROT + d), nrep, d);
-    }
-    hipLaunchKernelGGL(k_bin_batch<real>, dim3(total(MK_BIN)), dim3(256), P.shm_bin, s, mr, pk(MK_BIN),
-                       nrep);
-    if (total(MK_MODES) > 0)
-        hipLaunchKernelGGL(k_modes_batch<real>, dim3(total(MK_MODES)), dim3(256), 0, s, mr, pk(MK_MODES),
-                           nrep);
-    if (P.any_series)
-        hipLaunchKernelGGL(k_series_batch, dim3(1), dim3(64), 0, s, mr, nrep, step_base, step_off);
+    auto block = [&](int k) { return dim3(unsigned(P.threads[k])); };
+    hipLaunchKernelGGL((k_sk_rows<L, real>), grid(MK_ROWS), block(MK_ROWS), P.shm[MK_ROWS], s, mr, pk(MK_ROWS),
+                       nrep, par, step_base, advance);
+    if (L::D == 3)
+        hipLaunchKernelGGL(k_sk_mid<real>, grid(MK_MID), block(MK_MID), P.shm[MK_MID], s, mr, pk(MK_MID), nrep);
+    hipLaunchKernelGGL(k_sk_last<real>, grid(MK_LAST), block(MK_LAST), P.shm[MK_LAST], s, mr, pk(MK_LAST), nrep,
+                       step_base, step_off);
     return hipGetLastError();
 }
 
 hipError_t launch_measure(const MeasPlan &P, const MeasRep *dev_reps, const int *dev_pre, int precision,
-                          int parity, const uint64_t *step_base, uint32_t step_off, hipStream_t s) {
+                          int parity, uint64_t *step_base, uint64_t advance, uint32_t step_off, hipStream_t s) {
     if (P.nrep < 1 || P.pre.size() != size_t(MK_COUNT) * (P.nrep + 1)) return hipErrorInvalidValue;
-    if (P.D == 2)
-        return precision == 0 ? measure_impl<D2Q9, float>(P, dev_reps, dev_pre, parity, step_base, step_off, s)
-                              : measure_impl<D2Q9, double>(P, dev_reps, dev_pre, parity, step_base, step_off, s);
-    return precision == 0 ? measure_impl<D3Q19, float>(P, dev_reps, dev_pre, parity, step_base, step_off, s)
-                          : measure_impl<D3Q19, double>(P, dev_reps, dev_pre, parity, step_base, step_off, s);
+    auto go = [&](auto impl) { return impl(P, dev_reps, dev_pre, parity, step_base, advance, step_off, s); };
+    if (P.D == 2) return precision == 0 ? go(measure_impl<D2Q9, float>) : go(measure_impl<D2Q9, double>);
+    return precision == 0 ? go(measure_impl<D3Q19, float>) : go(measure_impl<D3Q19, double>);
+}
+
+// ---------------------------------------------------------------------------
+// S(k) of device fields: the same passes over a batch of equal square fields.
+// Field f has its half spectrum at spec + f spec_len and its sums at acc +
+// f acc_len: the shells, then sum P and sum |k| P.
+// ---------------------------------------------------------------------------
+struct FieldJob {
+    const float *fields;
+    cplx<float> *spec;
+    double *acc;
+    const void *tab;
+    SkAxis ax;
+    int n, n_rad, lc_rows, lc_last;
+};
+
+__device__ inline MeasRep field_rep(const FieldJob &j, int f) {
+    MeasRep m{};
+    m.g = Geometry{2, j.n, j.n, 1, int64_t(j.n) * j.n};
+    m.cbuf = j.spec + size_t(f) * (j.n / 2 + 1) * j.n;
+    m.tab[0] = m.tab[1] = j.tab;
+    m.ax[0] = m.ax[1] = j.ax;
+    m.lc[0] = j.lc_rows;
+    m.lc[2] = j.lc_last;
+    m.invN = 1.0 / double(m.g.N);
+    m.t.n_rad = j.n_rad;
+    m.t.rad_sum = j.acc + size_t(f) * field_acc_len(j.n_rad);
+    m.t.mom = m.t.rad_sum + j.n_rad;
+    return m;
+}
+
+__global__ void __launch_bounds__(1024) k_field_rows(FieldJob j, int per) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const int f = int(blockIdx.x) / per;
+    const MeasRep m = field_rep(j, f);
+    const float *src = j.fields + size_t(f) * j.n * j.n;
+    sk_rows_block<float>(m, int(blockIdx.x) % per, reinterpret_cast<cplx<float> *>(smem_raw),
+                         [&](int x, int y, int) { return src[size_t(y) * j.n + x]; });
+}
+
+__global__ void __launch_bounds__(1024) k_field_last(FieldJob j, int per) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+    const MeasRep m = field_rep(j, int(blockIdx.x) / per);
+    sk_last_block<float>(m, int(blockIdx.x) % per, smem_raw);
+}
+
+hipError_t launch_field_sk(const float *fields, int batch, int n, int n_rad, void *spec, const void *tab,
+                           double *acc, hipStream_t s) {
+    FieldJob j{fields, static_cast<cplx<float> *>(spec), acc, tab, sk_axis(n, 0), n, n_rad, 0, 0};
+    const Geometry g{2, n, n, 1, int64_t(n) * n};
+    const int hx = n / 2 + 1;
+    j.lc_rows = sk_lines_per_block(j.ax.m, 0, int64_t(batch) * ((n + 1) / 2));
+    j.lc_last = sk_lines_per_block(j.ax.m, 0, int64_t(batch) * hx);
+    while (j.lc_last > 1 && sk_line_bytes(8, j.lc_last, j.ax.m) + sk_window(g, j.lc_last) > SK_LDS) j.lc_last >>= 1;
+    const int pr = (n + 2 * j.lc_rows - 1) / (2 * j.lc_rows), pl = (hx + j.lc_last - 1) / j.lc_last;
+    if (int64_t(batch) * std::max(pr, pl) > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_field_rows, dim3(unsigned(batch * pr)), dim3(unsigned(sk_threads(j.lc_rows, j.ax.m))),
+                       sk_line_bytes(8, j.lc_rows, j.ax.m), s, j, pr);
+    hipLaunchKernelGGL(k_field_last, dim3(unsigned(batch * pl)), dim3(unsigned(sk_threads(j.lc_last, j.ax.m))),
+                       sk_line_bytes(8, j.lc_last, j.ax.m) + (j.lc_last > 1 ? sk_window(g, j.lc_last) : 0), s, j, pl);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

@@ -1143,20 +1143,6 @@ hipError_t launch_coarsen(const Geometry &g, int precision, const void *buf, dou
     return hipGetLastError();
 }
 
-// real field -> complex (for the S(k) pipeline on coarse fields)
-__global__ void k_field_cplx(const float *__restrict__ f, int n, float *__restrict__ c) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= n) return;
-    c[2 * k] = f[k];
-    c[2 * k + 1] = 0.f;
-}
-
-hipError_t launch_field_cplx(const float *f, int n, void *c, hipStream_t s) {
-    hipLaunchKernelGGL(k_field_cplx, dim3(unsigned((n + 255) / 256)), dim3(256), 0, s, f, n,
-                       static_cast<float *>(c));
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // Training batches from a snapshot stack S[K][R][H][W]: image b of the batch
 // is snapshot t_b + dt of run r_b, moved by a periodic shift and optionally
@@ -1215,20 +1201,6 @@ __global__ void __launch_bounds__(256) k_stack_moments(const float *__restrict__
         const int q = threadIdx.x;
         part[blockIdx.x * 4 + q] = sh[0][q] + sh[1][q] + sh[2][q] + sh[3][q];
     }
-}
-
-// Clears `words` 32-bit words (a fill kernel rather than a memset node, so the
-// clearing can also sit inside a caller's captured graph).
-__global__ void k_zero_words(uint32_t *p, int64_t words) {
-    const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < words) p[i] = 0u;
-}
-
-hipError_t launch_zero_words(void *p, int64_t words, hipStream_t s) {
-    if (words <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_words, dim3(unsigned((words + 255) / 256)), dim3(256), 0, s,
-                       static_cast<uint32_t *>(p), words);
-    return hipGetLastError();
 }
 
 }  // namespace fsc
