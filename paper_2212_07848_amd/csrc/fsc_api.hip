@@ -78,6 +78,14 @@ struct GraphEntry {
     int flips = 0;  // parity of the number of kernel launches (each swaps the buffers)
 };
 
+// One launch of T steps by the block kernel over all replicas.
+struct BlockPlan {
+    int T = 0, ws = 0, blocks = 0;
+    size_t lds = 0;
+    double us = 0.0;  // modelled time of the launch
+    std::vector<BlockTile> tiles;
+};
+
 }  // namespace
 
 struct fsc_ens {
@@ -96,6 +104,10 @@ struct fsc_ens {
     int64_t step = 0;
     int cur = 0;  // index of the buffer that holds the current state
     int total_tiles = 0;
+    // several steps per launch on small 2D lattices: plan of T steps at [T - 1]
+    std::vector<BlockPlan> blocks;
+    BlockTile *d_blocks = nullptr;  // [plan][replica]
+    bool use_blocks = false, tuned_blocks = false;  // runs take it; the autotuner chose it
     // batched S(k) sample of all replicas: host copy of the device table and its plan
     std::vector<MeasRep> meas;
     MeasPlan mplan;
@@ -582,6 +594,123 @@ StepLaunch make_launch(fsc_ens *e, int parity, uint32_t off) {
     return L;
 }
 
+// -------------------------------------------------------------------------
+// Block kernel: tiles and step counts for small 2D ensembles.
+// -------------------------------------------------------------------------
+constexpr int BLOCK_MAX_T = 8;
+constexpr int CUS = 256;
+
+// The tile height (and width) of a T-step launch with the least modelled time:
+// small tiles spread over more CUs but repeat more halo rows, tall ones leave
+// CUs idle.  The model is a launch, per round of resident workgroups the tiles'
+// way in and out, and per step the rows of 64 columns that the workgroups on a
+// CU hold and the turns that a workgroup's waves need for its rows.  Its four
+// times (us) are a least-squares fit to 1100 timings, from one lattice of 64^2 to
+// one of 1000^2 and from 1 to 88 replicas, T = 1 .. 6, heights 1 .. 26, both widths
+// and stencils; the choice lies within 3% of the best of each sweep (one at 7%).
+bool block_plan(const fsc_ens *e, int T, BlockPlan &best) {
+    const int R = e->stencil == FSC_E8 ? 2 : 1, h = R + 1;
+    const bool f32 = e->precision == FSC_FP32_SHIFTED;
+    const double launch = f32 ? 1.55 : 1.25, load = f32 ? 3.65 : 2.4;
+    const double row = f32 ? 0.075 : 0.46, turn = f32 ? 0.3 : 0.0;
+    int ny = 1;
+    for (const auto &r : e->reps) ny = std::max(ny, r.p.ny);
+    bool found = false;
+    for (int ws = 64; ws <= 128; ws *= 2) {
+        const int waves = block_waves(e->precision, ws), rp = waves / (ws / 64);
+        const size_t rb = block_row_bytes(e->precision, ws);
+        const int rows = std::min(rp * BLOCK_ROWS, int((160 * 1024 - 512) / rb));
+        for (int ty = 1; ty <= std::min(rows - 2 * h * T, ny); ++ty) {
+            BlockPlan p;
+            p.T = T;
+            p.ws = ws;
+            int tall = 0;
+            int64_t n = 0;
+            bool ok = true;
+            for (const auto &r : e->reps) {
+                BlockTile b{int(n), 1, r.p.nx, 0};
+                if (r.p.nx > ws) {
+                    const int tx = ws - 2 * h * T;
+                    ok = ok && tx >= 1;
+                    if (!ok) break;
+                    b.tiles_x = (r.p.nx + tx - 1) / tx;
+                    b.tx = (r.p.nx + b.tiles_x - 1) / b.tiles_x;
+                    b.tiles_x = (r.p.nx + b.tx - 1) / b.tx;
+                }
+                const int nty = (r.p.ny + ty - 1) / ty;
+                b.ty = (r.p.ny + nty - 1) / nty;
+                tall = std::max(tall, b.ty);
+                n += int64_t(b.tiles_x) * ((r.p.ny + b.ty - 1) / b.ty);
+                p.tiles.push_back(b);
+            }
+            if (!ok || n > (1 << 20)) continue;
+            p.blocks = int(n);
+            p.lds = size_t(tall + 2 * h * T) * rb;
+            const int fit = std::min(int(160 * 1024 / p.lds), f32 ? 32 / waves : 1);  // resident per CU
+            const int share = int(std::min<int64_t>(std::max(1, fit), (n + CUS - 1) / CUS));
+            const double rounds = double((n + int64_t(CUS) * share - 1) / (int64_t(CUS) * share));
+            double t = load;
+            for (int s = 0; s < T; ++s) {
+                const int active = tall + 2 * h * (T - 1 - s) + 2 * R;
+                t += row * share * active * (ws / 64) + turn * ((active + rp - 1) / rp);
+            }
+            p.us = launch + rounds * t;
+            if (!found || p.us < best.us) best = p;
+            found = true;
+        }
+    }
+    return found;
+}
+
+// 2D below the size from which tilings are tuned automatically.
+bool block_size(const fsc_ens *e) {
+    int64_t nodes = 0;
+    for (const auto &r : e->reps) nodes += r.N;
+    return e->D == 2 && nodes < (int64_t(1) << 20);
+}
+
+// Plans every step count that fits and uploads the tables.  The descriptors
+// that the kernel reads otherwise are those of the step kernels.
+int ensure_blocks(fsc_ens *e) {
+    if (!e->blocks.empty()) return FSC_OK;
+    std::vector<BlockPlan> plans;
+    std::vector<BlockTile> table;
+    for (int T = 1; T <= BLOCK_MAX_T; ++T) {
+        BlockPlan p;
+        if (!block_plan(e, T, p)) break;
+        table.insert(table.end(), p.tiles.begin(), p.tiles.end());
+        plans.push_back(std::move(p));
+    }
+    if (plans.empty()) return FSC_OK;
+    if (hipMalloc(&e->d_blocks, sizeof(BlockTile) * table.size()) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(e, FSC_E_OOM, "tile table allocation failed");
+    }
+    HIPCHK(e, hipMemcpyAsync(e->d_blocks, table.data(), sizeof(BlockTile) * table.size(), hipMemcpyHostToDevice,
+                             e->stream));
+    HIPCHK(e, hipStreamSynchronize(e->stream));
+    e->blocks = std::move(plans);
+    return FSC_OK;
+}
+
+BlockLaunch make_block_launch(const fsc_ens *e, int T, int parity, uint32_t off) {
+    const BlockPlan &p = e->blocks[size_t(T - 1)];
+    const int n = int(e->reps.size());
+    return BlockLaunch{e->d_desc,  e->d_blocks + size_t(T - 1) * size_t(n), n,        p.blocks, parity, T,
+                       e->d_step, off, e->stencil, e->precision, e->noise, p.ws, p.lds};
+}
+
+// Steps of the next launch when `left` steps remain to the next sample or the
+// end: the even division into the fewest launches of the step count with the
+// least modelled time per step.
+int block_steps(const fsc_ens *e, int64_t left) {
+    int T = 1;
+    for (int k = 2; k <= int(e->blocks.size()); ++k)
+        if (e->blocks[size_t(k - 1)].us / k < e->blocks[size_t(T - 1)].us / T) T = k;
+    const int64_t launches = (left + T - 1) / T;
+    return int((left + launches - 1) / launches);
+}
+
 // Enqueues n steps from buffer `cur`: with a two-step tiling, steps go in
 // pairs except where an S(k) sample falls between them (and a last odd one);
 // those run the single-step kernel of the same tile width, which uses the
@@ -590,10 +719,17 @@ bool pair_from(const fsc_ens *e, int64_t k, int64_t n, int64_t sk_every) {
     return e->tile.steps == 2 && k + 1 < n && !(sk_every > 0 && (k + 1) % sk_every == 0);
 }
 
+// steps of the launch at step k of n
+int launch_steps(const fsc_ens *e, int64_t k, int64_t n, int64_t sk_every) {
+    if (!e->use_blocks) return pair_from(e, k, n, sk_every) ? 2 : 1;
+    const int64_t next = sk_every > 0 ? std::min(n, (k / sk_every + 1) * sk_every) : n;
+    return block_steps(e, next - k);
+}
+
 // number of kernel launches enqueue_steps makes for n steps
 int64_t count_launches(const fsc_ens *e, int64_t n, int64_t sk_every) {
     int64_t m = 0;
-    for (int64_t k = 0; k < n; k += pair_from(e, k, n, sk_every) ? 2 : 1) ++m;
+    for (int64_t k = 0; k < n; k += launch_steps(e, k, n, sk_every)) ++m;
     return m;
 }
 
@@ -601,13 +737,17 @@ int enqueue_steps(fsc_ens *e, int cur, int64_t n, int64_t sk_every, int64_t *sam
     int c = cur, launches = 0;
     bool advanced = false;
     for (int64_t k = 0; k < n;) {
-        const bool two = pair_from(e, k, n, sk_every);
-        StepLaunch L = make_launch(e, c, uint32_t(k));
-        if (!two && L.tile.steps == 2) L.tile = TileShape{L.tile.tx, 1, 1};
-        HIPCHK(e, launch_step(L, e->stream));
+        const int steps = launch_steps(e, k, n, sk_every);
+        if (e->use_blocks) {
+            HIPCHK(e, launch_block(make_block_launch(e, steps, c, uint32_t(k)), e->stream));
+        } else {
+            StepLaunch L = make_launch(e, c, uint32_t(k));
+            if (steps == 1 && L.tile.steps == 2) L.tile = TileShape{L.tile.tx, 1, 1};
+            HIPCHK(e, launch_step(L, e->stream));
+        }
         c ^= 1;
         ++launches;
-        k += two ? 2 : 1;
+        k += steps;
         if (sk_every > 0 && k % sk_every == 0) {
             // a sample after the last step moves the step counter on as well
             // (a launch of its own for one addition takes 4 us)
@@ -647,6 +787,7 @@ bool two_step_ok(const fsc_ens *e) {
 struct TuneChoice {
     TileShape tile;
     int64_t target;
+    bool blocks = false;  // the block kernel is faster still
 };
 std::mutex g_tune_mu;
 std::map<std::string, TuneChoice> g_tune_cache;
@@ -668,6 +809,7 @@ int ens_autotune(fsc_ens *e) {
         if (it != g_tune_cache.end()) {
             e->tile = it->second.tile;
             e->target_blocks = it->second.target;
+            e->tuned_blocks = it->second.blocks;
             drop_graphs(e);
             e->autotune = 1;
             return upload_desc(e);
@@ -772,10 +914,32 @@ int ens_autotune(fsc_ens *e) {
     for (size_t c = 1; c < lead; ++c)
         if (best_ms[c] < best_ms[win]) win = c;
     if (lead > 0) choice = timed[win].second;
+    if (block_size(e) && lead > 0) {
+        // the block kernel, timed like a leader
+        int rc = ensure_blocks(e);
+        if (rc) return rc;
+        float ms = 0.f;
+        for (int round = 0; round < 4 && !e->blocks.empty(); ++round) {
+            const int T = block_steps(e, 64);
+            int n = 0;
+            for (int k = -2; k < 12; ++k) {
+                if (k == 0) HIPCHK(e, hipEventRecord(a, e->stream));
+                const int par = alternate ? parity ^ (n++ & 1) : parity;
+                HIPCHK(e, launch_block(make_block_launch(e, T, par, 0), e->stream));
+            }
+            HIPCHK(e, hipEventRecord(b, e->stream));
+            HIPCHK(e, hipEventSynchronize(b));
+            float t = 0.f;
+            HIPCHK(e, hipEventElapsedTime(&t, a, b));
+            ms += t / float(12 * T);
+        }
+        choice.blocks = !e->blocks.empty() && ms < best_ms[win];
+    }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     e->tile = choice.tile;
     e->target_blocks = choice.target;
+    e->tuned_blocks = choice.blocks;
     drop_graphs(e);
     e->autotune = 1;
     {
@@ -783,6 +947,20 @@ int ens_autotune(fsc_ens *e) {
         g_tune_cache[key] = choice;
     }
     return upload_desc(e);
+}
+
+// Whether runs go through the block kernel: small 2D lattices, unless the caller
+// has fixed a tiling or the autotuner found one that is faster.
+int choose_blocks(fsc_ens *e) {
+    bool use = block_size(e) && (e->autotune == 0 || e->tuned_blocks);
+    if (use) {
+        int rc = ensure_blocks(e);
+        if (rc) return rc;
+        use = !e->blocks.empty();
+    }
+    if (use != e->use_blocks) drop_graphs(e);
+    e->use_blocks = use;
+    return FSC_OK;
 }
 
 int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
@@ -808,11 +986,13 @@ int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
             e->autotune = 0;
         }
     }
+    int rc_blocks = choose_blocks(e);
+    if (rc_blocks) return rc_blocks;
     // whole chunks as graph replays; a graph holds the buffer of its first
     // launch, so a chunk must make an even number of launches (each launch
     // swaps the buffers)
     int64_t chunk = sk_every > 0 ? sk_every : 64;
-    if (count_launches(e, chunk, sk_every) & 1) chunk *= 2;
+    for (int k = 0; k < 4 && (count_launches(e, chunk, sk_every) & 1); ++k) chunk *= 2;
     int64_t done = 0;
     const int64_t nchunks = nsteps / chunk;
     if (nchunks >= 2) {
@@ -932,6 +1112,7 @@ void ens_free(fsc_ens *e) {
             if (p) (void)hipFree(p);
     }
     for (auto &kv : e->tabs) (void)hipFree(kv.second);
+    if (e->d_blocks) (void)hipFree(e->d_blocks);
     if (e->d_desc) (void)hipFree(e->d_desc);
     if (e->d_tile_begin) (void)hipFree(e->d_tile_begin);
     if (e->d_step) (void)hipFree(e->d_step);
@@ -1478,6 +1659,7 @@ static int set_tiling(fsc_ens *e, int tx, int ty, int pf, int steps, int64_t tar
             e->target_blocks = target_blocks;
             drop_graphs(e);
             e->autotune = 1;  // an explicit choice is never re-tuned
+            e->tuned_blocks = false;
             return upload_desc(e);
         }
     return fail(e, FSC_E_INVAL, "tile shape not compiled for this lattice (see fsc_tile_shapes)");

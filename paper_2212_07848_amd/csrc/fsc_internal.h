@@ -47,6 +47,32 @@ struct StepLaunch {
 // buf[parity ^ 1] at two steps later).  hipErrorInvalidValue when no
 // instantiation matches.
 hipError_t launch_step(const StepLaunch &L, hipStream_t s);
+// Several steps per launch on small 2D lattices (fsc_block_kernel.h).  Tiles of
+// one replica: tiles_x x ceil(ny / ty) tiles of tx x ty nodes (tx == nx with one
+// tile across: whole periodic rows).
+struct BlockTile {
+    int begin, tiles_x, tx, ty;
+};
+constexpr int BLOCK_ROWS = 4;  // rows of a step per wave, at most
+struct BlockLaunch {
+    const RepDesc *reps;       // device
+    const BlockTile *tiles;    // device, [nrep]
+    int nrep, blocks;
+    int parity, T;             // source buffer, steps
+    const uint64_t *step_base; // device
+    uint32_t step_off;
+    int stencil, precision;
+    bool noise;
+    int ws;                    // columns of the region: 64 or 128
+    size_t lds;
+};
+// The state goes from buf[parity] at step_base + step_off to buf[parity ^ 1] T
+// steps later.
+hipError_t launch_block(const BlockLaunch &L, hipStream_t s);
+// Waves of a block and LDS bytes of one row of its region.
+inline int block_waves(int precision, int ws) { return ws == 128 && precision == 0 ? 16 : 8; }
+inline size_t block_row_bytes(int precision, int ws) { return size_t(10) * ws * (precision == 0 ? 4 : 8); }
+
 // Tile shapes compiled for a lattice/stencil; the first is the default.
 int tile_shapes(int D, int stencil, int precision, TileShape *out, int max);
 

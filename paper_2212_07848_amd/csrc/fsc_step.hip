@@ -13,6 +13,16 @@ hipError_t launch_step_d3e4_f64(const StepLaunch &P, hipStream_t s);
 hipError_t launch_step2_e4(const StepLaunch &P, hipStream_t s);
 hipError_t launch_step2_e8(const StepLaunch &P, hipStream_t s);
 
+hipError_t launch_block_e4_f32(const BlockLaunch &P, hipStream_t s);
+hipError_t launch_block_e4_f64(const BlockLaunch &P, hipStream_t s);
+hipError_t launch_block_e8_f32(const BlockLaunch &P, hipStream_t s);
+hipError_t launch_block_e8_f64(const BlockLaunch &P, hipStream_t s);
+
+hipError_t launch_block(const BlockLaunch &P, hipStream_t s) {
+    if (P.precision == 0) return P.stencil == 8 ? launch_block_e8_f32(P, s) : launch_block_e4_f32(P, s);
+    return P.stencil == 8 ? launch_block_e8_f64(P, s) : launch_block_e4_f64(P, s);
+}
+
 __global__ void k_step_advance(uint64_t *step_base, uint64_t k) {
     if (threadIdx.x == 0 && blockIdx.x == 0) step_base[0] += k;
 }
