@@ -26,6 +26,7 @@
 #include <map>
 #include <string>
 #include <tuple>
+#include <utility>
 #include <vector>
 
 #include "../../include/fsc.h"
@@ -1103,44 +1104,66 @@ __global__ void __launch_bounds__(256) k_update(float *__restrict__ p, int n, in
 }
 
 // ---------------------------------------------------------------------------
-// Coarse-graining: mean density over f x f blocks of the streamed state.
+// Coarse-graining: mean density over f x f blocks of the streamed state.  A
+// workgroup takes a strip of one coarse row: lanes run along x (coalesced pulls,
+// TX columns), TY = 1, 2 or 4 groups of them share the strip's rows; a lane sums
+// its column's density in FP64 and the columns of a cell meet in LDS.  It reads
+// 36 B per node: 4096^2 in blocks of 8 takes 115 us (one lane per cell,
+// walking f rows of 32-byte pieces, took 478), 128^2 to 512^2 5 (66).
 // ---------------------------------------------------------------------------
 template <class L, typename real>
 __global__ void __launch_bounds__(256) k_coarsen(Geometry g, const real *__restrict__ src,
-                                                 double rho0, int f, float *__restrict__ out) {
-    const int cx = g.nx / f, cy = g.ny / f;
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= cx * cy) return;
-    const int X = k % cx, Y = k / cx;
+                                                 double rho0, int f, int TX, int strips,
+                                                 float *__restrict__ out) {
+    __shared__ double sh[256];
+    const int TY = 256 / TX, tx = threadIdx.x % TX, ty = threadIdx.x / TX;
+    const int cells = f <= TX ? TX / f : 1, cx = g.nx / f;
+    const int Y = int(blockIdx.x) / strips, X0 = (int(blockIdx.x) % strips) * cells;
+    const int n = min(cells, cx - X0), width = n * f;
     double s = 0.0;
-    for (int dy = 0; dy < f; ++dy)
-        for (int dx = 0; dx < f; ++dx) {
-            const int x = X * f + dx, y = Y * f + dy;
-            const int xm = x == 0 ? g.nx - 1 : x - 1, xp = x + 1 == g.nx ? 0 : x + 1;
-            const int ym = y == 0 ? g.ny - 1 : y - 1, yp = y + 1 == g.ny ? 0 : y + 1;
+    for (int c = tx; c < width; c += TX) {
+        const int x = X0 * f + c;
+        const int xs[3] = {x + 1 == g.nx ? 0 : x + 1, x, x == 0 ? g.nx - 1 : x - 1};  // x - c_x
+        for (int dy = ty; dy < f; dy += TY) {
+            const int y = Y * f + dy;
+            const int ys[3] = {y + 1 == g.ny ? 0 : y + 1, y, y == 0 ? g.ny - 1 : y - 1};
 #pragma unroll
-            for (int i = 0; i < L::Q; ++i) {
-                const int c0 = L::c(i, 0), c1 = L::c(i, 1);
-                const int xs = c0 == 1 ? xm : (c0 == -1 ? xp : x);
-                const int ys = c1 == 1 ? ym : (c1 == -1 ? yp : y);
-                s += double(src[int64_t(i) * g.N + xs + int64_t(g.nx) * ys]);
-            }
+            for (int i = 0; i < L::Q; ++i)
+                s += double(src[int64_t(i) * g.N + xs[L::c(i, 0) + 1] + int64_t(g.nx) * ys[L::c(i, 1) + 1]]);
         }
-    out[k] = float(rho0 + s / double(f * f));
+    }
+    if (f > TX) {  // one cell, all lanes
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+        __syncthreads();
+        if (threadIdx.x == 0)
+            out[Y * cx + X0] = float(rho0 + ((sh[0] + sh[1]) + (sh[2] + sh[3])) / (double(f) * double(f)));
+        return;
+    }
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int k = threadIdx.x; k < n; k += 256) {
+        double t = 0.0;
+        for (int r = 0; r < TY; ++r)
+            for (int c = 0; c < f; ++c) t += sh[r * TX + k * f + c];
+        out[Y * cx + X0 + k] = float(rho0 + t / (double(f) * double(f)));
+    }
 }
 
 hipError_t launch_coarsen(const Geometry &g, int precision, const void *buf, double rho0, int f,
                           float *out, hipStream_t s) {
     if (g.D != 2 || f < 1 || g.nx % f || g.ny % f) return hipErrorInvalidValue;
-    const int n = (g.nx / f) * (g.ny / f);
-    const unsigned nb = unsigned((n + 255) / 256);
-    if (precision == 0)
-        hipLaunchKernelGGL((k_coarsen<D2Q9, float>), dim3(nb), dim3(256), 0, s, g,
-                           static_cast<const float *>(buf), rho0, f, out);
-    else
-        hipLaunchKernelGGL((k_coarsen<D2Q9, double>), dim3(nb), dim3(256), 0, s, g,
-                           static_cast<const double *>(buf), rho0, f, out);
-    return hipGetLastError();
+    const int TX = f >= 4 ? 64 : (f >= 2 ? 128 : 256);
+    const int cells = f <= TX ? TX / f : 1, strips = (g.nx / f + cells - 1) / cells;
+    const int64_t nb = int64_t(strips) * (g.ny / f);
+    if (nb > 0x7fffffff) return hipErrorInvalidValue;
+    auto go = [&](auto kernel, auto p) {
+        hipLaunchKernelGGL(kernel, dim3(unsigned(nb)), dim3(256), 0, s, g, p, rho0, f, TX, strips, out);
+        return hipGetLastError();
+    };
+    return precision == 0 ? go(k_coarsen<D2Q9, float>, static_cast<const float *>(buf))
+                          : go(k_coarsen<D2Q9, double>, static_cast<const double *>(buf));
 }
 
 // ---------------------------------------------------------------------------
@@ -1216,6 +1239,7 @@ struct fsc_sur {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     int64_t nparams = 0;
+    void *arena = nullptr;  // holds every device buffer below
     std::vector<int64_t> woff, boff;  // offsets of each layer's weights / biases
     float *params = nullptr, *grads = nullptr, *m = nullptr, *v = nullptr;
     bf16 *wf = nullptr, *wb = nullptr;  // [mid layer][9][32][32]
@@ -1261,14 +1285,7 @@ int nmid(const fsc_sur *s) { return s->layers - 2; }
 void sur_free(fsc_sur *s) {
     if (!s) return;
     (void)hipStreamSynchronize(s->stream);
-    void *ptrs[] = {s->params, s->grads, s->m,    s->v,    s->wf,   s->wb, s->wl3, s->dzA,
-                    s->dzB,    s->y,     s->gbuf, s->gsum, s->loss, s->wpart, s->part};
-    for (void *p : ptrs)
-        if (p) (void)hipFree(p);
-    for (auto p : s->z)
-        if (p) (void)hipFree(p);
-    for (auto p : s->a)
-        if (p) (void)hipFree(p);
+    if (s->arena) (void)hipFree(s->arena);
     for (auto &kv : s->rollouts) (void)hipGraphExecDestroy(kv.second);
     if (s->cap_stream) {
         (void)hipStreamSynchronize(s->cap_stream);
@@ -1506,28 +1523,34 @@ int fsc_sur_create(int layers, int in_ch, int H, int W, int max_batch, uint64_t 
     s->eblocks = std::min(wg_tiles(max_batch, H, W), WG_EDGE_BLOCKS);
     const size_t wlen = size_t(layers - 2) * s->wblocks * WG_LEN +
                         size_t(s->eblocks) * (wg_edge_len<2>() + wg_edge_len<1>());
-    bool ok = hipMalloc(&s->params, sizeof(float) * o) == hipSuccess &&
-              hipMalloc(&s->grads, sizeof(float) * o) == hipSuccess &&
-              hipMalloc(&s->m, sizeof(float) * o) == hipSuccess &&
-              hipMalloc(&s->v, sizeof(float) * o) == hipSuccess &&
-              hipMalloc(&s->wf, sizeof(bf16) * 9 * SC * SC * std::max(1, layers - 2)) == hipSuccess &&
-              hipMalloc(&s->wb, sizeof(bf16) * 9 * SC * SC * std::max(1, layers - 2)) == hipSuccess &&
-              hipMalloc(&s->wl3, sizeof(bf16) * 9 * 3 * SC) == hipSuccess &&
-              hipMalloc(&s->dzA, sizeof(bf16) * P * SC) == hipSuccess &&
-              hipMalloc(&s->dzB, sizeof(bf16) * P * SC) == hipSuccess &&
-              hipMalloc(&s->y, sizeof(float) * P) == hipSuccess &&
-              hipMalloc(&s->gbuf, sizeof(float) * P) == hipSuccess &&
-              hipMalloc(&s->wpart, sizeof(float) * wlen) == hipSuccess &&
-              hipMalloc(&s->part, sizeof(double) * 3 * IMG_PARTS * max_batch) == hipSuccess &&
-              hipMalloc(&s->gsum, sizeof(double) * max_batch) == hipSuccess &&
-              hipMalloc(&s->loss, sizeof(double)) == hipSuccess;
-    for (int l = 0; ok && l < layers - 1; ++l) {
-        float *zz = nullptr;
-        bf16 *aa = nullptr;
-        ok = hipMalloc(&zz, sizeof(float) * P * SC) == hipSuccess &&
-             hipMalloc(&aa, sizeof(bf16) * P * SC) == hipSuccess;
-        s->z.push_back(zz);
-        s->a.push_back(aa);
+    // every buffer of the object from one allocation (an allocation takes 30 to
+    // 300 us, and there are over thirty)
+    const size_t nw = sizeof(bf16) * 9 * SC * SC * std::max(1, layers - 2);
+    s->z.assign(size_t(layers - 1), nullptr);
+    s->a.assign(size_t(layers - 1), nullptr);
+    std::vector<std::pair<void **, size_t>> parts;
+    auto want = [&](auto *&p, size_t bytes) { parts.emplace_back(reinterpret_cast<void **>(&p), bytes); };
+    for (float **p : {&s->params, &s->grads, &s->m, &s->v}) want(*p, sizeof(float) * size_t(o));
+    want(s->wf, nw);
+    want(s->wb, nw);
+    want(s->wl3, sizeof(bf16) * 9 * 3 * SC);
+    want(s->dzA, sizeof(bf16) * P * SC);
+    want(s->dzB, sizeof(bf16) * P * SC);
+    want(s->y, sizeof(float) * P);
+    want(s->gbuf, sizeof(float) * P);
+    want(s->wpart, sizeof(float) * wlen);
+    want(s->part, sizeof(double) * 3 * IMG_PARTS * size_t(max_batch));
+    want(s->gsum, sizeof(double) * size_t(max_batch));
+    want(s->loss, sizeof(double));
+    for (auto &p : s->z) want(p, sizeof(float) * P * SC);
+    for (auto &p : s->a) want(p, sizeof(bf16) * P * SC);
+    size_t total = 0;
+    for (auto &q : parts) total += (q.second + 255) & ~size_t(255);
+    const bool ok = hipMalloc(&s->arena, total) == hipSuccess;
+    char *at = static_cast<char *>(s->arena);
+    for (auto &q : parts) {
+        *q.first = ok ? at : nullptr;
+        at += ok ? (q.second + 255) & ~size_t(255) : 0;
     }
     if (!ok) {
         (void)hipGetLastError();
