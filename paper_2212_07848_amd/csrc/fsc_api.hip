@@ -57,15 +57,24 @@ struct Rep {
     double *d_sk = nullptr;  // axis_sum, axis_sq, rad_sum, rad_sq
     void *cbuf = nullptr, *ctmp = nullptr;
     int *d_done = nullptr;  // blocks of a sample that have finished
-    double *d_stats = nullptr, *d_partials = nullptr;
+    double *d_partials = nullptr;
+    int *d_stats_done = nullptr;
     // time series of samples: rows (step, L, per-shell mean S) -- see fsc_series_enable
     double *d_mom = nullptr, *d_series = nullptr;
     int *d_series_n = nullptr;
     int series_cap = 0;
+    int64_t series_rows = 0;  // samples since it was enabled (the device counter's value)
     // recorded axis-mode amplitudes per sample -- see fsc_modes_enable
     double *d_modes = nullptr;
     int *d_modes_n = nullptr;
     int modes_nm = 0, modes_cap = 0;
+    int64_t modes_rows = 0;
+    size_t modes_bytes = 0;
+    void sampled(int64_t n) {
+        nsamples += n;
+        if (series_cap > 0) series_rows += n;
+        if (modes_cap > 0) modes_rows += n;
+    }
     Geometry geom() const { return Geometry{p.D, p.nx, p.ny, p.nz, N}; }
 };
 
@@ -113,6 +122,9 @@ struct fsc_ens {
     MeasPlan mplan;
     MeasRep *d_meas = nullptr;
     std::map<int, void *> tabs;  // transform tables by line length
+    void *pin = nullptr;         // READ_PIN bytes of pinned host memory for small results
+    double *work = nullptr;      // up to READ_WORK bytes on the device for large ones
+    size_t work_bytes = 0;
     int *d_mpre = nullptr;
     std::string err;
     std::map<std::pair<int, std::pair<int64_t, int64_t>>, GraphEntry> graphs;
@@ -250,7 +262,7 @@ int init_rep(Rep &r, const fsc_params &p, void *ext_a, void *ext_b, fsc_ens *e) 
     if (hipMalloc(&r.d_sk, sizeof(double) * nsk) != hipSuccess ||
         hipMalloc(&r.d_mom, sizeof(double) * 2) != hipSuccess ||
         hipMalloc(&r.d_series_n, sizeof(int)) != hipSuccess ||
-        hipMalloc(&r.d_stats, sizeof(double) * 8) != hipSuccess ||
+        hipMalloc(&r.d_stats_done, sizeof(int)) != hipSuccess ||
         hipMalloc(&r.d_partials, sizeof(double) * stats_partials_len()) != hipSuccess) {
         (void)hipGetLastError();
         return fail(e, FSC_E_OOM, "accumulator allocation failed");
@@ -258,6 +270,75 @@ int init_rep(Rep &r, const fsc_params &p, void *ext_a, void *ext_b, fsc_ens *e) 
     HIPCHK(e, hipMemsetAsync(r.d_sk, 0, sizeof(double) * nsk, e->stream));
     HIPCHK(e, hipMemsetAsync(r.d_mom, 0, sizeof(double) * 2, e->stream));
     HIPCHK(e, hipMemsetAsync(r.d_series_n, 0, sizeof(int), e->stream));
+    HIPCHK(e, hipMemsetAsync(r.d_stats_done, 0, sizeof(int), e->stream));
+    return FSC_OK;
+}
+
+// Results on their way to the host.  Small ones are written by the kernel into,
+// or copied to, pinned memory (a copy to pageable memory takes 20 us, to pinned
+// memory 11, a kernel's own stores none); large ones go through a device buffer
+// in pieces.  Both are made at first use and live as long as the ensemble.
+constexpr size_t READ_PIN = size_t(512) << 10, READ_WORK = size_t(64) << 20;
+
+int ensure_pin(fsc_ens *e) {
+    if (e->pin) return FSC_OK;
+    if (hipHostMalloc(&e->pin, READ_PIN, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        e->pin = nullptr;
+        return fail(e, FSC_E_OOM, "pinned buffer allocation failed");
+    }
+    return FSC_OK;
+}
+
+// `n` bytes from the device to the caller's memory, complete on return
+int read_back(fsc_ens *e, void *dst, const void *src, size_t n) {
+    if (n > READ_PIN) {
+        StreamDrain drain{e->stream};
+        HIPCHK(e, hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, e->stream));
+        HIPCHK(e, hipStreamSynchronize(e->stream));
+        return FSC_OK;
+    }
+    int rc = ensure_pin(e);
+    if (rc) return rc;
+    HIPCHK(e, hipMemcpyAsync(e->pin, src, n, hipMemcpyDeviceToHost, e->stream));
+    HIPCHK(e, hipStreamSynchronize(e->stream));
+    std::memcpy(dst, e->pin, n);
+    return FSC_OK;
+}
+
+// `count` doubles that launch(first, n, out) forms, n at a time (multiples of
+// `unit`), into the caller's memory
+template <class Launch>
+int read_formed(fsc_ens *e, double *dst, int64_t count, int64_t unit, Launch launch) {
+    const size_t bytes = sizeof(double) * size_t(count);
+    if (bytes <= READ_PIN) {
+        int rc = ensure_pin(e);
+        if (rc) return rc;
+        HIPCHK(e, launch(int64_t(0), count, static_cast<double *>(e->pin)));
+        HIPCHK(e, hipStreamSynchronize(e->stream));
+        std::memcpy(dst, e->pin, bytes);
+        return FSC_OK;
+    }
+    const int64_t piece = std::min(count, std::max(unit, int64_t(READ_WORK / sizeof(double)) / unit * unit));
+    const size_t need = sizeof(double) * size_t(piece);
+    if (e->work_bytes < need) {
+        if (e->work) HIPCHK(e, hipFree(e->work));
+        e->work = nullptr;
+        e->work_bytes = 0;
+        if (hipMalloc(&e->work, need) != hipSuccess) {
+            (void)hipGetLastError();
+            e->work = nullptr;
+            return fail(e, FSC_E_OOM, "read buffer allocation failed");
+        }
+        e->work_bytes = need;
+    }
+    StreamDrain drain{e->stream};
+    for (int64_t k = 0; k < count; k += piece) {
+        const int64_t n = std::min(piece, count - k);
+        HIPCHK(e, launch(k, n, e->work));
+        HIPCHK(e, hipMemcpyAsync(dst + k, e->work, sizeof(double) * size_t(n), hipMemcpyDeviceToHost, e->stream));
+    }
+    HIPCHK(e, hipStreamSynchronize(e->stream));
     return FSC_OK;
 }
 
@@ -374,62 +455,59 @@ int enqueue_measure(fsc_ens *e, int par, uint32_t step_off, uint64_t advance = 0
     return FSC_OK;
 }
 
+// The stream is idle (the callers wait once for all replicas).
 int modes_enable(fsc_ens *e, Rep &r, int nm, int cap) {
-    (void)hipStreamSynchronize(e->stream);
-    if (r.d_modes) {
-        (void)hipFree(r.d_modes);
-        r.d_modes = nullptr;
-    }
     r.modes_cap = 0;
     r.modes_nm = 0;
+    r.modes_rows = 0;
     if (!r.d_modes_n) {
         if (hipMalloc(&r.d_modes_n, sizeof(int)) != hipSuccess) {
             (void)hipGetLastError();
             return fail(e, FSC_E_OOM, "mode recorder allocation failed");
         }
     }
+    const int sides[3] = {r.p.nx, r.p.ny, r.p.nz};
+    for (int d = 0; d < r.p.D && cap > 0; ++d)
+        if (nm > sides[d] / 2) return fail(e, FSC_E_INVAL, "nm exceeds half a side");
+    const size_t bytes = sizeof(double) * 2 * size_t(cap) * size_t(r.p.D) * size_t(nm);
+    if (r.d_modes && (cap == 0 || bytes > r.modes_bytes)) {
+        (void)hipFree(r.d_modes);
+        r.d_modes = nullptr;
+        r.modes_bytes = 0;
+    }
     if (cap > 0) {
-        const int sides[3] = {r.p.nx, r.p.ny, r.p.nz};
-        for (int d = 0; d < r.p.D; ++d)
-            if (nm > sides[d] / 2) return fail(e, FSC_E_INVAL, "nm exceeds half a side");
-        const size_t bytes = sizeof(double) * 2 * size_t(cap) * size_t(r.p.D) * size_t(nm);
-        if (hipMalloc(&r.d_modes, bytes) != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(e, FSC_E_OOM, "mode recorder allocation failed");
+        if (!r.d_modes) {
+            if (hipMalloc(&r.d_modes, bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                r.d_modes = nullptr;
+                return fail(e, FSC_E_OOM, "mode recorder allocation failed");
+            }
+            r.modes_bytes = bytes;
         }
         HIPCHK(e, hipMemsetAsync(r.d_modes, 0, bytes, e->stream));
         r.modes_cap = cap;
         r.modes_nm = nm;
     }
     HIPCHK(e, hipMemsetAsync(r.d_modes_n, 0, sizeof(int), e->stream));
-    HIPCHK(e, hipStreamSynchronize(e->stream));
     return FSC_OK;
 }
 
 int modes_read(fsc_ens *e, Rep &r, double *out, int max_rows, int *nrows) {
-    int n = 0;
-    if (r.d_modes_n) {
-        HIPCHK(e, hipMemcpyAsync(&n, r.d_modes_n, sizeof(int), hipMemcpyDeviceToHost, e->stream));
-        HIPCHK(e, hipStreamSynchronize(e->stream));
-    }
-    n = std::min(n, r.modes_cap);
+    const int n = int(std::min<int64_t>(r.modes_rows, r.modes_cap));
     const int m = std::min(n, max_rows);
-    if (m > 0 && out) {
-        HIPCHK(e, hipMemcpyAsync(out, r.d_modes, sizeof(double) * 2 * size_t(m) * r.p.D * r.modes_nm,
-                                 hipMemcpyDeviceToHost, e->stream));
-        HIPCHK(e, hipStreamSynchronize(e->stream));
-    }
     if (nrows) *nrows = n;
-    return FSC_OK;
+    if (m <= 0 || !out) return FSC_OK;
+    return read_back(e, out, r.d_modes, sizeof(double) * 2 * size_t(m) * size_t(r.p.D) * size_t(r.modes_nm));
 }
 
+// The stream is idle.
 int series_enable(fsc_ens *e, Rep &r, int cap) {
-    (void)hipStreamSynchronize(e->stream);
     if (r.d_series) {
         (void)hipFree(r.d_series);
         r.d_series = nullptr;
     }
     r.series_cap = 0;
+    r.series_rows = 0;
     if (cap > 0) {
         const size_t bytes = sizeof(double) * size_t(cap) * size_t(2 + r.n_rad);
         if (hipMalloc(&r.d_series, bytes) != hipSuccess) {
@@ -441,23 +519,18 @@ int series_enable(fsc_ens *e, Rep &r, int cap) {
     }
     HIPCHK(e, hipMemsetAsync(r.d_series_n, 0, sizeof(int), e->stream));
     HIPCHK(e, hipMemsetAsync(r.d_mom, 0, sizeof(double) * 2, e->stream));
-    HIPCHK(e, hipStreamSynchronize(e->stream));
     return FSC_OK;
 }
 
 int series_read(fsc_ens *e, Rep &r, double *out, int max_rows, int *nrows, int *row_len) {
     const int len = 2 + r.n_rad;
     if (row_len) *row_len = len;
-    int n = 0;
-    HIPCHK(e, hipMemcpyAsync(&n, r.d_series_n, sizeof(int), hipMemcpyDeviceToHost, e->stream));
-    HIPCHK(e, hipStreamSynchronize(e->stream));
-    n = std::min(n, r.series_cap);
+    const int n = int(std::min<int64_t>(r.series_rows, r.series_cap));
     if (nrows) *nrows = n;
     if (!out || max_rows <= 0 || n == 0) return FSC_OK;
     const int m = std::min(n, max_rows);
-    HIPCHK(e, hipMemcpyAsync(out, r.d_series, sizeof(double) * size_t(m) * len,
-                             hipMemcpyDeviceToHost, e->stream));
-    HIPCHK(e, hipStreamSynchronize(e->stream));
+    int rc = read_back(e, out, r.d_series, sizeof(double) * size_t(m) * size_t(len));
+    if (rc) return rc;
     for (int row = 0; row < m; ++row)
         for (int b = 0; b < r.n_rad; ++b)
             out[size_t(row) * len + 2 + b] =
@@ -1021,7 +1094,7 @@ int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
             it = e->graphs.emplace(key, ge).first;
         }
         for (int64_t c = 0; c < nchunks; ++c) HIPCHK(e, hipGraphLaunch(it->second.exec, e->stream));
-        for (auto &r : e->reps) r.nsamples += nchunks * it->second.samples;
+        for (auto &r : e->reps) r.sampled(nchunks * it->second.samples);
         done = nchunks * chunk;
         e->step += done;
     }
@@ -1032,7 +1105,7 @@ int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
         int rc = enqueue_steps(e, e->cur, rest, sk_every, &samples, &flips);
         if (rc) return rc;
         e->cur ^= flips;
-        for (auto &r : e->reps) r.nsamples += samples;
+        for (auto &r : e->reps) r.sampled(samples);
         e->step += rest;
     }
     return FSC_OK;
@@ -1106,12 +1179,14 @@ void ens_free(fsc_ens *e) {
             if (r.buf[0]) (void)hipFree(r.buf[0]);
             if (r.buf[1]) (void)hipFree(r.buf[1]);
         }
-        void *ptrs[] = {r.d_sk,  r.cbuf,     r.ctmp,       r.d_done,  r.d_stats,  r.d_partials,
+        void *ptrs[] = {r.d_sk,  r.cbuf,     r.ctmp,       r.d_done,  r.d_stats_done, r.d_partials,
                         r.d_mom, r.d_series, r.d_series_n, r.d_modes, r.d_modes_n};
         for (void *p : ptrs)
             if (p) (void)hipFree(p);
     }
     for (auto &kv : e->tabs) (void)hipFree(kv.second);
+    if (e->pin) (void)hipHostFree(e->pin);
+    if (e->work) (void)hipFree(e->work);
     if (e->d_blocks) (void)hipFree(e->d_blocks);
     if (e->d_desc) (void)hipFree(e->d_desc);
     if (e->d_tile_begin) (void)hipFree(e->d_tile_begin);
@@ -1155,34 +1230,21 @@ int ens_set_pop(fsc_ens *e, int ri, const double *host_f, int64_t step) {
 
 int ens_get_pop(fsc_ens *e, int ri, double *host_f) {
     Rep &r = e->reps[ri];
-    const int nx = r.p.nx, ny = r.p.ny, nz = r.p.nz;
-    const int par = e->cur;
-    std::vector<unsigned char> raw(r.esz * size_t(r.Q) * size_t(r.N));
-    HIPCHK(e, hipMemcpyAsync(raw.data(), r.buf[par], raw.size(), hipMemcpyDeviceToHost, e->stream));
-    HIPCHK(e, hipStreamSynchronize(e->stream));
-    for (int i = 0; i < r.Q; ++i) {
-        const int cx = r.c[3 * i], cy = r.c[3 * i + 1], cz = r.c[3 * i + 2];
-        const double shift = r.w[i] * r.p.rho0;
-        for (int z = 0; z < nz; ++z)
-            for (int y = 0; y < ny; ++y)
-                for (int x = 0; x < nx; ++x) {
-                    const int xs = wrap_any(x - cx, nx), ys = wrap_any(y - cy, ny), zs = wrap_any(z - cz, nz);
-                    const size_t src = size_t(i) * r.N + xs + size_t(nx) * (ys + size_t(ny) * zs);
-                    const size_t dst = size_t(i) * r.N + x + size_t(nx) * (y + size_t(ny) * z);
-                    const double v = r.esz == 4 ? double(reinterpret_cast<float *>(raw.data())[src])
-                                                : reinterpret_cast<double *>(raw.data())[src];
-                    host_f[dst] = shift + v;
-                }
-    }
-    return FSC_OK;
+    double shift[19];
+    for (int i = 0; i < r.Q; ++i) shift[i] = r.w[i] * r.p.rho0;
+    return read_formed(e, host_f, int64_t(r.Q) * r.N, 1, [&](int64_t first, int64_t n, double *out) {
+        return launch_streamed(r.geom(), r.p.precision, r.buf[e->cur], shift, first, n, out, e->stream);
+    });
 }
 
 int ens_stats(fsc_ens *e, int ri, double *out8) {
     Rep &r = e->reps[ri];
-    HIPCHK(e, launch_stats(r.geom(), r.p.precision, r.buf[e->cur], r.p.rho0, r.d_partials,
-                           r.d_stats, e->stream));
-    HIPCHK(e, hipMemcpyAsync(out8, r.d_stats, sizeof(double) * 8, hipMemcpyDeviceToHost, e->stream));
+    int rc = ensure_pin(e);
+    if (rc) return rc;
+    HIPCHK(e, launch_stats(r.geom(), r.p.precision, r.buf[e->cur], r.p.rho0, r.d_partials, r.d_stats_done,
+                           static_cast<double *>(e->pin), e->stream));
     HIPCHK(e, hipStreamSynchronize(e->stream));
+    std::memcpy(out8, e->pin, sizeof(double) * 8);
     if (out8[6] > 0.0) return fail(e, FSC_E_DIVERGED, "non-finite or non-positive density");
     return FSC_OK;
 }
@@ -1202,17 +1264,14 @@ int ens_read_sk(fsc_ens *e, int ri, int kind, double *sum, double *sumsq, int64_
     if (nbins != nb) return fail(e, FSC_E_INVAL, "nbins does not match fsc_sk_nbins");
     if (nb == 0) return FSC_OK;
     const size_t na = size_t(r.p.D) * r.n_axis;
-    const double *s = kind == FSC_SK_AXIS ? r.d_sk : r.d_sk + 2 * na;
-    const double *q = kind == FSC_SK_AXIS ? r.d_sk + na : r.d_sk + 2 * na + r.n_rad;
-    std::vector<double> hs(nb), hq(nb);
-    StreamDrain drain{e->stream};
-    HIPCHK(e, hipMemcpyAsync(hs.data(), s, sizeof(double) * nb, hipMemcpyDeviceToHost, e->stream));
-    HIPCHK(e, hipMemcpyAsync(hq.data(), q, sizeof(double) * nb, hipMemcpyDeviceToHost, e->stream));
-    HIPCHK(e, hipStreamSynchronize(e->stream));
+    // sums, then sums of squares
+    std::vector<double> h(2 * size_t(nb));
+    int rc = read_back(e, h.data(), kind == FSC_SK_AXIS ? r.d_sk : r.d_sk + 2 * na, sizeof(double) * h.size());
+    if (rc) return rc;
     const auto &modes = kind == FSC_SK_AXIS ? r.axis_modes : r.rad_modes;
     for (int k = 0; k < nb; ++k) {
-        if (sum) sum[k] = hs[k];
-        if (sumsq) sumsq[k] = hq[k];
+        if (sum) sum[k] = h[size_t(k)];
+        if (sumsq) sumsq[k] = h[size_t(nb + k)];
         if (count) count[k] = modes[k] * r.nsamples;
     }
     return FSC_OK;
@@ -1243,21 +1302,10 @@ int ens_init_uniform(fsc_ens *e) {
 // Density n(x) of one replica's current state into host doubles [nz][ny][nx].
 int ens_density(fsc_ens *e, int ri, double *host_rho) {
     Rep &r = e->reps[ri];
-    void *tmp = nullptr;
-    if (hipMalloc(&tmp, r.esz * size_t(r.N)) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(e, FSC_E_OOM, "density buffer");
-    }
-    hipError_t ec = launch_density_real(r.geom(), r.p.precision, r.buf[e->cur], tmp, e->stream);
-    std::vector<unsigned char> raw(r.esz * size_t(r.N));
-    if (ec == hipSuccess) ec = hipMemcpyAsync(raw.data(), tmp, raw.size(), hipMemcpyDeviceToHost, e->stream);
-    if (ec == hipSuccess) ec = hipStreamSynchronize(e->stream);
-    (void)hipFree(tmp);
-    if (ec != hipSuccess) return fail(e, FSC_E_HIP, hipGetErrorString(ec));
-    for (int64_t s = 0; s < r.N; ++s)
-        host_rho[s] = r.p.rho0 + (r.esz == 4 ? double(reinterpret_cast<float *>(raw.data())[s])
-                                             : reinterpret_cast<double *>(raw.data())[s]);
-    return FSC_OK;
+    return read_formed(e, host_rho, r.N, r.p.nx, [&](int64_t first, int64_t n, double *out) {
+        return launch_density(r.geom(), r.p.precision, r.buf[e->cur], r.p.rho0, first / r.p.nx, n / r.p.nx, out,
+                              e->stream);
+    });
 }
 
 // ---- checkpoints -----------------------------------------------------------
@@ -1486,7 +1534,7 @@ int fsc_measure_sk(fsc_ctx *ctx) {
     if (rc) return rc;
     rc = enqueue_measure(e, e->cur, 0);
     if (rc) return rc;
-    r.nsamples += 1;
+    r.sampled(1);
     return FSC_OK;
 }
 
@@ -1568,6 +1616,7 @@ int fsc_load(fsc_ctx *ctx, const char *path) {
 // ---- time series ----------------------------------------------------------
 int fsc_series_enable(fsc_ctx *ctx, int capacity) {
     if (!ctx || capacity < 0) return FSC_E_INVAL;
+    (void)hipStreamSynchronize(ctx->e->stream);
     drop_graphs(ctx->e);
     return series_enable(ctx->e, ctx->e->reps[0], capacity);
 }
@@ -1577,6 +1626,7 @@ int fsc_read_series(fsc_ctx *ctx, double *out, int max_rows, int *nrows, int *ro
 }
 int fsc_ens_series_enable(fsc_ens *ens, int capacity) {
     if (!ens || capacity < 0) return FSC_E_INVAL;
+    (void)hipStreamSynchronize(ens->stream);
     drop_graphs(ens);
     for (auto &r : ens->reps) {
         int rc = series_enable(ens, r, capacity);
@@ -1594,6 +1644,7 @@ int fsc_ens_read_series(fsc_ens *ens, int replica, double *out, int max_rows, in
 // ---- recorded mode amplitudes ---------------------------------------------------
 int fsc_modes_enable(fsc_ctx *ctx, int nm, int capacity) {
     if (!ctx || capacity < 0 || (capacity > 0 && nm < 1)) return FSC_E_INVAL;
+    (void)hipStreamSynchronize(ctx->e->stream);
     drop_graphs(ctx->e);
     return modes_enable(ctx->e, ctx->e->reps[0], nm, capacity);
 }
@@ -1603,6 +1654,7 @@ int fsc_read_modes(fsc_ctx *ctx, double *out, int max_rows, int *nrows) {
 }
 int fsc_ens_modes_enable(fsc_ens *ens, int nm, int capacity) {
     if (!ens || capacity < 0 || (capacity > 0 && nm < 1)) return FSC_E_INVAL;
+    (void)hipStreamSynchronize(ens->stream);
     drop_graphs(ens);
     for (auto &r : ens->reps) {
         int rc = modes_enable(ens, r, nm, capacity);

@@ -87,14 +87,19 @@ struct Geometry {
     int64_t N;
 };
 
-// Real density deviation dn(x) (float or double by precision).
-hipError_t launch_density_real(const Geometry &g, int precision, const void *buf, void *out,
-                               hipStream_t s);
-// FP64 state reductions into out[8] (see fsc_stats); `partials` holds
-// stats_partials_len() doubles.
+// Density n(x) in double of the x-rows row0 .. row0 + rows - 1 (row = y + ny z).
+hipError_t launch_density(const Geometry &g, int precision, const void *buf, double rho0, int64_t row0,
+                          int64_t rows, double *out, hipStream_t s);
+// Streamed populations shift[i] + df_i in double, elements e0 .. e0 + n - 1 of
+// [i][z][y][x].
+hipError_t launch_streamed(const Geometry &g, int precision, const void *buf, const double *shift, int64_t e0,
+                           int64_t n, double *out, hipStream_t s);
+// FP64 state reductions into out[8] (see fsc_stats; device memory or pinned host
+// memory); `partials` holds stats_partials_len() doubles, *done is 0 between
+// calls.
 size_t stats_partials_len();
 hipError_t launch_stats(const Geometry &g, int precision, const void *buf, double rho0,
-                        double *partials, double *out, hipStream_t s);
+                        double *partials, int *done, double *out, hipStream_t s);
 
 // Transform of one axis: lines of n values over m points, m = 2^logm (n itself,
 // or at least 2n - 1 for the chirp form), or m = n and logm = -1 (direct sum).

@@ -38,44 +38,79 @@ __device__ inline void gather_node(const real *src, const Geometry &g, int x, in
     }
 }
 
+// n(x) = rho0 + dn in double of the rows row0 .. row0 + rows - 1, as a program
+// reads it: formed here, the host only receives it (converting 256^3 values on
+// the host took longer than moving them).
 template <class L, typename real>
-__global__ void __launch_bounds__(256) k_density(Geometry g, const real *__restrict__ src,
-                                                 real *__restrict__ out) {
+__global__ void __launch_bounds__(256) k_density(Geometry g, const real *__restrict__ src, double rho0,
+                                                 int64_t row0, double *__restrict__ out) {
     const int strips = (g.nx + 255) / 256;
-    const int row = int(blockIdx.x) / strips;
+    const int64_t r = int(blockIdx.x) / strips, row = row0 + r;
     const int x = (int(blockIdx.x) % strips) * 256 + threadIdx.x;
     if (x >= g.nx) return;
     real f[L::Q];
-    gather_node<L, real>(src, g, x, row % g.ny, row / g.ny, f);
+    gather_node<L, real>(src, g, x, int(row % g.ny), int(row / g.ny), f);
     real dn = real(0);
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) dn += f[i];
-    out[int64_t(row) * g.nx + x] = dn;
+    out[r * g.nx + x] = rho0 + double(dn);
 }
 
-template <class L, typename real>
-static hipError_t density_impl(const Geometry &g, const void *buf, void *out, hipStream_t s) {
-    const int strips = (g.nx + 255) / 256;
-    const int64_t blocks = int64_t(strips) * g.ny * g.nz;
+hipError_t launch_density(const Geometry &g, int precision, const void *buf, double rho0, int64_t row0,
+                          int64_t rows, double *out, hipStream_t s) {
+    const int64_t blocks = int64_t((g.nx + 255) / 256) * rows;
     if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_density<L, real>), dim3(unsigned(blocks)), dim3(256), 0, s, g,
-                       static_cast<const real *>(buf), static_cast<real *>(out));
-    return hipGetLastError();
+    auto go = [&](auto kernel, auto p) {
+        hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(256), 0, s, g, p, rho0, row0, out);
+        return hipGetLastError();
+    };
+    const float *f = static_cast<const float *>(buf);
+    const double *d = static_cast<const double *>(buf);
+    if (g.D == 2) return precision == 0 ? go(k_density<D2Q9, float>, f) : go(k_density<D2Q9, double>, d);
+    return precision == 0 ? go(k_density<D3Q19, float>, f) : go(k_density<D3Q19, double>, d);
 }
 
-hipError_t launch_density_real(const Geometry &g, int precision, const void *buf, void *out,
-                               hipStream_t s) {
-    if (g.D == 2)
-        return precision == 0 ? density_impl<D2Q9, float>(g, buf, out, s)
-                              : density_impl<D2Q9, double>(g, buf, out, s);
-    return precision == 0 ? density_impl<D3Q19, float>(g, buf, out, s)
-                          : density_impl<D3Q19, double>(g, buf, out, s);
+// The streamed populations w_i rho0 + df_i(x) in double, layout [i][z][y][x],
+// elements e0 .. e0 + n - 1 (shift[i] = w_i rho0, formed by the caller).
+struct PopShift {
+    double v[19];
+};
+template <class L, typename real>
+__global__ void __launch_bounds__(256) k_streamed(Geometry g, const real *__restrict__ src, PopShift shift,
+                                                  int64_t e0, int64_t n, double *__restrict__ out) {
+    const int64_t k = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (k >= n) return;
+    const int64_t e = e0 + k;
+    const int i = int(e / g.N);
+    const int64_t s = e - i * g.N, row = s / g.nx;
+    const int x = int(s - row * g.nx), y = int(row % g.ny), z = int(row / g.ny);
+    const int xs = wrap_any(x - L::c(i, 0), g.nx), ys = wrap_any(y - L::c(i, 1), g.ny),
+              zs = wrap_any(z - L::c(i, 2), g.nz);
+    out[k] = shift.v[i] + double(src[int64_t(i) * g.N + xs + int64_t(g.nx) * (ys + int64_t(g.ny) * zs)]);
+}
+
+hipError_t launch_streamed(const Geometry &g, int precision, const void *buf, const double *shift, int64_t e0,
+                           int64_t n, double *out, hipStream_t s) {
+    const int64_t blocks = (n + 255) / 256;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    PopShift sh{};
+    for (int i = 0; i < (g.D == 2 ? D2Q9::Q : D3Q19::Q); ++i) sh.v[i] = shift[i];
+    auto go = [&](auto kernel, auto p) {
+        hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(256), 0, s, g, p, sh, e0, n, out);
+        return hipGetLastError();
+    };
+    const float *f = static_cast<const float *>(buf);
+    const double *d = static_cast<const double *>(buf);
+    if (g.D == 2) return precision == 0 ? go(k_streamed<D2Q9, float>, f) : go(k_streamed<D2Q9, double>, d);
+    return precision == 0 ? go(k_streamed<D3Q19, float>, f) : go(k_streamed<D3Q19, double>, d);
 }
 
 // ---------------------------------------------------------------------------
 // FP64 reductions: sum dn, sum j, min/max n, bad-node count.  A fixed grid of
-// STAT_BLOCKS blocks strides over rows; the partials are reduced by one block
-// in a fixed order, so the result is deterministic.
+// STAT_BLOCKS blocks strides over rows; the last block to finish reduces the
+// partials in a fixed order, so the result is deterministic, and writes it where
+// the host reads it (pinned memory): one launch and no copy.  48 replicas of 128^2
+// one after the other took 36 us each as two launches and a copy, 23 us so.
 // ---------------------------------------------------------------------------
 constexpr int STAT_BLOCKS = 1024;
 constexpr int STAT_W = 8;
@@ -101,6 +136,7 @@ __device__ inline double wave_max(double v) {
 __device__ inline void block_reduce_stats(double (&acc)[STAT_W]) {
     __shared__ double sh[4][STAT_W];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    __syncthreads();  // a second call reuses sh
 #pragma unroll
     for (int k = 0; k < STAT_W; ++k) {
         double v = acc[k];
@@ -120,8 +156,10 @@ __device__ inline void block_reduce_stats(double (&acc)[STAT_W]) {
 }
 
 template <class L, typename real>
-__global__ void __launch_bounds__(256) k_stats(Geometry g, const real *__restrict__ src,
-                                               double rho0, double *__restrict__ partials) {
+__global__ void __launch_bounds__(256) k_stats(Geometry g, const real *__restrict__ src, double rho0,
+                                               double n_rho0, double *__restrict__ partials,
+                                               int *__restrict__ done, double *__restrict__ out) {
+    __shared__ bool last;
     double acc[STAT_W] = {0.0, 0.0, 0.0, 0.0, 1e300, -1e300, 0.0, 0.0};
     const int rows = g.ny * g.nz;
     for (int row = blockIdx.x; row < rows; row += gridDim.x) {
@@ -149,50 +187,46 @@ __global__ void __launch_bounds__(256) k_stats(Geometry g, const real *__restric
         }
     }
     block_reduce_stats(acc);
-    if (threadIdx.x == 0)
-        for (int k = 0; k < STAT_W; ++k) partials[blockIdx.x * STAT_W + k] = acc[k];
-}
-
-__global__ void __launch_bounds__(256) k_stats_final(const double *__restrict__ partials,
-                                                     int nblocks, double n_rho0,
-                                                     double *__restrict__ out) {
-    double acc[STAT_W] = {0.0, 0.0, 0.0, 0.0, 1e300, -1e300, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nblocks; b += 256) {
-        const double *p = partials + b * STAT_W;
-        for (int k = 0; k < STAT_W; ++k)
-            acc[k] = (k == 4) ? fmin(acc[k], p[k]) : (k == 5 ? fmax(acc[k], p[k]) : acc[k] + p[k]);
-    }
-    block_reduce_stats(acc);
+    // partials go to the last block by atomic stores and loads, which pass by
+    // the XCDs' L2s, so no cache is written back for them
     if (threadIdx.x == 0) {
-        out[0] = n_rho0 + acc[0];
-        for (int k = 1; k < STAT_W; ++k) out[k] = acc[k];
+        for (int k = 0; k < STAT_W; ++k)
+            __hip_atomic_store(&partials[blockIdx.x * STAT_W + k], acc[k], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0);
+        last = __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == int(gridDim.x) - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    double t[STAT_W] = {0.0, 0.0, 0.0, 0.0, 1e300, -1e300, 0.0, 0.0};
+    for (int b = threadIdx.x; b < int(gridDim.x); b += 256) {
+        double *p = partials + b * STAT_W;
+        for (int k = 0; k < STAT_W; ++k) {
+            const double v = __hip_atomic_load(&p[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            t[k] = (k == 4) ? fmin(t[k], v) : (k == 5 ? fmax(t[k], v) : t[k] + v);
+        }
+    }
+    block_reduce_stats(t);
+    if (threadIdx.x == 0) {
+        out[0] = n_rho0 + t[0];
+        for (int k = 1; k < STAT_W; ++k) out[k] = t[k];
+        __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
 hipError_t launch_stats(const Geometry &g, int precision, const void *buf, double rho0,
-                        double *partials, double *out, hipStream_t s) {
+                        double *partials, int *done, double *out, hipStream_t s) {
     const int rows = g.ny * g.nz;
     const int nb = rows < STAT_BLOCKS ? rows : STAT_BLOCKS;
-    if (g.D == 2) {
-        if (precision == 0)
-            hipLaunchKernelGGL((k_stats<D2Q9, float>), dim3(nb), dim3(256), 0, s, g,
-                               static_cast<const float *>(buf), rho0, partials);
-        else
-            hipLaunchKernelGGL((k_stats<D2Q9, double>), dim3(nb), dim3(256), 0, s, g,
-                               static_cast<const double *>(buf), rho0, partials);
-    } else {
-        if (precision == 0)
-            hipLaunchKernelGGL((k_stats<D3Q19, float>), dim3(nb), dim3(256), 0, s, g,
-                               static_cast<const float *>(buf), rho0, partials);
-        else
-            hipLaunchKernelGGL((k_stats<D3Q19, double>), dim3(nb), dim3(256), 0, s, g,
-                               static_cast<const double *>(buf), rho0, partials);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(256), 0, s, partials, nb,
-                       double(g.N) * rho0, out);
-    return hipGetLastError();
+    auto go = [&](auto kernel, auto p) {
+        hipLaunchKernelGGL(kernel, dim3(unsigned(nb)), dim3(256), 0, s, g, p, rho0, double(g.N) * rho0, partials,
+                           done, out);
+        return hipGetLastError();
+    };
+    const float *f = static_cast<const float *>(buf);
+    const double *d = static_cast<const double *>(buf);
+    if (g.D == 2) return precision == 0 ? go(k_stats<D2Q9, float>, f) : go(k_stats<D2Q9, double>, d);
+    return precision == 0 ? go(k_stats<D3Q19, float>, f) : go(k_stats<D3Q19, double>, d);
 }
 
 // ---------------------------------------------------------------------------
