@@ -12,8 +12,11 @@
 // Doubling stays well posed where A has a unit-modulus eigenvalue the
 // noise does not excite (k = pi on an axis at tau = 1).
 //
-// One 64-lane workgroup per wave vector; the three Q x Q complex matrices
-// live in LDS (17 KB for D3Q19).  FP64 throughout.
+// With every relaxation rate 1 (the paper's case) the collision forgets all but
+// the conserved moments, and the same sum is one over (D + 1) x (D + 1) real
+// matrices, one wave vector per lane (k_linear_conserved).  Other rates: one
+// 64-lane workgroup per wave vector, the three Q x Q complex matrices in LDS
+// (17 KB for D3Q19).  FP64 throughout.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -41,6 +44,29 @@ struct LinArgs {
     double mu;            // kBT / c_s^2
     double lam[4];        // per class
     int doublings;
+};
+
+// c_i is the one of +-c_i whose first non-zero component is positive
+template <class L>
+__host__ __device__ constexpr bool first_of_pair(int i) {
+    return L::c(i, 0) != 0 ? L::c(i, 0) > 0 : (L::c(i, 1) != 0 ? L::c(i, 1) > 0 : L::c(i, 2) > 0);
+}
+// per moment row: 1/b_a, and whether M_ai takes the same value at c_i and -c_i
+template <class L>
+struct RowTable {
+    double inv_norm[L::Q];
+    bool even[L::Q];
+    constexpr RowTable() : inv_norm{}, even{} {
+        for (int a = 0; a < L::Q; ++a) {
+            inv_norm[a] = 1.0 / moment_norm<L>(a);
+            even[a] = true;
+            for (int i = 0; i < L::Q; ++i)
+                for (int j = 0; j < L::Q; ++j)
+                    if (L::c(i, 0) == -L::c(j, 0) && L::c(i, 1) == -L::c(j, 1) && L::c(i, 2) == -L::c(j, 2) &&
+                        L::M(a, i) != L::M(a, j))
+                        even[a] = false;
+        }
+    }
 };
 
 // C = A B (all Q x Q), lanes stride over the entries.
@@ -195,15 +221,199 @@ __device__ void doubling_sum(const LinArgs &la, cplx64 (&A)[Q][Q], cplx64 (&X)[Q
     }
 }
 
+// The wave vectors of one call: a caller's list, or (kv null) the fundamental
+// domain of an n^D lattice's square / cubic group, 0 <= m_z <= m_y <= m_x <= n/2
+// without the origin, in ascending (m_x, m_y, m_z).
+struct KSource {
+    const double *kv;
+    int64_t nk;
+    double unit;  // 2 pi / n
+};
+
+__device__ __forceinline__ void wave_vector(const KSource &ks, int D, int64_t id, double (&k)[3]) {
+    k[2] = 0.0;
+    if (ks.kv) {
+        for (int d = 0; d < D; ++d) k[d] = ks.kv[D * id + d];
+        return;
+    }
+    const int64_t r = id + 1;  // rank, the origin included
+    auto tri = [](int64_t a) { return a * (a + 1) / 2; };
+    auto tet = [](int64_t a) { return a * (a + 1) * (a + 2) / 6; };
+    int64_t a = 0, rest = r;
+    if (D == 3) {
+        a = int64_t(cbrt(6.0 * double(r)));
+        while (tet(a) > r) --a;
+        while (tet(a + 1) <= r) ++a;
+        rest = r - tet(a);
+    }
+    int64_t b = int64_t(sqrt(2.0 * double(rest)));
+    while (tri(b) > rest) --b;
+    while (tri(b + 1) <= rest) ++b;
+    const int64_t c = rest - tri(b);
+    k[0] = ks.unit * double(D == 3 ? a : b);
+    k[1] = ks.unit * double(D == 3 ? b : c);
+    if (D == 3) k[2] = ks.unit * double(c);
+}
+
+// All relaxation rates 1.  After a collision the populations depend on the
+// conserved moments (n, j) alone, f* = E (n, j) with
+//   f*_i = w_i (n + c_i . (j + dF) / c_s^2),
+// so with B = (1, c) the moments' covariance is Z = sum_m K^m W (K^m)^H, K = B P E
+// and W = B Qn B^H, both (D + 1) x (D + 1), and S = Z_00.  Rows and columns of j
+// taken times i make K and W real: with theta_i = c_i . k, dF = i g dn,
+//   s_d = sum w_i c_id sin theta_i,  q_de = sum w_i c_id c_ie cos theta_i,
+//   K_00 = sum w_i cos theta_i + s . g / c_s^2,  K_0d = s_d / c_s^2,
+//   K_d0 = -s_d + sum_e q_de g_e / c_s^2,        K_de = q_de / c_s^2,
+// and W = sum_a amp_a^2 u_a u_a^T over the noise rows m_a, with u_a = (sum m_ai
+// cos theta_i, -sum c_id m_ai sin theta_i) for rows even in c and (sum m_ai sin
+// theta_i, sum c_id m_ai cos theta_i) for odd ones.
+//
+// Near k = 0, K is 1 + O(k) and the sum has O(1/k^2) terms, so what is held is
+// K - 1, from -2 sin^2(theta/2) instead of cos theta - 1 (the ones fall out of
+// every sum by the rows' orthogonality): squaring keeps it to a relative
+// rounding, (1 + L)^2 - 1 = 2L + L L.
+//
+// A lane holds its three matrices in registers: 20 doublings of 170 FMAs where the
+// Q x Q complex form takes 20 x 82000 in 3D.  What bounds it is the one wave's
+// serial FP64 chain (a 64^3 lattice has 103 waves of wave vectors).  The radial
+// S(k) of 64^3, whole call: 1785 us as Q x Q matrices, 64 us so, with a quarter of
+// the error (1.1e-14).
 template <class L, class ST>
-__global__ void __launch_bounds__(64) k_linear_sk(LinArgs la, const double *__restrict__ kv,
-                                                  int64_t nk, double *__restrict__ out) {
-    constexpr int D = L::D, Q = L::Q;
+__global__ void __launch_bounds__(64) k_linear_conserved(LinArgs la, KSource ks, double *__restrict__ out) {
+    constexpr int D = L::D, Q = L::Q, N = D + 1;
+    constexpr double ICS2 = 3.0;
+    constexpr RowTable<L> rows;
+    const int64_t id = int64_t(blockIdx.x) * 64 + threadIdx.x;
+    double k[3];
+    wave_vector(ks, D, id < ks.nk ? id : ks.nk - 1, k);
+
+    double g[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int a = 0; a < ST::NH; ++a) {
+        double kd = 0.0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) kd += k[d] * ST::e(a, d);
+        const double s = la.coupling * 2.0 * ST::w(a) * sin(kd);
+#pragma unroll
+        for (int d = 0; d < D; ++d) g[d] += s * ST::e(a, d);
+    }
+    // one of each pair +-c: sin theta and cos theta - 1
+    double sn[Q], cm[Q];
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+        if (!first_of_pair<L>(i)) continue;
+        double th = 0.0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) th += k[d] * L::c(i, d);
+        sn[i] = sin(th);
+        const double h = sin(0.5 * th);
+        cm[i] = -2.0 * h * h;
+    }
+
+    double Lm[N][N], X[N][N];  // K - 1 and the covariance (lower triangle)
+#pragma unroll
+    for (int a = 0; a < N; ++a)
+#pragma unroll
+        for (int b = 0; b < N; ++b) Lm[a][b] = X[a][b] = 0.0;
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+        if (!first_of_pair<L>(i)) continue;
+        Lm[0][0] += 2.0 * L::w(i) * cm[i];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            if (L::c(i, d) == 0) continue;
+            Lm[0][d + 1] += 2.0 * ICS2 * L::w(i) * L::c(i, d) * sn[i];
+#pragma unroll
+            for (int e = 0; e < D; ++e)
+                if (L::c(i, e) != 0) Lm[d + 1][e + 1] += 2.0 * ICS2 * L::w(i) * (L::c(i, d) * L::c(i, e)) * cm[i];
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        Lm[0][0] = fma(Lm[0][d + 1], g[d], Lm[0][0]);
+        double v = g[d] - Lm[0][d + 1] / ICS2;
+#pragma unroll
+        for (int e = 0; e < D; ++e) v = fma(Lm[d + 1][e + 1], g[e], v);
+        Lm[d + 1][0] = v;
+    }
+#pragma unroll
+    for (int a = N; a < Q; ++a) {
+        double u[N];
+        const bool even = rows.even[a];
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+            double v = 0.0;
+#pragma unroll
+            for (int i = 1; i < Q; ++i) {
+                if (!first_of_pair<L>(i)) continue;
+                const double cf = 2.0 * L::w(i) * L::M(a, i) * (r == 0 ? 1 : L::c(i, r > 0 ? r - 1 : 0));
+                if (cf == 0.0) continue;
+                const double t = (r == 0) == even ? cm[i] : sn[i];
+                v += (r > 0 && even ? -cf : cf) * t;
+            }
+            u[r] = v;
+        }
+        const double amp2 = la.mu * la.n0 * rows.inv_norm[a];
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+#pragma unroll
+            for (int q = 0; q <= r; ++q) X[r][q] = fma(amp2 * u[r], u[q], X[r][q]);
+    }
+
+    for (int it = 0; it < la.doublings; ++it) {
+        double T[N][N];  // K X
+#pragma unroll
+        for (int a = 0; a < N; ++a)
+#pragma unroll
+            for (int b = 0; b < N; ++b) {
+                double v = a >= b ? X[a][b] : X[b][a];
+#pragma unroll
+                for (int m = 0; m < N; ++m) v = fma(Lm[a][m], m >= b ? X[m][b] : X[b][m], v);
+                T[a][b] = v;
+            }
+#pragma unroll
+        for (int a = 0; a < N; ++a)  // X += T K^T
+#pragma unroll
+            for (int b = 0; b <= a; ++b) {
+                double v = T[a][b];
+#pragma unroll
+                for (int m = 0; m < N; ++m) v = fma(T[a][m], Lm[b][m], v);
+                X[a][b] += v;
+            }
+        double P[N][N];
+        bool small = true;
+#pragma unroll
+        for (int a = 0; a < N; ++a)
+#pragma unroll
+            for (int b = 0; b < N; ++b) {
+                double v = 2.0 * Lm[a][b];
+#pragma unroll
+                for (int m = 0; m < N; ++m) v = fma(Lm[a][m], Lm[m][b], v);
+                P[a][b] = v;
+            }
+#pragma unroll
+        for (int a = 0; a < N; ++a)
+#pragma unroll
+            for (int b = 0; b < N; ++b) {
+                Lm[a][b] = P[a][b];
+                small = small && fabs(P[a][b] + (a == b ? 1.0 : 0.0)) < 1e-12;
+            }
+        // what remains is K Z K^T, below 1e-22 of Z; a lane that is done adds
+        // nothing while the others go on
+        if (__all(small)) break;
+    }
+    if (id < ks.nk) out[id] = X[0][0];
+}
+
+template <class L, class ST>
+__global__ void __launch_bounds__(64) k_linear_sk(LinArgs la, KSource ks, double *__restrict__ out) {
+    constexpr int Q = L::Q;
     __shared__ cplx64 A[Q][Q], X[Q][Q], T[Q][Q];
     __shared__ double red[64];
     const int lane = threadIdx.x;
-    for (int64_t kid = blockIdx.x; kid < nk; kid += gridDim.x) {
-        const double k[3] = {kv[3 * kid], kv[3 * kid + 1], D == 3 ? kv[3 * kid + 2] : 0.0};
+    for (int64_t kid = blockIdx.x; kid < ks.nk; kid += gridDim.x) {
+        double k[3];
+        wave_vector(ks, L::D, kid, k);
         build_operator<L, ST>(la, k, A, X, T);
         doubling_sum<Q>(la, A, X, T, red);
         double s = 0.0;
@@ -275,11 +485,24 @@ __global__ void __launch_bounds__(64) k_linear_corr(LinArgs la, const double *__
     }
 }
 
+// rates of exactly 1 take the conserved-moment form (any other rate keeps its
+// class of moments from step to step)
 template <class L, class ST>
-hipError_t launch_linear(const LinArgs &la, const double *kv, int64_t nk, double *out, hipStream_t s) {
-    const unsigned blocks = unsigned(nk < 65536 ? nk : 65536);
-    hipLaunchKernelGGL((k_linear_sk<L, ST>), dim3(blocks), dim3(64), 0, s, la, kv, nk, out);
+hipError_t launch_linear(const LinArgs &la, const KSource &ks, double *out, hipStream_t s) {
+    const int64_t waves = (ks.nk + 63) / 64;
+    if (la.lam[1] == 1.0 && la.lam[2] == 1.0 && la.lam[3] == 1.0 && waves <= 0x7fffffff) {
+        hipLaunchKernelGGL((k_linear_conserved<L, ST>), dim3(unsigned(waves)), dim3(64), 0, s, la, ks, out);
+        return hipGetLastError();
+    }
+    const unsigned blocks = unsigned(ks.nk < 65536 ? ks.nk : 65536);
+    hipLaunchKernelGGL((k_linear_sk<L, ST>), dim3(blocks), dim3(64), 0, s, la, ks, out);
     return hipGetLastError();
+}
+
+hipError_t launch_linear(const fsc_params *p, const LinArgs &la, const KSource &ks, double *out, hipStream_t s) {
+    if (p->D == 2 && p->stencil == FSC_E4) return launch_linear<D2Q9, StencilE4_2D>(la, ks, out, s);
+    if (p->D == 2) return launch_linear<D2Q9, StencilE8_2D>(la, ks, out, s);
+    return launch_linear<D3Q19, StencilE4_3D>(la, ks, out, s);
 }
 
 template <class L, class ST>
@@ -330,24 +553,18 @@ int fsc_linear_sk(const fsc_params *p, const double *host_k, int64_t nk, double 
     if (rc) return rc;
     if (nk == 0) return FSC_OK;
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    std::vector<double> k3(size_t(nk) * 3, 0.0);
-    for (int64_t i = 0; i < nk; ++i)
-        for (int d = 0; d < p->D; ++d) k3[3 * i + d] = host_k[p->D * i + d];
     double *dk = nullptr, *ds = nullptr;
-    if (hipMalloc(&dk, sizeof(double) * 3 * nk) != hipSuccess ||
-        hipMalloc(&ds, sizeof(double) * nk) != hipSuccess) {
+    const size_t kbytes = sizeof(double) * size_t(p->D) * size_t(nk);
+    if (hipMalloc(&dk, kbytes) != hipSuccess || hipMalloc(&ds, sizeof(double) * nk) != hipSuccess) {
         (void)hipGetLastError();
         if (dk) (void)hipFree(dk);
         return FSC_E_OOM;
     }
-    hipError_t e = hipMemcpyAsync(dk, k3.data(), sizeof(double) * 3 * nk, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) {
-        if (p->D == 2 && p->stencil == FSC_E4) e = launch_linear<D2Q9, StencilE4_2D>(la, dk, nk, ds, st);
-        else if (p->D == 2) e = launch_linear<D2Q9, StencilE8_2D>(la, dk, nk, ds, st);
-        else e = launch_linear<D3Q19, StencilE4_3D>(la, dk, nk, ds, st);
-    }
+    hipError_t e = hipMemcpyAsync(dk, host_k, kbytes, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = launch_linear(p, la, KSource{dk, nk, 0.0}, ds, st);
     if (e == hipSuccess) e = hipMemcpyAsync(host_s, ds, sizeof(double) * nk, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    const hipError_t es = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = es;
     (void)hipFree(dk);
     (void)hipFree(ds);
     return e == hipSuccess ? FSC_OK : FSC_E_HIP;
@@ -397,47 +614,53 @@ int fsc_linear_sk_radial(const fsc_params *p, double *host_shell_mean, int64_t *
     if (!p || !host_shell_mean || nbins < 1) return FSC_E_INVAL;
     const int D = p->D, n = p->nx;
     if (n < 2 || p->ny != n || (D == 3 && p->nz != n) || (D == 2 && p->nz != 1)) return FSC_E_INVAL;
-    // wave vectors of the fundamental domain of the square / cubic group,
-    // 0 <= m_z <= m_y <= m_x <= n/2, each with the number of lattice modes
-    // it stands for (sign choices x distinct permutations)
-    const int h = n / 2;
-    auto signs = [&](int v) { return (v == 0 || (2 * v == n)) ? 1 : 2; };
-    auto round_sqrt = [](int64_t m) {
-        int64_t b = int64_t(std::sqrt(double(m)));
-        while (b * b > m) --b;
-        while ((b + 1) * (b + 1) <= m) ++b;
-        if (m - b * b > b) ++b;
-        return int(b);
-    };
-    std::vector<double> kv;
-    std::vector<int64_t> mult;
-    std::vector<int> bin;
-    const double two_pi_n = 2.0 * M_PI / n;
-    for (int a = 0; a <= h; ++a)
-        for (int b = 0; b <= a; ++b)
-            for (int c = 0; c <= (D == 3 ? b : 0); ++c) {
-                const int64_t m2 = int64_t(a) * a + int64_t(b) * b + int64_t(c) * c;
-                if (m2 == 0) continue;
-                int64_t perms;
-                if (D == 2) perms = (a == b) ? 1 : 2;
-                else perms = (a == b && b == c) ? 1 : ((a == b || b == c) ? 3 : 6);
-                const int64_t mu = perms * signs(a) * signs(b) * (D == 3 ? signs(c) : 1);
-                kv.push_back(two_pi_n * a);
-                kv.push_back(two_pi_n * b);
-                if (D == 3) kv.push_back(two_pi_n * c);
-                mult.push_back(mu);
-                bin.push_back(round_sqrt(m2));
-            }
-    const int64_t nk = int64_t(mult.size());
-    std::vector<double> S(static_cast<size_t>(nk));
-    int rc = fsc_linear_sk(p, kv.data(), nk, S.data(), stream);
+    LinArgs la;
+    const int rc = resolve_linear(p, la);
     if (rc) return rc;
+    // the wave vectors of the fundamental domain of the square / cubic group,
+    // 0 <= m_z <= m_y <= m_x <= n/2 (formed on the device), each with the number
+    // of lattice modes it stands for (sign choices x distinct permutations)
+    const int64_t h = n / 2;
+    const int64_t nk = (D == 2 ? (h + 1) * (h + 2) / 2 : (h + 1) * (h + 2) * (h + 3) / 6) - 1;
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    double *ds = nullptr;
+    if (hipMalloc(&ds, sizeof(double) * nk) != hipSuccess) {
+        (void)hipGetLastError();
+        return FSC_E_OOM;
+    }
+    hipError_t e = launch_linear(p, la, KSource{nullptr, nk, 2.0 * M_PI / n}, ds, st);
+    // modes and shells while the device works; the shell grows along c
+    std::vector<int64_t> mult(static_cast<size_t>(nk));
+    std::vector<int> bin(static_cast<size_t>(nk));
+    std::vector<double> S(static_cast<size_t>(nk));
+    auto signs = [&](int64_t v) { return (v == 0 || 2 * v == n) ? 1 : 2; };
+    size_t id = 0;
+    for (int64_t a = 0; a <= h; ++a) {
+        int64_t first = a;  // round(sqrt(a^2 + b^2)), which grows with b
+        for (int64_t b = 0; b <= a; ++b) {
+            const int64_t base = a * a + b * b;
+            while (base > first * first + first) ++first;
+            int64_t shell = first;
+            for (int64_t c = 0; c <= (D == 3 ? b : 0); ++c) {
+                if (a == 0) continue;
+                while (base + c * c > shell * shell + shell) ++shell;
+                const int perms = D == 2 ? (a == b ? 1 : 2) : (a == b && b == c ? 1 : (a == b || b == c ? 3 : 6));
+                mult[id] = perms * signs(a) * signs(b) * (D == 3 ? signs(c) : 1);
+                bin[id++] = int(shell);
+            }
+        }
+    }
+    if (e == hipSuccess) e = hipMemcpyAsync(S.data(), ds, sizeof(double) * nk, hipMemcpyDeviceToHost, st);
+    const hipError_t es = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = es;
+    (void)hipFree(ds);
+    if (e != hipSuccess) return FSC_E_HIP;
     std::vector<double> sum(size_t(nbins), 0.0);
     std::vector<int64_t> cnt(size_t(nbins), 0);
-    for (int64_t i = 0; i < nk; ++i) {
+    for (size_t i = 0; i < size_t(nk); ++i) {
         if (bin[i] >= nbins) continue;
-        sum[bin[i]] += double(mult[i]) * S[i];
-        cnt[bin[i]] += mult[i];
+        sum[size_t(bin[i])] += double(mult[i]) * S[i];
+        cnt[size_t(bin[i])] += mult[i];
     }
     for (int b = 0; b < nbins; ++b) {
         host_shell_mean[b] = cnt[b] ? sum[b] / double(cnt[b]) : 0.0;

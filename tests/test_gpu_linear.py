@@ -91,3 +91,39 @@ def test_measured_3d_radial_structure_factor_matches_the_linear_theory():
     print("relative deviation per shell", np.round(rel, 4))
     assert np.max(np.abs(rel)) < 0.05
     assert abs(np.mean(rel)) < 0.01
+
+
+@pytest.mark.parametrize("D,stencil", [(2, 4), (2, 8), (3, 4)])
+@pytest.mark.parametrize("nk", [1, 63, 64, 65, 130])
+def test_unit_rates_equal_the_general_form(D, stencil, nk):
+    # rates of exactly 1 take the conserved-moment sum, the next double below the
+    # general one; both carry about 1e-16 / (1 - |eigenvalue|), 1e-11 at |k| = 0.01
+    rng = np.random.default_rng(nk)
+    kv = rng.uniform(-math.pi, math.pi, size=(nk, D))
+    kv[0] = 0.0
+    kv[0, -1] = math.pi  # a unit-modulus eigenvalue that the noise does not excite
+    kv[nk // 2] = 0.01
+    below = float(np.nextafter(1.0, 0.0))
+    for T_hat, n0 in ((0.9, 0.5), (0.8, 2.2), (0.8, 1.0)):  # the last one unstable at small k
+        got = fsc.linear_sk(_p(D, stencil, T_hat, n0, 1e-4), kv)
+        ref = fsc.linear_sk(_p(D, stencil, T_hat, n0, 1e-4, (below,) * 3), kv)
+        assert np.array_equal(np.isfinite(got), np.isfinite(ref))
+        ok = np.isfinite(ref)
+        assert np.allclose(got[ok], ref[ok], rtol=1e-9, atol=0), np.max(np.abs(got[ok] / ref[ok] - 1))
+
+
+@pytest.mark.parametrize("lam", [(1, 1, 1), (0.8, 1.3, 1.7)])
+@pytest.mark.parametrize("D,n", [(2, 2), (2, 3), (2, 65), (3, 2), (3, 5), (3, 14)])
+def test_device_wave_vectors_of_the_radial_shells(D, n, lam):
+    p = _p(D, 4, 0.85, 0.55, 1e-4, lam, n=n)
+    m = np.arange(n)
+    m = np.where(m > n // 2, m - n, m)
+    modes = np.stack([g.ravel() for g in np.meshgrid(*([m] * D), indexing="ij")], axis=1)
+    modes = modes[np.any(modes != 0, axis=1)]
+    nb = O.radial_bin(D * (n // 2) ** 2) + 1
+    mean, cnt = fsc.linear_sk_radial(p, nb)
+    b = O.radial_bins_of((modes ** 2).sum(axis=1))
+    S = fsc.linear_sk(p, 2 * np.pi * modes / n)
+    assert np.array_equal(cnt, np.bincount(b, minlength=nb)[:nb])
+    ref = np.bincount(b, weights=S, minlength=nb)[:nb] / np.maximum(cnt, 1)
+    assert np.allclose(mean, ref, rtol=1e-11, atol=0)
