@@ -122,7 +122,8 @@ struct fsc_ens {
     MeasPlan mplan;
     MeasRep *d_meas = nullptr;
     std::map<int, void *> tabs;  // transform tables by line length
-    void *pin = nullptr;         // READ_PIN bytes of pinned host memory for small results
+    double *pin = nullptr;       // READ_PIN bytes of pinned host memory for small results
+    uint32_t *pin_flag = nullptr, pin_seq = 0;  // the last one announced there
     double *work = nullptr;      // up to READ_WORK bytes on the device for large ones
     size_t work_bytes = 0;
     int *d_mpre = nullptr;
@@ -274,35 +275,65 @@ int init_rep(Rep &r, const fsc_params &p, void *ext_a, void *ext_b, fsc_ens *e) 
     return FSC_OK;
 }
 
-// Results on their way to the host.  Small ones are written by the kernel into,
-// or copied to, pinned memory (a copy to pageable memory takes 20 us, to pinned
-// memory 11, a kernel's own stores none); large ones go through a device buffer
-// in pieces.  Both are made at first use and live as long as the ensemble.
-constexpr size_t READ_PIN = size_t(512) << 10, READ_WORK = size_t(64) << 20;
+// Results on their way to the host.  Small ones are written by a kernel into
+// pinned memory and announced there (see Mail), or copied to it; large ones go
+// through a device buffer in pieces.  Both are made at first use and live as
+// long as the ensemble.  The first PIN_HEAD bytes of the pinned buffer hold the
+// announcing word.
+constexpr size_t READ_PIN = size_t(512) << 10, READ_WORK = size_t(64) << 20, READ_MAIL = size_t(8) << 10;
+constexpr size_t PIN_HEAD = 64;
 
 int ensure_pin(fsc_ens *e) {
     if (e->pin) return FSC_OK;
-    if (hipHostMalloc(&e->pin, READ_PIN, hipHostMallocDefault) != hipSuccess) {
+    void *p = nullptr;
+    if (hipHostMalloc(&p, PIN_HEAD + READ_PIN, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
-        e->pin = nullptr;
         return fail(e, FSC_E_OOM, "pinned buffer allocation failed");
     }
+    std::memset(p, 0, PIN_HEAD);
+    e->pin_flag = static_cast<uint32_t *>(p);
+    e->pin = reinterpret_cast<double *>(static_cast<char *>(p) + PIN_HEAD);
     return FSC_OK;
 }
 
-// `n` bytes from the device to the caller's memory, complete on return
-int read_back(fsc_ens *e, void *dst, const void *src, size_t n) {
-    if (n > READ_PIN) {
+// Waits for what launch(mail) sends: polls for about a millisecond, then waits
+// for the stream (long runs, and whatever keeps the kernel from running).
+constexpr int MAIL_POLLS = 20000;
+
+template <class Launch>
+int wait_mail(fsc_ens *e, Launch launch) {
+    int rc = ensure_pin(e);
+    if (rc) return rc;
+    const uint32_t seq = ++e->pin_seq;
+    HIPCHK(e, launch(Mail{e->pin, e->pin_flag, seq}));
+    auto sent = [&] { return __atomic_load_n(e->pin_flag, __ATOMIC_ACQUIRE) == seq; };
+    for (int k = 0; k < MAIL_POLLS; ++k) {
+        if (sent()) return FSC_OK;
+        __builtin_ia32_pause();
+    }
+    HIPCHK(e, hipStreamSynchronize(e->stream));
+    return sent() ? FSC_OK : fail(e, FSC_E_HIP, "a read-out kernel ended without its result");
+}
+
+// `n` doubles from the device to the caller's memory, complete on return
+int read_back(fsc_ens *e, double *dst, const double *src, size_t n) {
+    const size_t bytes = sizeof(double) * n;
+    if (bytes > READ_PIN) {
         StreamDrain drain{e->stream};
-        HIPCHK(e, hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, e->stream));
+        HIPCHK(e, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, e->stream));
         HIPCHK(e, hipStreamSynchronize(e->stream));
         return FSC_OK;
     }
     int rc = ensure_pin(e);
     if (rc) return rc;
-    HIPCHK(e, hipMemcpyAsync(e->pin, src, n, hipMemcpyDeviceToHost, e->stream));
-    HIPCHK(e, hipStreamSynchronize(e->stream));
-    std::memcpy(dst, e->pin, n);
+    if (bytes <= READ_MAIL) {
+        rc = wait_mail(e, [&](const Mail &m) { return launch_mail(src, int(n), m, e->stream); });
+        if (rc) return rc;
+    } else {
+        HIPCHK(e, hipMemcpyAsync(e->pin, src, bytes, hipMemcpyDeviceToHost, e->stream));
+        HIPCHK(e, hipStreamSynchronize(e->stream));
+    }
+    std::memcpy(dst, e->pin, bytes);
     return FSC_OK;
 }
 
@@ -314,7 +345,7 @@ int read_formed(fsc_ens *e, double *dst, int64_t count, int64_t unit, Launch lau
     if (bytes <= READ_PIN) {
         int rc = ensure_pin(e);
         if (rc) return rc;
-        HIPCHK(e, launch(int64_t(0), count, static_cast<double *>(e->pin)));
+        HIPCHK(e, launch(int64_t(0), count, e->pin));
         HIPCHK(e, hipStreamSynchronize(e->stream));
         std::memcpy(dst, e->pin, bytes);
         return FSC_OK;
@@ -497,7 +528,7 @@ int modes_read(fsc_ens *e, Rep &r, double *out, int max_rows, int *nrows) {
     const int m = std::min(n, max_rows);
     if (nrows) *nrows = n;
     if (m <= 0 || !out) return FSC_OK;
-    return read_back(e, out, r.d_modes, sizeof(double) * 2 * size_t(m) * size_t(r.p.D) * size_t(r.modes_nm));
+    return read_back(e, out, r.d_modes, 2 * size_t(m) * size_t(r.p.D) * size_t(r.modes_nm));
 }
 
 // The stream is idle.
@@ -529,7 +560,7 @@ int series_read(fsc_ens *e, Rep &r, double *out, int max_rows, int *nrows, int *
     if (nrows) *nrows = n;
     if (!out || max_rows <= 0 || n == 0) return FSC_OK;
     const int m = std::min(n, max_rows);
-    int rc = read_back(e, out, r.d_series, sizeof(double) * size_t(m) * size_t(len));
+    int rc = read_back(e, out, r.d_series, size_t(m) * size_t(len));
     if (rc) return rc;
     for (int row = 0; row < m; ++row)
         for (int b = 0; b < r.n_rad; ++b)
@@ -1185,7 +1216,7 @@ void ens_free(fsc_ens *e) {
             if (p) (void)hipFree(p);
     }
     for (auto &kv : e->tabs) (void)hipFree(kv.second);
-    if (e->pin) (void)hipHostFree(e->pin);
+    if (e->pin_flag) (void)hipHostFree(e->pin_flag);
     if (e->work) (void)hipFree(e->work);
     if (e->d_blocks) (void)hipFree(e->d_blocks);
     if (e->d_desc) (void)hipFree(e->d_desc);
@@ -1239,11 +1270,11 @@ int ens_get_pop(fsc_ens *e, int ri, double *host_f) {
 
 int ens_stats(fsc_ens *e, int ri, double *out8) {
     Rep &r = e->reps[ri];
-    int rc = ensure_pin(e);
+    int rc = wait_mail(e, [&](const Mail &m) {
+        return launch_stats(r.geom(), r.p.precision, r.buf[e->cur], r.p.rho0, r.d_partials, r.d_stats_done, m,
+                            e->stream);
+    });
     if (rc) return rc;
-    HIPCHK(e, launch_stats(r.geom(), r.p.precision, r.buf[e->cur], r.p.rho0, r.d_partials, r.d_stats_done,
-                           static_cast<double *>(e->pin), e->stream));
-    HIPCHK(e, hipStreamSynchronize(e->stream));
     std::memcpy(out8, e->pin, sizeof(double) * 8);
     if (out8[6] > 0.0) return fail(e, FSC_E_DIVERGED, "non-finite or non-positive density");
     return FSC_OK;
@@ -1266,7 +1297,7 @@ int ens_read_sk(fsc_ens *e, int ri, int kind, double *sum, double *sumsq, int64_
     const size_t na = size_t(r.p.D) * r.n_axis;
     // sums, then sums of squares
     std::vector<double> h(2 * size_t(nb));
-    int rc = read_back(e, h.data(), kind == FSC_SK_AXIS ? r.d_sk : r.d_sk + 2 * na, sizeof(double) * h.size());
+    int rc = read_back(e, h.data(), kind == FSC_SK_AXIS ? r.d_sk : r.d_sk + 2 * na, h.size());
     if (rc) return rc;
     const auto &modes = kind == FSC_SK_AXIS ? r.axis_modes : r.rad_modes;
     for (int k = 0; k < nb; ++k) {

@@ -94,12 +94,20 @@ hipError_t launch_density(const Geometry &g, int precision, const void *buf, dou
 // [i][z][y][x].
 hipError_t launch_streamed(const Geometry &g, int precision, const void *buf, const double *shift, int64_t e0,
                            int64_t n, double *out, hipStream_t s);
-// FP64 state reductions into out[8] (see fsc_stats; device memory or pinned host
-// memory); `partials` holds stats_partials_len() doubles, *done is 0 between
-// calls.
+// A result in pinned host memory and the word there that announces it: the
+// kernel stores `seq` to *flag, visible to the host, after the result.
+struct Mail {
+    double *out;
+    uint32_t *flag;
+    uint32_t seq;
+};
+// FP64 state reductions into mail.out[8] (see fsc_stats); `partials` holds
+// stats_partials_len() doubles, *done is 0 between calls.
 size_t stats_partials_len();
 hipError_t launch_stats(const Geometry &g, int precision, const void *buf, double rho0,
-                        double *partials, int *done, double *out, hipStream_t s);
+                        double *partials, int *done, const Mail &mail, hipStream_t s);
+// n doubles of device memory into mail.out.
+hipError_t launch_mail(const double *src, int n, const Mail &mail, hipStream_t s);
 
 // Transform of one axis: lines of n values over m points, m = 2^logm (n itself,
 // or at least 2n - 1 for the chirp form), or m = n and logm = -1 (direct sum).
