@@ -552,12 +552,18 @@ __device__ __forceinline__ void sk_bin(const MeasRep &m, const cplx<real> *a, in
         if (srow_bins) unsafeAtomicAdd(&srow_bins[b], s);
     };
     if (t.n_rad > 0) {
-        int lo2 = 0x7fffffff, hi2 = 0;
-        for (int l = 0; l < lines; ++l) {
-            int kx, ky;
-            other(l, kx, ky);
-            lo2 = min(lo2, kx * kx + ky * ky);
-            hi2 = max(hi2, kx * kx + ky * ky);
+        // the other components' |k|^2 of the lines: kx grows with l, |ky| grows up
+        // to ny / 2 and falls from there
+        const int i1 = i0 + lines - 1;
+        int lo2, hi2;
+        if (d3) {
+            const int p = abs(signed_mode(i0, g.ny)), q = abs(signed_mode(i1, g.ny)), top = g.ny / 2;
+            const int lo = min(p, q), hi = i0 <= top && top <= i1 ? top : max(p, q);
+            lo2 = o * o + lo * lo;
+            hi2 = o * o + hi * hi;
+        } else {
+            lo2 = i0 * i0;
+            hi2 = i1 * i1;
         }
         const int blo = shell_of(lo2), W = shell_of(hi2 + half * half) - blo + 1;
         if (wnd) {
@@ -604,14 +610,17 @@ __device__ __forceinline__ void sk_bin(const MeasRep &m, const cplx<real> *a, in
             unsafeAtomicAdd(&t.axis_sum[d * t.n_axis + abs(k)], w * p);
             unsafeAtomicAdd(&t.axis_sq[d * t.n_axis + abs(k)], w * p * p);
         };
-        for (int l = threadIdx.x; l < lines; l += nt) {  // modes with no last component
+        // (from the other end of the block: beside the shells' flush, not after it)
+        const int back = nt - 1 - int(threadIdx.x);
+        for (int l = back; l < lines; l += nt) {  // modes with no last component
             int kx, ky;
             other(l, kx, ky);
             if (ky == 0 && kx != 0) add_axis(0, kx, weight(kx), power(l, 0));
             if (kx == 0 && ky != 0) add_axis(1, ky, 1.0, power(l, 0));
         }
         if ((!d3 || o == 0) && i0 == 0)  // line 0 has no other component
-            for (int i = threadIdx.x + 1; i < n; i += nt) add_axis(g.D - 1, signed_mode(i, n), 1.0, power(0, i));
+            for (int i = ((back + nt / 2) & (nt - 1)) + 1; i < n; i += nt)
+                add_axis(g.D - 1, signed_mode(i, n), 1.0, power(0, i));
     }
     if (t.mom) {
         const double ux = 2.0 * M_PI / g.nx, uy = 2.0 * M_PI / g.ny, uz = 2.0 * M_PI / n;
