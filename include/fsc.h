@@ -353,11 +353,11 @@ int fsc_sur_rollout(fsc_sur *s, const float *dev_prev, float *dev_traj, int batc
 
 /* Inference (forward passes and rollouts) can run pairs of consecutive
  * 32 -> 32 layers as one launch that keeps the first layer's activations in
- * LDS (needs H % 4 == 0 and W % 64 == 0, else one launch per layer).  The
- * results are bit for bit those of one launch per layer.  mode 0: never;
- * 1: always; 2 (the default): when batch * H * W <= 8 * 128 * 128, where it
- * measured faster (its LDS halves the blocks per CU, which costs more than
- * it saves on larger batches).  Other modes: FSC_E_INVAL.  Changing the mode,
+ * LDS (wider than 128 pixels: needs H % 4 == 0 and W % 64 == 0, else one
+ * launch per layer).  The results are bit for bit those of one launch per
+ * layer.  mode 0: never; 1: always; 2 (the default): where it measured faster,
+ * that is up to 128 pixels wide, and wider ones when batch * H * W <=
+ * 8 * 128 * 128.  Other modes: FSC_E_INVAL.  Changing the mode,
  * or the normalisation (fsc_sur_set_norm), drops the captured rollout
  * graphs (waiting for a replay still running). */
 int fsc_sur_set_fusion(fsc_sur *s, int mode);

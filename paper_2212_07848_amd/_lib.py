@@ -580,7 +580,7 @@ class Surrogate:
 
     def set_fusion(self, mode: int):
         """Pairs of 32 -> 32 layers in one launch at inference: 0 never, 1
-        always, 2 small batches (the default); bit-identical either way (see
+        always, 2 where it is faster (the default); bit-identical either way (see
         fsc_sur_set_fusion)."""
         self._c(lib().fsc_sur_set_fusion(self._h, int(mode)))
 

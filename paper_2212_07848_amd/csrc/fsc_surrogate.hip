@@ -26,6 +26,7 @@
 #include <map>
 #include <string>
 #include <tuple>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -37,6 +38,7 @@ namespace fsc {
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int SC = 32;          // hidden channels
 constexpr int IMG_PARTS = 256;  // segments per image of the per-image FP64 sums
@@ -438,6 +440,176 @@ __global__ void __launch_bounds__(256) k_mid2_lds(const bf16 *__restrict__ ain,
 }
 
 // ---------------------------------------------------------------------------
+// The same pair for rows of at most 128 pixels, marching down the image.  A
+// workgroup takes R rows over the whole width, so that columns wrap inside it.
+// Four waves per layer hold that layer's weights in registers; a step takes one
+// input row, and the row that this completes goes to the other layer's waves
+// through LDS.  A layer's input row j adds to the output rows j, j - 1 and j - 2
+// (taps ky = 0, 1, 2), whose accumulators stay in registers: a row is read from
+// LDS once per kx instead of once per tap, and two rows of each layer are all that
+// is held.  The second layer is three steps behind the first, which computes the
+// two rows beyond the strip as well.  Bit for bit the unfused layers.
+//
+// R gives at most one workgroup per CU; two of them on a CU with half the rows
+// each are slower (9-layer passes over 16 images: 98.6 us, 114).  What bounds it
+// is the chain of a step (LDS reads, 18 MFMAs per tile, SiLU, barrier), about
+// 2800 cycles where a SIMD's MFMAs take 1150.  9-layer passes, us, unfused / as
+// tiles (k_mid2_lds) / marching: 1 image of 128^2 74 / 62 / 53, 4 88 / 74 / 65, 16
+// 130 / 132 / 99, 32 222 / 238 / 154.  (Three and four layers per launch spill; a
+// SiLU that runs a step late, beside the other layer's products, took 19.1 us per
+// pair against 17.2.)
+// LDS: [layer][2][W pixels][4 pieces of 8 channels], a pixel's piece g at slot
+// g ^ (pixel / 4 % 4): 16 lanes that read one piece of 16 pixels in a row then
+// meet every bank once.
+// ---------------------------------------------------------------------------
+constexpr int CH_W = 128;             // widest row
+constexpr int CH_WAVES = 4;           // waves per layer
+constexpr int CH_BLOCKS = 256;        // one workgroup per CU
+constexpr int CH_LOADERS = CH_WAVES * 64;
+
+// TPW: tiles of 16 pixels per wave; a row has at most 4 TPW of them.
+template <int TPW>
+__global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restrict__ ain,
+                                                            const bf16 *__restrict__ wA,
+                                                            const float *__restrict__ bA,
+                                                            const bf16 *__restrict__ wB,
+                                                            const float *__restrict__ bB, int R, int strips,
+                                                            int H, int W, bf16 *__restrict__ aout) {
+    constexpr int ROW = CH_WAVES * TPW * 16 * SC;
+    __shared__ __attribute__((aligned(16))) bf16 rows[2][2][ROW];
+#ifdef FSC_LDS_POISON
+    lds_poison(&rows[0][0][0], 4 * ROW);
+    __syncthreads();
+#endif
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, g = lane >> 4;
+    const int layer = wave / CH_WAVES, wl = wave % CH_WAVES;
+    const int n = blockIdx.x / strips, y0 = (blockIdx.x % strips) * R;
+    const int Rr = min(R, H - y0), tiles = W / 16;
+    const size_t img = size_t(n) * H;
+    auto slot = [](int px, int piece) { return px * SC + ((piece ^ ((px >> 2) & 3)) * 8); };
+
+    const bf16 *wpk = layer == 0 ? wA : wB;
+    const float *bias = layer == 0 ? bA : bB;
+    bf16x8 bop[9][2];
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+            bop[t][nt] = *reinterpret_cast<const bf16x8 *>(wpk + (t * SC + mid_row_channel(nt, r16)) * SC + g * 8);
+    const f32x4 bv[2] = {*reinterpret_cast<const f32x4 *>(bias + 8 * g),
+                         *reinterpret_cast<const f32x4 *>(bias + 8 * g + 4)};
+    __builtin_amdgcn_s_waitcnt(0);  // the weights: here, not in the loops, where it would wait for more
+    // this lane's pixels and the LDS offsets of their columns x - 1, x, x + 1
+    // (tiles past a narrower row's end repeat its last one: the same values again)
+    int at[TPW][3], pix[TPW];
+    f32x4 p0[TPW][2], p1[TPW][2];
+#pragma unroll
+    for (int q = 0; q < TPW; ++q) {
+        pix[q] = min(wl + CH_WAVES * q, tiles - 1) * 16 + r16;
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) at[q][kx] = slot(wrapi(pix[q] + kx - 1, W), g);
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) p0[q][nt] = p1[q][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    const int nin = Rr + 4;  // rows that the first layer reads
+    // (past the last row, and past the row's end: loaded again)
+    auto fetch = [&](int row, u32x4 (&v)[TPW]) {
+        const size_t base = (img + size_t(wrap_any(y0 - 2 + min(row, nin - 1), H))) * W;
+#pragma unroll
+        for (int k = 0; k < TPW; ++k) {
+            const int e = min(tid + k * CH_LOADERS, W * 4 - 1);
+            v[k] = *reinterpret_cast<const u32x4 *>(ain + (base + (e >> 2)) * SC + (e & 3) * 8);
+        }
+    };
+    auto put = [&](int row, const u32x4 (&v)[TPW]) {
+#pragma unroll
+        for (int k = 0; k < TPW; ++k) {
+            const int e = min(tid + k * CH_LOADERS, W * 4 - 1);
+            *reinterpret_cast<u32x4 *>(&rows[0][row & 1][slot(e >> 2, e & 3)]) = v[k];
+        }
+    };
+    auto sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
+    auto step = [&](int s, auto first) {
+        const int j = first ? s : s - 3;  // this layer's input row
+        if (j < 0 || j >= (first ? nin : nin - 2)) return;
+        const bf16 *src = rows[first ? 0 : 1][(first ? s : s - 1) & 1];
+        bf16x8 x[TPW][3];
+#pragma unroll
+        for (int q = 0; q < TPW; ++q)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) x[q][kx] = *reinterpret_cast<const bf16x8 *>(src + at[q][kx]);
+        f32x4 done[TPW][2];
+#pragma unroll
+        for (int q = 0; q < TPW; ++q) {
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                done[q][nt] = p1[q][nt];
+                p1[q][nt] = p0[q][nt];
+                p0[q][nt] = bv[nt];
+            }
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt) {
+                    done[q][nt] = mfma16(bop[6 + kx][nt], x[q][kx], done[q][nt]);
+                    p1[q][nt] = mfma16(bop[3 + kx][nt], x[q][kx], p1[q][nt]);
+                    p0[q][nt] = mfma16(bop[kx][nt], x[q][kx], p0[q][nt]);
+                }
+        }
+        if (j < 2) return;  // no output row is complete
+#pragma unroll
+        for (int q = 0; q < TPW; ++q) {
+            if constexpr (!first) {
+                mid_epilogue<false, false>(done[q], (img + size_t(y0 + j - 2)) * W + pix[q], g, nullptr, aout, nullptr);
+            } else {
+                bf16x8 o;
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[4 * nt + r] = bf16(silu(done[q][nt][r]));
+                *reinterpret_cast<bf16x8 *>(&rows[1][s & 1][slot(pix[q], g)]) = o;
+            }
+        }
+    };
+    // One loop per kind of wave: only the first layer's waves load and only the
+    // second one's store, so that none waits for the other kind's memory operations.
+    const int steps = Rr + 5;
+    auto march = [&](auto first) {
+        // row q is asked for two steps before it is put down, and read one step later
+        u32x4 va[TPW], vb[TPW];
+        if constexpr (first) {
+            fetch(0, va);
+            fetch(1, vb);
+            put(0, va);
+            fetch(2, va);
+        }
+        sync();
+        for (int s = 0; s < steps; s += 2) {
+            step(s, first);
+            if constexpr (first) {
+                put(s + 1, vb);
+                fetch(s + 3, vb);
+            }
+            sync();
+            step(s + 1, first);  // (past the last step: nothing to do)
+            if constexpr (first) {
+                put(s + 2, va);
+                fetch(s + 4, va);
+            }
+            sync();
+        }
+    };
+    if (layer == 0) march(std::true_type{});
+    else march(std::false_type{});
+}
+
+// ---------------------------------------------------------------------------
 // Last layer (C -> 1) forward on the matrix cores.  Its FP32 weights enter as
 // three BF16 parts each, w = hi + mid + lo (k_pack_last; exact for normal FP32
 // values), in rows 0..2 of the A operand (rows 3..15 zero); B is 32 channels
@@ -676,8 +848,6 @@ __global__ void __launch_bounds__(256) k_last_bwd(const float *__restrict__ g,
 // result; k_wgrad_sum adds the partials in FP64 in a fixed order, so the
 // gradient does not depend on the order in which blocks finish.
 // ---------------------------------------------------------------------------
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int WG_TR = 16, WG_TW = 32;  // pixel tile (W is a multiple of 32)
 constexpr int WG_AW = WG_TW + 2;       // activations with their one-pixel halo
 constexpr int WG_MAX_BLOCKS = 256;     // one per CU
@@ -1259,7 +1429,7 @@ struct fsc_sur {
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
     std::map<std::tuple<const float *, float *, int, int>, hipGraphExec_t> rollouts;
     std::deque<std::tuple<const float *, float *, int, int>> rollout_order;  // oldest first
-    int fuse = 2;  // pairs of C -> C layers as one k_mid2_lds: 0 never, 1 always, 2 small batches
+    int fuse = 2;  // pairs of C -> C layers in one launch: 0 never, 1 always, 2 where it is faster
     std::string err;
 };
 
@@ -1297,11 +1467,11 @@ void sur_free(fsc_sur *s) {
     delete s;
 }
 
-// Fused pairs of C -> C layers (k_mid2_lds) hold 60 KB of LDS per block, so
-// 2 blocks per CU instead of 4: measured on 9-layer passes over 128^2 images,
-// they win up to 8 images (62.5 against 73.3 us for one, 87.0 against 100.3
-// for eight) and lose from 16 (135.9 against 128.3).  Mode 2 fuses up to
-// FUSE_MAX_PIXELS pixels per batch.
+// Fused pairs of C -> C layers in images wider than 128 (narrower ones march, see
+// k_chain): k_mid2_lds holds 60 KB of LDS per block, so 2 blocks per CU instead of
+// 4.  Measured on 9-layer passes over 128^2 images, it wins up to 8 images (62.5
+// against 73.3 us for one, 87.0 against 100.3 for eight) and loses from 16 (135.9
+// against 128.3).  Mode 2 fuses up to FUSE_MAX_PIXELS pixels per batch.
 constexpr int64_t FUSE_MAX_PIXELS = 8 * 128 * 128;
 bool fuse_pairs(const fsc_sur *s, int B) {
     return s->fuse == 1 || (s->fuse == 2 && int64_t(B) * s->H * s->W <= FUSE_MAX_PIXELS);
@@ -1365,6 +1535,21 @@ int sur_forward_core(fsc_sur *s, const float *prev, const float *cur, int B, boo
         const size_t off = size_t(l - 1) * 9 * SC * SC;
         const bf16 *ain = s->a[l - 1], *wl = s->wf + off;
         const float *bl = s->params + s->boff[l];
+        if (!train && s->fuse != 0 && s->W <= CH_W && l + 1 <= nmid(s)) {
+            // layers l and l + 1 in one launch; a[l] is not written
+            const int most = std::min(s->H, std::max(1, CH_BLOCKS / B));
+            const int R = (s->H + most - 1) / most, strips = (s->H + R - 1) / R;
+            auto chain = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, dim3(unsigned(B * strips)), dim3(2 * CH_WAVES * 64), 0, s->stream, ain,
+                                   wl, bl, wl + size_t(9) * SC * SC, s->params + s->boff[l + 1], R, strips, s->H,
+                                   s->W, s->a[l + 1]);
+            };
+            if (s->W <= CH_W / 2) chain(k_chain<1>);
+            else chain(k_chain<2>);
+            SCHK(s, hipGetLastError());
+            ++l;
+            continue;
+        }
         if (!train && fuse_pairs(s, B) && l + 1 <= nmid(s) && s->H % F2R == 0 && s->W % F2W == 0) {
             // layers l and l + 1 in one launch; a[l] is not written
             const dim3 g(unsigned(B * (s->H / F2R) * (s->W / F2W)));

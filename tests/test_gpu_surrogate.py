@@ -314,3 +314,27 @@ def test_stack_scales_match_fp64_moments():
     dx = (snaps[t_first + 1:].astype(np.float64) - snaps[t_first:-1].astype(np.float64))
     assert a == pytest.approx(x.std(ddof=1), rel=1e-12)
     assert b == pytest.approx(dx.std(ddof=1), rel=1e-12)
+
+
+@pytest.mark.parametrize("layers", [4, 5])
+@pytest.mark.parametrize("H,W,B", [(1, 32, 1), (2, 64, 3), (5, 128, 2), (90, 96, 3), (33, 160, 2), (128, 128, 1),
+                                   (128, 128, 12), (7, 32, 300)])
+def test_marching_pairs_equal_single_layers(H, W, B, layers):
+    # strips of one row to the whole image, partial last strips, rows of one tile
+    # of 16 pixels per wave and of two, more images than CUs, and a width beyond
+    # the marching form's: the same MFMA sequence per activation, so the same bits
+    print(f"marching pairs {H}x{W} batch {B} layers {layers}", flush=True)
+    sur = fsc.Surrogate(layers, H, W, B, seed=3, in_ch=1)
+    sur.set_norm(1.0, 0.7, 0.15)
+    g = torch.Generator().manual_seed(H + W)
+    x = (1.0 + 0.5 * torch.randn(B, H, W, generator=g)).cuda()
+    got = []
+    for mode in (0, 1, 2):
+        sur.set_fusion(mode)
+        out = torch.zeros_like(x)
+        sur.forward(None, x, out, B)
+        torch.cuda.synchronize()
+        got.append(out.cpu())
+    sur.close()
+    assert torch.isfinite(got[0]).all()
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
