@@ -122,8 +122,7 @@ struct fsc_ens {
     MeasPlan mplan;
     MeasRep *d_meas = nullptr;
     std::map<int, void *> tabs;  // transform tables by line length
-    double *pin = nullptr;       // READ_PIN bytes of pinned host memory for small results
-    uint32_t *pin_flag = nullptr, pin_seq = 0;  // the last one announced there
+    Mailbox box;                 // READ_PIN bytes of pinned host memory for small results
     double *work = nullptr;      // up to READ_WORK bytes on the device for large ones
     size_t work_bytes = 0;
     int *d_mpre = nullptr;
@@ -278,41 +277,22 @@ int init_rep(Rep &r, const fsc_params &p, void *ext_a, void *ext_b, fsc_ens *e) 
 // Results on their way to the host.  Small ones are written by a kernel into
 // pinned memory and announced there (see Mail), or copied to it; large ones go
 // through a device buffer in pieces.  Both are made at first use and live as
-// long as the ensemble.  The first PIN_HEAD bytes of the pinned buffer hold the
-// announcing word.
+// long as the ensemble.
 constexpr size_t READ_PIN = size_t(512) << 10, READ_WORK = size_t(64) << 20, READ_MAIL = size_t(8) << 10;
-constexpr size_t PIN_HEAD = 64;
 
 int ensure_pin(fsc_ens *e) {
-    if (e->pin) return FSC_OK;
-    void *p = nullptr;
-    if (hipHostMalloc(&p, PIN_HEAD + READ_PIN, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(e, FSC_E_OOM, "pinned buffer allocation failed");
-    }
-    std::memset(p, 0, PIN_HEAD);
-    e->pin_flag = static_cast<uint32_t *>(p);
-    e->pin = reinterpret_cast<double *>(static_cast<char *>(p) + PIN_HEAD);
+    if (e->box.make(READ_PIN) != hipSuccess) return fail(e, FSC_E_OOM, "pinned buffer allocation failed");
     return FSC_OK;
 }
 
-// Waits for what launch(mail) sends: polls for about a millisecond, then waits
-// for the stream (long runs, and whatever keeps the kernel from running).
-constexpr int MAIL_POLLS = 20000;
-
+// Waits for what launch(mail) sends.
 template <class Launch>
 int wait_mail(fsc_ens *e, Launch launch) {
     int rc = ensure_pin(e);
     if (rc) return rc;
-    const uint32_t seq = ++e->pin_seq;
-    HIPCHK(e, launch(Mail{e->pin, e->pin_flag, seq}));
-    auto sent = [&] { return __atomic_load_n(e->pin_flag, __ATOMIC_ACQUIRE) == seq; };
-    for (int k = 0; k < MAIL_POLLS; ++k) {
-        if (sent()) return FSC_OK;
-        __builtin_ia32_pause();
-    }
-    HIPCHK(e, hipStreamSynchronize(e->stream));
-    return sent() ? FSC_OK : fail(e, FSC_E_HIP, "a read-out kernel ended without its result");
+    HIPCHK(e, launch(e->box.next()));
+    HIPCHK(e, e->box.wait(e->stream));
+    return FSC_OK;
 }
 
 // `n` doubles from the device to the caller's memory, complete on return
@@ -330,10 +310,10 @@ int read_back(fsc_ens *e, double *dst, const double *src, size_t n) {
         rc = wait_mail(e, [&](const Mail &m) { return launch_mail(src, int(n), m, e->stream); });
         if (rc) return rc;
     } else {
-        HIPCHK(e, hipMemcpyAsync(e->pin, src, bytes, hipMemcpyDeviceToHost, e->stream));
+        HIPCHK(e, hipMemcpyAsync(e->box.data(), src, bytes, hipMemcpyDeviceToHost, e->stream));
         HIPCHK(e, hipStreamSynchronize(e->stream));
     }
-    std::memcpy(dst, e->pin, bytes);
+    std::memcpy(dst, e->box.data(), bytes);
     return FSC_OK;
 }
 
@@ -345,9 +325,9 @@ int read_formed(fsc_ens *e, double *dst, int64_t count, int64_t unit, Launch lau
     if (bytes <= READ_PIN) {
         int rc = ensure_pin(e);
         if (rc) return rc;
-        HIPCHK(e, launch(int64_t(0), count, e->pin));
+        HIPCHK(e, launch(int64_t(0), count, e->box.data()));
         HIPCHK(e, hipStreamSynchronize(e->stream));
-        std::memcpy(dst, e->pin, bytes);
+        std::memcpy(dst, e->box.data(), bytes);
         return FSC_OK;
     }
     const int64_t piece = std::min(count, std::max(unit, int64_t(READ_WORK / sizeof(double)) / unit * unit));
@@ -1216,7 +1196,6 @@ void ens_free(fsc_ens *e) {
             if (p) (void)hipFree(p);
     }
     for (auto &kv : e->tabs) (void)hipFree(kv.second);
-    if (e->pin_flag) (void)hipHostFree(e->pin_flag);
     if (e->work) (void)hipFree(e->work);
     if (e->d_blocks) (void)hipFree(e->d_blocks);
     if (e->d_desc) (void)hipFree(e->d_desc);
@@ -1275,7 +1254,7 @@ int ens_stats(fsc_ens *e, int ri, double *out8) {
                             e->stream);
     });
     if (rc) return rc;
-    std::memcpy(out8, e->pin, sizeof(double) * 8);
+    std::memcpy(out8, e->box.data(), sizeof(double) * 8);
     if (out8[6] > 0.0) return fail(e, FSC_E_DIVERGED, "non-finite or non-positive density");
     return FSC_OK;
 }
@@ -1792,14 +1771,18 @@ size_t field_work_bytes(int L, int nrad, int chunk) {
     return field_tab_bytes(L) + size_t(chunk) * (field_spec_bytes(L) + sizeof(double) * field_acc_len(nrad));
 }
 
+// `box`: pinned memory of FIELD_MAIL bytes for sums that fit it, or null
+constexpr size_t FIELD_MAIL = size_t(16) << 10;
+
 hipError_t field_sk_batches(const float *dev_fields, int batch, int L, hipStream_t st, void *work, int chunk,
-                            int nrad, double *host_shell_mean, double *host_L) {
+                            int nrad, Mailbox *box, double *host_shell_mean, double *host_L) {
     std::vector<int64_t> modes(size_t(nrad), 0);
     count_shells(2, L, nrad, modes.data());
     const size_t N = size_t(L) * L, len = field_acc_len(nrad);
     unsigned char *tab = static_cast<unsigned char *>(work);
     unsigned char *spec = tab + field_tab_bytes(L);
     std::vector<double> h(len * size_t(std::min(batch, chunk)));
+    if (sizeof(double) * h.size() > FIELD_MAIL) box = nullptr;
     hipError_t ec = hipSuccess;
     for (int b = 0; b < batch && ec == hipSuccess; b += chunk) {
         const int nb = std::min(chunk, batch - b);
@@ -1807,12 +1790,13 @@ hipError_t field_sk_batches(const float *dev_fields, int batch, int L, hipStream
         ec = sk_table(0, sk_axis(L, 0), tab, acc, int64_t(2 * len) * nb, st);
         if (ec == hipSuccess) ec = launch_field_sk(dev_fields + size_t(b) * N, nb, L, nrad, spec, tab, acc, st);
         if (ec == hipSuccess)
-            ec = hipMemcpyAsync(h.data(), acc, sizeof(double) * len * nb, hipMemcpyDeviceToHost, st);
-        const hipError_t es = hipStreamSynchronize(st);
+            ec = box ? launch_mail(acc, int(len) * nb, box->next(), st)
+                     : hipMemcpyAsync(h.data(), acc, sizeof(double) * len * nb, hipMemcpyDeviceToHost, st);
+        const hipError_t es = box && ec == hipSuccess ? box->wait(st) : hipStreamSynchronize(st);
         if (ec == hipSuccess) ec = es;
         if (ec != hipSuccess) break;
         for (int f = 0; f < nb; ++f) {
-            const double *q = h.data() + len * size_t(f), *mom = q + nrad;
+            const double *q = (box ? box->data() : h.data()) + len * size_t(f), *mom = q + nrad;
             if (host_shell_mean)
                 for (int k = 0; k < nrad; ++k)
                     host_shell_mean[size_t(b + f) * nrad + k] = modes[size_t(k)] ? q[k] / double(modes[size_t(k)]) : 0.0;
@@ -1821,6 +1805,53 @@ hipError_t field_sk_batches(const float *dev_fields, int batch, int L, hipStream
     }
     return ec;
 }
+
+// What a thread's calls of fsc_field_sk keep between them: the pinned result and
+// up to FIELD_KEEP bytes of device work area on the device it last ran on (beyond
+// 256 KB hipMalloc and hipFree take 20 us, as much as the transforms of 16 fields
+// of 128^2).  Every call ends with its device work done, so the next one may use
+// another stream.  Given back when the thread ends.
+class FieldPool {
+  public:
+    ~FieldPool() { drop(); }
+    Mailbox *mailbox() { return box_.make(FIELD_MAIL) == hipSuccess ? &box_ : nullptr; }
+    int take(size_t bytes, void **out) {
+        int dev = -1;
+        if (hipGetDevice(&dev) != hipSuccess) return FSC_E_HIP;
+        if (bytes > FIELD_KEEP) return get(bytes, out);
+        if (dev != dev_ || bytes > bytes_) {
+            drop();
+            const int rc = get(bytes, &kept_);
+            if (rc) return rc;
+            dev_ = dev;
+            bytes_ = bytes;
+        }
+        *out = kept_;
+        return FSC_OK;
+    }
+    void done(void *p) {
+        if (p != kept_) (void)hipFree(p);
+    }
+
+  private:
+    static constexpr size_t FIELD_KEEP = size_t(8) << 20;
+    static int get(size_t bytes, void **out) {
+        if (hipMalloc(out, bytes) == hipSuccess) return FSC_OK;
+        (void)hipGetLastError();
+        *out = nullptr;
+        return FSC_E_OOM;
+    }
+    void drop() {
+        if (kept_) (void)hipFree(kept_);
+        kept_ = nullptr;
+        bytes_ = 0;
+        dev_ = -1;
+    }
+    Mailbox box_;
+    void *kept_ = nullptr;
+    size_t bytes_ = 0;
+    int dev_ = -1;
+};
 
 // ---- fixed-size scratch of the allocation-free field S(k) ----------------
 // 16 MiB and some: at least one field of FIELD_STATIC_MAX_SIDE^2 at a time (its
@@ -1872,13 +1903,13 @@ int fsc_field_sk(const float *dev_fields, int batch, int ny, int nx, void *strea
     const hipStream_t st = static_cast<hipStream_t>(stream);
     // the spectra of a chunk stay within 1 GiB
     const int chunk = int(std::min<int64_t>(batch, std::max<int64_t>(1, (int64_t(1) << 30) / int64_t(field_spec_bytes(nx)))));
+    static thread_local FieldPool pool;
     void *work = nullptr;
-    if (hipMalloc(&work, field_work_bytes(nx, nrad, chunk)) != hipSuccess) {
-        (void)hipGetLastError();
-        return FSC_E_OOM;
-    }
-    const hipError_t ec = field_sk_batches(dev_fields, batch, nx, st, work, chunk, nrad, host_shell_mean, host_L);
-    (void)hipFree(work);
+    rc = pool.take(field_work_bytes(nx, nrad, chunk), &work);
+    if (rc) return rc;
+    const hipError_t ec = field_sk_batches(dev_fields, batch, nx, st, work, chunk, nrad, pool.mailbox(), host_shell_mean,
+                                           host_L);
+    pool.done(work);
     return ec == hipSuccess ? FSC_OK : FSC_E_HIP;
 }
 
@@ -1896,7 +1927,7 @@ int fsc_field_sk_noalloc(const float *dev_fields, int batch, int ny, int nx, voi
     if (scratch_on(dev, &base) != hipSuccess) return FSC_E_HIP;
     int chunk = 1;
     while (chunk < batch && field_work_bytes(nx, nrad, chunk + 1) <= FS_BYTES) ++chunk;
-    ec = field_sk_batches(dev_fields, batch, nx, st, base, chunk, nrad, host_shell_mean, host_L);
+    ec = field_sk_batches(dev_fields, batch, nx, st, base, chunk, nrad, nullptr, host_shell_mean, host_L);
     return ec == hipSuccess ? FSC_OK : FSC_E_HIP;
 }
 

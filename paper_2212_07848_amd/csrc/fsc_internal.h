@@ -109,6 +109,50 @@ hipError_t launch_stats(const Geometry &g, int precision, const void *buf, doubl
 // n doubles of device memory into mail.out.
 hipError_t launch_mail(const double *src, int n, const Mail &mail, hipStream_t s);
 
+// Pinned host memory that kernels mail results to, one result at a time.
+class Mailbox {
+  public:
+    Mailbox() = default;
+    Mailbox(const Mailbox &) = delete;
+    Mailbox &operator=(const Mailbox &) = delete;
+    ~Mailbox() {
+        if (flag_) (void)hipHostFree(flag_);
+    }
+    double *data() const { return data_; }
+    // allocates at the first call (always the same size)
+    hipError_t make(size_t bytes) {
+        if (flag_) return hipSuccess;
+        void *p = nullptr;
+        const hipError_t e = hipHostMalloc(&p, HEAD + bytes, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return e;
+        }
+        flag_ = static_cast<uint32_t *>(p);
+        *flag_ = 0;
+        data_ = reinterpret_cast<double *>(static_cast<char *>(p) + HEAD);
+        return hipSuccess;
+    }
+    Mail next() { return Mail{data_, flag_, ++seq_}; }
+    // Waits for the last mail of next(): polls for about a millisecond, then waits
+    // for the stream (long runs, and whatever keeps the kernel from running).
+    hipError_t wait(hipStream_t s) const {
+        for (int k = 0; k < POLLS; ++k) {
+            if (__atomic_load_n(flag_, __ATOMIC_ACQUIRE) == seq_) return hipSuccess;
+            __builtin_ia32_pause();
+        }
+        const hipError_t e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return e;
+        return __atomic_load_n(flag_, __ATOMIC_ACQUIRE) == seq_ ? hipSuccess : hipErrorUnknown;
+    }
+
+  private:
+    static constexpr size_t HEAD = 64;  // the flag's line
+    static constexpr int POLLS = 20000;
+    uint32_t *flag_ = nullptr, seq_ = 0;
+    double *data_ = nullptr;
+};
+
 // Transform of one axis: lines of n values over m points, m = 2^logm (n itself,
 // or at least 2n - 1 for the chirp form), or m = n and logm = -1 (direct sum).
 struct SkAxis {

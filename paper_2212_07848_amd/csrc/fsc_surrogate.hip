@@ -1422,6 +1422,7 @@ struct fsc_sur {
     int wblocks = 0, eblocks = 0;  // blocks of a weight-gradient launch at max_batch
     double *gsum = nullptr, *loss = nullptr;
     double *part = nullptr;  // [3][maxB][IMG_PARTS] segment sums of y, dL/dy and the squared errors
+    Mailbox box;             // the loss on its way to the host
     int64_t adam_t = 0;
     // captured rollouts: (prev, traj, batch, passes) -> graph, replayed on a
     // stream of the surrogate's own that is ordered after and before `stream`
@@ -1836,12 +1837,19 @@ int fsc_sur_grad(fsc_sur *s, const float *dev_prev, const float *dev_in, const f
     if (rc) return rc;
     rc = sur_backward(s, dev_prev, dev_in, dev_target, batch);
     if (rc) return rc;
+    // the loss goes ahead of the copy, not in a second one
+    const bool mailed = s->box.make(sizeof(double)) == hipSuccess;
+    if (mailed) SCHK(s, launch_mail(s->loss, 1, s->box.next(), s->stream));
     if (host_grad)
         SCHK(s, hipMemcpyAsync(host_grad, s->grads, sizeof(float) * s->nparams,
                                hipMemcpyDeviceToHost, s->stream));
     double l = 0.0;
-    SCHK(s, hipMemcpyAsync(&l, s->loss, sizeof(double), hipMemcpyDeviceToHost, s->stream));
+    if (!mailed) SCHK(s, hipMemcpyAsync(&l, s->loss, sizeof(double), hipMemcpyDeviceToHost, s->stream));
     SCHK(s, hipStreamSynchronize(s->stream));
+    if (mailed) {
+        SCHK(s, s->box.wait(s->stream));
+        l = s->box.data()[0];
+    }
     if (loss) *loss = l / double(batch * s->H * s->W);
     return FSC_OK;
 }
@@ -1867,8 +1875,14 @@ int fsc_sur_train_step(fsc_sur *s, const float *dev_prev, const float *dev_in,
     if (rc) return rc;
     if (loss) {
         double l = 0.0;
-        SCHK(s, hipMemcpyAsync(&l, s->loss, sizeof(double), hipMemcpyDeviceToHost, s->stream));
-        SCHK(s, hipStreamSynchronize(s->stream));
+        if (s->box.make(sizeof(double)) == hipSuccess) {
+            SCHK(s, launch_mail(s->loss, 1, s->box.next(), s->stream));
+            SCHK(s, s->box.wait(s->stream));
+            l = s->box.data()[0];
+        } else {
+            SCHK(s, hipMemcpyAsync(&l, s->loss, sizeof(double), hipMemcpyDeviceToHost, s->stream));
+            SCHK(s, hipStreamSynchronize(s->stream));
+        }
         *loss = l / double(batch * s->H * s->W);
     }
     return FSC_OK;
