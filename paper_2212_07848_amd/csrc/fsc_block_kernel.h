@@ -48,12 +48,7 @@ __global__ void __launch_bounds__(NW * 64)
     real *cell = reinterpret_cast<real *>(smem_raw);
 
     const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    int lo = 0, hi = nrep - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (tiles[mid].begin <= lb) lo = mid;
-        else hi = mid - 1;
-    }
+    const int lo = owner_of<sizeof(BlockTile) / sizeof(int)>(&tiles[0].begin, nrep, lb);
     const RepDesc &d = reps[lo];
     const BlockTile bt = tiles[lo];
     const int nx = d.nx, ny = d.ny;

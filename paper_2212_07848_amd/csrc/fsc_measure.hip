@@ -499,7 +499,7 @@ __device__ inline int shell_of(int v) {
 __device__ inline int signed_mode(int q, int n) { return q <= n / 2 ? q : q - n; }
 
 // Closes one sample: the time series' row gets (step, L) with L = 2 pi sum P /
-// sum |k| P, the moments are cleared, the row counters advance.  One thread,
+// sum |k| P, the moments are cleared, the row counter advances.  One thread,
 // after every block of the replica has added its share.
 __device__ __forceinline__ void sk_close(const MeasRep &m, uint64_t step) {
     if (m.t.mom != nullptr) {
@@ -515,7 +515,6 @@ __device__ __forceinline__ void sk_close(const MeasRep &m, uint64_t step) {
         __hip_atomic_store(&m.t.mom[1], 0.0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         m.series_n[0] = row + 1;
     }
-    if (m.modes_cap > 0) m.modes_n[0] += 1;
 }
 
 // Bins of `lines` transformed lines in LDS.  Line l holds the modes (kx, ky, kz)
@@ -526,10 +525,11 @@ __device__ __forceinline__ void sk_close(const MeasRep &m, uint64_t step) {
 // whose ends are integer square roots: the lanes go over (line, shell) pairs
 // and sum their few modes in registers, instead of one shell lookup and two
 // contended atomics per mode.  `wnd` [2][W] collects the lines' shells in LDS
-// (nullptr: one line, added to memory directly).
+// (nullptr: one line, added to memory directly).  srow, mrow: this sample's rows of
+// the time series and of the mode recorder.
 template <typename real>
 __device__ __forceinline__ void sk_bin(const MeasRep &m, const cplx<real> *a, int ls, int lines, int o, int i0,
-                              double *wnd) {
+                              double *wnd, int srow, int mrow) {
     const Geometry &g = m.g;
     const BinTargets &t = m.t;
     const bool d3 = g.D == 3;
@@ -544,7 +544,6 @@ __device__ __forceinline__ void sk_bin(const MeasRep &m, const cplx<real> *a, in
         const cplx<real> v = a[l * ls + sk_pad(i)];
         return (double(v.re) * double(v.re) + double(v.im) * double(v.im)) * invN;
     };
-    const int srow = t.mom && t.series ? t.series_n[0] : 0;
     double *srow_bins = t.mom && t.series && srow < t.series_cap ? t.series + size_t(srow) * (2 + t.n_rad) + 2 : nullptr;
     auto add_shell = [&](int b, double s, double q) {
         unsafeAtomicAdd(&t.rad_sum[b], s);
@@ -650,9 +649,9 @@ __device__ __forceinline__ void sk_bin(const MeasRep &m, const cplx<real> *a, in
             unsafeAtomicAdd(&t.mom[threadIdx.x], v);
         }
     }
-    if (m.modes_cap > 0 && m.modes_n[0] < m.modes_cap) {
+    if (mrow < m.modes_cap) {
         // amplitudes of the modes 1 .. nm along each axis, row [D][nm][2]
-        double *row = m.modes + size_t(m.modes_n[0]) * g.D * m.modes_nm * 2;
+        double *row = m.modes + size_t(mrow) * g.D * m.modes_nm * 2;
         auto put = [&](int d, int k, int l, int i) {
             const cplx<real> v = a[l * ls + sk_pad(i)];
             row[(d * m.modes_nm + k - 1) * 2] = double(v.re);
@@ -728,8 +727,11 @@ __device__ __forceinline__ void sk_last_block(const MeasRep &m, int blk, unsigne
     cplx<real> *a = reinterpret_cast<cplx<real> *>(smem);
     double *wnd = lc > 1 ? reinterpret_cast<double *>(smem + sk_line_bytes(sizeof(cplx<real>), lc, x.m)) : nullptr;
     const cplx<real> *in = static_cast<const cplx<real> *>(d3 ? m.ctmp : m.cbuf);
+    // (asked for here, ahead of the transform)
+    const int srow = m.t.mom && m.t.series ? m.t.series_n[0] : 0;
+    const int mrow = m.modes_cap > 0 ? m.modes_n[0] - 1 : 0;  // k_sk_rows counted this sample
     sk_lines<real>(in + (int64_t(o) * inner + i0) * x.n, lines, x, m.tab[d3 ? 2 : 1], a);
-    sk_bin<real>(m, a, ls, lines, o, i0, wnd);
+    sk_bin<real>(m, a, ls, lines, o, i0, wnd, srow, mrow);
 }
 
 // ---------------------------------------------------------------------------
@@ -738,18 +740,6 @@ __device__ __forceinline__ void sk_last_block(const MeasRep &m, int blk, unsigne
 // belongs to the replica r with pre[r] <= b < pre[r + 1] (a prefix table per
 // kind of work).
 // ---------------------------------------------------------------------------
-__device__ inline int rep_of(const int *__restrict__ pre, int nrep, int b) {
-    // largest r with pre[r] <= b; replicas without blocks of this kind have
-    // pre[r] == pre[r + 1] and are never returned
-    int lo = 0, hi = nrep - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (pre[mid] <= b) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 template <class L, typename real>
 __device__ inline auto sk_density(const MeasRep &m, int par) {
     const real *src = static_cast<const real *>(m.buf[par]);
@@ -769,7 +759,9 @@ __global__ void __launch_bounds__(1024) k_sk_rows(const MeasRep *__restrict__ mr
                                                   uint64_t advance) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     if (blockIdx.x == 0 && threadIdx.x == 0 && advance) step_base[0] += advance;
-    const int r = rep_of(pre, nrep, int(blockIdx.x));
+    const int r = owner_of(pre, nrep, int(blockIdx.x));
+    // the recorder's row counter, which nothing else in this launch reads
+    if (threadIdx.x == 0 && int(blockIdx.x) == pre[r] && mr[r].modes_cap > 0) mr[r].modes_n[0] += 1;
     sk_rows_block<real>(mr[r], int(blockIdx.x) - pre[r], reinterpret_cast<cplx<real> *>(smem_raw),
                         sk_density<L, real>(mr[r], par));
 }
@@ -779,7 +771,7 @@ __global__ void __launch_bounds__(1024) k_sk_mid(const MeasRep *__restrict__ mr,
                                                  int nrep) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     cplx<real> *a = reinterpret_cast<cplx<real> *>(smem_raw);
-    const int r = rep_of(pre, nrep, int(blockIdx.x));
+    const int r = owner_of(pre, nrep, int(blockIdx.x));
     const MeasRep &m = mr[r];
     const Geometry &g = m.g;
     const int blk = int(blockIdx.x) - pre[r], lc = m.lc[1], per = (g.nz + lc - 1) / lc;
@@ -793,14 +785,14 @@ __global__ void __launch_bounds__(1024) k_sk_mid(const MeasRep *__restrict__ mr,
     }
 }
 
-// The replica's last block to finish closes the sample (series row, counters).
+// The replica's last block to finish closes the sample (series row, counter).
 // What it reads of the others went through atomics and is read back by atomics,
 // so every wave only has to see its own ones done before the block counts
 // itself; a device-wide fence writes back the L2 of the block's XCD, which cost
 // 40 us of a launch of 544 blocks.
 __device__ __forceinline__ void sk_finish(const MeasRep &m, int blocks, const uint64_t *step_base,
                                           uint32_t step_off) {
-    if (m.t.mom == nullptr && m.modes_cap == 0) return;
+    if (m.t.mom == nullptr) return;
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x != 0) return;
@@ -816,7 +808,7 @@ __global__ void __launch_bounds__(1024) k_sk_last(const MeasRep *__restrict__ mr
                                                   int nrep, const uint64_t *__restrict__ step_base,
                                                   uint32_t step_off) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    const int r = rep_of(pre, nrep, int(blockIdx.x));
+    const int r = owner_of(pre, nrep, int(blockIdx.x));
     sk_last_block<real>(mr[r], int(blockIdx.x) - pre[r], smem_raw);
     sk_finish(mr[r], pre[r + 1] - pre[r], step_base, step_off);
 }

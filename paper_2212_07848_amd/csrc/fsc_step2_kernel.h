@@ -90,13 +90,7 @@ __global__ void __launch_bounds__((step2_lanes<ST, TX, HIN>()))
 
     // ---- which replica / tile (as in the single-step kernel) ----------------
     const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    int lo = 0, hi = nrep - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (tile_begin[mid] <= lb) lo = mid;
-        else hi = mid - 1;
-    }
-    const RepDesc &d = reps[lo];
+    const RepDesc &d = reps[owner_of(tile_begin, nrep, lb)];
     const int nx = d.nx, ns = d.ny;
     const int t = lb - d.tile_begin;
     const int tix = t % d.tiles_x;

@@ -363,13 +363,7 @@ __global__ void __launch_bounds__(TX *TY)
 
     // ---- which replica / tile -------------------------------------------
     const int lb = xcd_remap(blockIdx.x, gridDim.x);
-    int lo = 0, hi = nrep - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (tile_begin[mid] <= lb) lo = mid;
-        else hi = mid - 1;
-    }
-    const RepDesc &d = reps[lo];
+    const RepDesc &d = reps[owner_of(tile_begin, nrep, lb)];
     const int nx = d.nx, ny = d.ny, ns = d.ns, plane = d.plane;
     const int t = lb - d.tile_begin;
     const int tix = t % d.tiles_x;
