@@ -66,7 +66,7 @@ struct Rep {
     int64_t series_rows = 0;  // samples since it was enabled (the device counter's value)
     // recorded axis-mode amplitudes per sample -- see fsc_modes_enable
     double *d_modes = nullptr;
-    int *d_modes_n = nullptr;
+    int *d_modes_n = nullptr;  // this replica's in fsc_ens::d_modes_n
     int modes_nm = 0, modes_cap = 0;
     int64_t modes_rows = 0;
     size_t modes_bytes = 0;
@@ -126,6 +126,7 @@ struct fsc_ens {
     double *work = nullptr;      // up to READ_WORK bytes on the device for large ones
     size_t work_bytes = 0;
     int *d_mpre = nullptr;
+    int *d_modes_n = nullptr;  // [replica] rows of the mode recorder
     std::string err;
     std::map<std::pair<int, std::pair<int64_t, int64_t>>, GraphEntry> graphs;
 };
@@ -471,12 +472,6 @@ int modes_enable(fsc_ens *e, Rep &r, int nm, int cap) {
     r.modes_cap = 0;
     r.modes_nm = 0;
     r.modes_rows = 0;
-    if (!r.d_modes_n) {
-        if (hipMalloc(&r.d_modes_n, sizeof(int)) != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(e, FSC_E_OOM, "mode recorder allocation failed");
-        }
-    }
     const int sides[3] = {r.p.nx, r.p.ny, r.p.nz};
     for (int d = 0; d < r.p.D && cap > 0; ++d)
         if (nm > sides[d] / 2) return fail(e, FSC_E_INVAL, "nm exceeds half a side");
@@ -495,11 +490,27 @@ int modes_enable(fsc_ens *e, Rep &r, int nm, int cap) {
             }
             r.modes_bytes = bytes;
         }
-        HIPCHK(e, hipMemsetAsync(r.d_modes, 0, bytes, e->stream));
-        r.modes_cap = cap;
+        r.modes_cap = cap;  // (only rows that a sample has filled are read)
         r.modes_nm = nm;
     }
-    HIPCHK(e, hipMemsetAsync(r.d_modes_n, 0, sizeof(int), e->stream));
+    return FSC_OK;
+}
+
+// Mode recorders of all replicas: their row counters are one array, cleared at once.
+int modes_enable_all(fsc_ens *e, int nm, int cap) {
+    (void)hipStreamSynchronize(e->stream);
+    const size_t n = e->reps.size();
+    if (!e->d_modes_n && hipMalloc(&e->d_modes_n, sizeof(int) * n) != hipSuccess) {
+        (void)hipGetLastError();
+        e->d_modes_n = nullptr;
+        return fail(e, FSC_E_OOM, "mode recorder allocation failed");
+    }
+    for (size_t k = 0; k < n; ++k) {
+        e->reps[k].d_modes_n = e->d_modes_n + k;
+        const int rc = modes_enable(e, e->reps[k], nm, cap);
+        if (rc) return rc;
+    }
+    HIPCHK(e, hipMemsetAsync(e->d_modes_n, 0, sizeof(int) * n, e->stream));
     return FSC_OK;
 }
 
@@ -1047,6 +1058,8 @@ int choose_blocks(fsc_ens *e) {
     return FSC_OK;
 }
 
+constexpr int CHUNK_SAMPLES = 8;
+
 int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
     TraceRange trace_("fsc run");
     if (nsteps < 0) return fail(e, FSC_E_INVAL, "nsteps < 0");
@@ -1077,6 +1090,9 @@ int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
     // swaps the buffers)
     int64_t chunk = sk_every > 0 ? sk_every : 64;
     for (int k = 0; k < 4 && (count_launches(e, chunk, sk_every) & 1); ++k) chunk *= 2;
+    // a replay costs a few us between graphs: chunks of frequent samples are
+    // several sampling intervals long
+    while (sk_every > 0 && chunk / sk_every < CHUNK_SAMPLES && 4 * chunk <= nsteps) chunk *= 2;
     int64_t done = 0;
     const int64_t nchunks = nsteps / chunk;
     if (nchunks >= 2) {
@@ -1191,12 +1207,13 @@ void ens_free(fsc_ens *e) {
             if (r.buf[1]) (void)hipFree(r.buf[1]);
         }
         void *ptrs[] = {r.d_sk,  r.cbuf,     r.ctmp,       r.d_done,  r.d_stats_done, r.d_partials,
-                        r.d_mom, r.d_series, r.d_series_n, r.d_modes, r.d_modes_n};
+                        r.d_mom, r.d_series, r.d_series_n, r.d_modes};
         for (void *p : ptrs)
             if (p) (void)hipFree(p);
     }
     for (auto &kv : e->tabs) (void)hipFree(kv.second);
     if (e->work) (void)hipFree(e->work);
+    if (e->d_modes_n) (void)hipFree(e->d_modes_n);
     if (e->d_blocks) (void)hipFree(e->d_blocks);
     if (e->d_desc) (void)hipFree(e->d_desc);
     if (e->d_tile_begin) (void)hipFree(e->d_tile_begin);
@@ -1654,9 +1671,7 @@ int fsc_ens_read_series(fsc_ens *ens, int replica, double *out, int max_rows, in
 // ---- recorded mode amplitudes ---------------------------------------------------
 int fsc_modes_enable(fsc_ctx *ctx, int nm, int capacity) {
     if (!ctx || capacity < 0 || (capacity > 0 && nm < 1)) return FSC_E_INVAL;
-    (void)hipStreamSynchronize(ctx->e->stream);
-    drop_graphs(ctx->e);
-    return modes_enable(ctx->e, ctx->e->reps[0], nm, capacity);
+    return modes_enable_all(ctx->e, nm, capacity);
 }
 int fsc_read_modes(fsc_ctx *ctx, double *out, int max_rows, int *nrows) {
     if (!ctx) return FSC_E_INVAL;
@@ -1664,13 +1679,7 @@ int fsc_read_modes(fsc_ctx *ctx, double *out, int max_rows, int *nrows) {
 }
 int fsc_ens_modes_enable(fsc_ens *ens, int nm, int capacity) {
     if (!ens || capacity < 0 || (capacity > 0 && nm < 1)) return FSC_E_INVAL;
-    (void)hipStreamSynchronize(ens->stream);
-    drop_graphs(ens);
-    for (auto &r : ens->reps) {
-        int rc = modes_enable(ens, r, nm, capacity);
-        if (rc) return rc;
-    }
-    return FSC_OK;
+    return modes_enable_all(ens, nm, capacity);
 }
 int fsc_ens_read_modes(fsc_ens *ens, int replica, double *out, int max_rows, int *nrows) {
     if (!ens) return FSC_E_INVAL;
