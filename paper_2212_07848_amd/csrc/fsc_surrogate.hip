@@ -695,32 +695,27 @@ __device__ inline double image_total(const double *__restrict__ part, int img) {
 }
 static_assert(IMG_PARTS % 64 == 0, "a wave sums the segment sums (and k_last's blocks of four)");
 
-// prediction rho_t + out_scale (y - <y>_image); block (image, segment), the
+// prediction rho_t + out_scale (y - <y>_image); a wave per (image, segment), the
 // image's mean from its IMG_PARTS segment sums
 __global__ void __launch_bounds__(256) k_pred(const float *__restrict__ in,
                                               const float *__restrict__ y,
                                               const double *__restrict__ part, int HW,
                                               float out_scale, float *__restrict__ out) {
-    __shared__ float mean_sh;
-    const int img = blockIdx.x / IMG_PARTS, seg = blockIdx.x % IMG_PARTS;
-    if (threadIdx.x < 64) {
-        const double t = image_total(part, img);
-        if (threadIdx.x == 0) mean_sh = float(t / HW);
-    }
-    __syncthreads();
-    const float mean = mean_sh;
+    const int sg = blockIdx.x * 4 + (threadIdx.x >> 6), img = sg / IMG_PARTS, seg = sg % IMG_PARTS;
+    const float mean = float(image_total(part, img) / HW);
     const int len = (HW + IMG_PARTS - 1) / IMG_PARTS;
     const int lo = seg * len, hi = min(HW, lo + len);
-    for (int i = lo + threadIdx.x; i < hi; i += 256) {
+    for (int i = lo + int(threadIdx.x & 63); i < hi; i += 64) {
         const size_t p = size_t(img) * HW + i;
         out[p] = in[p] + out_scale * (y[p] - mean);
     }
 }
 
-// Loss terms and dL/dyhat; block (image, segment) as k_pred, the image's mean
-// of y from its segment sums.  Every block leaves the FP64 sums of its
-// segment's dL/dyhat and of its squared errors (fixed order, no atomics: 2048
-// blocks adding to one double took 27 us at 32 images of 128^2).
+// Loss terms and dL/dyhat; a wave per (image, segment) as k_pred, the image's mean
+// of y from its segment sums.  Every wave leaves the FP64 sums of its segment's
+// dL/dyhat and of its squared errors (fixed order, no atomics: 2048 blocks adding
+// to one double took 27 us at 32 images of 128^2; a block of 256 per segment, of
+// which 64 lanes had a pixel, 14.5 us; like this 6.6).
 __global__ void __launch_bounds__(256) k_loss(const float *__restrict__ in,
                                               const float *__restrict__ tgt,
                                               const float *__restrict__ y,
@@ -728,19 +723,12 @@ __global__ void __launch_bounds__(256) k_loss(const float *__restrict__ in,
                                               float inv_out_scale, float invM,
                                               float *__restrict__ gout, double *__restrict__ gpart,
                                               double *__restrict__ epart) {
-    __shared__ float mean_sh;
-    __shared__ double sh[2][4];
-    const int img = blockIdx.x / IMG_PARTS, seg = blockIdx.x % IMG_PARTS;
-    if (threadIdx.x < 64) {
-        const double t = image_total(ypart, img);
-        if (threadIdx.x == 0) mean_sh = float(t / HW);
-    }
-    __syncthreads();
-    const float mean = mean_sh;
+    const int sg = blockIdx.x * 4 + (threadIdx.x >> 6), img = sg / IMG_PARTS, seg = sg % IMG_PARTS;
+    const float mean = float(image_total(ypart, img) / HW);
     const int len = (HW + IMG_PARTS - 1) / IMG_PARTS;
     const int lo = seg * len, hi = min(HW, lo + len);
     double gs = 0.0, e2 = 0.0;
-    for (int i = lo + threadIdx.x; i < hi; i += 256) {
+    for (int i = lo + int(threadIdx.x & 63); i < hi; i += 64) {
         const size_t p = size_t(img) * HW + i;
         const float e = (y[p] - mean) - (tgt[p] - in[p]) * inv_out_scale;
         const float gv = 2.f * e * invM;
@@ -754,13 +742,8 @@ __global__ void __launch_bounds__(256) k_loss(const float *__restrict__ in,
         e2 += __shfl_xor(e2, o, 64);
     }
     if ((threadIdx.x & 63) == 0) {
-        sh[0][threadIdx.x >> 6] = gs;
-        sh[1][threadIdx.x >> 6] = e2;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        gpart[blockIdx.x] = sh[0][0] + sh[0][1] + sh[0][2] + sh[0][3];
-        epart[blockIdx.x] = sh[1][0] + sh[1][1] + sh[1][2] + sh[1][3];
+        gpart[sg] = gs;
+        epart[sg] = e2;
     }
 }
 
@@ -1149,80 +1132,116 @@ struct WgradSum {
     const float *mid, *first, *last;  // [layer][block][WG_LEN], [block][len]
     int woff0, boff0, woff1, mid_stride, woffl, boffl;  // offsets in the gradient vector
 };
-constexpr int WG_MID_GROUPS = (WG_LEN + 63) / 64;
+constexpr int WG_MID_GROUPS = (WG_LEN + 255) / 256;
+static_assert(WG_LEN % 4 == 0, "whole 16-byte pieces");
 
-__device__ inline double wg_column(const float *__restrict__ part, int blocks, int len, int e) {
-    // sixteen loads in flight: one at a time the sum is a chain of memory
-    // latencies (258 us for the nine-layer network, 44 us like this)
-    const float *p = part + e;
-    double s = 0.0;
-    int b = threadIdx.x >> 6;
-    for (; b + 60 < blocks; b += 64) {
-        float v[16];
+// Sums of the blocks' partials by workgroups of sixteen waves.  C -> C layers (66
+// MB at nine layers and 32 images): 256 columns each, a wave reads 1 KB of a partial
+// at a time and keeps sixteen such loads in flight.  First and last layers: eight
+// columns each, 128 lanes per column; their columns lie apart, a load touches 64
+// lines, and with 64 columns per workgroup the fifteen CUs that had them took 44
+// us.  Nine-layer network, 32 images: 45 -> 22.6 us; five layers, 6 images of 90 x
+// 96: 17.6 -> 5.4.
+constexpr int WG_SUM_WAVES = 16;
+
+__device__ inline double to_double(float v) { return double(v); }
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ inline f64x4 to_double(f32x4 v) { return f64x4{double(v[0]), double(v[1]), double(v[2]), double(v[3])}; }
+
+// Sum of the partials first, first + step, ..., U at a time; V: float or f32x4,
+// len in units of V.
+template <int U, class V>
+__device__ inline auto wg_column(const V *__restrict__ part, int blocks, int len, int e, int first, int step) {
+    const V *p = part + e;
+    decltype(to_double(V{})) s{};
+    for (int b = first; b < blocks; b += U * step) {
+        V v[U];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) v[k] = p[size_t(b + 4 * k) * len];
+        for (int k = 0; k < U; ++k) v[k] = p[size_t(min(b + step * k, blocks - 1)) * len];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) s += double(v[k]);
+        for (int k = 0; k < U; ++k)
+            if (b + step * k < blocks) s += to_double(v[k]);
     }
-    for (; b < blocks; b += 4) s += double(p[size_t(b) * len]);
     return s;
+}
+
+constexpr int WG_EDGE_COLS = 8, WG_EDGE_STEP = WG_SUM_WAVES * 64 / WG_EDGE_COLS;
+__device__ inline double wg_edge_column(const float *__restrict__ part, int blocks, int len, int e) {
+    return wg_column<4>(part, blocks, len, e, int(threadIdx.x) / WG_EDGE_COLS, WG_EDGE_STEP);
 }
 
 template <int K>
 __device__ inline double wg_edge_value(const float *__restrict__ part, int blocks, int ch, int col) {
     const int mt = ch & 1, row = ch >> 1;  // channel 2 (4g + r) + mt
     const int e = ((col >> 4) * 2 + mt) * 256 + (row & 3) * 64 + (row >> 2) * 16 + (col & 15);
-    return wg_column(part, blocks, wg_edge_len<K>(), e);
+    return wg_edge_column(part, blocks, wg_edge_len<K>(), e);
 }
 
-__global__ void __launch_bounds__(256) k_wgrad_sum(WgradSum a, float *__restrict__ grads) {
-    __shared__ double sh[4][64];
+__global__ void __launch_bounds__(64 * WG_SUM_WAVES) k_wgrad_sum(WgradSum a, float *__restrict__ grads) {
+    __shared__ __attribute__((aligned(32))) double sh[WG_SUM_WAVES][256];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int mid_groups = a.nmid * WG_MID_GROUPS;
+    auto total = [&](int col) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < WG_SUM_WAVES; ++w) t += sh[w][col];
+        return float(t);
+    };
+    if (int(blockIdx.x) < mid_groups) {
+        const int l = blockIdx.x / WG_MID_GROUPS, e0 = (blockIdx.x % WG_MID_GROUPS) * 256;
+        if (e0 + lane * 4 < WG_LEN) {
+            const f32x4 *part = reinterpret_cast<const f32x4 *>(a.mid + size_t(l) * a.mid_blocks * WG_LEN);
+            *reinterpret_cast<f64x4 *>(&sh[wave][lane * 4]) =
+                wg_column<16>(part, a.mid_blocks, WG_LEN / 4, e0 / 4 + lane, wave, WG_SUM_WAVES);
+        }
+        __syncthreads();
+        const int e = e0 + int(threadIdx.x);
+        if (threadIdx.x >= 256 || e >= WG_LEN) return;
+        int dst = a.woff1 + l * a.mid_stride;
+        if (e < 9 * SC * SC) {
+            const int q = e >> 6, el = e & 63;
+            const int r = q & 3, nt = (q >> 2) & 1, mt = (q >> 3) & 1, t = q >> 4;
+            const int co = 2 * (4 * (el >> 4) + r) + mt, ci = 2 * (el & 15) + nt;
+            dst += (co * SC + ci) * 9 + t;
+        } else {
+            dst += e;  // the biases follow the weights
+        }
+        grads[dst] = total(threadIdx.x);
+        return;
+    }
     double s = 0.0;
     int dst = -1;
-    if (int(blockIdx.x) < mid_groups) {
-        const int l = blockIdx.x / WG_MID_GROUPS, e = (blockIdx.x % WG_MID_GROUPS) * 64 + lane;
-        if (e < WG_LEN) {
-            s = wg_column(a.mid + size_t(l) * a.mid_blocks * WG_LEN, a.mid_blocks, WG_LEN, e);
-            const int base = a.woff1 + l * a.mid_stride;
-            if (e < 9 * SC * SC) {
-                const int q = e >> 6, el = e & 63;
-                const int r = q & 3, nt = (q >> 2) & 1, mt = (q >> 3) & 1, t = q >> 4;
-                const int co = 2 * (4 * (el >> 4) + r) + mt, ci = 2 * (el & 15) + nt;
-                dst = base + (co * SC + ci) * 9 + t;
-            } else {
-                dst = base + e;  // the biases follow the weights
-            }
+    const int e = (int(blockIdx.x) - mid_groups) * WG_EDGE_COLS + lane % WG_EDGE_COLS;
+    const int n0 = SC * (9 * a.in_ch + 1), nl = SC * 9 + 1;  // first layer, last layer
+    if (e < n0) {
+        const int ch = e / (9 * a.in_ch + 1), k = e % (9 * a.in_ch + 1);
+        const bool bias = k == 9 * a.in_ch;  // the column of ones
+        dst = bias ? a.boff0 + ch : a.woff0 + ch * 9 * a.in_ch + k;
+        for (int pt = 0; pt < (bias ? 1 : 3); ++pt) {
+            const int col = (bias ? 27 * a.in_ch : pt * 9 * a.in_ch + k);
+            s += a.in_ch == 2 ? wg_edge_value<2>(a.first, a.edge_blocks, ch, col)
+                              : wg_edge_value<1>(a.first, a.edge_blocks, ch, col);
         }
-    } else {
-        const int e = (int(blockIdx.x) - mid_groups) * 64 + lane;
-        const int n0 = SC * (9 * a.in_ch + 1), nl = SC * 9 + 1;  // first layer, last layer
-        if (e < n0) {
-            const int ch = e / (9 * a.in_ch + 1), k = e % (9 * a.in_ch + 1);
-            const bool bias = k == 9 * a.in_ch;  // the column of ones
-            dst = bias ? a.boff0 + ch : a.woff0 + ch * 9 * a.in_ch + k;
-            for (int pt = 0; pt < (bias ? 1 : 3); ++pt) {
-                const int col = (bias ? 27 * a.in_ch : pt * 9 * a.in_ch + k);
-                s += a.in_ch == 2 ? wg_edge_value<2>(a.first, a.edge_blocks, ch, col)
-                                  : wg_edge_value<1>(a.first, a.edge_blocks, ch, col);
-            }
-        } else if (e < n0 + nl) {
-            const int k = e - n0;
-            if (k < SC * 9) {
-                dst = a.woffl + k;
-                for (int pt = 0; pt < 3; ++pt)
-                    s += wg_edge_value<1>(a.last, a.edge_blocks, k / 9, pt * 9 + k % 9);
-            } else {
-                dst = a.boffl;
-                s = wg_column(a.last, a.edge_blocks, wg_edge_len<1>(), wg_edge_len<1>() - 1);
-            }
+    } else if (e < n0 + nl) {
+        const int k = e - n0;
+        if (k < SC * 9) {
+            dst = a.woffl + k;
+            for (int pt = 0; pt < 3; ++pt)
+                s += wg_edge_value<1>(a.last, a.edge_blocks, k / 9, pt * 9 + k % 9);
+        } else {
+            dst = a.boffl;
+            s = wg_edge_column(a.last, a.edge_blocks, wg_edge_len<1>(), wg_edge_len<1>() - 1);
         }
     }
     sh[wave][lane] = s;
     __syncthreads();
-    if (wave == 0 && dst >= 0)
-        grads[dst] = float((sh[0][lane] + sh[1][lane]) + (sh[2][lane] + sh[3][lane]));
+    if (int(threadIdx.x) < WG_EDGE_COLS && dst >= 0) {
+        double t = 0.0;
+        for (int w = 0; w < WG_SUM_WAVES; ++w)
+#pragma unroll
+            for (int k = 0; k < 64; k += WG_EDGE_COLS) t += sh[w][lane + k];
+        grads[dst] = float(t);
+    }
 }
 
 // Packed copies of the parameters for the matrix cores, one parameter per
@@ -1589,7 +1608,7 @@ int sur_backward(fsc_sur *s, const float *prev, const float *in, const float *tg
     const int H = s->H, W = s->W, P = B * H * W;
     const float ii = 1.f / s->in_scale, io = 1.f / s->out_scale;
     double *gpart = s->part + size_t(IMG_PARTS) * s->maxB, *epart = gpart + size_t(IMG_PARTS) * s->maxB;
-    hipLaunchKernelGGL(k_loss, dim3(unsigned(B * IMG_PARTS)), dim3(256), 0, s->stream, in, tgt, s->y, s->part,
+    hipLaunchKernelGGL(k_loss, dim3(unsigned(B * IMG_PARTS / 4)), dim3(256), 0, s->stream, in, tgt, s->y, s->part,
                        H * W, io, 1.f / float(P), s->gbuf, gpart, epart);
     SCHK(s, hipGetLastError());
     hipLaunchKernelGGL(k_loss_total, dim3(unsigned(B + 1)), dim3(256), 0, s->stream, gpart, epart, B, s->gsum,
@@ -1646,7 +1665,9 @@ int sur_backward(fsc_sur *s, const float *prev, const float *in, const float *tg
                            nullptr, B, H, W, pfirst);
     SCHK(s, hipGetLastError());
     const int edge = SC * (9 * s->in_ch + 1) + SC * 9 + 1;
-    hipLaunchKernelGGL(k_wgrad_sum, dim3(unsigned(ws.nmid * WG_MID_GROUPS + (edge + 63) / 64)), dim3(256), 0,
+    hipLaunchKernelGGL(k_wgrad_sum,
+                       dim3(unsigned(ws.nmid * WG_MID_GROUPS + (edge + WG_EDGE_COLS - 1) / WG_EDGE_COLS)),
+                       dim3(64 * WG_SUM_WAVES), 0,
                        s->stream, ws, s->grads);
     SCHK(s, hipGetLastError());
     return FSC_OK;
@@ -1820,7 +1841,7 @@ int fsc_sur_forward(fsc_sur *s, const float *dev_prev, const float *dev_in, floa
     if (rc) return rc;
     rc = sur_forward_core(s, dev_prev, dev_in, batch, false);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_pred, dim3(unsigned(batch * IMG_PARTS)), dim3(256), 0, s->stream, dev_in,
+    hipLaunchKernelGGL(k_pred, dim3(unsigned(batch * IMG_PARTS / 4)), dim3(256), 0, s->stream, dev_in,
                        s->y, s->part, s->H * s->W, s->out_scale, dev_out);
     SCHK(s, hipGetLastError());
     return FSC_OK;
@@ -1916,7 +1937,7 @@ int fsc_sur_rollout(fsc_sur *s, const float *dev_prev, float *dev_traj, int batc
                 const float *prev = k == 0 ? dev_prev : dev_traj + (k - 1) * img;
                 frc = sur_forward_core(s, prev, dev_traj + k * img, batch, false);
                 if (frc == FSC_OK) {
-                    hipLaunchKernelGGL(k_pred, dim3(unsigned(batch * IMG_PARTS)), dim3(256), 0,
+                    hipLaunchKernelGGL(k_pred, dim3(unsigned(batch * IMG_PARTS / 4)), dim3(256), 0,
                                        s->stream, dev_traj + k * img, s->y, s->part, s->H * s->W,
                                        s->out_scale, dev_traj + (k + 1) * img);
                     if (hipGetLastError() != hipSuccess) frc = FSC_E_HIP;
