@@ -87,20 +87,15 @@ __device__ __forceinline__ int mid_row_channel(int nt, int m) { return 8 * (m >>
 template <bool BWD, bool ZOUT>
 __device__ __forceinline__ void mid_epilogue(const f32x4 (&acc)[2], size_t pix, int g,
                                              float *__restrict__ zout, bf16 *__restrict__ aout,
-                                             const float *__restrict__ zprev) {
+                                             const f32x4 (&zprev)[2]) {
     const size_t o = pix * SC + 8 * g;
     bf16x8 out;
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
-        if (BWD) {
-            const f32x4 zp = *reinterpret_cast<const f32x4 *>(zprev + o + 4 * nt);
+        if (!BWD && ZOUT) *reinterpret_cast<f32x4 *>(zout + o + 4 * nt) = acc[nt];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) out[4 * nt + r] = bf16(acc[nt][r] * dsilu(zp[r]));
-        } else {
-            if (ZOUT) *reinterpret_cast<f32x4 *>(zout + o + 4 * nt) = acc[nt];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) out[4 * nt + r] = bf16(silu(acc[nt][r]));
-        }
+        for (int r = 0; r < 4; ++r)
+            out[4 * nt + r] = bf16(BWD ? acc[nt][r] * dsilu(zprev[nt][r]) : silu(acc[nt][r]));
     }
     // inference: non-temporal, the next layer reads the records from memory
     // anyway (3% per rollout pass against the default policy).  Training keeps
@@ -108,6 +103,11 @@ __device__ __forceinline__ void mid_epilogue(const f32x4 (&acc)[2], size_t pix, 
     // nine-layer network on 32 images of 128^2: 876 against 920 us).
     if (BWD || ZOUT) *reinterpret_cast<bf16x8 *>(aout + o) = out;
     else __builtin_nontemporal_store(out, reinterpret_cast<bf16x8 *>(aout + o));
+}
+__device__ __forceinline__ void load_z(const float *__restrict__ z, size_t pix, int g, f32x4 (&v)[2]) {
+    const f32x4 *p = reinterpret_cast<const f32x4 *>(z + pix * SC + 8 * g);
+    v[0] = p[0];
+    v[1] = p[1];
 }
 
 __global__ void k_mfma_probe(const float *A, const float *B, float *Cm) {
@@ -251,7 +251,9 @@ __global__ void __launch_bounds__(256) k_mid(const bf16 *__restrict__ ain,
                 acc[1] = mfma16(bop[ky * 3 + kx][1], aop, acc[1]);
             }
         }
-        mid_epilogue<BWD, ZOUT>(acc, size_t(p0 + r16), g, zout, aout, zprev);
+        f32x4 zp[2];
+        if (BWD) load_z(zprev, size_t(p0 + r16), g, zp);
+        mid_epilogue<BWD, ZOUT>(acc, size_t(p0 + r16), g, zout, aout, zp);
     }
 }
 
@@ -327,7 +329,9 @@ __global__ void __launch_bounds__(256) k_mid_lds(const bf16 *__restrict__ ain,
                 acc[1] = mfma16(bop[ky * 3 + kx][1], aop, acc[1]);
             }
         const size_t p0 = size_t((n * H + y) * W + x0 + tx * 16);
-        mid_epilogue<BWD, ZOUT>(acc, p0 + r16, g, zout, aout, zprev);
+        f32x4 zp[2];
+        if (BWD) load_z(zprev, p0 + r16, g, zp);
+        mid_epilogue<BWD, ZOUT>(acc, p0 + r16, g, zout, aout, zp);
     }
 }
 
@@ -435,7 +439,7 @@ __global__ void __launch_bounds__(256) k_mid2_lds(const bf16 *__restrict__ ain,
         f32x4 acc[2];
         tile(mid, F2MW, row, cx, acc);
         const size_t p = size_t((n * H + y0 + row) * W + x0 + cx);
-        mid_epilogue<false, false>(acc, p, g, nullptr, aout, nullptr);
+        mid_epilogue<false, false>(acc, p, g, nullptr, aout, bv);
     }
 }
 
@@ -462,6 +466,14 @@ __global__ void __launch_bounds__(256) k_mid2_lds(const bf16 *__restrict__ ain,
 // g ^ (pixel / 4 % 4): 16 lanes that read one piece of 16 pixels in a row then
 // meet every bank once.
 // ---------------------------------------------------------------------------
+// element of a pixel's piece of eight channels in a row's LDS buffer
+__device__ __forceinline__ int row_slot(int px, int piece) { return px * SC + ((piece ^ ((px >> 2) & 3)) * 8); }
+// barrier that orders LDS accesses alone: global loads and stores stay in flight
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 constexpr int CH_W = 128;             // widest row
 constexpr int CH_WAVES = 4;           // waves per layer
 constexpr int CH_BLOCKS = 256;        // one workgroup per CU
@@ -487,8 +499,6 @@ __global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restr
     const int n = blockIdx.x / strips, y0 = (blockIdx.x % strips) * R;
     const int Rr = min(R, H - y0), tiles = W / 16;
     const size_t img = size_t(n) * H;
-    auto slot = [](int px, int piece) { return px * SC + ((piece ^ ((px >> 2) & 3)) * 8); };
-
     const bf16 *wpk = layer == 0 ? wA : wB;
     const float *bias = layer == 0 ? bA : bB;
     bf16x8 bop[9][2];
@@ -508,7 +518,7 @@ __global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restr
     for (int q = 0; q < TPW; ++q) {
         pix[q] = min(wl + CH_WAVES * q, tiles - 1) * 16 + r16;
 #pragma unroll
-        for (int kx = 0; kx < 3; ++kx) at[q][kx] = slot(wrapi(pix[q] + kx - 1, W), g);
+        for (int kx = 0; kx < 3; ++kx) at[q][kx] = row_slot(wrapi(pix[q] + kx - 1, W), g);
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) p0[q][nt] = p1[q][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -527,13 +537,8 @@ __global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restr
 #pragma unroll
         for (int k = 0; k < TPW; ++k) {
             const int e = min(tid + k * CH_LOADERS, W * 4 - 1);
-            *reinterpret_cast<u32x4 *>(&rows[0][row & 1][slot(e >> 2, e & 3)]) = v[k];
+            *reinterpret_cast<u32x4 *>(&rows[0][row & 1][row_slot(e >> 2, e & 3)]) = v[k];
         }
-    };
-    auto sync = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
     };
     auto step = [&](int s, auto first) {
         const int j = first ? s : s - 3;  // this layer's input row
@@ -566,14 +571,14 @@ __global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restr
 #pragma unroll
         for (int q = 0; q < TPW; ++q) {
             if constexpr (!first) {
-                mid_epilogue<false, false>(done[q], (img + size_t(y0 + j - 2)) * W + pix[q], g, nullptr, aout, nullptr);
+                mid_epilogue<false, false>(done[q], (img + size_t(y0 + j - 2)) * W + pix[q], g, nullptr, aout, bv);
             } else {
                 bf16x8 o;
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) o[4 * nt + r] = bf16(silu(done[q][nt][r]));
-                *reinterpret_cast<bf16x8 *>(&rows[1][s & 1][slot(pix[q], g)]) = o;
+                *reinterpret_cast<bf16x8 *>(&rows[1][s & 1][row_slot(pix[q], g)]) = o;
             }
         }
     };
@@ -589,24 +594,133 @@ __global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restr
             put(0, va);
             fetch(2, va);
         }
-        sync();
+        lds_barrier();
         for (int s = 0; s < steps; s += 2) {
             step(s, first);
             if constexpr (first) {
                 put(s + 1, vb);
                 fetch(s + 3, vb);
             }
-            sync();
+            lds_barrier();
             step(s + 1, first);  // (past the last step: nothing to do)
             if constexpr (first) {
                 put(s + 2, va);
                 fetch(s + 4, va);
             }
-            sync();
+            lds_barrier();
         }
     };
     if (layer == 0) march(std::true_type{});
     else march(std::false_type{});
+}
+
+// One C -> C layer in the same form, forward or backward (training, and the odd
+// layer of an inference pass): CW waves multiply, a tile of 16 pixels each, and CW/4
+// more load the rows, so that the multiplying waves have only stores in flight,
+// which nothing waits for; backward they load their next row's pre-activations a
+// step ahead.  MARCH_FIGURES
+template <int CW, bool BWD, bool ZOUT>
+__global__ void __launch_bounds__((CW + CW / 4) * 64) k_march(const bf16 *__restrict__ ain,
+                                                              const bf16 *__restrict__ wpk,
+                                                              const float *__restrict__ bias, int R, int strips,
+                                                              int H, int W, float *__restrict__ zout,
+                                                              bf16 *__restrict__ aout,
+                                                              const float *__restrict__ zprev) {
+    constexpr int ROW = CW * 16 * SC, LOADERS = CW / 4 * 64, NP = 4;
+    __shared__ __attribute__((aligned(16))) bf16 rows[2][ROW];
+#ifdef FSC_LDS_POISON
+    lds_poison(&rows[0][0], 2 * ROW);
+    __syncthreads();
+#endif
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = blockIdx.x / strips, y0 = (blockIdx.x % strips) * R;
+    const int Rr = min(R, H - y0), nin = Rr + 2;  // rows written and read
+    const size_t img = size_t(n) * H;
+    if (wave >= CW) {
+        const int t = tid - CW * 64;
+        auto fetch = [&](int row, u32x4 (&v)[NP]) {
+            const size_t base = (img + size_t(wrap_any(y0 - 1 + min(row, nin - 1), H))) * W;
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                const int e = min(t + k * LOADERS, W * 4 - 1);
+                v[k] = *reinterpret_cast<const u32x4 *>(ain + (base + (e >> 2)) * SC + (e & 3) * 8);
+            }
+        };
+        auto put = [&](int row, const u32x4 (&v)[NP]) {
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                const int e = min(t + k * LOADERS, W * 4 - 1);
+                *reinterpret_cast<u32x4 *>(&rows[row & 1][row_slot(e >> 2, e & 3)]) = v[k];
+            }
+        };
+        // row q is asked for two steps before it is put down, and read one step later
+        u32x4 va[NP], vb[NP];
+        fetch(0, va);
+        fetch(1, vb);
+        put(0, va);
+        fetch(2, va);
+        lds_barrier();
+        for (int s = 0; s < nin; s += 2) {
+            put(s + 1, vb);
+            fetch(s + 3, vb);
+            lds_barrier();
+            put(s + 2, va);
+            fetch(s + 4, va);
+            lds_barrier();
+        }
+        return;
+    }
+    const int r16 = lane & 15, g = lane >> 4;
+    bf16x8 bop[9][2];
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+            bop[t][nt] = *reinterpret_cast<const bf16x8 *>(wpk + (t * SC + mid_row_channel(nt, r16)) * SC + g * 8);
+    f32x4 bv[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    if (!BWD) {
+        bv[0] = *reinterpret_cast<const f32x4 *>(bias + 8 * g);
+        bv[1] = *reinterpret_cast<const f32x4 *>(bias + 8 * g + 4);
+    }
+    // (waves past a narrower row's end repeat its last tile: the same values again)
+    const int px = min(wave, W / 16 - 1) * 16 + r16;
+    int at[3];
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) at[kx] = row_slot(wrapi(px + kx - 1, W), g);
+    auto pixel = [&](int row) { return (img + size_t(y0 + row)) * W + px; };
+    f32x4 p0[2], p1[2], za[2], zb[2];
+    p0[0] = p0[1] = p1[0] = p1[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (BWD) load_z(zprev, pixel(0), g, za);
+    __builtin_amdgcn_s_waitcnt(0);  // the weights: here, not in the loop, where it would wait for more
+    auto step = [&](int s, const f32x4 (&z)[2], f32x4 (&znext)[2]) {
+        if (BWD) load_z(zprev, pixel(min(max(s - 1, 0), Rr - 1)), g, znext);
+        const bf16 *src = rows[s & 1];
+        bf16x8 x[3];
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) x[kx] = *reinterpret_cast<const bf16x8 *>(src + at[kx]);
+        f32x4 done[2];
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            done[nt] = p1[nt];
+            p1[nt] = p0[nt];
+            p0[nt] = bv[nt];
+        }
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                done[nt] = mfma16(bop[6 + kx][nt], x[kx], done[nt]);
+                p1[nt] = mfma16(bop[3 + kx][nt], x[kx], p1[nt]);
+                p0[nt] = mfma16(bop[kx][nt], x[kx], p0[nt]);
+            }
+        if (s >= 2 && s < nin) mid_epilogue<BWD, ZOUT>(done, pixel(s - 2), g, zout, aout, z);
+        lds_barrier();
+    };
+    lds_barrier();
+    for (int s = 0; s < nin; s += 2) {  // (a step past the last row writes nothing)
+        step(s, za, zb);
+        step(s + 1, zb, za);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1527,9 +1641,31 @@ int update_params(fsc_sur *s, const AdamArgs *o) {
     return FSC_OK;
 }
 
+// rows per workgroup of the marching kernels, and workgroups per image: at most
+// one per CU
+void chain_strips(const fsc_sur *s, int B, int &R, int &strips) {
+    const int most = std::min(s->H, std::max(1, CH_BLOCKS / B));
+    R = (s->H + most - 1) / most;
+    strips = (s->H + R - 1) / R;
+}
+
 int check_batch(fsc_sur *s, int batch) {
     if (batch < 1 || batch > s->maxB) return sur_fail(s, FSC_E_INVAL, "batch out of range");
     return FSC_OK;
+}
+
+// one C -> C layer, marching; rows of at most CH_W pixels
+template <bool BWD, bool ZOUT>
+void launch_march(const fsc_sur *s, int B, const bf16 *ain, const bf16 *w, const float *bias, float *zout, bf16 *aout,
+                  const float *zprev) {
+    int R, strips;
+    chain_strips(s, B, R, strips);
+    auto go = [&](auto kernel, int cw) {
+        hipLaunchKernelGGL(kernel, dim3(unsigned(B * strips)), dim3(unsigned((cw + cw / 4) * 64)), 0, s->stream, ain, w,
+                           bias, R, strips, s->H, s->W, zout, aout, zprev);
+    };
+    if (s->W <= CH_W / 2) go(k_march<4, BWD, ZOUT>, 4);
+    else go(k_march<8, BWD, ZOUT>, 8);
 }
 
 // the LDS-staged C -> C layer applies when its tiles divide the image
@@ -1557,8 +1693,8 @@ int sur_forward_core(fsc_sur *s, const float *prev, const float *cur, int B, boo
         const float *bl = s->params + s->boff[l];
         if (!train && s->fuse != 0 && s->W <= CH_W && l + 1 <= nmid(s)) {
             // layers l and l + 1 in one launch; a[l] is not written
-            const int most = std::min(s->H, std::max(1, CH_BLOCKS / B));
-            const int R = (s->H + most - 1) / most, strips = (s->H + R - 1) / R;
+            int R, strips;
+            chain_strips(s, B, R, strips);
             auto chain = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, dim3(unsigned(B * strips)), dim3(2 * CH_WAVES * 64), 0, s->stream, ain,
                                    wl, bl, wl + size_t(9) * SC * SC, s->params + s->boff[l + 1], R, strips, s->H,
@@ -1580,7 +1716,10 @@ int sur_forward_core(fsc_sur *s, const float *prev, const float *cur, int B, boo
             ++l;
             continue;
         }
-        if (lds_tiles(s)) {
+        if (s->W <= CH_W) {
+            if (train) launch_march<false, true>(s, B, ain, wl, bl, s->z[l], s->a[l], nullptr);
+            else launch_march<false, false>(s, B, ain, wl, bl, nullptr, s->a[l], nullptr);
+        } else if (lds_tiles(s)) {
             const dim3 g(unsigned(B * (s->H / MR) * (s->W / MW)));
             if (train)
                 hipLaunchKernelGGL((k_mid_lds<false, true>), g, dim3(256), 0, s->stream, ain, wl, bl, B,
@@ -1648,7 +1787,9 @@ int sur_backward(fsc_sur *s, const float *prev, const float *in, const float *tg
                            B, H, W, pmid + size_t(l - 1) * ws.mid_blocks * WG_LEN);
         SCHK(s, hipGetLastError());
         const size_t off = size_t(l - 1) * 9 * SC * SC;
-        if (lds_tiles(s))
+        if (s->W <= CH_W)
+            launch_march<true, true>(s, B, dz, s->wb + off, nullptr, nullptr, dzn, s->z[l - 1]);
+        else if (lds_tiles(s))
             hipLaunchKernelGGL((k_mid_lds<true, true>), dim3(unsigned(B * (H / MR) * (W / MW))), dim3(256),
                                0, s->stream, dz, s->wb + off, nullptr, B, H, W, nullptr, dzn, s->z[l - 1]);
         else
