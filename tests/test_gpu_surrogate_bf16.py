@@ -154,3 +154,10 @@ def test_gradients_match_bf16_reference_per_element(in_ch, shape):
             _compare(gr, rr, f"grad layer {l} {part} K={in_ch} {shape}", med_tol=1e-3,
                      max_tol=5e-3, tail_tol=2e-3, tail_frac=0.02)
         o += n + co
+
+
+# rows of one and of several tiles, strips of one row and partial last strips, and
+# the widths beyond 128 that keep the tiled and the generic layer
+@pytest.mark.parametrize("shape", [(7, 5, 32), (100, 5, 32), (3, 11, 96), (2, 6, 160), (1, 8, 192)])
+def test_gradients_on_edge_shapes(shape):
+    test_gradients_match_bf16_reference_per_element(1, shape)
