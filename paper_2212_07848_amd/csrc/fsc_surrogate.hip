@@ -614,11 +614,55 @@ __global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restr
     else march(std::false_type{});
 }
 
+// The loading waves of a marching layer: rows 0 .. nin - 1 of its input (image rows
+// y0 - 1 .., periodic) into the two LDS rows, one step ahead of the multiplying
+// waves, with which they share every barrier (one, then one per step, steps in
+// pairs).
+template <int CW>
+__device__ __forceinline__ void march_load(const bf16 *__restrict__ ain, size_t img, int y0, int nin, int H, int W,
+                                           bf16 (&rows)[2][CW * 16 * SC]) {
+    constexpr int LOADERS = CW / 4 * 64, NP = 4;
+    const int t = int(threadIdx.x) - CW * 64;
+    auto fetch = [&](int row, u32x4 (&v)[NP]) {
+        const size_t base = (img + size_t(wrap_any(y0 - 1 + min(row, nin - 1), H))) * W;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int e = min(t + k * LOADERS, W * 4 - 1);
+            v[k] = *reinterpret_cast<const u32x4 *>(ain + (base + (e >> 2)) * SC + (e & 3) * 8);
+        }
+    };
+    auto put = [&](int row, const u32x4 (&v)[NP]) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int e = min(t + k * LOADERS, W * 4 - 1);
+            *reinterpret_cast<u32x4 *>(&rows[row & 1][row_slot(e >> 2, e & 3)]) = v[k];
+        }
+    };
+    // row q is asked for two steps before it is put down, and read one step later
+    u32x4 va[NP], vb[NP];
+    fetch(0, va);
+    fetch(1, vb);
+    put(0, va);
+    fetch(2, va);
+    lds_barrier();
+    for (int s = 0; s < nin; s += 2) {
+        put(s + 1, vb);
+        fetch(s + 3, vb);
+        lds_barrier();
+        put(s + 2, va);
+        fetch(s + 4, va);
+        lds_barrier();
+    }
+}
+
 // One C -> C layer in the same form, forward or backward (training, and the odd
 // layer of an inference pass): CW waves multiply, a tile of 16 pixels each, and CW/4
 // more load the rows, so that the multiplying waves have only stores in flight,
 // which nothing waits for; backward they load their next row's pre-activations a
-// step ahead.  MARCH_FIGURES
+// step ahead.  Per layer at 32 images of 128^2, tiles and marching, us: forward with
+// pre-activations 32.4 and 26.0 (134 MB, 5.2 TB/s), backward 35.6 and 30.4, inference
+// at 16 images 13.6 and 11.7; 6 images of 90 x 96 (no tiles divide them) 11.1 and
+// 9.3, 15.0 and 9.7.
 template <int CW, bool BWD, bool ZOUT>
 __global__ void __launch_bounds__((CW + CW / 4) * 64) k_march(const bf16 *__restrict__ ain,
                                                               const bf16 *__restrict__ wpk,
@@ -626,7 +670,7 @@ __global__ void __launch_bounds__((CW + CW / 4) * 64) k_march(const bf16 *__rest
                                                               int H, int W, float *__restrict__ zout,
                                                               bf16 *__restrict__ aout,
                                                               const float *__restrict__ zprev) {
-    constexpr int ROW = CW * 16 * SC, LOADERS = CW / 4 * 64, NP = 4;
+    constexpr int ROW = CW * 16 * SC;
     __shared__ __attribute__((aligned(16))) bf16 rows[2][ROW];
 #ifdef FSC_LDS_POISON
     lds_poison(&rows[0][0], 2 * ROW);
@@ -636,40 +680,7 @@ __global__ void __launch_bounds__((CW + CW / 4) * 64) k_march(const bf16 *__rest
     const int n = blockIdx.x / strips, y0 = (blockIdx.x % strips) * R;
     const int Rr = min(R, H - y0), nin = Rr + 2;  // rows written and read
     const size_t img = size_t(n) * H;
-    if (wave >= CW) {
-        const int t = tid - CW * 64;
-        auto fetch = [&](int row, u32x4 (&v)[NP]) {
-            const size_t base = (img + size_t(wrap_any(y0 - 1 + min(row, nin - 1), H))) * W;
-#pragma unroll
-            for (int k = 0; k < NP; ++k) {
-                const int e = min(t + k * LOADERS, W * 4 - 1);
-                v[k] = *reinterpret_cast<const u32x4 *>(ain + (base + (e >> 2)) * SC + (e & 3) * 8);
-            }
-        };
-        auto put = [&](int row, const u32x4 (&v)[NP]) {
-#pragma unroll
-            for (int k = 0; k < NP; ++k) {
-                const int e = min(t + k * LOADERS, W * 4 - 1);
-                *reinterpret_cast<u32x4 *>(&rows[row & 1][row_slot(e >> 2, e & 3)]) = v[k];
-            }
-        };
-        // row q is asked for two steps before it is put down, and read one step later
-        u32x4 va[NP], vb[NP];
-        fetch(0, va);
-        fetch(1, vb);
-        put(0, va);
-        fetch(2, va);
-        lds_barrier();
-        for (int s = 0; s < nin; s += 2) {
-            put(s + 1, vb);
-            fetch(s + 3, vb);
-            lds_barrier();
-            put(s + 2, va);
-            fetch(s + 4, va);
-            lds_barrier();
-        }
-        return;
-    }
+    if (wave >= CW) return march_load<CW>(ain, img, y0, nin, H, W, rows);
     const int r16 = lane & 15, g = lane >> 4;
     bf16x8 bop[9][2];
 #pragma unroll
@@ -796,6 +807,87 @@ __global__ void __launch_bounds__(256) k_last(const bf16 *__restrict__ a, int B,
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     if (lane == 0) part[sg] = s;
 }
+
+// The last layer in the marching form (rows of at most 128 pixels; see k_march):
+// the same MFMA sequence per pixel.  A strip's sum of y goes to entry `strip` of the
+// image's segment sums, the entries past the last strip are zero.  Forward pass at
+// 16 images of 128^2: 12.4 us as k_last, 8.1 so; 32 images 23.0 and 11.0.
+template <int CW>
+__global__ void __launch_bounds__((CW + CW / 4) * 64) k_last_march(const bf16 *__restrict__ ain, int R, int strips,
+                                                                   int H, int W, const bf16 *__restrict__ wl3,
+                                                                   const float *__restrict__ b,
+                                                                   float *__restrict__ y,
+                                                                   double *__restrict__ part) {
+    constexpr int ROW = CW * 16 * SC;
+    __shared__ __attribute__((aligned(16))) bf16 rows[2][ROW];
+    __shared__ double sums[CW];
+#ifdef FSC_LDS_POISON
+    lds_poison(&rows[0][0], 2 * ROW);
+    __syncthreads();
+#endif
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = blockIdx.x / strips, strip = blockIdx.x % strips, y0 = strip * R;
+    const int Rr = min(R, H - y0), nin = Rr + 2;  // rows written and read
+    const size_t img = size_t(n) * H;
+    if (wave >= CW) {
+        march_load<CW>(ain, img, y0, nin, H, W, rows);
+        __syncthreads();
+        return;
+    }
+    const int r16 = lane & 15, g = lane >> 4;
+    bf16x8 wop[9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        if (r16 < 3) {
+            wop[t] = *reinterpret_cast<const bf16x8 *>(wl3 + (t * 3 + r16) * SC + g * 8);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) wop[t][e] = bf16(0.f);
+        }
+    }
+    const float bias = b[0];
+    const int px = min(wave, W / 16 - 1) * 16 + r16;
+    const bool on = g == 0 && wave < W / 16;
+    int at[3];
+#pragma unroll
+    for (int kx = 0; kx < 3; ++kx) at[kx] = row_slot(wrapi(px + kx - 1, W), g);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 p0 = zero, p1 = zero;
+    double sum = 0.0;
+    __builtin_amdgcn_s_waitcnt(0);  // the weights: here, not in the loop
+    lds_barrier();
+    for (int s = 0; s < nin + (nin & 1); ++s) {
+        const bf16 *src = rows[s & 1];
+        f32x4 done = p1;
+        p1 = p0;
+        p0 = zero;
+#pragma unroll
+        for (int kx = 0; kx < 3; ++kx) {
+            const bf16x8 x = *reinterpret_cast<const bf16x8 *>(src + at[kx]);
+            done = mfma16(wop[6 + kx], x, done);
+            p1 = mfma16(wop[3 + kx], x, p1);
+            p0 = mfma16(wop[kx], x, p0);
+        }
+        if (s >= 2 && s < nin && on) {
+            const float v = (done[0] + done[1]) + done[2] + bias;
+            y[(img + size_t(y0 + s - 2)) * W + px] = v;
+            sum += double(v);
+        }
+        lds_barrier();
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) sums[wave] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int w = 0; w < CW; ++w) t += sums[w];
+        part[n * IMG_PARTS + strip] = t;
+    }
+    for (int k = strip + strips * (1 + int(threadIdx.x)); k < IMG_PARTS; k += strips * CW * 64)
+        part[n * IMG_PARTS + k] = 0.0;
+}
+static_assert(CH_BLOCKS <= IMG_PARTS, "an entry per strip");
 
 // sum of an image's IMG_PARTS segment sums by one wave, in a fixed order
 __device__ inline double image_total(const double *__restrict__ part, int img) {
@@ -1737,8 +1829,20 @@ int sur_forward_core(fsc_sur *s, const float *prev, const float *cur, int B, boo
         SCHK(s, hipGetLastError());
     }
     const int last = s->layers - 1;
-    hipLaunchKernelGGL(k_last, dim3(unsigned(B * IMG_PARTS / 4)), dim3(256), 0, s->stream, s->a[last - 1], B,
-                       s->H, s->W, s->wl3, s->params + s->boff[last], s->y, s->part);
+    if (s->W <= CH_W) {
+        int R, strips;
+        chain_strips(s, B, R, strips);
+        auto go = [&](auto kernel, int cw) {
+            hipLaunchKernelGGL(kernel, dim3(unsigned(B * strips)), dim3(unsigned((cw + cw / 4) * 64)), 0, s->stream,
+                               s->a[last - 1], R, strips, s->H, s->W, s->wl3, s->params + s->boff[last], s->y,
+                               s->part);
+        };
+        if (s->W <= CH_W / 2) go(k_last_march<4>, 4);
+        else go(k_last_march<8>, 8);
+    } else {
+        hipLaunchKernelGGL(k_last, dim3(unsigned(B * IMG_PARTS / 4)), dim3(256), 0, s->stream, s->a[last - 1], B,
+                           s->H, s->W, s->wl3, s->params + s->boff[last], s->y, s->part);
+    }
     SCHK(s, hipGetLastError());
     return FSC_OK;
 }
