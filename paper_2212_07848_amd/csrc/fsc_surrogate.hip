@@ -477,11 +477,52 @@ __device__ __forceinline__ void lds_barrier() {
 constexpr int CH_W = 128;             // widest row
 constexpr int CH_WAVES = 4;           // waves per layer
 constexpr int CH_BLOCKS = 256;        // one workgroup per CU
-constexpr int CH_LOADERS = CH_WAVES * 64;
+
+// The loading waves of a marching layer: rows 0 .. nin - 1 of its input (image rows
+// y0 - 1 .., periodic) into the two LDS rows, one step ahead of the multiplying
+// waves, with which they share every barrier (one, then one per step, steps in
+// pairs).
+// (`first` .. is their first thread; LW: their number)
+template <int LW, int ROW>
+__device__ __forceinline__ void march_load(const bf16 *__restrict__ ain, size_t img, int y0, int nin, int steps, int H,
+                                           int W, int first, bf16 (&rows)[2][ROW]) {
+    constexpr int LOADERS = LW * 64, NP = ROW / 8 / LOADERS;
+    const int t = int(threadIdx.x) - first;
+    auto fetch = [&](int row, u32x4 (&v)[NP]) {
+        const size_t base = (img + size_t(wrap_any(y0 - 1 + min(row, nin - 1), H))) * W;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int e = min(t + k * LOADERS, W * 4 - 1);
+            v[k] = *reinterpret_cast<const u32x4 *>(ain + (base + (e >> 2)) * SC + (e & 3) * 8);
+        }
+    };
+    auto put = [&](int row, const u32x4 (&v)[NP]) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int e = min(t + k * LOADERS, W * 4 - 1);
+            *reinterpret_cast<u32x4 *>(&rows[row & 1][row_slot(e >> 2, e & 3)]) = v[k];
+        }
+    };
+    // row q is asked for two steps before it is put down, and read one step later
+    u32x4 va[NP], vb[NP];
+    fetch(0, va);
+    fetch(1, vb);
+    put(0, va);
+    fetch(2, va);
+    lds_barrier();
+    for (int s = 0; s < steps; s += 2) {
+        put(s + 1, vb);
+        fetch(s + 3, vb);
+        lds_barrier();
+        put(s + 2, va);
+        fetch(s + 4, va);
+        lds_barrier();
+    }
+}
 
 // TPW: tiles of 16 pixels per wave; a row has at most 4 TPW of them.
 template <int TPW>
-__global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restrict__ ain,
+__global__ void __launch_bounds__((2 * CH_WAVES + TPW) * 64) k_chain(const bf16 *__restrict__ ain,
                                                             const bf16 *__restrict__ wA,
                                                             const float *__restrict__ bA,
                                                             const bf16 *__restrict__ wB,
@@ -499,6 +540,8 @@ __global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restr
     const int n = blockIdx.x / strips, y0 = (blockIdx.x % strips) * R;
     const int Rr = min(R, H - y0), tiles = W / 16;
     const size_t img = size_t(n) * H;
+    const int nin = Rr + 4, steps = Rr + 5;  // rows that the first layer reads
+    if (layer == 2) return march_load<TPW>(ain, img, y0 - 1, nin, steps, H, W, 2 * CH_WAVES * 64, rows[0]);
     const bf16 *wpk = layer == 0 ? wA : wB;
     const float *bias = layer == 0 ? bA : bB;
     bf16x8 bop[9][2];
@@ -523,23 +566,6 @@ __global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restr
         for (int nt = 0; nt < 2; ++nt) p0[q][nt] = p1[q][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    const int nin = Rr + 4;  // rows that the first layer reads
-    // (past the last row, and past the row's end: loaded again)
-    auto fetch = [&](int row, u32x4 (&v)[TPW]) {
-        const size_t base = (img + size_t(wrap_any(y0 - 2 + min(row, nin - 1), H))) * W;
-#pragma unroll
-        for (int k = 0; k < TPW; ++k) {
-            const int e = min(tid + k * CH_LOADERS, W * 4 - 1);
-            v[k] = *reinterpret_cast<const u32x4 *>(ain + (base + (e >> 2)) * SC + (e & 3) * 8);
-        }
-    };
-    auto put = [&](int row, const u32x4 (&v)[TPW]) {
-#pragma unroll
-        for (int k = 0; k < TPW; ++k) {
-            const int e = min(tid + k * CH_LOADERS, W * 4 - 1);
-            *reinterpret_cast<u32x4 *>(&rows[0][row & 1][row_slot(e >> 2, e & 3)]) = v[k];
-        }
-    };
     auto step = [&](int s, auto first) {
         const int j = first ? s : s - 3;  // this layer's input row
         if (j < 0 || j >= (first ? nin : nin - 2)) return;
@@ -582,77 +608,17 @@ __global__ void __launch_bounds__(2 * CH_WAVES * 64) k_chain(const bf16 *__restr
             }
         }
     };
-    // One loop per kind of wave: only the first layer's waves load and only the
-    // second one's store, so that none waits for the other kind's memory operations.
-    const int steps = Rr + 5;
     auto march = [&](auto first) {
-        // row q is asked for two steps before it is put down, and read one step later
-        u32x4 va[TPW], vb[TPW];
-        if constexpr (first) {
-            fetch(0, va);
-            fetch(1, vb);
-            put(0, va);
-            fetch(2, va);
-        }
         lds_barrier();
         for (int s = 0; s < steps; s += 2) {
             step(s, first);
-            if constexpr (first) {
-                put(s + 1, vb);
-                fetch(s + 3, vb);
-            }
             lds_barrier();
             step(s + 1, first);  // (past the last step: nothing to do)
-            if constexpr (first) {
-                put(s + 2, va);
-                fetch(s + 4, va);
-            }
             lds_barrier();
         }
     };
     if (layer == 0) march(std::true_type{});
     else march(std::false_type{});
-}
-
-// The loading waves of a marching layer: rows 0 .. nin - 1 of its input (image rows
-// y0 - 1 .., periodic) into the two LDS rows, one step ahead of the multiplying
-// waves, with which they share every barrier (one, then one per step, steps in
-// pairs).
-template <int CW>
-__device__ __forceinline__ void march_load(const bf16 *__restrict__ ain, size_t img, int y0, int nin, int H, int W,
-                                           bf16 (&rows)[2][CW * 16 * SC]) {
-    constexpr int LOADERS = CW / 4 * 64, NP = 4;
-    const int t = int(threadIdx.x) - CW * 64;
-    auto fetch = [&](int row, u32x4 (&v)[NP]) {
-        const size_t base = (img + size_t(wrap_any(y0 - 1 + min(row, nin - 1), H))) * W;
-#pragma unroll
-        for (int k = 0; k < NP; ++k) {
-            const int e = min(t + k * LOADERS, W * 4 - 1);
-            v[k] = *reinterpret_cast<const u32x4 *>(ain + (base + (e >> 2)) * SC + (e & 3) * 8);
-        }
-    };
-    auto put = [&](int row, const u32x4 (&v)[NP]) {
-#pragma unroll
-        for (int k = 0; k < NP; ++k) {
-            const int e = min(t + k * LOADERS, W * 4 - 1);
-            *reinterpret_cast<u32x4 *>(&rows[row & 1][row_slot(e >> 2, e & 3)]) = v[k];
-        }
-    };
-    // row q is asked for two steps before it is put down, and read one step later
-    u32x4 va[NP], vb[NP];
-    fetch(0, va);
-    fetch(1, vb);
-    put(0, va);
-    fetch(2, va);
-    lds_barrier();
-    for (int s = 0; s < nin; s += 2) {
-        put(s + 1, vb);
-        fetch(s + 3, vb);
-        lds_barrier();
-        put(s + 2, va);
-        fetch(s + 4, va);
-        lds_barrier();
-    }
 }
 
 // One C -> C layer in the same form, forward or backward (training, and the odd
@@ -680,7 +646,7 @@ __global__ void __launch_bounds__((CW + CW / 4) * 64) k_march(const bf16 *__rest
     const int n = blockIdx.x / strips, y0 = (blockIdx.x % strips) * R;
     const int Rr = min(R, H - y0), nin = Rr + 2;  // rows written and read
     const size_t img = size_t(n) * H;
-    if (wave >= CW) return march_load<CW>(ain, img, y0, nin, H, W, rows);
+    if (wave >= CW) return march_load<CW / 4>(ain, img, y0, nin, nin, H, W, CW * 64, rows);
     const int r16 = lane & 15, g = lane >> 4;
     bf16x8 bop[9][2];
 #pragma unroll
@@ -830,7 +796,7 @@ __global__ void __launch_bounds__((CW + CW / 4) * 64) k_last_march(const bf16 *_
     const int Rr = min(R, H - y0), nin = Rr + 2;  // rows written and read
     const size_t img = size_t(n) * H;
     if (wave >= CW) {
-        march_load<CW>(ain, img, y0, nin, H, W, rows);
+        march_load<CW / 4>(ain, img, y0, nin, nin, H, W, CW * 64, rows);
         __syncthreads();
         return;
     }
@@ -1787,13 +1753,13 @@ int sur_forward_core(fsc_sur *s, const float *prev, const float *cur, int B, boo
             // layers l and l + 1 in one launch; a[l] is not written
             int R, strips;
             chain_strips(s, B, R, strips);
-            auto chain = [&](auto kernel) {
-                hipLaunchKernelGGL(kernel, dim3(unsigned(B * strips)), dim3(2 * CH_WAVES * 64), 0, s->stream, ain,
+            auto chain = [&](auto kernel, int tpw) {
+                hipLaunchKernelGGL(kernel, dim3(unsigned(B * strips)), dim3(unsigned((2 * CH_WAVES + tpw) * 64)), 0, s->stream, ain,
                                    wl, bl, wl + size_t(9) * SC * SC, s->params + s->boff[l + 1], R, strips, s->H,
                                    s->W, s->a[l + 1]);
             };
-            if (s->W <= CH_W / 2) chain(k_chain<1>);
-            else chain(k_chain<2>);
+            if (s->W <= CH_W / 2) chain(k_chain<1>, 1);
+            else chain(k_chain<2>, 2);
             SCHK(s, hipGetLastError());
             ++l;
             continue;
