@@ -54,7 +54,9 @@ struct Rep {
     int n_axis = 0, n_rad = 0;
     std::vector<int64_t> axis_modes, rad_modes;
     int64_t nsamples = 0;
-    double *d_sk = nullptr;  // axis_sum, axis_sq, rad_sum, rad_sq
+    // axis_sum, axis_sq, rad_sum, rad_sq; d_mom, the counters and d_partials lie
+    // behind them in the same allocation
+    double *d_sk = nullptr;
     void *cbuf = nullptr, *ctmp = nullptr;
     int *d_done = nullptr;  // blocks of a sample that have finished
     double *d_partials = nullptr;
@@ -260,18 +262,18 @@ int init_rep(Rep &r, const fsc_params &p, void *ext_a, void *ext_b, fsc_ens *e) 
         }
     if (cubic) count_shells(D, p.nx, r.n_rad, r.rad_modes.data());
     const size_t nsk = 2 * size_t(D) * r.n_axis + 2 * size_t(r.n_rad);
-    if (hipMalloc(&r.d_sk, sizeof(double) * nsk) != hipSuccess ||
-        hipMalloc(&r.d_mom, sizeof(double) * 2) != hipSuccess ||
-        hipMalloc(&r.d_series_n, sizeof(int)) != hipSuccess ||
-        hipMalloc(&r.d_stats_done, sizeof(int)) != hipSuccess ||
-        hipMalloc(&r.d_partials, sizeof(double) * stats_partials_len()) != hipSuccess) {
+    // one allocation: S(k) sums, moments, the counters, and the reductions' partials
+    const size_t cleared = sizeof(double) * (nsk + 4);
+    if (hipMalloc(&r.d_sk, cleared + sizeof(double) * stats_partials_len()) != hipSuccess) {
         (void)hipGetLastError();
+        r.d_sk = nullptr;
         return fail(e, FSC_E_OOM, "accumulator allocation failed");
     }
-    HIPCHK(e, hipMemsetAsync(r.d_sk, 0, sizeof(double) * nsk, e->stream));
-    HIPCHK(e, hipMemsetAsync(r.d_mom, 0, sizeof(double) * 2, e->stream));
-    HIPCHK(e, hipMemsetAsync(r.d_series_n, 0, sizeof(int), e->stream));
-    HIPCHK(e, hipMemsetAsync(r.d_stats_done, 0, sizeof(int), e->stream));
+    r.d_mom = r.d_sk + nsk;
+    r.d_series_n = reinterpret_cast<int *>(r.d_mom + 2);
+    r.d_stats_done = reinterpret_cast<int *>(r.d_mom + 3);
+    r.d_partials = r.d_mom + 4;
+    HIPCHK(e, hipMemsetAsync(r.d_sk, 0, cleared, e->stream));
     return FSC_OK;
 }
 
@@ -1045,8 +1047,16 @@ int ens_autotune(fsc_ens *e) {
 }
 
 // Whether runs go through the block kernel: small 2D lattices, unless the caller
-// has fixed a tiling or the autotuner found one that is faster.
+// has fixed a tiling or the autotuner found one that is faster.  A run that the
+// caller captures into a graph of its own takes one launch per step: an even
+// number of steps then leaves the state in the buffer that the next replay reads.
 int choose_blocks(fsc_ens *e) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    HIPCHK(e, hipStreamIsCapturing(e->stream, &cs));
+    if (cs != hipStreamCaptureStatusNone) {
+        e->use_blocks = false;
+        return FSC_OK;
+    }
     bool use = block_size(e) && (e->autotune == 0 || e->tuned_blocks);
     if (use) {
         int rc = ensure_blocks(e);
@@ -1206,8 +1216,7 @@ void ens_free(fsc_ens *e) {
             if (r.buf[0]) (void)hipFree(r.buf[0]);
             if (r.buf[1]) (void)hipFree(r.buf[1]);
         }
-        void *ptrs[] = {r.d_sk,  r.cbuf,     r.ctmp,       r.d_done,  r.d_stats_done, r.d_partials,
-                        r.d_mom, r.d_series, r.d_series_n, r.d_modes};
+        void *ptrs[] = {r.d_sk, r.cbuf, r.ctmp, r.d_done, r.d_series, r.d_modes};
         for (void *p : ptrs)
             if (p) (void)hipFree(p);
     }

@@ -457,11 +457,12 @@ __global__ void __launch_bounds__(256) k_mid2_lds(const bf16 *__restrict__ ain,
 // R gives at most one workgroup per CU; two of them on a CU with half the rows
 // each are slower (9-layer passes over 16 images: 98.6 us, 114).  What bounds it
 // is the chain of a step (LDS reads, 18 MFMAs per tile, SiLU, barrier), about
-// 2800 cycles where a SIMD's MFMAs take 1150.  9-layer passes, us, unfused / as
-// tiles (k_mid2_lds) / marching: 1 image of 128^2 74 / 62 / 53, 4 88 / 74 / 65, 16
-// 130 / 132 / 99, 32 222 / 238 / 154.  (Three and four layers per launch spill; a
-// SiLU that runs a step late, beside the other layer's products, took 19.1 us per
-// pair against 17.2.)
+// 2800 cycles where a SIMD's MFMAs take 1150.  A pair at 16 images of 128^2: 27.4 us
+// as two tiled layers, 17.0 so.  9-layer passes, us, tiled layers / tiled pairs
+// (k_mid2_lds) / with the pairs marching / and the single and last layers (k_march,
+// k_last_march): 1 image 74 / 62 / 53 / 48, 4 88 / 74 / 65 / 61, 16 130 / 132 / 99 /
+// 91, 32 222 / 238 / 154 / 136.  (Three and four layers per launch spill; a SiLU
+// that runs a step late, beside the other layer's products, took 19.1 us per pair.)
 // LDS: [layer][2][W pixels][4 pieces of 8 channels], a pixel's piece g at slot
 // g ^ (pixel / 4 % 4): 16 lanes that read one piece of 16 pixels in a row then
 // meet every bank once.

@@ -79,3 +79,21 @@ def test_autotune_of_a_small_lattice_keeps_the_state_and_the_results():
             lat.step(40)
             got.append(lat.get_populations())
     assert np.array_equal(got[0], got[1])
+
+
+def test_steps_captured_by_the_caller_replay_like_eager_ones():
+    stream = torch.cuda.Stream()
+    p = _p(96, 80, 4, "fp32", 1e-5)
+    with fsc.Lattice(p, stream=stream) as lat, fsc.Lattice(p) as ref:
+        for q in (lat, ref):
+            q.init_uniform()
+            q.step(3)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+            lat.step(10)
+        for _ in range(3):
+            with torch.cuda.stream(stream):
+                g.replay()
+            stream.synchronize()
+            ref.step(10)
+            assert np.array_equal(lat.get_populations(), ref.get_populations())
