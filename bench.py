@@ -267,7 +267,8 @@ def summarize_surrogate_trace(trace_dir: str, log_path: str, out_path: str):
     """Markdown summary of the surrogate's kernels in a `rocprofv3
     --kernel-trace --stats --output-format csv` run of this script: per
     kernel, the dispatches and mean duration; for the 32 -> 32 matrix-core
-    layer (k_mid) the achieved BF16 rate per launch from the rollout's batch
+    layers (k_chain: two, k_march: one) the achieved BF16 rate per launch from
+    the rollout's batch
     (the bench's held-out seeds, 128^2 pixels each)."""
     import csv
     import re
@@ -293,8 +294,7 @@ def summarize_surrogate_trace(trace_dir: str, log_path: str, out_path: str):
                 short = name.replace("void ", "").split("(")[0].replace("fsc::", "")
             else:
                 continue
-            if short.split("<")[0] in ("k_first", "k_mid", "k_mid_lds", "k_last",
-                                       "k_img_part", "k_img_total", "k_pred"):
+            if short.split("<")[0] in ("k_first", "k_chain", "k_march", "k_last_march", "k_pred"):
                 per[short].append(int(r["End_Timestamp"]) - int(r["Start_Timestamp"]))
     lines = ["# Surrogate kernels: rocprofv3 kernel trace of bench.py (rollout part)", "",
              "Command (repository root as working directory, TMPDIR=/tmp):", "",
@@ -320,22 +320,24 @@ def summarize_surrogate_trace(trace_dir: str, log_path: str, out_path: str):
         mean = sum(v) / len(v)
         means[name] = mean
         note = ""
-        if name.startswith("k_mid") and batch:  # the generic and the LDS-staged forms
-            flops = 2 * 9 * 32 * 32 * batch * 128 * 128
+        if name.startswith(("k_chain", "k_march")) and batch:
+            flops = 2 * 9 * 32 * 32 * batch * 128 * 128 * (2 if name.startswith("k_chain") else 1)
             tf = flops / (mean * 1e-9) / 1e12
             note = (f"{flops / 1e9:.2f} GFLOP per launch: {tf:.1f} TFLOP/s, "
                     f"{tf / BF16_PEAK_TFLOPS * 100:.1f}% of the BF16 peak")
         lines.append(f"| `{name}` | {len(v)} | {mean / 1e3:.2f} | {note} |")
     # kernel time of one inference pass of each model from the per-kernel means
-    mid = means.get("k_mid_lds<false, false>") or means.get("k_mid<false, false>")
+    kernels = {k: means.get(n) for k, n in (("pair", "k_chain<2>"), ("one", "k_march<8, false, false>"),
+                                            ("last", "k_last_march<8>"), ("pred", "k_pred"))}
     for name, mo in models.items():
         K = 2 if "2ch" in name else 1
         layers = int(name.split("layer")[0])
         first = means.get(f"k_first<{K}, false>")
-        if first and mid and "k_last" in means and "k_pred" in means:
-            tot = first + (layers - 2) * mid + means["k_last"] + means["k_pred"]
-            lines.append(f"\n{name}: kernel time per pass {tot / 1e3:.1f} us (k_first + "
-                         f"{layers - 2} x k_mid_lds + k_last + k_pred); the rollout takes "
+        if first and all(kernels.values()):
+            pairs, odd = divmod(layers - 2, 2)
+            tot = first + pairs * kernels["pair"] + odd * kernels["one"] + kernels["last"] + kernels["pred"]
+            lines.append(f"\n{name}: kernel time per pass {tot / 1e3:.1f} us (k_first + {pairs} x k_chain + "
+                         f"{odd} x k_march + k_last_march + k_pred); the rollout takes "
                          f"{mo['surrogate_s_per_stride'] * 1e6:.1f} us per pass in wall time.")
     with open(out_path, "w") as fh:
         fh.write("\n".join(lines) + "\n")
