@@ -141,6 +141,32 @@ namespace {
 thread_local std::string g_create_error;
 }
 
+ThreadWork &fsc::thread_work() {
+    static thread_local ThreadWork work;
+    return work;
+}
+
+int ThreadWork::take(size_t bytes, void **out) {
+    auto get = [](size_t n, void **q) {
+        if (hipMalloc(q, n) == hipSuccess) return int(FSC_OK);
+        (void)hipGetLastError();
+        *q = nullptr;
+        return int(FSC_E_OOM);
+    };
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return FSC_E_HIP;
+    if (bytes > KEEP) return get(bytes, out);
+    if (dev != dev_ || bytes > bytes_) {
+        drop();
+        const int rc = get(bytes, &kept_);
+        if (rc) return rc;
+        dev_ = dev;
+        bytes_ = bytes;
+    }
+    *out = kept_;
+    return FSC_OK;
+}
+
 namespace {
 
 void ens_free(fsc_ens *e);
@@ -1789,9 +1815,7 @@ size_t field_work_bytes(int L, int nrad, int chunk) {
     return field_tab_bytes(L) + size_t(chunk) * (field_spec_bytes(L) + sizeof(double) * field_acc_len(nrad));
 }
 
-// `box`: pinned memory of FIELD_MAIL bytes for sums that fit it, or null
-constexpr size_t FIELD_MAIL = size_t(16) << 10;
-
+// `box`: pinned memory of ThreadWork::MAIL bytes for sums that fit it, or null
 hipError_t field_sk_batches(const float *dev_fields, int batch, int L, hipStream_t st, void *work, int chunk,
                             int nrad, Mailbox *box, double *host_shell_mean, double *host_L) {
     std::vector<int64_t> modes(size_t(nrad), 0);
@@ -1800,7 +1824,7 @@ hipError_t field_sk_batches(const float *dev_fields, int batch, int L, hipStream
     unsigned char *tab = static_cast<unsigned char *>(work);
     unsigned char *spec = tab + field_tab_bytes(L);
     std::vector<double> h(len * size_t(std::min(batch, chunk)));
-    if (sizeof(double) * h.size() > FIELD_MAIL) box = nullptr;
+    if (sizeof(double) * h.size() > ThreadWork::MAIL) box = nullptr;
     hipError_t ec = hipSuccess;
     for (int b = 0; b < batch && ec == hipSuccess; b += chunk) {
         const int nb = std::min(chunk, batch - b);
@@ -1823,53 +1847,6 @@ hipError_t field_sk_batches(const float *dev_fields, int batch, int L, hipStream
     }
     return ec;
 }
-
-// What a thread's calls of fsc_field_sk keep between them: the pinned result and
-// up to FIELD_KEEP bytes of device work area on the device it last ran on (beyond
-// 256 KB hipMalloc and hipFree take 20 us, as much as the transforms of 16 fields
-// of 128^2).  Every call ends with its device work done, so the next one may use
-// another stream.  Given back when the thread ends.
-class FieldPool {
-  public:
-    ~FieldPool() { drop(); }
-    Mailbox *mailbox() { return box_.make(FIELD_MAIL) == hipSuccess ? &box_ : nullptr; }
-    int take(size_t bytes, void **out) {
-        int dev = -1;
-        if (hipGetDevice(&dev) != hipSuccess) return FSC_E_HIP;
-        if (bytes > FIELD_KEEP) return get(bytes, out);
-        if (dev != dev_ || bytes > bytes_) {
-            drop();
-            const int rc = get(bytes, &kept_);
-            if (rc) return rc;
-            dev_ = dev;
-            bytes_ = bytes;
-        }
-        *out = kept_;
-        return FSC_OK;
-    }
-    void done(void *p) {
-        if (p != kept_) (void)hipFree(p);
-    }
-
-  private:
-    static constexpr size_t FIELD_KEEP = size_t(8) << 20;
-    static int get(size_t bytes, void **out) {
-        if (hipMalloc(out, bytes) == hipSuccess) return FSC_OK;
-        (void)hipGetLastError();
-        *out = nullptr;
-        return FSC_E_OOM;
-    }
-    void drop() {
-        if (kept_) (void)hipFree(kept_);
-        kept_ = nullptr;
-        bytes_ = 0;
-        dev_ = -1;
-    }
-    Mailbox box_;
-    void *kept_ = nullptr;
-    size_t bytes_ = 0;
-    int dev_ = -1;
-};
 
 // ---- fixed-size scratch of the allocation-free field S(k) ----------------
 // 16 MiB and some: at least one field of FIELD_STATIC_MAX_SIDE^2 at a time (its
@@ -1921,7 +1898,7 @@ int fsc_field_sk(const float *dev_fields, int batch, int ny, int nx, void *strea
     const hipStream_t st = static_cast<hipStream_t>(stream);
     // the spectra of a chunk stay within 1 GiB
     const int chunk = int(std::min<int64_t>(batch, std::max<int64_t>(1, (int64_t(1) << 30) / int64_t(field_spec_bytes(nx)))));
-    static thread_local FieldPool pool;
+    ThreadWork &pool = thread_work();
     void *work = nullptr;
     rc = pool.take(field_work_bytes(nx, nrad, chunk), &work);
     if (rc) return rc;

@@ -153,6 +153,35 @@ class Mailbox {
     double *data_ = nullptr;
 };
 
+// What a thread's synchronous calls without a handle (field S(k), linear S(k)) keep
+// between them: the pinned result and up to KEEP bytes of device work area on the
+// device it last ran on (beyond 256 KB hipMalloc and hipFree take 20 us, as much
+// as the transforms of 16 fields of 128^2).  Every call ends with its device work
+// done, so the next one may use another stream.  Given back when the thread ends.
+class ThreadWork {
+  public:
+    static constexpr size_t MAIL = size_t(16) << 10, KEEP = size_t(8) << 20;
+    ~ThreadWork() { drop(); }
+    Mailbox *mailbox() { return box_.make(MAIL) == hipSuccess ? &box_ : nullptr; }
+    int take(size_t bytes, void **out);  // an FSC_ code
+    void done(void *p) {
+        if (p != kept_) (void)hipFree(p);
+    }
+
+  private:
+    void drop() {
+        if (kept_) (void)hipFree(kept_);
+        kept_ = nullptr;
+        bytes_ = 0;
+        dev_ = -1;
+    }
+    Mailbox box_;
+    void *kept_ = nullptr;
+    size_t bytes_ = 0;
+    int dev_ = -1;
+};
+ThreadWork &thread_work();
+
 // Transform of one axis: lines of n values over m points, m = 2^logm (n itself,
 // or at least 2n - 1 for the chirp form), or m = n and logm = -1 (direct sum).
 struct SkAxis {

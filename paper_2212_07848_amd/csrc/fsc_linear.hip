@@ -19,12 +19,13 @@
 // (17 KB for D3Q19).  FP64 throughout.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <vector>
 
 #include "../../include/fsc.h"
-#include "fsc_device.h"
+#include "fsc_internal.h"
 
 namespace fsc {
 namespace {
@@ -230,6 +231,9 @@ struct KSource {
     double unit;  // 2 pi / n
 };
 
+__host__ __device__ inline int64_t tri(int64_t a) { return a * (a + 1) / 2; }
+__host__ __device__ inline int64_t tet(int64_t a) { return a * (a + 1) * (a + 2) / 6; }
+
 __device__ __forceinline__ void wave_vector(const KSource &ks, int D, int64_t id, double (&k)[3]) {
     k[2] = 0.0;
     if (ks.kv) {
@@ -237,8 +241,6 @@ __device__ __forceinline__ void wave_vector(const KSource &ks, int D, int64_t id
         return;
     }
     const int64_t r = id + 1;  // rank, the origin included
-    auto tri = [](int64_t a) { return a * (a + 1) / 2; };
-    auto tet = [](int64_t a) { return a * (a + 1) * (a + 2) / 6; };
     int64_t a = 0, rest = r;
     if (D == 3) {
         a = int64_t(cbrt(6.0 * double(r)));
@@ -276,8 +278,8 @@ __device__ __forceinline__ void wave_vector(const KSource &ks, int D, int64_t id
 // A lane holds its three matrices in registers: 4 to 15 doublings of 170 FMAs where
 // the Q x Q complex form takes 82000 each in 3D.  What bounds it is the one wave's
 // serial FP64 chain (a 64^3 lattice has 103 waves of wave vectors).  The radial
-// S(k) of 64^3, whole call: 1785 us as Q x Q matrices, 44 us so (the kernel 14), with
-// half the error (1.6e-14).
+// S(k) of 64^3, whole call: 1785 us as Q x Q matrices, 31 us so (this kernel 14), with
+// half the error (2e-14).
 template <class L, class ST>
 __global__ void __launch_bounds__(64) k_linear_conserved(LinArgs la, KSource ks, double *__restrict__ out) {
     constexpr int D = L::D, Q = L::Q, N = D + 1;
@@ -486,6 +488,63 @@ __global__ void __launch_bounds__(64) k_linear_corr(LinArgs la, const double *__
     }
 }
 
+// floor(sqrt(v)), v >= 0
+__device__ inline int64_t root(int64_t v) {
+    int64_t b = int64_t(sqrt(double(v)));
+    while (b * b > v) --b;
+    while ((b + 1) * (b + 1) <= v) ++b;
+    return b;
+}
+
+// Shell sums over the fundamental domain (see KSource): one block per shell
+// round(|m|), its lanes over (m_x, m_y) (2D: m_x), whose last components in the
+// shell are a range.  out[b]: sum of modes times S, out[nbins + b]: modes, both in a
+// fixed order.  On the host the loop over all wave vectors and the copy of their S
+// took as long as forming them (64^3: 44 us a call, 31 so).
+template <int D>
+__global__ void __launch_bounds__(256) k_linear_shells(const double *__restrict__ S, int n, int nbins,
+                                                       double *__restrict__ out) {
+    __shared__ double sh[2][4];
+    const int64_t h = n / 2, b = blockIdx.x;
+    const int64_t pairs = D == 3 ? tri(h + 1) : h + 1;
+    auto signs = [&](int64_t v) { return v == 0 || 2 * v == n ? 1 : 2; };
+    double sum = 0.0, modes = 0.0;
+    for (int64_t p = threadIdx.x; p < pairs; p += 256) {
+        int64_t x = p, y = 0;
+        if (D == 3) {
+            x = int64_t(sqrt(2.0 * double(p)));
+            while (tri(x) > p) --x;
+            while (tri(x + 1) <= p) ++x;
+            y = p - tri(x);
+        }
+        // the last component m: b^2 - b < base + m^2 <= b^2 + b (b = 0: the origin)
+        const int64_t base = x * x + y * y, top = b * b + b - base;
+        if (b == 0 || top < 0) continue;
+        const int64_t last = D == 3 ? y : x;
+        const int64_t hi = min(last, root(top));
+        const int64_t lo = top - 2 * b < 0 ? 0 : root(top - 2 * b) + 1;
+        const int64_t first = (D == 3 ? tet(x) + tri(y) : tri(x)) - 1;
+        for (int64_t m = lo; m <= hi; ++m) {
+            const int perms = D == 2 ? (x == m ? 1 : 2) : (x == y && y == m ? 1 : (x == y || y == m ? 3 : 6));
+            const double w = double(perms * signs(x) * signs(m) * (D == 3 ? signs(y) : 1));
+            sum += w * S[first + m];
+            modes += w;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        sum += __shfl_xor(sum, o, 64);
+        modes += __shfl_xor(modes, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sh[0][threadIdx.x >> 6] = sum;
+        sh[1][threadIdx.x >> 6] = modes;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2)
+        out[threadIdx.x * nbins + b] = (sh[threadIdx.x][0] + sh[threadIdx.x][1]) + (sh[threadIdx.x][2] + sh[threadIdx.x][3]);
+}
+
 // rates of exactly 1 take the conserved-moment form (any other rate keeps its
 // class of moments from step to step)
 template <class L, class ST>
@@ -616,56 +675,42 @@ int fsc_linear_sk_radial(const fsc_params *p, double *host_shell_mean, int64_t *
     const int D = p->D, n = p->nx;
     if (n < 2 || p->ny != n || (D == 3 && p->nz != n) || (D == 2 && p->nz != 1)) return FSC_E_INVAL;
     LinArgs la;
-    const int rc = resolve_linear(p, la);
+    int rc = resolve_linear(p, la);
     if (rc) return rc;
     // the wave vectors of the fundamental domain of the square / cubic group,
-    // 0 <= m_z <= m_y <= m_x <= n/2 (formed on the device), each with the number
-    // of lattice modes it stands for (sign choices x distinct permutations)
+    // 0 <= m_z <= m_y <= m_x <= n/2, each with the number of lattice modes it stands
+    // for (sign choices x distinct permutations), and their shell sums: all on the
+    // device
     const int64_t h = n / 2;
-    const int64_t nk = (D == 2 ? (h + 1) * (h + 2) / 2 : (h + 1) * (h + 2) * (h + 3) / 6) - 1;
+    const int64_t nk = (D == 2 ? tri(h + 1) : tet(h + 1)) - 1;
+    const int64_t most = (D == 2 ? 2 * h : 3 * h) + 1;  // shells beyond are empty
+    const int nb = int(std::min<int64_t>(nbins, most));
     const hipStream_t st = static_cast<hipStream_t>(stream);
-    double *ds = nullptr;
-    if (hipMalloc(&ds, sizeof(double) * nk) != hipSuccess) {
-        (void)hipGetLastError();
-        return FSC_E_OOM;
-    }
+    ThreadWork &work = thread_work();
+    void *area = nullptr;
+    rc = work.take(sizeof(double) * (size_t(nk) + 2 * size_t(nb)), &area);
+    if (rc) return rc;
+    double *ds = static_cast<double *>(area), *sums = ds + nk;
+    std::vector<double> host(2 * size_t(nb));
+    Mailbox *box = sizeof(double) * host.size() <= ThreadWork::MAIL ? work.mailbox() : nullptr;
     hipError_t e = launch_linear(p, la, KSource{nullptr, nk, 2.0 * M_PI / n}, ds, st);
-    // modes and shells while the device works; the shell grows along c
-    std::vector<int64_t> mult(static_cast<size_t>(nk));
-    std::vector<int> bin(static_cast<size_t>(nk));
-    std::vector<double> S(static_cast<size_t>(nk));
-    auto signs = [&](int64_t v) { return (v == 0 || 2 * v == n) ? 1 : 2; };
-    size_t id = 0;
-    for (int64_t a = 0; a <= h; ++a) {
-        int64_t first = a;  // round(sqrt(a^2 + b^2)), which grows with b
-        for (int64_t b = 0; b <= a; ++b) {
-            const int64_t base = a * a + b * b;
-            while (base > first * first + first) ++first;
-            int64_t shell = first;
-            for (int64_t c = 0; c <= (D == 3 ? b : 0); ++c) {
-                if (a == 0) continue;
-                while (base + c * c > shell * shell + shell) ++shell;
-                const int perms = D == 2 ? (a == b ? 1 : 2) : (a == b && b == c ? 1 : (a == b || b == c ? 3 : 6));
-                mult[id] = perms * signs(a) * signs(b) * (D == 3 ? signs(c) : 1);
-                bin[id++] = int(shell);
-            }
-        }
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL((D == 3 ? k_linear_shells<3> : k_linear_shells<2>), dim3(unsigned(nb)), dim3(256), 0, st, ds,
+                           n, nb, sums);
+        e = hipGetLastError();
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(S.data(), ds, sizeof(double) * nk, hipMemcpyDeviceToHost, st);
-    const hipError_t es = hipStreamSynchronize(st);
+    if (e == hipSuccess)
+        e = box ? launch_mail(sums, 2 * nb, box->next(), st)
+                : hipMemcpyAsync(host.data(), sums, sizeof(double) * host.size(), hipMemcpyDeviceToHost, st);
+    const hipError_t es = box && e == hipSuccess ? box->wait(st) : hipStreamSynchronize(st);
     if (e == hipSuccess) e = es;
-    (void)hipFree(ds);
+    work.done(area);
     if (e != hipSuccess) return FSC_E_HIP;
-    std::vector<double> sum(size_t(nbins), 0.0);
-    std::vector<int64_t> cnt(size_t(nbins), 0);
-    for (size_t i = 0; i < size_t(nk); ++i) {
-        if (bin[i] >= nbins) continue;
-        sum[size_t(bin[i])] += double(mult[i]) * S[i];
-        cnt[size_t(bin[i])] += mult[i];
-    }
+    const double *sum = box ? box->data() : host.data(), *modes = sum + nb;
     for (int b = 0; b < nbins; ++b) {
-        host_shell_mean[b] = cnt[b] ? sum[b] / double(cnt[b]) : 0.0;
-        if (host_count) host_count[b] = cnt[b];
+        const bool any = b < nb && modes[b] > 0.0;
+        host_shell_mean[b] = any ? sum[b] / modes[b] : 0.0;
+        if (host_count) host_count[b] = any ? int64_t(modes[b]) : 0;
     }
     return FSC_OK;
 }
