@@ -249,7 +249,8 @@ int fsc_ens_load(fsc_ens *ens, const char *path);
  * dn^(k) = sum_x (n(x) - n0) e^{-i k.x} of the modes m = 1..nm along each
  * lattice axis (k = 2 pi m / side) as a row [D][nm][2] of doubles (real,
  * imaginary); rows past `capacity` are dropped.  Enabling (capacity >= 1,
- * 1 <= nm <= side/2) allocates and clears the rows; capacity 0 disables.
+ * 1 <= nm <= side/2) starts an empty record; capacity 0 disables, and so does a
+ * call that fails (of an ensemble: for every replica).
  * fsc_read_modes copies min(recorded, max_rows) rows to `out` and returns
  * the number recorded in *nrows.  Errors: FSC_E_INVAL, FSC_E_OOM, FSC_E_HIP. */
 int fsc_modes_enable(fsc_ctx *ctx, int nm, int capacity);

@@ -495,50 +495,56 @@ int enqueue_measure(fsc_ens *e, int par, uint32_t step_off, uint64_t advance = 0
     return FSC_OK;
 }
 
-// The stream is idle (the callers wait once for all replicas).
-int modes_enable(fsc_ens *e, Rep &r, int nm, int cap) {
-    r.modes_cap = 0;
-    r.modes_nm = 0;
-    r.modes_rows = 0;
-    const int sides[3] = {r.p.nx, r.p.ny, r.p.nz};
-    for (int d = 0; d < r.p.D && cap > 0; ++d)
-        if (nm > sides[d] / 2) return fail(e, FSC_E_INVAL, "nm exceeds half a side");
-    const size_t bytes = sizeof(double) * 2 * size_t(cap) * size_t(r.p.D) * size_t(nm);
-    if (r.d_modes && (cap == 0 || bytes > r.modes_bytes)) {
-        (void)hipFree(r.d_modes);
-        r.d_modes = nullptr;
-        r.modes_bytes = 0;
-    }
-    if (cap > 0) {
-        if (!r.d_modes) {
-            if (hipMalloc(&r.d_modes, bytes) != hipSuccess) {
-                (void)hipGetLastError();
-                r.d_modes = nullptr;
-                return fail(e, FSC_E_OOM, "mode recorder allocation failed");
-            }
-            r.modes_bytes = bytes;
+// Mode recorders of all replicas: all on, or (capacity 0, or the call fails) all
+// off.  A replica is switched on only when every one can be and the row counters,
+// one array, are cleared: the samples take their row from them.
+int modes_enable_all(fsc_ens *e, int nm, int cap) {
+    (void)hipStreamSynchronize(e->stream);
+    auto bytes = [&](const Rep &r) { return sizeof(double) * 2 * size_t(cap) * size_t(r.p.D) * size_t(nm); };
+    auto off = [&] {
+        for (auto &r : e->reps) {
+            if (r.d_modes) (void)hipFree(r.d_modes);
+            r.d_modes = nullptr;
+            r.modes_bytes = 0;
         }
+    };
+    bool fits = true;
+    for (auto &r : e->reps) {
+        r.modes_cap = 0;
+        r.modes_nm = 0;
+        r.modes_rows = 0;
+        const int sides[3] = {r.p.nx, r.p.ny, r.p.nz};
+        for (int d = 0; d < r.p.D && cap > 0; ++d) fits = fits && nm <= sides[d] / 2;
+    }
+    if (!fits || cap == 0) {
+        off();
+        return fits ? FSC_OK : fail(e, FSC_E_INVAL, "nm exceeds half a side");
+    }
+    bool got = e->d_modes_n || hipMalloc(&e->d_modes_n, sizeof(int) * e->reps.size()) == hipSuccess;
+    if (!got) e->d_modes_n = nullptr;
+    for (auto &r : e->reps) {
+        if (r.d_modes && bytes(r) > r.modes_bytes) {
+            (void)hipFree(r.d_modes);
+            r.d_modes = nullptr;
+        }
+        if (got && !r.d_modes) {
+            got = hipMalloc(&r.d_modes, bytes(r)) == hipSuccess;
+            if (!got) r.d_modes = nullptr;
+            r.modes_bytes = bytes(r);
+        }
+    }
+    if (!got) {
+        (void)hipGetLastError();
+        off();
+        return fail(e, FSC_E_OOM, "mode recorder allocation failed");
+    }
+    HIPCHK(e, hipMemsetAsync(e->d_modes_n, 0, sizeof(int) * e->reps.size(), e->stream));
+    for (size_t k = 0; k < e->reps.size(); ++k) {
+        Rep &r = e->reps[k];
+        r.d_modes_n = e->d_modes_n + k;
         r.modes_cap = cap;  // (only rows that a sample has filled are read)
         r.modes_nm = nm;
     }
-    return FSC_OK;
-}
-
-// Mode recorders of all replicas: their row counters are one array, cleared at once.
-int modes_enable_all(fsc_ens *e, int nm, int cap) {
-    (void)hipStreamSynchronize(e->stream);
-    const size_t n = e->reps.size();
-    if (!e->d_modes_n && hipMalloc(&e->d_modes_n, sizeof(int) * n) != hipSuccess) {
-        (void)hipGetLastError();
-        e->d_modes_n = nullptr;
-        return fail(e, FSC_E_OOM, "mode recorder allocation failed");
-    }
-    for (size_t k = 0; k < n; ++k) {
-        e->reps[k].d_modes_n = e->d_modes_n + k;
-        const int rc = modes_enable(e, e->reps[k], nm, cap);
-        if (rc) return rc;
-    }
-    HIPCHK(e, hipMemsetAsync(e->d_modes_n, 0, sizeof(int) * n, e->stream));
     return FSC_OK;
 }
 

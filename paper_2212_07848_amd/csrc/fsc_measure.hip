@@ -646,7 +646,7 @@ __device__ __forceinline__ void sk_bin(const MeasRep &m, const cplx<real> *a, in
             unsafeAtomicAdd(&t.mom[threadIdx.x], v);
         }
     }
-    if (mrow < m.modes_cap) {
+    if (mrow >= 0 && mrow < m.modes_cap) {
         // amplitudes of the modes 1 .. nm along each axis, row [D][nm][2]
         double *row = m.modes + size_t(mrow) * g.D * m.modes_nm * 2;
         auto put = [&](int d, int k, int l, int i) {

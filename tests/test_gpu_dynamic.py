@@ -2,6 +2,7 @@
 the recorder against a direct FFT of the density, the exact correlation
 routine against the oracle's linear operator, and the measured C(k, tau)
 and S(k, omega) against the exact linear values."""
+import ctypes
 import math
 
 import numpy as np
@@ -108,3 +109,36 @@ def test_measured_correlation_and_spectrum_match_the_linear_theory():
     omf = np.fft.fftfreq(M, d=every) * 2.0 * math.pi
     Sth = DY.theory_spectrum(plist[0], n, nm, every, omf, 6000)
     assert np.allclose(Sth.sum(axis=0) / (M * every), Cth[0].real, rtol=1e-9)
+
+
+def _rows(ens, r):
+    n = ctypes.c_int(-1)
+    assert fsc.lib().fsc_ens_read_modes(ens._h, r, None, 0, ctypes.byref(n)) == 0
+    return n.value
+
+
+def test_a_refused_recorder_is_off_for_every_replica_and_starts_afresh():
+    # 10 modes fit the first replica's 64 nodes and not the second's 16
+    ps = [fsc.make_params(D=2, nx=n, ny=n, stencil=4, precision="fp64", T_hat=0.9, rho0=0.5, kBT=1e-4, seed=3,
+                          replica=r) for r, n in enumerate((64, 16))]
+    ens = fsc.Ensemble(ps)
+    ens.init_uniform()
+    for valid_before in (False, True):
+        if valid_before:  # counters left by an earlier record must not show either
+            ens.modes_enable(4, 8)
+            ens.run(10, 2)
+            assert [_rows(ens, r) for r in range(2)] == [5, 5]
+        with pytest.raises(fsc.FscError):
+            ens.modes_enable(10, 8)
+        assert [_rows(ens, r) for r in range(2)] == [0, 0]
+        ens.run(6, 2)  # samples with the recorder off
+        assert [_rows(ens, r) for r in range(2)] == [0, 0]
+        ens.modes_enable(4, 8)
+        for row in range(2):
+            ens.run(2, 2)
+            for r in range(2):
+                d = np.fft.fft2(ens.density(r) - 0.5)
+                got = ens.read_modes(r)
+                assert got.shape[0] == row + 1
+                assert np.allclose(got[row], np.stack([d[0, 1:5], d[1:5, 0]]), rtol=1e-9, atol=1e-9)
+    ens.close()
