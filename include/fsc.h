@@ -252,7 +252,10 @@ int fsc_ens_load(fsc_ens *ens, const char *path);
  * 1 <= nm <= side/2) starts an empty record; capacity 0 disables, and so does a
  * call that fails (of an ensemble: for every replica).
  * fsc_read_modes copies min(recorded, max_rows) rows to `out` and returns
- * the number recorded in *nrows.  Errors: FSC_E_INVAL, FSC_E_OOM, FSC_E_HIP. */
+ * the number recorded in *nrows.  Samples that the caller captures into a graph
+ * of its own are recorded (here and in the time series) by every replay; such a
+ * graph ends with the next call that enables or disables either record.  Errors:
+ * FSC_E_INVAL, FSC_E_OOM, FSC_E_HIP. */
 int fsc_modes_enable(fsc_ctx *ctx, int nm, int capacity);
 int fsc_read_modes(fsc_ctx *ctx, double *out, int max_rows, int *nrows);
 int fsc_ens_modes_enable(fsc_ens *ens, int nm, int capacity);

@@ -65,15 +65,16 @@ struct Rep {
     double *d_mom = nullptr, *d_series = nullptr;
     int *d_series_n = nullptr;
     int series_cap = 0;
-    int64_t series_rows = 0;  // samples since it was enabled (the device counter's value)
+    int64_t series_rows = 0;  // eager samples since it was enabled (see fsc_ens::captured)
     // recorded axis-mode amplitudes per sample -- see fsc_modes_enable
     double *d_modes = nullptr;
     int *d_modes_n = nullptr;  // this replica's in fsc_ens::d_modes_n
     int modes_nm = 0, modes_cap = 0;
     int64_t modes_rows = 0;
     size_t modes_bytes = 0;
-    void sampled(int64_t n) {
+    void sampled(int64_t n, bool capturing = false) {
         nsamples += n;
+        if (capturing) return;
         if (series_cap > 0) series_rows += n;
         if (modes_cap > 0) modes_rows += n;
     }
@@ -129,6 +130,9 @@ struct fsc_ens {
     size_t work_bytes = 0;
     int *d_mpre = nullptr;
     int *d_modes_n = nullptr;  // [replica] rows of the mode recorder
+    // a caller's graph holds samples of this ensemble, now or once: only the device
+    // knows how many rows were recorded
+    bool captured = false;
     std::string err;
     std::map<std::pair<int, std::pair<int64_t, int64_t>>, GraphEntry> graphs;
 };
@@ -548,8 +552,25 @@ int modes_enable_all(fsc_ens *e, int nm, int cap) {
     return FSC_OK;
 }
 
+// Rows recorded: the host's count of eager samples (a read-out less), or the
+// device's once samples can come from a graph of the caller's.
+int recorded(fsc_ens *e, int64_t eager, const int *d_count, int cap, int *rows) {
+    int64_t n = eager;
+    if (e->captured && cap > 0) {
+        int c = 0;
+        StreamDrain drain{e->stream};
+        HIPCHK(e, hipMemcpyAsync(&c, d_count, sizeof(int), hipMemcpyDeviceToHost, e->stream));
+        HIPCHK(e, hipStreamSynchronize(e->stream));
+        n = c;
+    }
+    *rows = int(std::min<int64_t>(n, cap));
+    return FSC_OK;
+}
+
 int modes_read(fsc_ens *e, Rep &r, double *out, int max_rows, int *nrows) {
-    const int n = int(std::min<int64_t>(r.modes_rows, r.modes_cap));
+    int n = 0;
+    const int rc = recorded(e, r.modes_rows, r.d_modes_n, r.modes_cap, &n);
+    if (rc) return rc;
     const int m = std::min(n, max_rows);
     if (nrows) *nrows = n;
     if (m <= 0 || !out) return FSC_OK;
@@ -581,11 +602,13 @@ int series_enable(fsc_ens *e, Rep &r, int cap) {
 int series_read(fsc_ens *e, Rep &r, double *out, int max_rows, int *nrows, int *row_len) {
     const int len = 2 + r.n_rad;
     if (row_len) *row_len = len;
-    const int n = int(std::min<int64_t>(r.series_rows, r.series_cap));
+    int n = 0;
+    int rc = recorded(e, r.series_rows, r.d_series_n, r.series_cap, &n);
+    if (rc) return rc;
     if (nrows) *nrows = n;
     if (!out || max_rows <= 0 || n == 0) return FSC_OK;
     const int m = std::min(n, max_rows);
-    int rc = read_back(e, out, r.d_series, size_t(m) * size_t(len));
+    rc = read_back(e, out, r.d_series, size_t(m) * size_t(len));
     if (rc) return rc;
     for (int row = 0; row < m; ++row)
         for (int b = 0; b < r.n_rad; ++b)
@@ -1078,14 +1101,20 @@ int ens_autotune(fsc_ens *e) {
     return upload_desc(e);
 }
 
+// Whether the stream is being captured into a graph of the caller's.
+int stream_captures(fsc_ens *e, bool *capturing) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    HIPCHK(e, hipStreamIsCapturing(e->stream, &cs));
+    *capturing = cs != hipStreamCaptureStatusNone;
+    return FSC_OK;
+}
+
 // Whether runs go through the block kernel: small 2D lattices, unless the caller
 // has fixed a tiling or the autotuner found one that is faster.  A run that the
 // caller captures into a graph of its own takes one launch per step: an even
 // number of steps then leaves the state in the buffer that the next replay reads.
-int choose_blocks(fsc_ens *e) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    HIPCHK(e, hipStreamIsCapturing(e->stream, &cs));
-    if (cs != hipStreamCaptureStatusNone) {
+int choose_blocks(fsc_ens *e, bool capturing) {
+    if (capturing) {
         e->use_blocks = false;
         return FSC_OK;
     }
@@ -1125,8 +1154,11 @@ int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
             e->autotune = 0;
         }
     }
-    int rc_blocks = choose_blocks(e);
+    bool capturing = false;
+    int rc_blocks = stream_captures(e, &capturing);
+    if (rc_blocks == FSC_OK) rc_blocks = choose_blocks(e, capturing);
     if (rc_blocks) return rc_blocks;
+    e->captured = e->captured || (capturing && sk_every > 0);
     // whole chunks as graph replays; a graph holds the buffer of its first
     // launch, so a chunk must make an even number of launches (each launch
     // swaps the buffers)
@@ -1163,7 +1195,7 @@ int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
             it = e->graphs.emplace(key, ge).first;
         }
         for (int64_t c = 0; c < nchunks; ++c) HIPCHK(e, hipGraphLaunch(it->second.exec, e->stream));
-        for (auto &r : e->reps) r.sampled(nchunks * it->second.samples);
+        for (auto &r : e->reps) r.sampled(nchunks * it->second.samples, capturing);
         done = nchunks * chunk;
         e->step += done;
     }
@@ -1174,7 +1206,7 @@ int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
         int rc = enqueue_steps(e, e->cur, rest, sk_every, &samples, &flips);
         if (rc) return rc;
         e->cur ^= flips;
-        for (auto &r : e->reps) r.sampled(samples);
+        for (auto &r : e->reps) r.sampled(samples, capturing);
         e->step += rest;
     }
     return FSC_OK;
@@ -1600,9 +1632,13 @@ int fsc_measure_sk(fsc_ctx *ctx) {
     if (rc) return rc;
     rc = ensure_measure_plan(e);
     if (rc) return rc;
+    bool capturing = false;
+    rc = stream_captures(e, &capturing);
+    if (rc) return rc;
+    e->captured = e->captured || capturing;
     rc = enqueue_measure(e, e->cur, 0);
     if (rc) return rc;
-    r.sampled(1);
+    r.sampled(1, capturing);
     return FSC_OK;
 }
 

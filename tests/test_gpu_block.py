@@ -97,3 +97,38 @@ def test_steps_captured_by_the_caller_replay_like_eager_ones():
             stream.synchronize()
             ref.step(10)
             assert np.array_equal(lat.get_populations(), ref.get_populations())
+
+
+def test_samples_captured_by_the_caller_are_recorded_by_every_replay():
+    stream = torch.cuda.Stream()
+    p = _p(48, 48, 4, "fp64", 1e-5)
+    with fsc.Lattice(p, stream=stream) as lat, fsc.Lattice(p) as ref:
+        def rows():
+            a, b = lat.read_series(), ref.read_series()
+            assert np.array_equal(a["step"], b["step"])
+            for key in ("L", "S"):  # FP64 sums in another order
+                assert np.allclose(a[key], b[key], rtol=1e-12, atol=0.0)
+            assert np.array_equal(lat.read_modes(), ref.read_modes())
+            return len(a["step"])
+
+        for q in (lat, ref):
+            q.init_uniform()
+            q.series_enable(8)
+            q.modes_enable(3, 8)
+            q.step(3)
+            q.measure_sk()
+        stream.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream, capture_error_mode="thread_local"):
+            lat.run(2, 2)
+            lat.measure_sk()
+        assert rows() == 1  # a capture records nothing
+        for k in range(1, 4):
+            with torch.cuda.stream(stream):
+                g.replay()
+            ref.run(2, 2)
+            ref.measure_sk()
+            assert rows() == 1 + 2 * k
+        for q in (lat, ref):  # eager samples go on from there, up to the capacity
+            q.run(4, 2)
+        assert rows() == 8
