@@ -410,7 +410,7 @@ int ensure_fft(Rep &r, fsc_ens *e) {
         if (e->tabs.count(sides[d])) continue;
         const SkAxis x = sk_axis(sides[d], r.p.precision);
         void *tab = nullptr;
-        if (hipMalloc(&tab, 2 * r.esz * sk_table_len(x)) != hipSuccess) {
+        if (hipMalloc(&tab, sk_value_bytes(r.p.precision, x) * sk_table_len(x)) != hipSuccess) {
             (void)hipGetLastError();
             return fail(e, FSC_E_OOM, "transform table allocation failed");
         }
@@ -1851,7 +1851,10 @@ namespace {
 // passes over the chunk, one copy of its sums to the host.  Shared by
 // fsc_field_sk (which allocates the areas per call) and fsc_field_sk_noalloc
 // (which uses the library's static scratch).
-size_t field_tab_bytes(int L) { return (8 * sk_table_len(sk_axis(L, 0)) + 255) & ~size_t(255); }
+size_t field_tab_bytes(int L) {
+    const SkAxis x = sk_axis(L, 0);
+    return (sk_value_bytes(0, x) * sk_table_len(x) + 255) & ~size_t(255);
+}
 size_t field_spec_bytes(int L) { return 8 * size_t(L / 2 + 1) * L; }
 size_t field_work_bytes(int L, int nrad, int chunk) {
     return field_tab_bytes(L) + size_t(chunk) * (field_spec_bytes(L) + sizeof(double) * field_acc_len(nrad));

@@ -184,10 +184,14 @@ ThreadWork &thread_work();
 
 // Transform of one axis: lines of n values over m points, m = 2^logm (n itself,
 // or at least 2n - 1 for the chirp form), or m = n and logm = -1 (direct sum).
+// wide: a chirp transform of FP32 data, with its lines in LDS and its table in
+// doubles (see sk_axis).
 struct SkAxis {
-    int n, m, logm;
+    int n, m, logm, wide;
 };
 SkAxis sk_axis(int n, int precision);
+// bytes of a complex value of an axis' lines in LDS and of its table
+inline size_t sk_value_bytes(int precision, const SkAxis &x) { return precision == 0 && !x.wide ? 8 : 16; }
 // complex values of an axis' table: the m-th roots of unity, and for the chirp
 // form the chirp and its spectrum
 size_t sk_table_len(const SkAxis &x);
@@ -237,6 +241,7 @@ struct MeasPlan {
     std::vector<int> pre;    // [MK_COUNT][nrep + 1]: first block of each replica per kind
     size_t shm[MK_COUNT] = {};
     int threads[MK_COUNT] = {};
+    bool wide[MK_COUNT] = {};  // some replica's axis is wide
 };
 // Fills the block prefixes, block sizes and LDS sizes of P, and the transforms
 // of the host copy of the replica table; -1 if a side exceeds 8192 or a grid

@@ -394,8 +394,8 @@ __device__ __forceinline__ void sk_pow2(cplx<real> *a, int lines, int m, int log
 //     a product with the chirp's spectrum and an inverse transform, multiply by
 //     the chirp.  O(m log m) where the direct sum is O(n^2): at 750 x 487 in
 //     FP64 a sample's transforms took 458 us as direct sums;
-//   logm < 0 (FP64 lines beyond 4096 whose chirp form does not fit the LDS):
-//     the direct sum.
+//   logm < 0 (FP64 lines beyond 4096 whose chirp form does not fit the LDS): the
+//     direct sum.
 template <typename real>
 __device__ __forceinline__ void sk_fft(cplx<real> *a, int lines, const SkAxis &x, const cplx<real> *__restrict__ tab) {
     const int n = x.n, m = x.m, ls = sk_stride(m);
@@ -675,45 +675,64 @@ __device__ __forceinline__ void sk_unpack(const cplx<real> *line, int n, int k, 
 }
 
 // the rows y0, y0 + 1, .. of plane z as packed lines; val(x, y, z) is the field
-template <typename real, class Val>
-__device__ __forceinline__ void sk_load_rows(const Geometry &g, int y0, int z, int lines, int ls, cplx<real> *a, Val val) {
+template <typename T, class Val>
+__device__ __forceinline__ void sk_load_rows(const Geometry &g, int y0, int z, int lines, int ls, cplx<T> *a, Val val) {
     for (int id = threadIdx.x; id < lines * g.nx; id += blockDim.x) {
         const int l = id / g.nx, x = id % g.nx, y = y0 + 2 * l;
-        a[l * ls + sk_pad(x)] = {val(x, y, z), y + 1 < g.ny ? val(x, y + 1, z) : real(0)};
+        a[l * ls + sk_pad(x)] = {T(val(x, y, z)), y + 1 < g.ny ? T(val(x, y + 1, z)) : T(0)};
     }
 }
 
-template <typename real, class Val>
-__device__ __forceinline__ void sk_rows_block(const MeasRep &m, int blk, cplx<real> *a, Val val) {
+// In the three passes real is the type of the spectra in memory, T that of the
+// lines in LDS (double where the axis is wide).
+template <typename T, typename real, class Val>
+__device__ __forceinline__ void sk_rows_block(const MeasRep &m, int blk, unsigned char *smem, Val val) {
+    cplx<T> *a = reinterpret_cast<cplx<T> *>(smem);
     const Geometry &g = m.g;
     const int lc = m.lc[0], per = (g.ny + 2 * lc - 1) / (2 * lc);
     const int z = blk / per, y0 = (blk % per) * 2 * lc;
     const int lines = min(lc, (g.ny - y0 + 1) / 2), ls = sk_stride(m.ax[0].m);
-    sk_load_rows<real>(g, y0, z, lines, ls, a, val);
-    sk_fft<real>(a, lines, m.ax[0], static_cast<const cplx<real> *>(m.tab[0]));
+    sk_load_rows<T>(g, y0, z, lines, ls, a, val);
+    sk_fft<T>(a, lines, m.ax[0], static_cast<const cplx<T> *>(m.tab[0]));
     cplx<real> *out = static_cast<cplx<real> *>(m.cbuf);
     const int hx = g.nx / 2 + 1;
     for (int id = threadIdx.x; id < hx * lines; id += blockDim.x) {
         const int l = id % lines, k = id / lines, y = y0 + 2 * l;
-        cplx<real> r0, r1;
-        sk_unpack<real>(a + l * ls, g.nx, k, r0, r1);
+        cplx<T> r0, r1;
+        sk_unpack<T>(a + l * ls, g.nx, k, r0, r1);
         cplx<real> *o = out + (int64_t(k) * g.nz + z) * g.ny + y;
-        o[0] = r0;
-        if (y + 1 < g.ny) o[1] = r1;
+        o[0] = {real(r0.re), real(r0.im)};
+        if (y + 1 < g.ny) o[1] = {real(r1.re), real(r1.im)};
     }
 }
 
 // transform of `lines` contiguous lines of `in` into LDS
-template <typename real>
+template <typename T, typename real>
 __device__ __forceinline__ void sk_lines(const cplx<real> *__restrict__ in, int lines, const SkAxis &x, const void *tab,
-                                cplx<real> *a) {
+                                cplx<T> *a) {
     const int ls = sk_stride(x.m);
     for (int id = threadIdx.x; id < lines * x.n; id += blockDim.x)
-        a[(id / x.n) * ls + sk_pad(id % x.n)] = in[id];
-    sk_fft<real>(a, lines, x, static_cast<const cplx<real> *>(tab));
+        a[(id / x.n) * ls + sk_pad(id % x.n)] = {T(in[id].re), T(in[id].im)};
+    sk_fft<T>(a, lines, x, static_cast<const cplx<T> *>(tab));
 }
 
-template <typename real>
+// 3D: transform along y of lines (kx, z)
+template <typename T, typename real>
+__device__ __forceinline__ void sk_mid_block(const MeasRep &m, int blk, unsigned char *smem) {
+    cplx<T> *a = reinterpret_cast<cplx<T> *>(smem);
+    const Geometry &g = m.g;
+    const int lc = m.lc[1], per = (g.nz + lc - 1) / lc;
+    const int kx = blk / per, z0 = (blk % per) * lc, lines = min(lc, g.nz - z0), ls = sk_stride(m.ax[1].m);
+    sk_lines<T>(static_cast<const cplx<real> *>(m.cbuf) + (int64_t(kx) * g.nz + z0) * g.ny, lines, m.ax[1], m.tab[1], a);
+    cplx<real> *out = static_cast<cplx<real> *>(m.ctmp) + int64_t(kx) * g.ny * g.nz + z0;
+    for (int id = threadIdx.x; id < lines * g.ny; id += blockDim.x) {
+        const int l = id % lines, k = id / lines;
+        const cplx<T> v = a[l * ls + sk_pad(k)];
+        out[int64_t(k) * g.nz + l] = {real(v.re), real(v.im)};
+    }
+}
+
+template <typename T, typename real>
 __device__ __forceinline__ void sk_last_block(const MeasRep &m, int blk, unsigned char *smem) {
     const Geometry &g = m.g;
     const bool d3 = g.D == 3;
@@ -721,14 +740,14 @@ __device__ __forceinline__ void sk_last_block(const MeasRep &m, int blk, unsigne
     const int inner = d3 ? g.ny : g.nx / 2 + 1, lc = m.lc[2];
     const int per = (inner + lc - 1) / lc, o = blk / per, i0 = (blk % per) * lc;
     const int lines = min(lc, inner - i0), ls = sk_stride(x.m);
-    cplx<real> *a = reinterpret_cast<cplx<real> *>(smem);
-    double *wnd = lc > 1 ? reinterpret_cast<double *>(smem + sk_line_bytes(sizeof(cplx<real>), lc, x.m)) : nullptr;
+    cplx<T> *a = reinterpret_cast<cplx<T> *>(smem);
+    double *wnd = lc > 1 ? reinterpret_cast<double *>(smem + sk_line_bytes(sizeof(cplx<T>), lc, x.m)) : nullptr;
     const cplx<real> *in = static_cast<const cplx<real> *>(d3 ? m.ctmp : m.cbuf);
     // (asked for here, ahead of the transform)
     const int srow = m.t.mom && m.t.series ? m.t.series_n[0] : 0;
     const int mrow = m.modes_cap > 0 ? m.modes_n[0] - 1 : 0;  // k_sk_rows counted this sample
-    sk_lines<real>(in + (int64_t(o) * inner + i0) * x.n, lines, x, m.tab[d3 ? 2 : 1], a);
-    sk_bin<real>(m, a, ls, lines, o, i0, wnd, srow, mrow);
+    sk_lines<T>(in + (int64_t(o) * inner + i0) * x.n, lines, x, m.tab[d3 ? 2 : 1], a);
+    sk_bin<T>(m, a, ls, lines, o, i0, wnd, srow, mrow);
 }
 
 // ---------------------------------------------------------------------------
@@ -750,7 +769,9 @@ __device__ inline auto sk_density(const MeasRep &m, int par) {
     };
 }
 
-template <class L, typename real>
+// WIDE: some replica's lines are transformed in doubles (real is float); a kernel
+// of its own, so that the others keep their registers.
+template <class L, typename real, bool WIDE>
 __global__ void __launch_bounds__(1024) k_sk_rows(const MeasRep *__restrict__ mr, const int *__restrict__ pre,
                                                   int nrep, int par, uint64_t *__restrict__ step_base,
                                                   uint64_t advance) {
@@ -759,27 +780,18 @@ __global__ void __launch_bounds__(1024) k_sk_rows(const MeasRep *__restrict__ mr
     const int r = owner_of(pre, nrep, int(blockIdx.x));
     // the recorder's row counter, which nothing else in this launch reads
     if (threadIdx.x == 0 && int(blockIdx.x) == pre[r] && mr[r].modes_cap > 0) mr[r].modes_n[0] += 1;
-    sk_rows_block<real>(mr[r], int(blockIdx.x) - pre[r], reinterpret_cast<cplx<real> *>(smem_raw),
-                        sk_density<L, real>(mr[r], par));
+    const int blk = int(blockIdx.x) - pre[r];
+    if (WIDE && mr[r].ax[0].wide) sk_rows_block<double, real>(mr[r], blk, smem_raw, sk_density<L, real>(mr[r], par));
+    else sk_rows_block<real, real>(mr[r], blk, smem_raw, sk_density<L, real>(mr[r], par));
 }
 
-template <typename real>
+template <typename real, bool WIDE>
 __global__ void __launch_bounds__(1024) k_sk_mid(const MeasRep *__restrict__ mr, const int *__restrict__ pre,
                                                  int nrep) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-    cplx<real> *a = reinterpret_cast<cplx<real> *>(smem_raw);
-    const int r = owner_of(pre, nrep, int(blockIdx.x));
-    const MeasRep &m = mr[r];
-    const Geometry &g = m.g;
-    const int blk = int(blockIdx.x) - pre[r], lc = m.lc[1], per = (g.nz + lc - 1) / lc;
-    const int kx = blk / per, z0 = (blk % per) * lc, lines = min(lc, g.nz - z0), ls = sk_stride(m.ax[1].m);
-    sk_lines<real>(static_cast<const cplx<real> *>(m.cbuf) + (int64_t(kx) * g.nz + z0) * g.ny, lines, m.ax[1],
-                   m.tab[1], a);
-    cplx<real> *out = static_cast<cplx<real> *>(m.ctmp) + int64_t(kx) * g.ny * g.nz + z0;
-    for (int id = threadIdx.x; id < lines * g.ny; id += blockDim.x) {
-        const int l = id % lines, k = id / lines;
-        out[int64_t(k) * g.nz + l] = a[l * ls + sk_pad(k)];
-    }
+    const int r = owner_of(pre, nrep, int(blockIdx.x)), blk = int(blockIdx.x) - pre[r];
+    if (WIDE && mr[r].ax[1].wide) sk_mid_block<double, real>(mr[r], blk, smem_raw);
+    else sk_mid_block<real, real>(mr[r], blk, smem_raw);
 }
 
 // The replica's last block to finish closes the sample (series row, counter).
@@ -800,29 +812,40 @@ __device__ __forceinline__ void sk_finish(const MeasRep &m, int blocks, const ui
     if (blocks > 1) __hip_atomic_store(m.done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <typename real>
+template <typename real, bool WIDE>
 __global__ void __launch_bounds__(1024) k_sk_last(const MeasRep *__restrict__ mr, const int *__restrict__ pre,
                                                   int nrep, const uint64_t *__restrict__ step_base,
                                                   uint32_t step_off) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int r = owner_of(pre, nrep, int(blockIdx.x));
-    sk_last_block<real>(mr[r], int(blockIdx.x) - pre[r], smem_raw);
+    const int blk = int(blockIdx.x) - pre[r];
+    if (WIDE && mr[r].ax[mr[r].g.D - 1].wide) sk_last_block<double, real>(mr[r], blk, smem_raw);
+    else sk_last_block<real, real>(mr[r], blk, smem_raw);
     sk_finish(mr[r], pre[r + 1] - pre[r], step_base, step_off);
 }
 
 // ---------------------------------------------------------------------------
 // Host side of the plan.
 // ---------------------------------------------------------------------------
-constexpr size_t SK_LDS = 160 * 1024 - 512;  // dynamic part
+constexpr size_t SK_LDS = 160 * 1024 - 1024;  // dynamic part
 
-static int sk_cap(int precision) { return precision == 0 ? 16384 : 8192; }  // lines x m of one block
+static int sk_cap(size_t csz) { return csz == 8 ? 16384 : 8192; }  // lines x m of one block, in values of csz bytes
 
+// The chirp form takes doubles, of FP32 data too, as far as they fit the LDS (sides
+// up to 4096).  In floats its two transforms and three products with rounded tables
+// lose a relative 2e-7 of every |X|^2 (white fields of side 48 to 4100; direct FP32
+// sums 1e-9 to 7e-8) and leave 4 to 8 times the noise of direct sums where a spectrum
+// is steep.  A sample of 100^2 takes 18.2 us so and 17.1 in floats, 1000^2 71 and 66,
+// 3000^2 690 and 440 (direct sums: 29, 1833, 58100).  Beyond 4096 direct sums are the
+// noisier ones (0.2 sqrt(n) of a rounding, the chirp 2.4), and it stays in floats, with
+// the loss taken out (root_loss).
 SkAxis sk_axis(int n, int precision) {
-    SkAxis x{n, 1, 0};
+    SkAxis x{n, 1, 0, 0};
     const bool pow2 = (n & (n - 1)) == 0;
     while (x.m < (pow2 ? n : 2 * n - 1)) x.m <<= 1;
     while ((1 << x.logm) < x.m) ++x.logm;
-    if (x.m > sk_cap(precision)) x.m = n, x.logm = -1;
+    x.wide = precision == 0 && !pow2 && x.m <= sk_cap(16);
+    if (x.m > sk_cap(sk_value_bytes(precision, x))) x = SkAxis{n, n, -1, 0};
     return x;
 }
 
@@ -870,10 +893,39 @@ static void chirp_spectrum(const SkAxis &x, std::vector<double> &re, std::vector
     }
 }
 
+// Power left, on average over the inputs, of a chirp transform with tables rounded to
+// floats (1 - 1.2e-7 beyond 4096 points; exact arithmetic on the same tables agrees to
+// 4e-9): the mean |root|^2 over each pass, the chirp's twice and its spectrum's.
+static double root_loss(const SkAxis &x, const std::vector<double> &re, const std::vector<double> &im) {
+    auto sq = [](double a, double b) { return double(float(a)) * float(a) + double(float(b)) * float(b); };
+    auto root = [&](int64_t k) { return sq(std::cos(2.0 * M_PI * double(k) / x.m), std::sin(2.0 * M_PI * double(k) / x.m)); };
+    double fft = 1.0;
+    for (int nsl = 0; nsl < x.logm;) {
+        const int lr = std::min(3, x.logm - nsl), R = 1 << lr;
+        double sum = 0.0;
+        for (int64_t k = 0; nsl > 0 && k < (int64_t(1) << nsl); ++k)
+            for (int r = 1; r < R; ++r) sum += root((k << (x.logm - lr - nsl)) * r);
+        if (nsl > 0) fft *= (1.0 + sum / double(1 << nsl)) / R;
+        if (lr == 3) fft *= 1.0 + (sq(std::sqrt(0.5), std::sqrt(0.5)) - 1.0) / 4.0;  // two of the eight
+        nsl += lr;
+    }
+    double chirp = 0.0, spec = 0.0, exact = 0.0;
+    for (int64_t j = 0; j < x.n; ++j) {
+        const double a = M_PI * double((j * j) % (2 * x.n)) / x.n;
+        chirp += sq(std::cos(a), std::sin(a)) / x.n;
+    }
+    for (size_t k = 0; k < re.size(); ++k) {
+        spec += sq(re[k], im[k]);
+        exact += re[k] * re[k] + im[k] * im[k];
+    }
+    return fft * fft * chirp * chirp * spec / exact;
+}
+
 hipError_t sk_table(int precision, const SkAxis &x, void *tab, void *zero, int64_t zero_words, hipStream_t s) {
     const int64_t n = std::max(int64_t(sk_table_len(x)), zero_words);
     const dim3 nb(unsigned((n + 255) / 256));
-    if (precision == 0)
+    const size_t csz = sk_value_bytes(precision, x);
+    if (csz == 8)
         hipLaunchKernelGGL(k_sk_table<float>, nb, dim3(256), 0, s, static_cast<cplx<float> *>(tab), x,
                            static_cast<uint32_t *>(zero), zero_words);
     else
@@ -883,11 +935,12 @@ hipError_t sk_table(int precision, const SkAxis &x, void *tab, void *zero, int64
     if (e != hipSuccess || x.logm < 0 || x.m == x.n) return e;
     std::vector<double> re, im;
     chirp_spectrum(x, re, im);
-    const size_t csz = precision == 0 ? 8 : 16, m = size_t(x.m);
+    const size_t m = size_t(x.m);
     std::vector<double> d(2 * m);
-    if (precision == 0) {
+    if (csz == 8) {
+        const double up = 1.0 / std::sqrt(root_loss(x, re, im));
         float *f = reinterpret_cast<float *>(d.data());
-        for (size_t k = 0; k < m; ++k) f[2 * k] = float(re[k]), f[2 * k + 1] = float(im[k]);
+        for (size_t k = 0; k < m; ++k) f[2 * k] = float(re[k] * up), f[2 * k + 1] = float(im[k] * up);
     } else {
         for (size_t k = 0; k < m; ++k) d[2 * k] = re[k], d[2 * k + 1] = im[k];
     }
@@ -900,8 +953,8 @@ hipError_t sk_table(int precision, const SkAxis &x, void *tab, void *zero, int64
 // Lines per block: enough to write pieces of 64 to 256 bytes (of up to 16384
 // values, whose LDS still leaves a block its 160 KB), but not so many that an
 // axis with few lines leaves CUs without a block.
-static int sk_lines_per_block(int m, int precision, int64_t lines) {
-    const int cap = sk_cap(precision), base = precision == 0 ? 8192 : 4096;
+static int sk_lines_per_block(int m, size_t csz, int64_t lines) {
+    const int cap = sk_cap(csz), base = cap / 2;
     int lc = std::min(16, std::max(std::max(1, base / m), std::min(4, cap / m)));
     while (lc > 2 && lines / lc < 512) lc >>= 1;
     return std::max(1, std::min(lc, cap / m));
@@ -919,10 +972,9 @@ static size_t sk_window(const Geometry &g, int lc) {
 int measure_plan(MeasRep *reps, int nrep, MeasPlan &P) {
     P.nrep = nrep;
     P.pre.assign(size_t(MK_COUNT) * (nrep + 1), 0);
-    for (int k = 0; k < MK_COUNT; ++k) P.shm[k] = 0, P.threads[k] = 256;
+    for (int k = 0; k < MK_COUNT; ++k) P.shm[k] = 0, P.threads[k] = 256, P.wide[k] = false;
     if (nrep < 1) return -1;
     const int D = reps[0].g.D, prec = P.esz == 4 ? 0 : 1;
-    const size_t csz = 2 * P.esz;
     P.D = D;
     int64_t nlines[3] = {};
     for (int r = 0; r < nrep; ++r) {
@@ -945,25 +997,26 @@ int measure_plan(MeasRep *reps, int nrep, MeasPlan &P) {
         for (int k = 0; k < 3; ++k) {
             const int d = k == 2 ? D - 1 : k;
             if (k == 1 && D == 2) continue;
-            m.lc[k] = sk_lines_per_block(m.ax[d].m, prec, nlines[k]);
+            m.lc[k] = sk_lines_per_block(m.ax[d].m, sk_value_bytes(prec, m.ax[d]), nlines[k]);
+            P.wide[k] = P.wide[k] || m.ax[d].wide;
         }
         const SkAxis &last = m.ax[D - 1];
-        while (m.lc[2] > 1 && sk_line_bytes(csz, m.lc[2], last.m) + sk_window(g, m.lc[2]) > SK_LDS) m.lc[2] >>= 1;
+        auto line_bytes = [&](const SkAxis &x, int lc) { return sk_line_bytes(sk_value_bytes(prec, x), lc, x.m); };
+        while (m.lc[2] > 1 && line_bytes(last, m.lc[2]) + sk_window(g, m.lc[2]) > SK_LDS) m.lc[2] >>= 1;
         int64_t n[MK_COUNT] = {};
         auto need = [&](int k, size_t shm, int threads) {
             P.shm[k] = std::max(P.shm[k], shm);
             P.threads[k] = std::max(P.threads[k], threads);
         };
         n[MK_ROWS] = int64_t((g.ny + 2 * m.lc[0] - 1) / (2 * m.lc[0])) * g.nz;
-        need(MK_ROWS, sk_line_bytes(csz, m.lc[0], m.ax[0].m), sk_threads(m.lc[0], m.ax[0].m));
+        need(MK_ROWS, line_bytes(m.ax[0], m.lc[0]), sk_threads(m.lc[0], m.ax[0].m));
         if (D == 3) {
             n[MK_MID] = int64_t(hx) * ((g.nz + m.lc[1] - 1) / m.lc[1]);
-            need(MK_MID, sk_line_bytes(csz, m.lc[1], m.ax[1].m), sk_threads(m.lc[1], m.ax[1].m));
+            need(MK_MID, line_bytes(m.ax[1], m.lc[1]), sk_threads(m.lc[1], m.ax[1].m));
         }
         const int inner = D == 3 ? g.ny : hx;
         n[MK_LAST] = int64_t((inner + m.lc[2] - 1) / m.lc[2]) * (D == 3 ? hx : 1);
-        need(MK_LAST, sk_line_bytes(csz, m.lc[2], last.m) + (m.lc[2] > 1 ? sk_window(g, m.lc[2]) : 0),
-             sk_threads(m.lc[2], last.m));
+        need(MK_LAST, line_bytes(last, m.lc[2]) + (m.lc[2] > 1 ? sk_window(g, m.lc[2]) : 0), sk_threads(m.lc[2], last.m));
         for (int k = 0; k < MK_COUNT; ++k) {
             P.pre[size_t(k) * (nrep + 1) + r] = int(tot[k]);
             tot[k] += n[k];
@@ -984,12 +1037,13 @@ static hipError_t measure_impl(const MeasPlan &P, const MeasRep *mr, const int *
     auto grid = [&](int k) { return dim3(unsigned(P.pre[size_t(k) * (nrep + 1) + nrep])); };
     auto pk = [&](int k) { return pre + size_t(k) * (nrep + 1); };
     auto block = [&](int k) { return dim3(unsigned(P.threads[k])); };
-    hipLaunchKernelGGL((k_sk_rows<L, real>), grid(MK_ROWS), block(MK_ROWS), P.shm[MK_ROWS], s, mr, pk(MK_ROWS),
-                       nrep, par, step_base, advance);
-    if (L::D == 3)
-        hipLaunchKernelGGL(k_sk_mid<real>, grid(MK_MID), block(MK_MID), P.shm[MK_MID], s, mr, pk(MK_MID), nrep);
-    hipLaunchKernelGGL(k_sk_last<real>, grid(MK_LAST), block(MK_LAST), P.shm[MK_LAST], s, mr, pk(MK_LAST), nrep,
-                       step_base, step_off);
+    constexpr bool F32 = sizeof(real) == 4;  // doubles have no wide axes
+    auto launch = [&](int k, auto narrow, auto wide, auto... args) {
+        hipLaunchKernelGGL(P.wide[k] ? wide : narrow, grid(k), block(k), P.shm[k], s, mr, pk(k), nrep, args...);
+    };
+    launch(MK_ROWS, k_sk_rows<L, real, false>, k_sk_rows<L, real, F32>, par, step_base, advance);
+    if (L::D == 3) launch(MK_MID, k_sk_mid<real, false>, k_sk_mid<real, F32>);
+    launch(MK_LAST, k_sk_last<real, false>, k_sk_last<real, F32>, step_base, step_off);
     return hipGetLastError();
 }
 
@@ -1030,19 +1084,21 @@ __device__ inline MeasRep field_rep(const FieldJob &j, int f) {
     return m;
 }
 
+template <typename T>
 __global__ void __launch_bounds__(1024) k_field_rows(FieldJob j, int per) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const int f = int(blockIdx.x) / per;
     const MeasRep m = field_rep(j, f);
     const float *src = j.fields + size_t(f) * j.n * j.n;
-    sk_rows_block<float>(m, int(blockIdx.x) % per, reinterpret_cast<cplx<float> *>(smem_raw),
-                         [&](int x, int y, int) { return src[size_t(y) * j.n + x]; });
+    sk_rows_block<T, float>(m, int(blockIdx.x) % per, smem_raw,
+                            [&](int x, int y, int) { return src[size_t(y) * j.n + x]; });
 }
 
+template <typename T>
 __global__ void __launch_bounds__(1024) k_field_last(FieldJob j, int per) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     const MeasRep m = field_rep(j, int(blockIdx.x) / per);
-    sk_last_block<float>(m, int(blockIdx.x) % per, smem_raw);
+    sk_last_block<T, float>(m, int(blockIdx.x) % per, smem_raw);
 }
 
 hipError_t launch_field_sk(const float *fields, int batch, int n, int n_rad, void *spec, const void *tab,
@@ -1050,15 +1106,16 @@ hipError_t launch_field_sk(const float *fields, int batch, int n, int n_rad, voi
     FieldJob j{fields, static_cast<cplx<float> *>(spec), acc, tab, sk_axis(n, 0), n, n_rad, 0, 0};
     const Geometry g{2, n, n, 1, int64_t(n) * n};
     const int hx = n / 2 + 1;
-    j.lc_rows = sk_lines_per_block(j.ax.m, 0, int64_t(batch) * ((n + 1) / 2));
-    j.lc_last = sk_lines_per_block(j.ax.m, 0, int64_t(batch) * hx);
-    while (j.lc_last > 1 && sk_line_bytes(8, j.lc_last, j.ax.m) + sk_window(g, j.lc_last) > SK_LDS) j.lc_last >>= 1;
+    const size_t csz = sk_value_bytes(0, j.ax);
+    j.lc_rows = sk_lines_per_block(j.ax.m, csz, int64_t(batch) * ((n + 1) / 2));
+    j.lc_last = sk_lines_per_block(j.ax.m, csz, int64_t(batch) * hx);
+    while (j.lc_last > 1 && sk_line_bytes(csz, j.lc_last, j.ax.m) + sk_window(g, j.lc_last) > SK_LDS) j.lc_last >>= 1;
     const int pr = (n + 2 * j.lc_rows - 1) / (2 * j.lc_rows), pl = (hx + j.lc_last - 1) / j.lc_last;
     if (int64_t(batch) * std::max(pr, pl) > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_field_rows, dim3(unsigned(batch * pr)), dim3(unsigned(sk_threads(j.lc_rows, j.ax.m))),
-                       sk_line_bytes(8, j.lc_rows, j.ax.m), s, j, pr);
-    hipLaunchKernelGGL(k_field_last, dim3(unsigned(batch * pl)), dim3(unsigned(sk_threads(j.lc_last, j.ax.m))),
-                       sk_line_bytes(8, j.lc_last, j.ax.m) + (j.lc_last > 1 ? sk_window(g, j.lc_last) : 0), s, j, pl);
+    hipLaunchKernelGGL(j.ax.wide ? k_field_rows<double> : k_field_rows<float>, dim3(unsigned(batch * pr)), dim3(unsigned(sk_threads(j.lc_rows, j.ax.m))),
+                       sk_line_bytes(csz, j.lc_rows, j.ax.m), s, j, pr);
+    hipLaunchKernelGGL(j.ax.wide ? k_field_last<double> : k_field_last<float>, dim3(unsigned(batch * pl)), dim3(unsigned(sk_threads(j.lc_last, j.ax.m))),
+                       sk_line_bytes(csz, j.lc_last, j.ax.m) + (j.lc_last > 1 ? sk_window(g, j.lc_last) : 0), s, j, pl);
     return hipGetLastError();
 }
 

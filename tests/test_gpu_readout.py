@@ -53,3 +53,71 @@ def test_structure_factor_readout_at_the_polled_size(nx):
             got, sq, cnt = lat.read_sk(fsc.FSC_SK_AXIS)
             ref = O.sk_sample(O.density(f))["axis"][0]
             assert np.allclose(got[:, : ref.shape[1]], k * ref, rtol=1e-9, atol=1e-9 * ref.max())
+
+
+def _shells(P):
+    n = P.shape[0]
+    m = np.minimum(np.arange(n), n - np.arange(n))
+    b = O.radial_bins_of((m[:, None] ** 2 + m[None] ** 2).ravel())
+    cnt = np.bincount(b).astype(float)
+    cnt[0] -= 1.0
+    w = P.ravel().copy()
+    w[0] = 0.0
+    return np.bincount(b, weights=w) / np.maximum(cnt, 1.0)
+
+
+# sides that are no power of two: chirp transforms of 8 points to 8192 in doubles,
+# and beyond 4096 in floats
+@pytest.mark.parametrize("n", [3, 5, 33, 48, 90, 100, 150, 301, 487, 750, 1000, 2047, 4095, 4097])
+def test_field_spectra_of_odd_sides_lose_no_norm(n):
+    """White fields, every |X|^2 / N about 1.  The half spectra are rounded to FP32
+    between the axes: 2^-24 / sqrt(3) of a value (rms), 5e-8 of a mode's |X|^2, less
+    in a shell of many, and no bias.  A chirp in floats adds 2.4 roundings of 2^-24 per
+    axis to a mode."""
+    torch = pytest.importorskip("torch")
+    batch = 8 if n < 400 else (2 if n < 2000 else 1)
+    rng = np.random.default_rng(n)
+    f = rng.normal(size=(batch, n, n)).astype(np.float32)
+    got, _ = fsc.field_sk(torch.from_numpy(f).cuda(), batch, n)
+    e = []
+    for b in range(batch):
+        ref = _shells(np.abs(np.fft.fft2(f[b].astype(np.float64))) ** 2 / n ** 2)[1:]
+        e.append((got[b][1:] - ref) / np.maximum(ref, 1.0))
+    e = np.concatenate(e)
+    assert abs(e.mean()) < 5e-8
+    assert np.sqrt(np.mean(e * e)) < 1e-7
+
+
+@pytest.mark.parametrize("n", [48, 90, 100, 150, 301])
+def test_field_spectra_of_odd_sides_keep_the_tail_of_a_steep_one(n):
+    """Spectra that fall by 8 decades.  The rounding between the axes leaves noise of
+    power (2^-24)^2 times a column's mean power, s, in every mode P: 2 sqrt(P s) + s,
+    and four times that is allowed."""
+    torch = pytest.importorskip("torch")
+    k = np.hypot(np.fft.fftfreq(n)[:, None], np.fft.fftfreq(n)[None]) * n
+    f = np.fft.ifft2(np.fft.fft2(np.random.default_rng(n).normal(size=(n, n))) / (1.0 + (k / 4.0) ** 4)).real
+    f = (f / f.std()).astype(np.float32)
+    got, _ = fsc.field_sk(torch.from_numpy(f[None]).cuda(), 1, n)
+    P = np.abs(np.fft.fft2(f.astype(np.float64))) ** 2 / n ** 2
+    ref, s = _shells(P), 2.0 ** -48 * P.mean(0).max()
+    assert np.all(np.abs(got[0] - ref)[1:] <= 4.0 * (2.0 * np.sqrt(ref * s) + s)[1:])
+
+
+@pytest.mark.parametrize("sides", [[(64, 64), (30, 64), (64, 45), (7, 128)],
+                                   [(16, 12, 10), (8, 16, 16), (9, 8, 12), (4, 7, 8)]])
+def test_samples_of_replicas_with_even_and_odd_sides(sides):
+    D = len(sides[0])
+    ps = [fsc.make_params(D=D, nx=s[-1], ny=s[-2], nz=s[0] if D == 3 else 1, stencil=4, precision="fp32", T_hat=0.8,
+                          rho0=0.62, kBT=1e-5, seed=5, replica=r) for r, s in enumerate(sides)]
+    ens = fsc.Ensemble(ps)
+    ens.init_uniform()
+    ens.run(4, 4)
+    for r, s in enumerate(sides):
+        P = np.abs(np.fft.fftn(ens.get_populations(r).sum(0) - 0.62)) ** 2 / np.prod(s)
+        got = ens.read_sk(r)[0]
+        for d in range(D):  # axis d = 0 is x, the last one of the array
+            line = np.moveaxis(P, D - 1 - d, 0).reshape(s[D - 1 - d], -1)[:, 0]
+            m = line.size
+            ref = [line[q] + (line[m - q] if 2 * q != m else 0.0) for q in range(1, m // 2 + 1)]
+            assert np.allclose(got[d, 1:m // 2 + 1], ref, rtol=1e-5, atol=1e-6 * np.mean(P))
+    ens.close()
