@@ -1167,8 +1167,8 @@ __global__ void __launch_bounds__(768) k_mid_wgrad(const bf16 *__restrict__ dz,
 // gradient (activation) of the 32 channels, the other an FP32 field per input
 // channel, the network input X formed from the fields (or dy = g - <g>).  Each
 // FP32 value enters as three BF16 parts that sum to it exactly, so that the
-// products are exact and the sums FP32, as with FP32 factors: columns (part,
-// ci, tap) of the second operand, 27 per input channel, then one of ones
+// products are exact and the sums FP32, as with FP32 factors (split_field): columns
+// (part, ci, tap) of the second operand, 27 per input channel, then one of ones
 // (sum_p dZ[p][co], the first layer's bias).  Four waves, four rows of the
 // tile each.  It reads 64 + 4K B per pixel.  Measured at 32 images of 128^2:
 // 21.1 us (first, K = 2) and 14.9 us (last); one lane per channel
@@ -1179,6 +1179,19 @@ template <int K>
 constexpr int wg_edge_tiles() { return K == 1 ? 2 : 4; }  // columns / 16
 template <int K>
 constexpr int wg_edge_len() { return wg_edge_tiles<K>() * 512 + 1; }
+
+// v = hi + mid + lo, each the leading 8 bits of what the ones before it leave.  Cut
+// off, not rounded: a v beyond the largest BF16 value would round to infinity, and
+// parts of one sign overflow to one infinity.  An infinite v is its first part.
+__device__ __forceinline__ void split_field(float v, uint16_t (&part)[3]) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const uint32_t bits = __builtin_bit_cast(uint32_t, v) & 0xffff0000u;
+        const float lead = __builtin_bit_cast(float, bits);
+        part[k] = uint16_t(bits >> 16);
+        v = v == lead ? 0.f : v - lead;
+    }
+}
 
 template <int K, bool LAST>
 __global__ void __launch_bounds__(256) k_edge_wgrad(const bf16 *__restrict__ act, const float *__restrict__ cur,
@@ -1240,13 +1253,10 @@ __global__ void __launch_bounds__(256) k_edge_wgrad(const bf16 *__restrict__ act
             if (LAST && r >= 1 && r <= WG_TR && c >= 1 && c <= WG_TW && y0 - 1 + r < H) fsum += double(v[0]);
 #pragma unroll
             for (int ci = 0; ci < K; ++ci) {
-                const bf16 hi = bf16(v[ci]);
-                const float r1 = v[ci] - float(hi);
-                const bf16 mid = bf16(r1);
-                const bf16 lo = bf16(r1 - float(mid));
-                sx[(ci * 3 + 0) * PL + k] = __builtin_bit_cast(uint16_t, hi);
-                sx[(ci * 3 + 1) * PL + k] = __builtin_bit_cast(uint16_t, mid);
-                sx[(ci * 3 + 2) * PL + k] = __builtin_bit_cast(uint16_t, lo);
+                uint16_t part[3];
+                split_field(v[ci], part);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) sx[(ci * 3 + q) * PL + k] = part[q];
             }
         }
         __syncthreads();

@@ -338,3 +338,23 @@ def test_marching_pairs_equal_single_layers(H, W, B, layers):
     sur.close()
     assert torch.isfinite(got[0]).all()
     assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+
+
+def test_first_layer_gradient_of_a_field_beyond_the_largest_bf16():
+    # A pixel of 3.4e38 (FP32, above BF16's 3.39e38).  Where its weight is negative the
+    # activation's derivative is zero, and zero times the pixel is zero; elsewhere the
+    # product overflows to one infinity.
+    B, H, W = 1, 8, 32
+    rng = np.random.default_rng(2)
+    rho = (1.0 + 0.3 * rng.normal(size=(B, H, W))).astype(np.float32)
+    rho[0, 3, 7] = 3.4e38
+    tgt = rho.copy()
+    tgt[rho < 10] += 0.05
+    sur = fsc.Surrogate(3, H, W, B, seed=1, in_ch=1)
+    sur.set_norm(0.0, 1.0, 1.0)
+    w = sur.get_params()[:32 * 9]
+    _, g = sur.grad(None, _dev(rho), _dev(tgt), B)
+    sur.close()
+    g = g[:32 * 9]
+    assert np.all(np.isfinite(g[w < 0]))
+    assert not np.any(np.isnan(g))
