@@ -10,6 +10,7 @@
 #include <map>
 #include <memory>
 #include <string>
+#include <tuple>
 #include <utility>
 #include <vector>
 
@@ -134,7 +135,8 @@ struct fsc_ens {
     // knows how many rows were recorded
     bool captured = false;
     std::string err;
-    std::map<std::pair<int, std::pair<int64_t, int64_t>>, GraphEntry> graphs;
+    // by buffer and kernels of the first launch, steps of the chunk, sampling interval
+    std::map<std::tuple<int, int64_t, int64_t>, GraphEntry> graphs;
 };
 
 struct fsc_ctx {
@@ -1124,7 +1126,6 @@ int choose_blocks(fsc_ens *e, bool capturing) {
         if (rc) return rc;
         use = !e->blocks.empty();
     }
-    if (use != e->use_blocks) drop_graphs(e);
     e->use_blocks = use;
     return FSC_OK;
 }
@@ -1171,7 +1172,7 @@ int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
     const int64_t nchunks = nsteps / chunk;
     if (nchunks >= 2) {
         const int parity = e->cur;
-        auto key = std::make_pair(parity, std::make_pair(chunk, sk_every));
+        const auto key = std::make_tuple(parity + (e->use_blocks ? 2 : 0), chunk, sk_every);
         auto it = e->graphs.find(key);
         if (it == e->graphs.end()) {
             TraceRange trace_capture("fsc capture chunk");
