@@ -1130,7 +1130,7 @@ int choose_blocks(fsc_ens *e, bool capturing) {
     return FSC_OK;
 }
 
-constexpr int CHUNK_SAMPLES = 8;
+constexpr int CHUNK_SAMPLES = 8, CHUNK_STEPS = 128;
 
 int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
     TraceRange trace_("fsc run");
@@ -1166,8 +1166,9 @@ int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
     int64_t chunk = sk_every > 0 ? sk_every : 64;
     for (int k = 0; k < 4 && (count_launches(e, chunk, sk_every) & 1); ++k) chunk *= 2;
     // a replay costs a few us between graphs: chunks of frequent samples are
-    // several sampling intervals long
-    while (sk_every > 0 && chunk / sk_every < CHUNK_SAMPLES && 4 * chunk <= nsteps) chunk *= 2;
+    // several sampling intervals long (not of rare ones, where capturing a graph of
+    // thousands of steps costs more than the gaps)
+    while (sk_every > 0 && chunk / sk_every < CHUNK_SAMPLES && chunk <= CHUNK_STEPS && 4 * chunk <= nsteps) chunk *= 2;
     int64_t done = 0;
     const int64_t nchunks = nsteps / chunk;
     if (nchunks >= 2) {
