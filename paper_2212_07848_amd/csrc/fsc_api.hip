@@ -353,30 +353,40 @@ int read_back(fsc_ens *e, double *dst, const double *src, size_t n) {
 }
 
 // `count` doubles that launch(first, n, out) forms, n at a time (multiples of
-// `unit`), into the caller's memory
+// `unit`), into the caller's memory: by way of the pinned buffer alone, and through
+// the device buffer where they are many.
+template <class Launch>
+int read_through_pin(fsc_ens *e, double *dst, int64_t count, int64_t unit, Launch launch) {
+    const int64_t piece = int64_t(READ_PIN / sizeof(double)) / unit * unit;
+    if (piece < 1) return fail(e, FSC_E_OOM, "read buffer allocation failed");
+    int rc = ensure_pin(e);
+    if (rc) return rc;
+    for (int64_t k = 0; k < count; k += piece) {
+        const int64_t n = std::min(piece, count - k);
+        HIPCHK(e, launch(k, n, e->box.data()));
+        HIPCHK(e, hipStreamSynchronize(e->stream));
+        std::memcpy(dst + k, e->box.data(), sizeof(double) * size_t(n));
+    }
+    return FSC_OK;
+}
+
 template <class Launch>
 int read_formed(fsc_ens *e, double *dst, int64_t count, int64_t unit, Launch launch) {
     const size_t bytes = sizeof(double) * size_t(count);
-    if (bytes <= READ_PIN) {
-        int rc = ensure_pin(e);
-        if (rc) return rc;
-        HIPCHK(e, launch(int64_t(0), count, e->box.data()));
-        HIPCHK(e, hipStreamSynchronize(e->stream));
-        std::memcpy(dst, e->box.data(), bytes);
-        return FSC_OK;
-    }
+    if (bytes <= READ_PIN) return read_through_pin(e, dst, count, unit, launch);
     const int64_t piece = std::min(count, std::max(unit, int64_t(READ_WORK / sizeof(double)) / unit * unit));
     const size_t need = sizeof(double) * size_t(piece);
     if (e->work_bytes < need) {
         if (e->work) HIPCHK(e, hipFree(e->work));
         e->work = nullptr;
         e->work_bytes = 0;
-        if (hipMalloc(&e->work, need) != hipSuccess) {
+        if (hipMalloc(&e->work, need) == hipSuccess) {
+            e->work_bytes = need;
+        } else {  // a full card
             (void)hipGetLastError();
             e->work = nullptr;
-            return fail(e, FSC_E_OOM, "read buffer allocation failed");
+            return read_through_pin(e, dst, count, unit, launch);
         }
-        e->work_bytes = need;
     }
     StreamDrain drain{e->stream};
     for (int64_t k = 0; k < count; k += piece) {
