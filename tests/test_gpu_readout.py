@@ -121,3 +121,29 @@ def test_samples_of_replicas_with_even_and_odd_sides(sides):
             ref = [line[q] + (line[m - q] if 2 * q != m else 0.0) for q in range(1, m // 2 + 1)]
             assert np.allclose(got[d, 1:m // 2 + 1], ref, rtol=1e-5, atol=1e-6 * np.mean(P))
     ens.close()
+
+
+@pytest.mark.parametrize("long_x", [True, False])
+@pytest.mark.parametrize("precision,n", [("fp64", 4096), ("fp64", 5000), ("fp64", 8192), ("fp32", 4100), ("fp32", 8190),
+                                         ("fp32", 8192)])
+def test_samples_of_long_lines(precision, n, long_x):
+    """Lines that fill a block's LDS, one or two at a time: radix-8 passes to 8192 values,
+    an FP32 chirp over 16384, FP64 direct sums.  FP32: the passes leave a few 2^-24 of
+    the root mean power in an amplitude, 1e-6 of sqrt(P <P>) in a power."""
+    shape = (4, n) if long_x else (n, 4)
+    with fsc.Lattice(fsc.make_params(D=2, nx=shape[1], ny=shape[0], stencil=4, precision=precision, T_hat=0.8,
+                                     rho0=0.62, kBT=0.0)) as lat:
+        lat.init_uniform()
+        f = _state(lat, shape, n)
+        lat.series_enable(1)
+        lat.measure_sk()
+        got, L = lat.read_sk(fsc.FSC_SK_AXIS)[0], lat.read_series()["L"][0]
+    P = np.abs(np.fft.fft2(f.sum(0) - 0.62)) ** 2 / (4 * n)
+    rel, mean = (1e-9, 1e-12) if precision == "fp64" else (1e-5, 1e-6)
+    for d, line in enumerate((P[0], P[:, 0])):
+        m = line.size
+        ref = [line[q] + (line[m - q] if 2 * q != m else 0.0) for q in range(1, m // 2 + 1)]
+        assert np.allclose(got[d, 1:m // 2 + 1], ref, rtol=rel, atol=mean * P[0, 1:].mean())
+    P[0, 0] = 0.0
+    k = 2 * np.pi * np.hypot(np.fft.fftfreq(shape[0])[:, None], np.fft.fftfreq(shape[1])[None])
+    assert L == pytest.approx(2 * np.pi * P.sum() / (k * P).sum(), rel=rel)
