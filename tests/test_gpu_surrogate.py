@@ -358,3 +358,32 @@ def test_first_layer_gradient_of_a_field_beyond_the_largest_bf16():
     g = g[:32 * 9]
     assert np.all(np.isfinite(g[w < 0]))
     assert not np.any(np.isnan(g))
+
+
+# wider than 128 pixels; the last shape lies beyond the size up to which mode 2 takes
+# pairs.  A pair of tiled layers, the single tiled layer and (160) the generic one form
+# the same MFMA sequence per activation
+@pytest.mark.parametrize("layers", [4, 5])
+@pytest.mark.parametrize("H,W,B", [(8, 192, 2), (4, 256, 1), (6, 192, 2), (8, 160, 3), (404, 320, 2)])
+def test_tiled_pairs_of_wide_images_equal_single_layers(H, W, B, layers):
+    print(f"tiled pairs {H}x{W} batch {B} layers {layers}", flush=True)
+    sur = fsc.Surrogate(layers, H, W, B, seed=3, in_ch=1)
+    sur.set_norm(1.0, 0.7, 0.15)
+    g = torch.Generator().manual_seed(H + W)
+    x = (1.0 + 0.5 * torch.randn(B, H, W, generator=g)).cuda()
+    got, last = [], []
+    for mode in (0, 1, 2):
+        sur.set_fusion(mode)
+        out = torch.zeros_like(x)
+        sur.forward(None, x, out, B)
+        traj = torch.zeros((3, B, H, W), device="cuda")
+        traj[0].copy_(x)
+        sur.rollout(None, traj, B, 2)
+        torch.cuda.synchronize()
+        got.append(out.cpu())
+        assert torch.equal(traj[1].cpu(), got[-1])
+        last.append(traj[2].cpu())
+    sur.close()
+    assert torch.isfinite(got[0]).all()
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
+    assert torch.equal(last[0], last[1]) and torch.equal(last[0], last[2])

@@ -161,3 +161,10 @@ def test_gradients_match_bf16_reference_per_element(in_ch, shape):
 @pytest.mark.parametrize("shape", [(7, 5, 32), (100, 5, 32), (3, 11, 96), (2, 6, 160), (1, 8, 192)])
 def test_gradients_on_edge_shapes(shape):
     test_gradients_match_bf16_reference_per_element(1, shape)
+
+
+# images wider than 128 pixels: pairs of tiled layers and a single tiled one (192, 256),
+# and the generic layer (160)
+@pytest.mark.parametrize("layers,in_ch,shape", [(5, 1, (2, 8, 192)), (5, 2, (1, 4, 256)), (5, 1, (2, 6, 160))])
+def test_forward_on_wide_images(layers, in_ch, shape):
+    test_forward_matches_bf16_reference_per_element(layers, in_ch, shape)
