@@ -436,8 +436,8 @@ int fsc_ens_autotune(fsc_ens *ens);
 
 /* out[0..4] = tile x, tile y, prefetch depth, workgroups per launch, time
  * steps per launch (1, or 2 for the two-step kernel).  2D lattices and ensembles
- * below 2^20 nodes whose tiling is neither fixed nor tuned run several steps
- * per launch in LDS-resident tiles of their own (the same bits); the tiling
+ * below 2^20 nodes whose tiling is neither fixed nor tuned mostly run several
+ * steps per launch in LDS-resident tiles of their own (the same bits); the tiling
  * reported is then the one that fsc_set_tiling or fsc_autotune would replace. */
 int fsc_get_tiling(const fsc_ctx *ctx, int *out5);
 int fsc_ens_get_tiling(const fsc_ens *ens, int *out5);

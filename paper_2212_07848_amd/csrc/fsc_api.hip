@@ -826,11 +826,50 @@ bool block_plan(const fsc_ens *e, int T, BlockPlan &best) {
     return found;
 }
 
-// 2D below the size from which tilings are tuned automatically.
+// 2D below the size from which tilings are tuned automatically, where the tuned
+// marching kernels are as fast (1020 x 1024, us per step, tuned / block kernel: FP32
+// E4 15.4 / 14.9, E8 18.7 / 17.7, FP64 46.2 / 55.9, 49.0 / 64.3) and pull away.
 bool block_size(const fsc_ens *e) {
     int64_t nodes = 0;
     for (const auto &r : e->reps) nodes += r.N;
     return e->D == 2 && nodes < (int64_t(1) << 20);
+}
+
+// Whether the block kernel takes less time per step than the marching kernel with the
+// default tile (lattices that are not tuned): the best of the modelled launches, with a
+// term for the state that they move, against the marching kernel's rows of a tile, its
+// second round of workgroups and the same.  Fitted to 700 timings of each kernel and
+// kind, single lattices of 1 to 200000 columns and rows and ensembles of up to 4000
+// replicas (errors 5 to 8% rms); the slower kernel is taken at most 7% off the line,
+// but for very flat lattices, where the block kernel is sometimes not taken though up to
+// 1.35 times as fast.  In FP32 it is nearly always the faster one, except on a few rows,
+// whose halo is most of its work (100000 x 1: 5.8 us per step marching, 8.7 in blocks).
+// In FP64 the two cross at 5 to 9 10^5 nodes (marching / blocks: E4 512^2 19.0 / 16.6,
+// 730 x 627 29.9 / 25.4, 768 x 749 27.9 / 29.9, 1000^2 49.9 / 54.8, 48 x 128^2 36.5 /
+// 45.3; E8 512^2 26.3 / 18.9, 800^2 42.3 / 40.6, 1000^2 53.9 / 60.2), later where a
+// marching tile is half empty (200 x 64^2: 71 / 41).
+bool blocks_pay(const fsc_ens *e) {
+    struct Fit {
+        double base, rows;      // marching: per launch, per 1000 rows of a tile,
+        int resident;           // workgroups at once
+        double round, state;    // and the time of a second round; per 10^6 nodes
+        double launch, bstate;  // blocks: of the modelled launch, per 10^6 nodes
+    };
+    static constexpr Fit fits[2][2] = {
+        {{4.26, 1.17, 1536, 0.14, 6.59, 1.03, 5.04}, {5.35, 1.27, 1024, 0.78, 5.70, 1.05, 4.95}},
+        {{6.42, 4.00, 1536, 2.38, 9.00, 1.05, 8.13}, {7.99, 4.40, 1024, 4.93, 10.74, 1.02, 13.38}}};
+    const Fit &f = fits[e->precision == FSC_FP64][e->stencil == FSC_E8];
+    double nodes = 0.0, rows = 0.0;
+    for (const RepDesc &d : e->desc) {
+        nodes += 1e-6 * double(d.N);
+        rows += 1e-3 * double(d.tiles_x) * d.nchunk * d.H;
+    }
+    const double march =
+        f.base + f.rows * rows + (e->total_tiles > f.resident ? f.round : 0.0) + f.state * nodes;
+    const BlockPlan *best = &e->blocks[0];
+    for (const BlockPlan &p : e->blocks)
+        if (p.us / p.T < best->us / best->T) best = &p;
+    return f.launch * best->us + f.bstate * nodes < march * best->T;
 }
 
 // Plans every step count that fits and uploads the tables.  The descriptors
@@ -1121,8 +1160,8 @@ int stream_captures(fsc_ens *e, bool *capturing) {
     return FSC_OK;
 }
 
-// Whether runs go through the block kernel: small 2D lattices, unless the caller
-// has fixed a tiling or the autotuner found one that is faster.  A run that the
+// Whether runs go through the block kernel: small 2D lattices where it is the faster
+// one, unless the caller has fixed a tiling or the autotuner found a better.  A run that the
 // caller captures into a graph of its own takes one launch per step: an even
 // number of steps then leaves the state in the buffer that the next replay reads.
 int choose_blocks(fsc_ens *e, bool capturing) {
@@ -1134,7 +1173,7 @@ int choose_blocks(fsc_ens *e, bool capturing) {
     if (use) {
         int rc = ensure_blocks(e);
         if (rc) return rc;
-        use = !e->blocks.empty();
+        use = !e->blocks.empty() && (e->tuned_blocks || blocks_pay(e));
     }
     e->use_blocks = use;
     return FSC_OK;
