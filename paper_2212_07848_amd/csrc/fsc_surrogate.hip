@@ -1523,6 +1523,31 @@ __global__ void __launch_bounds__(256) k_coarsen(Geometry g, const real *__restr
     }
 }
 
+// One lane per cell: single nodes, where there is nothing to sum, and small cells of
+// many narrow rows, which leave most lanes of a strip idle (nx f^3 <= 1300 and more
+// than 4096 strips, from the times over 1 to 128 columns, 1200 to 120000 rows and f = 1
+// to 8).  us, strips / so: f = 1 1000^2 10.1 / 8.9, 2048^2 32.2 / 29.3, 1 x 100000 94 / 6.2;
+// f = 2 64 x 24000 17.1 / 12.5; f = 4 8 x 120000 44 / 38, but 48 x 24000 12.6 / 24.8.
+template <class L, typename real>
+__global__ void __launch_bounds__(256) k_coarsen_cells(Geometry g, const real *__restrict__ src, double rho0, int f,
+                                                       float *__restrict__ out) {
+    const int cx = g.nx / f, cells = cx * (g.ny / f);
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= cells) return;
+    const int X = (k % cx) * f, Y = (k / cx) * f;
+    double s = 0.0;
+    for (int y = Y; y < Y + f; ++y) {
+        const int ys[3] = {y + 1 == g.ny ? 0 : y + 1, y, y == 0 ? g.ny - 1 : y - 1};
+        for (int x = X; x < X + f; ++x) {
+            const int xs[3] = {x + 1 == g.nx ? 0 : x + 1, x, x == 0 ? g.nx - 1 : x - 1};
+#pragma unroll
+            for (int i = 0; i < L::Q; ++i)
+                s += double(src[int64_t(i) * g.N + xs[L::c(i, 0) + 1] + int64_t(g.nx) * ys[L::c(i, 1) + 1]]);
+        }
+    }
+    out[k] = float(rho0 + s / (double(f) * double(f)));
+}
+
 hipError_t launch_coarsen(const Geometry &g, int precision, const void *buf, double rho0, int f,
                           float *out, hipStream_t s) {
     if (g.D != 2 || f < 1 || g.nx % f || g.ny % f) return hipErrorInvalidValue;
@@ -1530,6 +1555,15 @@ hipError_t launch_coarsen(const Geometry &g, int precision, const void *buf, dou
     const int cells = f <= TX ? TX / f : 1, strips = (g.nx / f + cells - 1) / cells;
     const int64_t nb = int64_t(strips) * (g.ny / f);
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
+    if (f == 1 || (nb > 4096 && f <= 10 && int64_t(g.nx) * f * f * f <= 1300)) {
+        const unsigned cb = unsigned((int64_t(g.nx / f) * (g.ny / f) + 255) / 256);
+        auto cells = [&](auto kernel, auto p) {
+            hipLaunchKernelGGL(kernel, dim3(cb), dim3(256), 0, s, g, p, rho0, f, out);
+            return hipGetLastError();
+        };
+        return precision == 0 ? cells(k_coarsen_cells<D2Q9, float>, static_cast<const float *>(buf))
+                              : cells(k_coarsen_cells<D2Q9, double>, static_cast<const double *>(buf));
+    }
     auto go = [&](auto kernel, auto p) {
         hipLaunchKernelGGL(kernel, dim3(unsigned(nb)), dim3(256), 0, s, g, p, rho0, f, TX, strips, out);
         return hipGetLastError();

@@ -147,3 +147,22 @@ def test_samples_of_long_lines(precision, n, long_x):
     P[0, 0] = 0.0
     k = 2 * np.pi * np.hypot(np.fft.fftfreq(shape[0])[:, None], np.fft.fftfreq(shape[1])[None])
     assert L == pytest.approx(2 * np.pi * P.sum() / (k * P).sum(), rel=rel)
+
+
+# one lane per cell: f = 1, and small cells of many narrow rows (10000 and 4097 strips
+# of the other kernel; 4096 of them take it)
+@pytest.mark.parametrize("shape,f", [((37, 41), 1), ((1, 300), 1), ((20000, 4), 2), ((8194, 2), 2), ((8192, 2), 2),
+                                     ((12300, 48), 3), ((16400, 20), 4), ((16400, 24), 4), ((12, 600), 6)])
+def test_block_means_of_narrow_and_wide_rows(shape, f):
+    torch = pytest.importorskip("torch")
+    ny, nx = shape
+    with fsc.Lattice(fsc.make_params(D=2, nx=nx, ny=ny, stencil=4, precision="fp32", T_hat=0.8, rho0=0.62,
+                                     kBT=0.0)) as lat:
+        lat.init_uniform()
+        rho = _state(lat, shape, nx + f).sum(0)
+        out = torch.full((ny // f, nx // f), -1.0, device="cuda")
+        torch.cuda.synchronize()
+        lat.coarsen(f, out)
+        lat.stats()
+    ref = rho.reshape(ny // f, f, nx // f, f).mean((1, 3))
+    assert np.allclose(out.cpu().numpy(), ref, rtol=3e-7, atol=0.0)  # FP64 sums, one rounding to FP32
