@@ -868,17 +868,19 @@ __device__ inline double image_total(const double *__restrict__ part, int img) {
 }
 static_assert(IMG_PARTS % 64 == 0, "a wave sums the segment sums (and k_last's blocks of four)");
 
-// prediction rho_t + out_scale (y - <y>_image); a wave per (image, segment), the
-// image's mean from its IMG_PARTS segment sums
+// prediction rho_t + out_scale (y - <y>_image); `lanes` per (image, segment), the
+// image's mean from its IMG_PARTS segment sums.  A wave per segment, or a workgroup
+// where a segment has as many pixels (pred): a few large images are else on 64 CUs
+// (three layers on one image of 1024^2: 336 us a pass, 321 so; 4096 x 2048 3013 and 2850).
 __global__ void __launch_bounds__(256) k_pred(const float *__restrict__ in,
                                               const float *__restrict__ y,
-                                              const double *__restrict__ part, int HW,
+                                              const double *__restrict__ part, int HW, int lanes,
                                               float out_scale, float *__restrict__ out) {
-    const int sg = blockIdx.x * 4 + (threadIdx.x >> 6), img = sg / IMG_PARTS, seg = sg % IMG_PARTS;
+    const int sg = (int(blockIdx.x) * 256 + int(threadIdx.x)) / lanes, img = sg / IMG_PARTS, seg = sg % IMG_PARTS;
     const float mean = float(image_total(part, img) / HW);
     const int len = (HW + IMG_PARTS - 1) / IMG_PARTS;
     const int lo = seg * len, hi = min(HW, lo + len);
-    for (int i = lo + int(threadIdx.x & 63); i < hi; i += 64) {
+    for (int i = lo + int(threadIdx.x) % lanes; i < hi; i += lanes) {
         const size_t p = size_t(img) * HW + i;
         out[p] = in[p] + out_scale * (y[p] - mean);
     }
@@ -1858,6 +1860,12 @@ int sur_forward_core(fsc_sur *s, const float *prev, const float *cur, int B, boo
     return FSC_OK;
 }
 
+void pred(const fsc_sur *s, const float *in, float *out, int B) {
+    const int HW = s->H * s->W, lanes = HW >= 256 * IMG_PARTS ? 256 : 64;
+    hipLaunchKernelGGL(k_pred, dim3(unsigned(B * IMG_PARTS / (256 / lanes))), dim3(256), 0, s->stream, in, s->y,
+                       s->part, HW, lanes, s->out_scale, out);
+}
+
 int sur_backward(fsc_sur *s, const float *prev, const float *in, const float *tgt, int B) {
     const int H = s->H, W = s->W, P = B * H * W;
     const float ii = 1.f / s->in_scale, io = 1.f / s->out_scale;
@@ -2097,8 +2105,7 @@ int fsc_sur_forward(fsc_sur *s, const float *dev_prev, const float *dev_in, floa
     if (rc) return rc;
     rc = sur_forward_core(s, dev_prev, dev_in, batch, false);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_pred, dim3(unsigned(batch * IMG_PARTS / 4)), dim3(256), 0, s->stream, dev_in,
-                       s->y, s->part, s->H * s->W, s->out_scale, dev_out);
+    pred(s, dev_in, dev_out, batch);
     SCHK(s, hipGetLastError());
     return FSC_OK;
 }
@@ -2193,9 +2200,7 @@ int fsc_sur_rollout(fsc_sur *s, const float *dev_prev, float *dev_traj, int batc
                 const float *prev = k == 0 ? dev_prev : dev_traj + (k - 1) * img;
                 frc = sur_forward_core(s, prev, dev_traj + k * img, batch, false);
                 if (frc == FSC_OK) {
-                    hipLaunchKernelGGL(k_pred, dim3(unsigned(batch * IMG_PARTS / 4)), dim3(256), 0,
-                                       s->stream, dev_traj + k * img, s->y, s->part, s->H * s->W,
-                                       s->out_scale, dev_traj + (k + 1) * img);
+                    pred(s, dev_traj + k * img, dev_traj + (k + 1) * img, batch);
                     if (hipGetLastError() != hipSuccess) frc = FSC_E_HIP;
                 }
             }

@@ -387,3 +387,22 @@ def test_tiled_pairs_of_wide_images_equal_single_layers(H, W, B, layers):
     assert torch.isfinite(got[0]).all()
     assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
     assert torch.equal(last[0], last[1]) and torch.equal(last[0], last[2])
+
+
+@pytest.mark.parametrize("H,W", [(255, 256), (256, 256), (257, 288)])
+def test_forward_where_a_segment_takes_a_workgroup(H, W):
+    # an image of 256^2 pixels or more: every pixel is written, the mean is conserved, and
+    # the prediction is the same as in a batch, image by image
+    sur = fsc.Surrogate(3, H, W, 2, seed=3, in_ch=1)
+    sur.set_norm(1.0, 0.7, 0.15)
+    g = torch.Generator().manual_seed(H)
+    x = (1.0 + 0.5 * torch.randn(2, H, W, generator=g)).cuda()
+    out, one = torch.full_like(x, float("nan")), torch.full_like(x, float("nan"))
+    sur.forward(None, x, out, 2)
+    for b in range(2):
+        sur.forward(None, x[b], one[b], 1)
+    torch.cuda.synchronize()
+    sur.close()
+    assert torch.isfinite(out).all() and torch.equal(out, one)
+    assert (out.double().mean((1, 2)) - x.double().mean((1, 2))).abs().max().item() < 1e-6
+    assert not torch.equal(out, x)
