@@ -9,6 +9,7 @@
 #include <mutex>
 #include <map>
 #include <memory>
+#include <new>
 #include <string>
 #include <tuple>
 #include <utility>
@@ -313,6 +314,7 @@ int init_rep(Rep &r, const fsc_params &p, void *ext_a, void *ext_b, fsc_ens *e) 
 // pinned memory and announced there (see Mail), or copied to it; large ones go
 // through a device buffer in pieces.  Both are made at first use and live as
 // long as the ensemble.
+constexpr int64_t DENSITY_FLOATS = int64_t(6) << 20;  // see ens_density
 constexpr size_t READ_PIN = size_t(512) << 10, READ_WORK = size_t(64) << 20, READ_MAIL = size_t(8) << 10;
 
 int ensure_pin(fsc_ens *e) {
@@ -352,6 +354,21 @@ int read_back(fsc_ens *e, double *dst, const double *src, size_t n) {
     return FSC_OK;
 }
 
+// `bytes` of device memory at e->work, or false (a full card)
+bool ensure_work(fsc_ens *e, size_t bytes) {
+    if (e->work_bytes >= bytes) return true;
+    if (e->work) (void)hipFree(e->work);
+    e->work = nullptr;
+    e->work_bytes = 0;
+    if (hipMalloc(&e->work, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        e->work = nullptr;
+        return false;
+    }
+    e->work_bytes = bytes;
+    return true;
+}
+
 // `count` doubles that launch(first, n, out) forms, n at a time (multiples of
 // `unit`), into the caller's memory: by way of the pinned buffer alone, and through
 // the device buffer where they are many.
@@ -375,19 +392,7 @@ int read_formed(fsc_ens *e, double *dst, int64_t count, int64_t unit, Launch lau
     const size_t bytes = sizeof(double) * size_t(count);
     if (bytes <= READ_PIN) return read_through_pin(e, dst, count, unit, launch);
     const int64_t piece = std::min(count, std::max(unit, int64_t(READ_WORK / sizeof(double)) / unit * unit));
-    const size_t need = sizeof(double) * size_t(piece);
-    if (e->work_bytes < need) {
-        if (e->work) HIPCHK(e, hipFree(e->work));
-        e->work = nullptr;
-        e->work_bytes = 0;
-        if (hipMalloc(&e->work, need) == hipSuccess) {
-            e->work_bytes = need;
-        } else {  // a full card
-            (void)hipGetLastError();
-            e->work = nullptr;
-            return read_through_pin(e, dst, count, unit, launch);
-        }
-    }
+    if (!ensure_work(e, sizeof(double) * size_t(piece))) return read_through_pin(e, dst, count, unit, launch);
     StreamDrain drain{e->stream};
     for (int64_t k = 0; k < count; k += piece) {
         const int64_t n = std::min(piece, count - k);
@@ -1453,6 +1458,22 @@ int ens_init_uniform(fsc_ens *e) {
 // Density n(x) of one replica's current state into host doubles [nz][ny][nx].
 int ens_density(fsc_ens *e, int ri, double *host_rho) {
     Rep &r = e->reps[ri];
+    // FP32 lattices of middling size move half the bytes and are converted here: us, formed
+    // on the device / so, 400^2 92 / 70, 1000^2 455 / 404, 128^3 973 / 843, but 256^3
+    // 12800 / 24200
+    if (r.esz == 4 && sizeof(double) * size_t(r.N) > READ_PIN && r.N <= DENSITY_FLOATS &&
+        ensure_work(e, sizeof(float) * size_t(r.N))) {
+        std::unique_ptr<float[]> dn(new (std::nothrow) float[size_t(r.N)]);
+        if (!dn) return fail(e, FSC_E_OOM, "density buffer");
+        StreamDrain drain{e->stream};
+        HIPCHK(e, launch_deviation(r.geom(), static_cast<const float *>(r.buf[e->cur]),
+                                   reinterpret_cast<float *>(e->work), e->stream));
+        HIPCHK(e, hipMemcpyAsync(dn.get(), e->work, sizeof(float) * size_t(r.N), hipMemcpyDeviceToHost, e->stream));
+        HIPCHK(e, hipStreamSynchronize(e->stream));
+        const double rho0 = r.p.rho0;
+        for (int64_t k = 0; k < r.N; ++k) host_rho[k] = rho0 + double(dn[size_t(k)]);
+        return FSC_OK;
+    }
     return read_formed(e, host_rho, r.N, r.p.nx, [&](int64_t first, int64_t n, double *out) {
         return launch_density(r.geom(), r.p.precision, r.buf[e->cur], r.p.rho0, first / r.p.nx, n / r.p.nx, out,
                               e->stream);

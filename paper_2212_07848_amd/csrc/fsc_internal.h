@@ -90,6 +90,8 @@ struct Geometry {
 // Density n(x) in double of the x-rows row0 .. row0 + rows - 1 (row = y + ny z).
 hipError_t launch_density(const Geometry &g, int precision, const void *buf, double rho0, int64_t row0,
                           int64_t rows, double *out, hipStream_t s);
+// Its deviation n(x) - rho0 from an FP32 lattice, as floats, all rows.
+hipError_t launch_deviation(const Geometry &g, const float *buf, float *out, hipStream_t s);
 // Streamed populations shift[i] + df_i in double, elements e0 .. e0 + n - 1 of
 // [i][z][y][x].
 hipError_t launch_streamed(const Geometry &g, int precision, const void *buf, const double *shift, int64_t e0,

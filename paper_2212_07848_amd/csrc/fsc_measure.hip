@@ -41,9 +41,10 @@ __device__ inline void gather_node(const real *src, const Geometry &g, int x, in
 // n(x) = rho0 + dn in double of the rows row0 .. row0 + rows - 1, as a program
 // reads it: formed here, the host only receives it (converting 256^3 values on
 // the host took longer than moving them).
-template <class L, typename real>
+// (Out float: dn itself.)
+template <class L, typename real, typename Out>
 __global__ void __launch_bounds__(256) k_density(Geometry g, const real *__restrict__ src, double rho0,
-                                                 int64_t row0, double *__restrict__ out) {
+                                                 int64_t row0, Out *__restrict__ out) {
     const int strips = (g.nx + 255) / 256;
     const int64_t r = int(blockIdx.x) / strips, row = row0 + r;
     const int x = (int(blockIdx.x) % strips) * 256 + threadIdx.x;
@@ -53,21 +54,34 @@ __global__ void __launch_bounds__(256) k_density(Geometry g, const real *__restr
     real dn = real(0);
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) dn += f[i];
-    out[r * g.nx + x] = rho0 + double(dn);
+    if constexpr (sizeof(Out) == 4) out[r * g.nx + x] = dn;
+    else out[r * g.nx + x] = rho0 + double(dn);
+}
+
+template <typename Out, typename Kernel, typename real>
+static hipError_t density_rows(Kernel kernel, const Geometry &g, const real *buf, double rho0, int64_t row0, int64_t rows,
+                               Out *out, hipStream_t s) {
+    const int64_t blocks = int64_t((g.nx + 255) / 256) * rows;
+    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(256), 0, s, g, buf, rho0, row0, out);
+    return hipGetLastError();
 }
 
 hipError_t launch_density(const Geometry &g, int precision, const void *buf, double rho0, int64_t row0,
                           int64_t rows, double *out, hipStream_t s) {
-    const int64_t blocks = int64_t((g.nx + 255) / 256) * rows;
-    if (blocks > 0x7fffffff) return hipErrorInvalidValue;
-    auto go = [&](auto kernel, auto p) {
-        hipLaunchKernelGGL(kernel, dim3(unsigned(blocks)), dim3(256), 0, s, g, p, rho0, row0, out);
-        return hipGetLastError();
-    };
     const float *f = static_cast<const float *>(buf);
     const double *d = static_cast<const double *>(buf);
-    if (g.D == 2) return precision == 0 ? go(k_density<D2Q9, float>, f) : go(k_density<D2Q9, double>, d);
-    return precision == 0 ? go(k_density<D3Q19, float>, f) : go(k_density<D3Q19, double>, d);
+    if (g.D == 2)
+        return precision == 0 ? density_rows(k_density<D2Q9, float, double>, g, f, rho0, row0, rows, out, s)
+                              : density_rows(k_density<D2Q9, double, double>, g, d, rho0, row0, rows, out, s);
+    return precision == 0 ? density_rows(k_density<D3Q19, float, double>, g, f, rho0, row0, rows, out, s)
+                          : density_rows(k_density<D3Q19, double, double>, g, d, rho0, row0, rows, out, s);
+}
+
+hipError_t launch_deviation(const Geometry &g, const float *buf, float *out, hipStream_t s) {
+    const int64_t rows = int64_t(g.ny) * g.nz;
+    return g.D == 2 ? density_rows(k_density<D2Q9, float, float>, g, buf, 0.0, 0, rows, out, s)
+                    : density_rows(k_density<D3Q19, float, float>, g, buf, 0.0, 0, rows, out, s);
 }
 
 // The streamed populations w_i rho0 + df_i(x) in double, layout [i][z][y][x],

@@ -166,3 +166,24 @@ def test_block_means_of_narrow_and_wide_rows(shape, f):
         lat.stats()
     ref = rho.reshape(ny // f, f, nx // f, f).mean((1, 3))
     assert np.allclose(out.cpu().numpy(), ref, rtol=3e-7, atol=0.0)  # FP64 sums, one rounding to FP32
+
+
+# FP32 densities go to the host formed, as floats (65537 to 6291456 nodes), and formed in
+# pieces; against the block means of single nodes, rounded once to FP32
+@pytest.mark.parametrize("shape", [(256, 256), (257, 256), (65537, 1), (1, 65537), (2400, 2600), (2600, 2600)])
+def test_density_by_the_three_ways_to_the_host(shape):
+    torch = pytest.importorskip("torch")
+    ny, nx = shape
+    with fsc.Lattice(fsc.make_params(D=2, nx=nx, ny=ny, stencil=4, precision="fp32", T_hat=0.8, rho0=0.62,
+                                     kBT=1e-4, seed=nx)) as lat:
+        lat.init_uniform()
+        lat.set_tiling(*fsc.tile_shapes(2, 4, "fp32")[0], 2048)
+        lat.step(3)
+        out = torch.zeros(ny, nx, device="cuda")
+        torch.cuda.synchronize()
+        lat.coarsen(1, out)
+        rho = lat.density()
+        mass = lat.stats()["mass"]
+    # nine FP32 additions against FP64 ones, of deviations a tenth of the density
+    assert np.allclose(out.cpu().numpy(), rho, rtol=3e-7, atol=0.0)
+    assert rho.std() > 1e-3 and rho.sum() == pytest.approx(mass, rel=1e-7)
