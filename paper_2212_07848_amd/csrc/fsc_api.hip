@@ -1184,7 +1184,7 @@ int choose_blocks(fsc_ens *e, bool capturing) {
     return FSC_OK;
 }
 
-constexpr int CHUNK_SAMPLES = 8, CHUNK_STEPS = 128;
+constexpr int CHUNK_SAMPLES = 8, CHUNK_STEPS = 256;
 
 int ens_run(fsc_ens *e, int64_t nsteps, int64_t sk_every) {
     TraceRange trace_("fsc run");
