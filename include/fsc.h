@@ -35,8 +35,16 @@
  *     lattice or ensemble created with NULL makes a stream of its own (its
  *     step chunks are captured into HIP graphs, which the null stream cannot
  *     hold); the surrogate and the field functions take NULL as the device's
- *     default stream.  Calls that return host data synchronise the stream.
+ *     default stream.  Calls that return host data do so when everything
+ *     enqueued on the stream before them is done (a small result is awaited in
+ *     pinned memory, so that the stream itself may show the call's own last
+ *     kernel as running for some microseconds longer).
  *     A context is not thread safe; distinct contexts are independent.
+ *   - Besides its buffers a lattice or ensemble keeps 512 KB of pinned memory
+ *     from its first read-out on, and from the first large one (beyond 512 KB)
+ *     up to 64 MB of device memory, until it is destroyed.  A thread that has
+ *     called fsc_field_sk or fsc_linear_sk_radial keeps 16 KB of pinned and up
+ *     to 8 MiB of device memory until it ends.
  */
 #ifndef FSC_H
 #define FSC_H
@@ -172,7 +180,7 @@ int fsc_read_density(fsc_ctx *ctx, double *host_rho);
  * out[5] = max n over nodes with a number as density (NaN nodes are skipped),
  * out[6] = number of nodes with a non-finite or non-positive density,
  * out[7] = node count.  Returns FSC_E_DIVERGED (after filling out) when
- * out[6] > 0.  Synchronises the stream. */
+ * out[6] > 0. */
 int fsc_stats(fsc_ctx *ctx, double *out8);
 /* The conserved sums alone: *mass = sum n, mom[0..D-1] = sum j.  Errors as
  * fsc_stats (FSC_E_DIVERGED after filling them). */
@@ -275,8 +283,9 @@ int fsc_ens_read_series(fsc_ens *ens, int replica, double *out, int max_rows, in
  * covariance of the noise; on a lattice axis with the E4 stencil this is
  * Eq. 16.  host_k: nk wave vectors [nk][D] in lattice units (k = 2 pi m / L);
  * host_s: nk doubles (out).  Uses p's D, stencil, T_hat or G, rho0, rates and
- * kBT (sides are ignored).  FP64 on the GPU, one workgroup per wave vector;
- * synchronous on `stream` (NULL: the default stream).  Errors: FSC_E_INVAL,
+ * kBT (sides are ignored).  FP64 on the GPU, one workgroup per wave vector, or
+ * one lane where every rate is 1; synchronous on `stream` (NULL: the default
+ * stream).  Errors: FSC_E_INVAL,
  * FSC_E_OOM, FSC_E_HIP. */
 int fsc_linear_sk(const fsc_params *p, const double *host_k, int64_t nk, double *host_s,
                   void *stream);

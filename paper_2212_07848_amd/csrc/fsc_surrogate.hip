@@ -703,7 +703,7 @@ __global__ void __launch_bounds__((CW + CW / 4) * 64) k_march(const bf16 *__rest
 
 // ---------------------------------------------------------------------------
 // Last layer (C -> 1) forward on the matrix cores.  Its FP32 weights enter as
-// three BF16 parts each, w = hi + mid + lo (k_pack_last; exact for normal FP32
+// three BF16 parts each, w = hi + mid + lo (k_update; exact for normal FP32
 // values), in rows 0..2 of the A operand (rows 3..15 zero); B is 32 channels
 // by 16 pixels for one tap, and the 9 taps accumulate.  Lane l < 16 ends with
 // the three partial sums of pixel l in acc[0..2]: y = (hi + mid) + lo + bias.
@@ -1310,8 +1310,7 @@ __global__ void __launch_bounds__(256) k_edge_wgrad(const bf16 *__restrict__ act
 }
 
 // Sums the blocks' partial results of every layer into the gradient vector
-// (each partial once, in FP64, in a fixed order): a block takes 64 elements
-// of one layer, its four waves a quarter of the partials each.
+// (each partial once, in FP64, in a fixed order; see k_wgrad_sum).
 struct WgradSum {
     int nmid, mid_blocks, edge_blocks, in_ch;
     const float *mid, *first, *last;  // [layer][block][WG_LEN], [block][len]
@@ -1320,7 +1319,7 @@ struct WgradSum {
 constexpr int WG_MID_GROUPS = (WG_LEN + 255) / 256;
 static_assert(WG_LEN % 4 == 0, "whole 16-byte pieces");
 
-// Sums of the blocks' partials by workgroups of sixteen waves.  C -> C layers (66
+// A workgroup of k_wgrad_sum is sixteen waves.  C -> C layers (66
 // MB at nine layers and 32 images): 256 columns each, a wave reads 1 KB of a partial
 // at a time and keeps sixteen such loads in flight.  First and last layers: eight
 // columns each, 128 lanes per column; their columns lie apart, a load touches 64
@@ -1651,7 +1650,7 @@ struct fsc_sur {
     std::vector<int64_t> woff, boff;  // offsets of each layer's weights / biases
     float *params = nullptr, *grads = nullptr, *m = nullptr, *v = nullptr;
     bf16 *wf = nullptr, *wb = nullptr;  // [mid layer][9][32][32]
-    bf16 *wl3 = nullptr;                // last layer, [9][3][32] (k_pack_last)
+    bf16 *wl3 = nullptr;                // last layer, [9][3][32] (see k_update)
     std::vector<float *> z;            // [layers - 1] of P x 32
     std::vector<bf16 *> a;             // [layers - 1] of P x 32
     bf16 *dzA = nullptr, *dzB = nullptr;
@@ -1708,9 +1707,10 @@ void sur_free(fsc_sur *s) {
 
 // Fused pairs of C -> C layers in images wider than 128 (narrower ones march, see
 // k_chain): k_mid2_lds holds 60 KB of LDS per block, so 2 blocks per CU instead of
-// 4.  Measured on 9-layer passes over 128^2 images, it wins up to 8 images (62.5
-// against 73.3 us for one, 87.0 against 100.3 for eight) and loses from 16 (135.9
-// against 128.3).  Mode 2 fuses up to FUSE_MAX_PIXELS pixels per batch.
+// 4, and wins while the blocks fit the chip in one round.  9-layer passes, us, single
+// layers / pairs: 192^2 88 / 72, 256^2 100 / 86, 2 x 256^2 111 / 96, 3 x 256^2 122 / 133,
+// 512^2 174 / 176, 8 x 256^2 225 / 241, 1024^2 624 / 667.  Mode 2 fuses up to
+// FUSE_MAX_PIXELS pixels per batch.
 constexpr int64_t FUSE_MAX_PIXELS = 8 * 128 * 128;
 bool fuse_pairs(const fsc_sur *s, int B) {
     return s->fuse == 1 || (s->fuse == 2 && int64_t(B) * s->H * s->W <= FUSE_MAX_PIXELS);

@@ -97,7 +97,7 @@ def test_forward_matches_reference(layers, in_ch):
 
 @pytest.mark.parametrize("in_ch,H,W", [(1, 32, 32), (2, 32, 32), (2, 16, 64)])
 def test_gradient_matches_reference(in_ch, H, W):
-    # 32 x 32 runs the generic C -> C kernels, 16 x 64 the LDS-staged ones
+    # (rows of up to 128 pixels march down the image)
     rng = np.random.default_rng(3)
     B, layers = 2, 5
     p = _net(4, L=layers, in_ch=in_ch).astype(np.float32)
@@ -219,7 +219,7 @@ def test_rollout_graph_equals_repeated_forward_passes():
 def test_fused_layer_pairs_equal_unfused_layers(layers, in_ch, shape):
     # inference can run pairs of 32 -> 32 layers as one launch with the first
     # layer's activations in LDS (9 layers: three pairs and one single layer;
-    # 4 layers: one pair; 3 layers: a single layer; W = 32: no fusion): the
+    # 4 layers: one pair; 3 layers: a single layer): the
     # forward pass and a rollout are bit-identical in every mode (these
     # batches are small enough for mode 2 to fuse).  Switching drops the
     # captured rollout graph, and so does a new normalisation, whose values

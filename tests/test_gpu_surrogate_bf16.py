@@ -80,8 +80,8 @@ def _compare(got, ref, what, med_tol=2e-5, max_tol=5e-3, tail_tol=1e-3, tail_fra
     return med, mx
 
 
-# shapes: W = 32 runs the generic C -> C kernel, W = 64 and 128 the LDS-staged
-# one; the 8-row image makes every tile touch the periodic wrap in y
+# shapes: rows of one tile of 16 pixels per wave and of two in the marching layers;
+# the 8-row image makes every strip touch the periodic wrap in y
 @pytest.mark.parametrize("layers,in_ch,shape", [(3, 1, (2, 32, 32)), (5, 1, (2, 32, 64)),
                                                 (5, 2, (2, 16, 64)), (5, 2, (1, 8, 128)),
                                                 (9, 2, (2, 32, 64))])
