@@ -405,7 +405,8 @@ __global__ void __launch_bounds__(64) k_linear_conserved(LinArgs la, KSource ks,
         for (int b = 1; b < N; ++b) small = small && fabs(P[0][b]) < 1e-12;
         if (__all(small)) break;
     }
-    if (id < ks.nk) out[id] = X[0][0];
+    // no stationary value (an unstable state): NaN, as the general form gives, not infinity
+    if (id < ks.nk) out[id] = X[0][0] + (X[0][0] - X[0][0]);
 }
 
 template <class L, class ST>
@@ -551,7 +552,9 @@ template <class L, class ST>
 hipError_t launch_linear(const LinArgs &la, const KSource &ks, double *out, hipStream_t s) {
     const int64_t waves = (ks.nk + 63) / 64;
     if (la.lam[1] == 1.0 && la.lam[2] == 1.0 && la.lam[3] == 1.0 && waves <= 0x7fffffff) {
-        hipLaunchKernelGGL((k_linear_conserved<L, ST>), dim3(unsigned(waves)), dim3(64), 0, s, la, ks, out);
+        LinArgs unit = la;
+        if (la.mu == 0.0) unit.doublings = 0;  // without noise the sum is 0, also where K grows beyond all bounds
+        hipLaunchKernelGGL((k_linear_conserved<L, ST>), dim3(unsigned(waves)), dim3(64), 0, s, unit, ks, out);
         return hipGetLastError();
     }
     const unsigned blocks = unsigned(ks.nk < 65536 ? ks.nk : 65536);

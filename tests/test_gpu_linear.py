@@ -127,3 +127,19 @@ def test_device_wave_vectors_of_the_radial_shells(D, n, lam):
     assert np.array_equal(cnt, np.bincount(b, minlength=nb)[:nb])
     ref = np.bincount(b, weights=S, minlength=nb)[:nb] / np.maximum(cnt, 1)
     assert np.allclose(mean, ref, rtol=1e-11, atol=0)
+
+
+@pytest.mark.parametrize("D,stencil", [(2, 4), (2, 8), (3, 4)])
+def test_unstable_and_noise_free_states_at_unit_rates(D, stencil):
+    # an unstable state has no stationary S(k) at small k (NaN), and without noise it is
+    # 0; a wave vector that is no number gives NaN
+    kv = np.concatenate([np.random.default_rng(2).uniform(-math.pi, math.pi, size=(100, D)),
+                         np.full((1, D), 1e-3), np.zeros((1, D)), np.full((1, D), math.nan)])
+    for n0, T_hat in ((1.0, 0.8), (1.0, 0.5), (0.5, 0.9)):
+        quiet = fsc.linear_sk(_p(D, stencil, T_hat, n0, 0.0), kv)
+        assert np.all(quiet[:-1] == 0.0) and np.isnan(quiet[-1])
+        got = fsc.linear_sk(_p(D, stencil, T_hat, n0, 1e-4), kv)
+        assert not np.any(np.isinf(got)) and np.isnan(got[-1])
+        assert np.isnan(got[100]) == (n0 == 1.0)
+    mean, _ = fsc.linear_sk_radial(_p(D, stencil, 0.5, 1.0, 0.0, n=8), 4)
+    assert np.all(mean == 0.0)
