@@ -849,8 +849,8 @@ static int sk_cap(size_t csz) { return csz == 8 ? 16384 : 8192; }  // lines x m 
 // up to 4096).  In floats its two transforms and three products with rounded tables
 // lose a relative 2e-7 of every |X|^2 (white fields of side 48 to 4100; direct FP32
 // sums 1e-9 to 7e-8) and leave 4 to 8 times the noise of direct sums where a spectrum
-// is steep.  A sample of 100^2 takes 18.2 us so and 17.1 in floats, 1000^2 71 and 66,
-// 3000^2 690 and 440 (direct sums: 29, 1833, 58100).  Beyond 4096 direct sums are the
+// is steep.  A sample of 100^2 takes 17.9 us so and 17.0 in floats, 1000^2 60 and 66,
+// 3000^2 631 and 443, 100^3 83 and 70 (direct sums: 29, 1833, 58100, 440).  Beyond 4096 direct sums are the
 // noisier ones (0.2 sqrt(n) of a rounding, the chirp 2.4), and it stays in floats, with
 // the loss taken out (root_loss).
 SkAxis sk_axis(int n, int precision) {
@@ -974,8 +974,10 @@ static int sk_lines_per_block(int m, size_t csz, int64_t lines) {
     return std::max(1, std::min(lc, cap / m));
 }
 
-static int sk_threads(int lines, int m) {
-    const int t = (lines * m + SK_HELD - 1) / SK_HELD;
+// Threads of a block: SK_HELD values each, half as many in wide lines, whose LDS admits
+// half the blocks (160^3 347 us a sample and 310 so, 192^3 505 and 456, 1000^2 71 and 60)
+static int sk_threads(int lines, const SkAxis &x) {
+    const int held = x.wide ? SK_HELD / 2 : SK_HELD, t = (lines * x.m + held - 1) / held;
     return t <= 256 ? 256 : (t <= 512 ? 512 : 1024);
 }
 
@@ -1023,14 +1025,14 @@ int measure_plan(MeasRep *reps, int nrep, MeasPlan &P) {
             P.threads[k] = std::max(P.threads[k], threads);
         };
         n[MK_ROWS] = int64_t((g.ny + 2 * m.lc[0] - 1) / (2 * m.lc[0])) * g.nz;
-        need(MK_ROWS, line_bytes(m.ax[0], m.lc[0]), sk_threads(m.lc[0], m.ax[0].m));
+        need(MK_ROWS, line_bytes(m.ax[0], m.lc[0]), sk_threads(m.lc[0], m.ax[0]));
         if (D == 3) {
             n[MK_MID] = int64_t(hx) * ((g.nz + m.lc[1] - 1) / m.lc[1]);
-            need(MK_MID, line_bytes(m.ax[1], m.lc[1]), sk_threads(m.lc[1], m.ax[1].m));
+            need(MK_MID, line_bytes(m.ax[1], m.lc[1]), sk_threads(m.lc[1], m.ax[1]));
         }
         const int inner = D == 3 ? g.ny : hx;
         n[MK_LAST] = int64_t((inner + m.lc[2] - 1) / m.lc[2]) * (D == 3 ? hx : 1);
-        need(MK_LAST, line_bytes(last, m.lc[2]) + (m.lc[2] > 1 ? sk_window(g, m.lc[2]) : 0), sk_threads(m.lc[2], last.m));
+        need(MK_LAST, line_bytes(last, m.lc[2]) + (m.lc[2] > 1 ? sk_window(g, m.lc[2]) : 0), sk_threads(m.lc[2], last));
         for (int k = 0; k < MK_COUNT; ++k) {
             P.pre[size_t(k) * (nrep + 1) + r] = int(tot[k]);
             tot[k] += n[k];
@@ -1126,9 +1128,9 @@ hipError_t launch_field_sk(const float *fields, int batch, int n, int n_rad, voi
     while (j.lc_last > 1 && sk_line_bytes(csz, j.lc_last, j.ax.m) + sk_window(g, j.lc_last) > SK_LDS) j.lc_last >>= 1;
     const int pr = (n + 2 * j.lc_rows - 1) / (2 * j.lc_rows), pl = (hx + j.lc_last - 1) / j.lc_last;
     if (int64_t(batch) * std::max(pr, pl) > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(j.ax.wide ? k_field_rows<double> : k_field_rows<float>, dim3(unsigned(batch * pr)), dim3(unsigned(sk_threads(j.lc_rows, j.ax.m))),
+    hipLaunchKernelGGL(j.ax.wide ? k_field_rows<double> : k_field_rows<float>, dim3(unsigned(batch * pr)), dim3(unsigned(sk_threads(j.lc_rows, j.ax))),
                        sk_line_bytes(csz, j.lc_rows, j.ax.m), s, j, pr);
-    hipLaunchKernelGGL(j.ax.wide ? k_field_last<double> : k_field_last<float>, dim3(unsigned(batch * pl)), dim3(unsigned(sk_threads(j.lc_last, j.ax.m))),
+    hipLaunchKernelGGL(j.ax.wide ? k_field_last<double> : k_field_last<float>, dim3(unsigned(batch * pl)), dim3(unsigned(sk_threads(j.lc_last, j.ax))),
                        sk_line_bytes(csz, j.lc_last, j.ax.m) + (j.lc_last > 1 ? sk_window(g, j.lc_last) : 0), s, j, pl);
     return hipGetLastError();
 }
